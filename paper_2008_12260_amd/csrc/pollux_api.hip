@@ -268,7 +268,7 @@ int pollux_goodput_per_gpu(const pollux_dims *dims, const double *job_params, co
     if (rc != PX_OK) return rc;
     rc = check_device();
     if (rc != PX_OK) return rc;
-    return px::launch_goodput_per_gpu(dims, job_params, m_grid, gpus_per_node, max_nodes, workspace, per_gpu,
+    return px::launch_goodput_per_gpu(dims, job_params, m_grid, gpus_per_node, max_nodes, per_gpu,
                                       (hipStream_t)hip_stream);
 }
 
@@ -295,7 +295,7 @@ int pollux_sim_tick(const pollux_dims *dims, const double *job_params, const int
     if (rc != PX_OK) return rc;
     rc = check_device();
     if (rc != PX_OK) return rc;
-    return px::launch_sim_tick(dims, job_params, m_grid, K, nodes, changed, target, dt, restart_delay, workspace,
+    return px::launch_sim_tick(dims, job_params, m_grid, K, nodes, changed, target, dt, restart_delay,
                                progress, goodput, finished, (hipStream_t)hip_stream);
 }
 

@@ -5,29 +5,25 @@
 // Sec. 4.1 (Eq. 13), SPEEDUP / FITNESS_p, re-allocation penalty and
 // interference avoidance Sec. 4.2 (Eq. 14-15).
 //
-// Kernels (one call = five launches on the caller's stream)
-//   tables_kernel     per job and grid point: T_grad(m) (Eq. 8), 1/T_grad, ln T_grad, phi/m and
-//                     the feasibility bounds; reciprocals; the largest node capacity; clears the status
-//                     word and the per-node counters
-//   last_kernel       per job, placement class and GPU count K <= 64 (one wavefront
-//                     per eight rows; the "one node" class only up to the largest node capacity):
-//                     T_sync (Eq. 9) and, for every batch size of the grid, the last pass of Eq. 10,
-//                     (T_grad^g + T_sync^g)^(1/g), and the two terms C and A0 the sweep needs of it.
-//                     They depend on the allocation only through K and on whether the job sits on
-//                     one node, so they are shared by the population;
-//                     also the feasible accumulation counts per (job, K, batch size)
-//   jobs_kernel       per job (one wavefront): parameter checks, restart factor,
-//                     fair-share goodput (denominator of Eq. 15)
+// Kernels (one call = three launches on the caller's stream)
+//   prepare_kernel    everything that depends on the jobs only.  Per job, placement class and GPU count K <= 64
+//                     (the "one node" class only up to the largest node capacity): T_sync (Eq. 9) and, for every
+//                     batch size of the grid, T_grad(m) (Eq. 8), the last pass of Eq. 10,
+//                     (T_grad^g + T_sync^g)^(1/g), the two terms C and A0 the sweep needs of it, and the feasible
+//                     accumulation counts.  They depend on the allocation only through K and on whether the job sits
+//                     on one node, so they are shared by the population.  Per job: parameter checks, restart
+//                     factor, fair-share goodput (denominator of Eq. 15).  Also the largest node capacity; clears
+//                     the status word and the per-node counters
 //   pairs_kernel      per (candidate, job) (one wavefront): row reduce, sweep of the
 //                     (m, s) grid, argmax; the row's non-zero entries are added to
 //                     per-candidate, per-node counters with integer atomics
 //   candidates_kernel per candidate (one workgroup): SPEEDUP, penalty, constraint
 //                     check from those counters and the generalized mean
-// With PX_FLAG_MEMOISE, memo_kernel sweeps once per (job, placement class, K <= 64) and the population pass looks
-// the result up: pairs_kernel, or for rows of 65 to 256 nodes memo_candidates_kernel, which takes a whole candidate
+// With PX_FLAG_MEMOISE, prepare_kernel takes the argmax once per (job, placement class, K <= 64) and the population pass
+// looks the result up: pairs_kernel, or for rows of 65 to 256 nodes memo_candidates_kernel, which takes a whole candidate
 // per workgroup and finishes its fitness as well (no per-pair scratch, no candidates_kernel).
 // With PX_FLAG_SAMPLE_M the sweep is replaced by sweep_sampled (Sec. 4.3), the kernels
-// instantiated with CH = 0, and last_kernel is not launched.
+// instantiated with CH = 0.
 // For pollux_generation the population pass takes a list of candidates (the children of the search step), or,
 // with PX_GA_INHERIT_ROWS, per job the list of rows the step has changed, after inherit_kernel has given every
 // unchanged row the results of the row it was copied from.
@@ -95,16 +91,17 @@ struct FitnessArgs {
     double *rs, *rk, *lntg, *pu, *qh5, *ql5, *lt, *denom, *factor, *G;
     float *rsf;                   // 1/(s+1) in fp32, as long as rs
     double2 *tg;                  // [J,Gm] (T_grad, 1 / T_grad)
-    double2 *ca;                  // [J,2,kTableK,Gm] (C, A0) of the sweep per (job, one node?, K, grid point) (see last_kernel)
-    int32_t *srange;              // [J,kTableK,Gm] feasible accumulation counts per (job, K, grid point) (see last_kernel)
-    int32_t *k1;                  // one word: the rows of the "one node" class are tabled for K <= *k1 only (tables_kernel)
+    double2 *ca;                  // [J,2,kTableK,Gm] (C, A0) of the sweep per (job, one node?, K, grid point) (see prepare_kernel)
+    int32_t *srange;              // [J,kTableK,Gm] feasible accumulation counts per (job, K, grid point) (see prepare_kernel)
+    int32_t *k1;                  // one word: the rows of the "one node" class are tabled for K <= *k1 only (prepare_kernel)
     int gs_pad;                   // Gs rounded up to a multiple of 32: length of rs
-    int32_t *running, *meta;
+    int32_t *jobstat;             // [J] status bits of each job (prepare_kernel), OR-ed into the status word by the call's last kernel
+    int32_t *meta;
     MemoEntry *memo;              // [J,2,kTableK] best point per (job, one node?, K), memoised mode only
     int32_t *redo;                // [P] memoised mode: candidates left to the second instance of memo_candidates_kernel
     unsigned long long *curmask;  // [J] rows of at most 256 entries in 16-byte groups: bit g set when group g of the job's
-                                  // current row holds a non-zero entry (jobs_kernel)
-    int32_t *zeros;               // 64 zero bytes (jobs_kernel): what lanes read where the current row holds nothing
+                                  // current row holds a non-zero entry (prepare_kernel)
+    int32_t *zeros;               // 64 zero bytes (prepare_kernel): what lanes read where the current row holds nothing
     unsigned long long *colpack;  // [P,N] per node: GPUs asked (low 40 bits, signed) + multi-node jobs present << 40
     int need_constraints;
     const int32_t *sel;           // candidates to evaluate (device list of n_sel indices into the population), or null: all P
@@ -113,8 +110,8 @@ struct FitnessArgs {
     const int32_t *src_row;       // [n_sel, J] the candidate whose row j the listed child holds unchanged, or -1
     const int32_t *odd;           // [n_sel] the listed child is to be evaluated in full
     int32_t *dirty_count, *dirty; // rows to sweep, per job: their number [J] and the candidates they belong to [J, n_sel]
-    int clear_status;             // tables_kernel starts a new status word (fitness calls; the query calls leave it alone)
-    int clear_counters;           // tables_kernel clears colpack (fitness calls whose population pass keeps the counters in memory)
+    int or_job_status;            // this call's prepare_kernel has left per-job status bits: its last kernel ORs them into the status word
+    int clear_counters;           // prepare_kernel clears colpack (fitness calls whose population pass keeps the counters in memory)
     // outputs
     double *fitness, *best_goodput, *speedup;
     int32_t *best_m, *best_s, *violations;
@@ -170,73 +167,50 @@ __device__ __forceinline__ SyncParams load_sync(const Job &q)
     return y;
 }
 
-// ---- tables ------------------------------------------------------------------
-// Per job and grid point i (batch size m = m_grid[j,i]):
-//   tg   = (T_grad(m), 1 / T_grad(m)) (Eq. 8)          lntg = ln T_grad(m)
-//   pu   = phi / m                      (u = phi / (K m) = pu / K)
-//   qh5  = floor(M_max / m) + 1/2       ql5  = ceil(M0 / m) - 1/2
+// ---- one batch size of a job's grid -------------------------------------------------
+//   tg, rtg = T_grad(m) (Eq. 8) and its reciprocal     lntg = ln T_grad(m)
+//   pu      = phi / m                      (u = phi / (K m) = pu / K)
+//   qh5     = floor(M_max / m) + 1/2       ql5 = ceil(M0 / m) - 1/2
 // M0 <= K m (s+1) <= M_max holds exactly when ceil(M0/m) <= K (s+1) <= floor(M_max/m),
 // i.e. for s between trunc(ql5 / K) and trunc(qh5 / K) - 1; the halves keep the
 // quotients at least 1/(2K) away from an integer, so a rounded 1/K cannot move them
-// across one.  Also rs[s] = 1/(s+1), rk[K] = 1/K, and a fitness call clears the status word here.
-__global__ void __launch_bounds__(256) tables_kernel(FitnessArgs a)
+// across one.
+struct GridPoint {
+    double tg, rtg, lntg, pu, qh5, ql5;
+};
+
+struct GridParams {
+    double alpha_g, beta_g, phi, M0, Mmax;
+};
+
+__device__ __forceinline__ GridParams load_grid_params(const double *__restrict__ jp, int J, int j)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0 && a.clear_status) *a.status = 0;
-    if (blockIdx.x == 0) {
-        // A job that sits on one node holds at most that node's GPUs, so the tables of the "one node" class stop at
-        // the largest capacity (all of kTableK when the call names no capacities); a row that claims more on one
-        // node, which no valid allocation does, is swept in place like a row beyond the tables.
-        __shared__ int cap_lds[256];
-        int c = 0;
-        if (a.node_capacity) {
-            for (int n = threadIdx.x; n < a.N; n += 256) {
-                const int v = a.node_capacity[n];
-                c = v > c ? v : c;
-            }
-        }
-        cap_lds[threadIdx.x] = c;
-        __syncthreads();
-        for (int half = 128; half > 0; half >>= 1) {
-            if ((int)threadIdx.x < half) cap_lds[threadIdx.x] = cap_lds[threadIdx.x] > cap_lds[threadIdx.x + half] ? cap_lds[threadIdx.x] : cap_lds[threadIdx.x + half];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) *a.k1 = (a.node_capacity && cap_lds[0] < kTableK) ? cap_lds[0] : kTableK;
+    return GridParams{jp[(size_t)PX_ALPHA_G * J + j], jp[(size_t)PX_BETA_G * J + j], jp[(size_t)PX_PHI * J + j],
+                      jp[(size_t)PX_M0 * J + j], jp[(size_t)PX_MMAX * J + j]};
+}
+
+__device__ __forceinline__ GridPoint grid_point(const GridParams &q, int mi)
+{
+    GridPoint g;
+    const double m = (double)mi;
+    g.tg = q.alpha_g + q.beta_g * m;                     // Eq. 8
+    g.rtg = g.tg > 0.0 ? 1.0 / g.tg : 0.0;
+    g.lntg = px_log(g.tg);
+    double qh = -1.5, ql = 1.0;
+    if (mi > 0) {
+        qh = floor(q.Mmax / m);
+        if (m * (qh + 1.0) <= q.Mmax) qh += 1.0;
+        if (m * qh > q.Mmax) qh -= 1.0;
+        ql = ceil(q.M0 / m);
+        if (m * (ql - 1.0) >= q.M0) ql -= 1.0;
+        if (m * ql < q.M0) ql += 1.0;
+        if (!(ql >= 1.0)) ql = 1.0;
+        if (!(qh >= 0.0)) qh = -1.5;
     }
-    const int rs_len = ((a.Gs + 31) / 32) * 32;
-    if (t < rs_len) {
-        a.rs[t] = 1.0 / (double)(t + 1);
-        a.rsf[t] = 1.0f / (float)(t + 1);
-    }
-    if (t < kRecipTable) a.rk[t] = t > 0 ? 1.0 / (double)t : 0.0;
-    if (a.clear_counters) {
-        // the per-candidate, per-node counters of the constraint check start the call at zero
-        const size_t n = (size_t)a.P * a.N;
-        for (size_t i = (size_t)t; i < n; i += (size_t)gridDim.x * blockDim.x) a.colpack[i] = 0ull;
-    }
-    if (t < a.J * a.Gm) {
-        const int j = t / a.Gm;
-        const int mi = a.m_grid[t];
-        const double m = (double)mi;
-        const double tg = a.job_params[(size_t)PX_ALPHA_G * a.J + j] + a.job_params[(size_t)PX_BETA_G * a.J + j] * m;   // Eq. 8
-        a.tg[t] = double2{tg, tg > 0.0 ? 1.0 / tg : 0.0};
-        a.lntg[t] = px_log(tg);
-        double qh = -1.5, ql = 1.0;
-        if (mi > 0) {
-            const double Mmax = a.job_params[(size_t)PX_MMAX * a.J + j], M0 = a.job_params[(size_t)PX_M0 * a.J + j];
-            qh = floor(Mmax / m);
-            if (m * (qh + 1.0) <= Mmax) qh += 1.0;
-            if (m * qh > Mmax) qh -= 1.0;
-            ql = ceil(M0 / m);
-            if (m * (ql - 1.0) >= M0) ql -= 1.0;
-            if (m * ql < M0) ql += 1.0;
-            if (!(ql >= 1.0)) ql = 1.0;
-            if (!(qh >= 0.0)) qh = -1.5;
-        }
-        a.pu[t] = mi > 0 ? a.job_params[(size_t)PX_PHI * a.J + j] / m : 0.0;
-        a.qh5[t] = qh + 0.5;
-        a.ql5[t] = ql - 0.5;
-    }
+    g.pu = mi > 0 ? q.phi / m : 0.0;
+    g.qh5 = qh + 0.5;
+    g.ql5 = ql - 0.5;
+    return g;
 }
 
 // ---- T_sync and the last pass of Eq. 10 ------------------------------------------
@@ -274,7 +248,7 @@ __device__ __forceinline__ double last_pass(const SyncTerm &t, double tg, double
 }
 
 // The feasible accumulation counts of grid point i with K GPUs: s_lo <= s <= s_hi
-// (empty when s_lo > s_hi), from the half-offset quotients of tables_kernel.
+// (empty when s_lo > s_hi), from the half-offset quotients of grid_point.
 __device__ __forceinline__ void feasible_range(double ql5, double qh5, double rK, int Gs, int &s_lo, int &s_hi)
 {
     s_lo = (int)(ql5 * rK);
@@ -288,69 +262,9 @@ __device__ __forceinline__ bool tabled_row(int K, bool one_node, int k1)
     return K <= (one_node ? k1 : kTableK);
 }
 
-// lt[row][i] for every grid point i, row index ((j * 2 + one_node) * kTableK + (K - 1)).
-// One wavefront fills kLastRows rows of one (job, placement class): their inputs are read once and lane r
-// prepares T_sync and its logarithm for the r-th of them.  The rows of the "several nodes"
-// class also write the feasible accumulation counts of (job, K, i), which do not depend on
-// the class: srange[j][K-1][i] = first | last << 16, first > last when there is none.
-// Beside lt[row][i] the wavefront writes ca[row][i] = (C, A0), the two terms the sweep needs of (job, class, K, i):
-//     h(m_i, s) = A0 + T_grad (s + C / (s + 1)),   u = phi / (K m_i),   A0 = last + u T_grad,   C = (last - T_grad) u / T_grad,
-// formed here once instead of by every (candidate, job) pair; A0 = +inf where no accumulation count is feasible, so
-// such a batch size never wins an election.
-constexpr int kLastRows = 8;
-static_assert(kTableK % kLastRows == 0, "the rows of a wavefront belong to one job and class");
-
 __device__ __forceinline__ double wave_read(double v, int src)
 {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
-}
-
-__global__ void __launch_bounds__(256) last_kernel(FitnessArgs a)
-{
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const long long row0 = ((long long)blockIdx.x * kWavesPerBlock + wave) * kLastRows;
-    if (row0 >= (long long)a.J * 2 * kTableK) return;
-    const int K0 = (int)(row0 % kTableK) + 1;
-    const bool one_node = ((row0 / kTableK) & 1) != 0;
-    const int j = (int)(row0 / (2 * kTableK));
-    if (one_node && K0 > *a.k1) return;             // no row of this wavefront is ever looked up
-    const Job q = load_job(a.job_params, a.J, j);
-    const int lane = lane_id();
-    const SyncTerm mine = sync_term(q, K0 + (lane < kLastRows ? lane : 0), one_node);
-    SyncTerm t[kLastRows];
-#pragma unroll
-    for (int r = 0; r < kLastRows; ++r) {
-        t[r].ts = wave_read(mine.ts, r);
-        t[r].lnts = wave_read(mine.lnts, r);
-        t[r].gamma = mine.gamma;
-        t[r].inv_gamma = mine.inv_gamma;
-        t[r].mode = __builtin_amdgcn_readlane(mine.mode, r);
-    }
-    double rK[kLastRows];
-#pragma unroll
-    for (int r = 0; r < kLastRows; ++r) rK[r] = a.rk[K0 + r];
-    const size_t o = (size_t)j * a.Gm;
-    int32_t *__restrict__ out = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
-    for (int i = lane; i < a.Gm; i += kWave) {
-        const double2 tgr = a.tg[o + i];
-        const double tg = tgr.x, lntg = a.lntg[o + i], pu = a.pu[o + i];
-        const double ql5 = a.ql5[o + i], qh5 = a.qh5[o + i];
-#pragma unroll
-        for (int r = 0; r < kLastRows; ++r) {
-            const double last = last_pass(t[r], tg, lntg);
-            a.lt[(size_t)(row0 + r) * a.Gm + i] = last;
-            int s_lo, s_hi;
-            feasible_range(ql5, qh5, rK[r], a.Gs, s_lo, s_hi);
-            const bool none = s_lo > s_hi || s_hi < 0;
-            if (none) { s_lo = 1; s_hi = 0; }
-            if (!one_node) out[(size_t)r * a.Gm + i] = s_lo | (s_hi << 16);
-            // what the sweep needs of (job, class, K, i): h(m_i, s) = A0 + T_grad (s + C / (s+1))
-            const double u = pu * rK[r];
-            const double A0 = px_fma(u, tg, last);
-            const double B0 = (last - tg) * u;
-            a.ca[(size_t)(row0 + r) * a.Gm + i] = double2{B0 * tgr.y, none ? __builtin_inf() : A0};
-        }
-    }
 }
 
 // ---- the sweep of one (job, K, nodes) ----------------------------------------
@@ -406,7 +320,7 @@ __device__ __forceinline__ double goodput_point(const Job &q, double Km, double 
 // With C = B0 / T_grad the quantity to minimise is  h = A0 + T_grad w(s),  w(s) = s + C / (s+1),
 // for the lane's batch size.  The lane scans w over all accumulation counts, feasible or not;
 // C >= 0 makes w convex in s, and the feasible counts of a batch size form an interval (tabled
-// per (job, K, i) by last_kernel), so the smallest feasible w sits at the scan's argmin clamped
+// per (job, K, i) by prepare_kernel), so the smallest feasible w sits at the scan's argmin clamped
 // to that interval (sweep_pick).  Inside a chunk of CH counts starting at s0, per group of four
 // positions b = 4 G .. 4 G + 3 and lane:
 //   w_b  = C * r + (b mod 16)  one v_fma_f64 each (v_mul_f64 for 0): r = 1/(s0 + b + 1) from scalar
@@ -655,6 +569,41 @@ struct Pick {
     int i, s;
 };
 
+// The lanes' smallest h and where each found it (accumulation count | index of its group of 64 batch sizes << 16; bit l of
+// `second` adds one to lane l's group index): the point with the smallest h over the wavefront, equal values to the lowest
+// flat index i * Gs + s.  Every lane returns the same result.
+__device__ __forceinline__ Pick elect(double kbest, int where, unsigned long long second, int Gs)
+{
+    const int lane = lane_id();
+    // positive doubles order like their bit patterns: unsigned 32-bit wave minima, high words first;
+    // the low words only among several lanes that share the smallest high word
+    const unsigned hi = (unsigned)__double2hiint(kbest), lo = (unsigned)__double2loint(kbest);
+    const unsigned hmin = wave_min(hi);
+    if (hmin >= 0x7FF00000u) return Pick{-1, -1};              // every lane still holds +inf
+    unsigned long long winners = __builtin_amdgcn_ballot_w64(hi == hmin);
+    if (winners & (winners - 1)) {
+        const unsigned lmin = wave_min(hi == hmin ? lo : 0xFFFFFFFFu);
+        winners &= __builtin_amdgcn_ballot_w64(lo == lmin);
+        if (winners & (winners - 1)) {
+            // equal values (duplicated batch sizes): the lowest flat index i * Gs + s.  Winners with one
+            // group of 64 and one count differ in the lane only, so the lowest lane has it; else a third minimum.
+            where |= (int)((second >> lane) & 1ull) << 16;
+            const int first_lane = __ffsll(winners) - 1;
+            const int where0 = __builtin_amdgcn_readlane(where, first_lane);
+            const unsigned long long same = __builtin_amdgcn_ballot_w64(where == where0);
+            if ((winners & ~same) != 0) {
+                const bool top = ((winners >> lane) & 1ull) != 0;
+                const int flat = ((where >> 16) * kWave + lane) * Gs + (where & 0xFFFF);
+                const int first = wave_min(top ? flat : 0x7FFFFFFF);
+                winners &= __builtin_amdgcn_ballot_w64(flat == first);
+            }
+        }
+    }
+    const int wl = __ffsll(winners) - 1;
+    const int wwhere = __builtin_amdgcn_readlane(where, wl);
+    return Pick{((wwhere >> 16) | (int)((second >> wl) & 1ull)) * kWave + wl, wwhere & 0xFFFF};
+}
+
 // All 64 lanes call this with the same (job, K >= 1, nodes).  Every lane returns the same result:
 // the feasible point with the smallest h over the whole grid (equal values resolve to the
 // lowest flat index i * Gs + s).
@@ -800,33 +749,7 @@ __device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, co
         }
     }
 
-    // positive doubles order like their bit patterns: unsigned 32-bit wave minima, high words first;
-    // the low words only among several lanes that share the smallest high word
-    const unsigned hi = (unsigned)__double2hiint(kbest), lo = (unsigned)__double2loint(kbest);
-    const unsigned hmin = wave_min(hi);
-    if (hmin >= 0x7FF00000u) return Pick{-1, -1};              // every lane still holds +inf
-    unsigned long long winners = __builtin_amdgcn_ballot_w64(hi == hmin);
-    if (winners & (winners - 1)) {
-        const unsigned lmin = wave_min(hi == hmin ? lo : 0xFFFFFFFFu);
-        winners &= __builtin_amdgcn_ballot_w64(lo == lmin);
-        if (winners & (winners - 1)) {
-            // equal values (duplicated batch sizes): the lowest flat index i * Gs + s.  Winners with one
-            // group of 64 and one count differ in the lane only, so the lowest lane has it; else a third minimum.
-            where |= (int)((second >> lane) & 1ull) << 16;
-            const int first_lane = __ffsll(winners) - 1;
-            const int where0 = __builtin_amdgcn_readlane(where, first_lane);
-            const unsigned long long same = __builtin_amdgcn_ballot_w64(where == where0);
-            if ((winners & ~same) != 0) {
-                const bool top = ((winners >> lane) & 1ull) != 0;
-                const int flat = ((where >> 16) * kWave + lane) * Gs + (where & 0xFFFF);
-                const int first = wave_min(top ? flat : 0x7FFFFFFF);
-                winners &= __builtin_amdgcn_ballot_w64(flat == first);
-            }
-        }
-    }
-    const int wl = __ffsll(winners) - 1;
-    const int wwhere = __builtin_amdgcn_readlane(where, wl);
-    return Pick{((wwhere >> 16) | (int)((second >> wl) & 1ull)) * kWave + wl, wwhere & 0xFFFF};
+    return elect(kbest, where, second, Gs);
 }
 
 // The same election for four (job, K, nodes) at once, one per row of 16 lanes, for small grids, where a sweep per
@@ -886,18 +809,6 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
     return hmin >= 0x7FF00000u ? -1 : (int)first;             // every lane of the row still holds +inf: no point
 }
 
-template <int CH>
-__device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, const double *__restrict__ rs,
-                                           const double *__restrict__ rk, int Gm, int Gs, int K, int nodes)
-{
-    K = __builtin_amdgcn_readfirstlane(K);             // the same in every lane: scalar from here on
-    nodes = __builtin_amdgcn_readfirstlane(nodes);
-    if (K <= 0) return Pick{-1, -1};
-    const RunSteps X = make_run_steps();
-    if (tabled_row(K, nodes == 1, tb.k1)) return sweep_pick<CH, true>(q, tb, X, rs, rk, Gm, Gs, K, nodes);
-    return sweep_pick<CH, false>(q, tb, X, rs, rk, Gm, Gs, K, nodes);
-}
-
 // Eq. 4 at grid point (i, s) in the paper's order of operations.  Arguments may differ
 // from lane to lane.
 __device__ __forceinline__ Best price_point(const Job &q, const JobTables &tb, int Gm, int K, bool one_node, int i, int s)
@@ -909,15 +820,6 @@ __device__ __forceinline__ Best price_point(const Job &q, const JobTables &tb, i
     if (tabled_row(K, one_node, tb.k1)) last = tb.lt[(unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm + (unsigned)i];
     else last = last_pass(sync_term(q, K, one_node), tg, tb.lntg[i]);
     return Best{goodput_point(q, (double)K * (double)m, tg, last, s), m, s};
-}
-
-// Sweep and price: every lane returns the same result.
-template <int CH>
-__device__ __forceinline__ Best sweep(const Job &q, const JobTables &tb, const double *__restrict__ rs,
-                                      const double *__restrict__ rk, int Gm, int Gs, int K, int nodes)
-{
-    const Pick pick = sweep_pick<CH>(q, tb, rs, rk, Gm, Gs, K, nodes);
-    return price_point(q, tb, Gm, K, nodes == 1, pick.i, pick.s);
 }
 
 __device__ __forceinline__ JobTables job_tables(const FitnessArgs &a, int j)
@@ -1007,7 +909,7 @@ __device__ __forceinline__ Best sweep_f32(const JobF32 &q, const JobTables &tb, 
     const double rK = K < kRecipTable ? rk[K] : 1.0 / (double)K;
     float ts = 0.0f;                                                          // Eq. 9
     if (K > 1) ts = (nodes == 1) ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
-    // Eq. 10 for K within the tables: the fp64 table of last_kernel, rounded to fp32 (two powf per batch size otherwise)
+    // Eq. 10 for K within the tables: the fp64 table of prepare_kernel, rounded to fp32 (two powf per batch size otherwise)
     const bool tabled = tabled_row(K, nodes == 1, tb.k1);
     const double *__restrict__ lrow = tb.lt + (unsigned)((nodes == 1 ? kTableK : 0) + (tabled ? K - 1 : 0)) * (unsigned)Gm;
     const float tsg = (!tabled && ts != 0.0f && q.gamma != 1.0f) ? powf(ts, q.gamma) : 0.0f;
@@ -1219,84 +1121,356 @@ __device__ __forceinline__ Best sweep_any_f32(const JobF32 &q, const JobTables &
     return price_point_f32(q, tb, Gm, K, nodes == 1, pick.i, pick.s);
 }
 
-// ---- per job -----------------------------------------------------------------
+// ---- per job: what the status word says of its parameters, and its current row ------------------
 
-template <int CH, bool F32>
-__global__ void __launch_bounds__(256) jobs_kernel(FitnessArgs a)
+__device__ __forceinline__ int job_status(const GridParams &g, const SyncParams &y, double weight)
+{
+    if (!(y.gamma >= 1.0 && y.gamma <= 10.0) || !(g.alpha_g >= 0.0) || !(g.beta_g >= 0.0) || !(y.alpha_sl >= 0.0) ||
+        !(y.beta_sl >= 0.0) || !(y.alpha_sn >= 0.0) || !(y.beta_sn >= 0.0) || !(g.phi > 0.0) || !(g.M0 >= 1.0) ||
+        !(g.Mmax >= g.M0) || !(weight >= 0.0) || !(g.Mmax <= 4503599627370496.0) || !(g.alpha_g + g.beta_g > 0.0))
+        return PX_ST_BAD_PARAM;
+    return 0;
+}
+
+struct CurrentRow {
+    long long total;                // GPUs the job holds now
+    bool negative;                  // the row has a negative entry
+    unsigned long long groups;      // 16-byte groups that hold a non-zero entry (rows that one 16-byte load per lane covers)
+};
+
+__device__ __forceinline__ CurrentRow current_row(const FitnessArgs &a, int j)
+{
+    const int lane = lane_id();
+    const int32_t *__restrict__ row = a.current_alloc + (size_t)j * a.N;
+    CurrentRow out = {0, false, 0ull};
+    long long sum = 0;
+    bool neg = false;
+    for (int n = lane; n < a.N; n += kWave) {
+        const int c = row[n];
+        sum += c;
+        neg |= c < 0;
+    }
+    out.total = wave_sum(sum);
+    out.negative = __ballot(neg) != 0ull;
+    if ((a.N & 3) == 0 && a.N <= 4 * kWave) {
+        bool any = false;
+        if (lane < (a.N >> 2)) {
+            const int32_t *g = row + 4 * lane;
+            any = (g[0] | g[1] | g[2] | g[3]) != 0;
+        }
+        out.groups = __ballot(any);
+    }
+    return out;
+}
+
+// ---- the argmax of one (job, K, placement) in place ------------------------------------------
+// What the calls that ask for a handful of argmaxes per job need (fair shares, memoised rows, rows beyond the memo table,
+// the queries outside the search): the same election as sweep_pick without any table.  Lane l forms the terms of its batch
+// sizes itself; the best accumulation count needs no scan, since w(s) = s + C / (s + 1) falls from t - 1 to t precisely when
+// C > t (t + 1), so its argmin over all counts is the largest t with C > t (t + 1), or 0.
+__device__ __forceinline__ int argmin_count(double C)
+{
+    // t is found in fp32, where it is off by less than one for every count a grid can have (below 2^14; C is capped far
+    // beyond them), and put right by the exact order of neighbours
+    const float c = (float)(C < 1073741824.0 ? C : 1073741824.0);
+    const int t = (int)(__builtin_amdgcn_sqrtf(c + 0.25f) - 0.5f);
+    const double td = (double)t;
+    const double t_lo = t > 0 ? px_fma(td, td, td) : -1.0, t_hi = px_fma(td, td, px_fma(3.0, td, 2.0));
+    return C <= t_lo ? t - 1 : (C > t_hi ? t + 1 : t);
+}
+
+// h of one batch size at its best feasible count s_c (+inf when no count is feasible).  tabled: h in the form the tables
+// give it (C and A0), else in the form of the untabled sweep: rounding decides elections between equal points, so a row
+// keeps the form its sweep has.
+__device__ __forceinline__ double best_count(const GridPoint &g, double last, double rK, int Gs, bool tabled, int &s_c)
+{
+    int s_lo, s_hi;
+    feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
+    const double u = g.pu * rK;
+    const double A0 = px_fma(u, g.tg, last);
+    const double B0 = (last - g.tg) * u;
+    const double C = B0 * g.rtg;
+    int s = argmin_count(C);
+    s = s < s_hi ? s : s_hi;
+    s = s > s_lo ? s : s_lo;
+    s_c = s;
+    const double sd = (double)s, r = 1.0 / (double)(s + 1);
+    const double h = tabled ? px_fma(g.tg, px_fma(C, r, sd), A0) : px_fma(B0, r, px_fma(sd, g.tg, A0));
+    return (s_lo > s_hi || s_hi < 0) ? __builtin_inf() : h;
+}
+
+// Eq. 4 at batch size m and count s in the paper's order of operations, T_grad and the last pass formed here.
+__device__ __forceinline__ double price_in_place(const Job &q, const GridParams &gp, const SyncTerm &st, int K, int m, int s)
+{
+    const double tg = gp.alpha_g + gp.beta_g * (double)m;
+    return goodput_point(q, (double)K * (double)m, tg, last_pass(st, tg, px_log(tg)), s);
+}
+
+// All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
+__device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs,
+                                         int K, bool one_node, bool tabled)
+{
+    const SyncTerm st = sync_term(q, K, one_node);
+    const double rK = 1.0 / (double)K;
+    double kbest = __builtin_inf();
+    int where = 0;
+    for (int i = lane_id(); i < Gm; i += kWave) {
+        const GridPoint g = grid_point(gp, m_row[i]);
+        int s_c;
+        const double h = best_count(g, last_pass(st, g.tg, g.lntg), rK, Gs, tabled, s_c);
+        if (h < kbest) {
+            kbest = h;
+            where = s_c | ((i / kWave) << 16);
+        }
+    }
+    const Pick pick = elect(kbest, where, 0ull, Gs);
+    if (pick.i < 0) return Best{0.0, -1, -1};
+    const int m = m_row[pick.i];
+    return Best{price_in_place(q, gp, st, K, m, pick.s), m, pick.s};
+}
+
+// ---- everything that depends on the jobs only: one launch ---------------------------------------
+// The wavefronts of a job: one that checks its parameters, finds its fair-share goodput (denominator of Eq. 15) and its
+// re-allocation factor, and further ones that take ROWS rows (placement class, K) each.  No wavefront reads what another
+// writes (each forms the terms of its own batch sizes, an eighth of a row's work), so a call needs one launch here where
+// it took three or four, one after the other: at 8 jobs 15 us of launches became 7, at 200 jobs 25 became 11.
+//   kPrepPlain    rows into the tables of the sweep (lt, ca, srange; per grid point tg, lntg, pu, qh5, ql5)
+//   kPrepTables   the same for the fp32 variant, whose fair shares are found from the tables (jobs_kernel_f32)
+//   kPrepMemo     memoised mode: the rows' argmaxes into the memo table, no other table
+//   kPrepSampled  the sampling argmax: fair shares only (no table)
+//   kPrepSampledMemo  and with its rows memoised
+// Rows of the "one node" class stop at the largest node capacity: a job on one node holds at most that node's GPUs.  A row
+// that claims more there, which no valid allocation does, is swept in place like a row beyond the tables (tabled_row).
+// Table rows: lt[row][i] the last pass, ca[row][i] = (C, A0) with A0 = +inf where no accumulation count is feasible (such a
+// batch size never wins an election), row = (j * 2 + one_node) * kTableK + K - 1; the rows of the "several nodes" class also
+// write the feasible counts of (job, K, i), which do not depend on the class: srange[j][K-1][i] = first | last << 16,
+// first > last when there is none.
+// Workgroups are dealt to the XCDs round-robin; a job's wavefronts run on XCD j % 8, as its pairs do.
+enum PrepMode { kPrepPlain, kPrepTables, kPrepMemo, kPrepSampled, kPrepSampledMemo };
+
+constexpr bool prep_has_tables(int mode) { return mode == kPrepPlain || mode == kPrepTables; }
+constexpr int prep_tasks(int mode, int rows) { return 1 + (mode == kPrepSampled ? 0 : 2 * kTableK / rows); }
+
+// Whether some node holds at least K GPUs.
+__device__ __forceinline__ bool node_holds(const FitnessArgs &a, int K)
+{
+    bool found = false;
+    for (int n0 = 0; n0 < a.N && !found; n0 += kWave) {
+        const int n = n0 + lane_id();
+        found = __ballot(n < a.N && a.node_capacity[n] >= K) != 0ull;
+    }
+    return found;
+}
+
+template <int MODE>
+__device__ __forceinline__ void prepare_job(const FitnessArgs &a, int j)
+{
+    const int lane = lane_id();
+    const double *__restrict__ jp = a.job_params;
+    const GridParams gp = load_grid_params(jp, a.J, j);
+    const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
+    if constexpr (prep_has_tables(MODE)) {
+        for (int i = lane; i < a.Gm; i += kWave) {
+            const GridPoint g = grid_point(gp, m_row[i]);
+            const size_t o = (size_t)j * a.Gm + i;
+            a.tg[o] = double2{g.tg, g.rtg};
+            a.lntg[o] = g.lntg;
+            a.pu[o] = g.pu;
+            a.qh5[o] = g.qh5;
+            a.ql5[o] = g.ql5;
+        }
+    }
+    if constexpr (MODE == kPrepTables) return;
+    const Job q = load_job(jp, a.J, j);
+    const SyncParams y = load_sync(q);
+    const double w = jp[(size_t)PX_WEIGHT * a.J + j];
+    const double T = jp[(size_t)PX_AGE_T * a.J + j];
+    const double R = jp[(size_t)PX_RESTARTS_R * a.J + j];
+    constexpr bool kSampled = MODE == kPrepSampled || MODE == kPrepSampledMemo;
+    int st = job_status(gp, y, w);
+    if constexpr (kSampled) {
+        const double m_mem = jp[(size_t)PX_M_MEM * a.J + j];
+        if (!(m_mem >= 1.0 && m_mem <= 2147483647.0)) st |= PX_ST_BAD_PARAM;
+    }
+    // re-allocation penalty factor of Sec. 4.2
+    const double factor = (T - R * a.delta) / (T + a.delta);
+    if (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
+    const CurrentRow cur = current_row(a, j);
+    if (cur.negative) st |= PX_ST_NEG_ALLOC;
+    // denominator of Eq. 15: the same argmax at the fair-share allocation
+    const int K = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j]);
+    const bool one_node = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j + 1]) == 1;
+    Best fair = {0.0, -1, -1};
+    if constexpr (kSampled) fair = sweep_sampled(q, m_row, a.Gm, a.Gs, K, one_node ? 1 : 2);
+    else if (K > 0) fair = row_best(q, gp, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
+    if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
+    if (lane == 0) {
+        a.denom[j] = fair.goodput;
+        a.factor[j] = (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && cur.total > 0) ? factor : 1.0;
+        a.curmask[j] = cur.groups;
+        a.jobstat[j] = st;
+    }
+    if (j == 0 && lane < 16) a.zeros[lane] = 0;
+}
+
+template <int ROWS, int MODE>
+__device__ __forceinline__ void prepare_rows(const FitnessArgs &a, int j, int K0, bool one_node)
+{
+    const int lane = lane_id();
+    const size_t row0 = ((size_t)j * 2 + (one_node ? 1 : 0)) * kTableK + (K0 - 1);
+    const Job q = load_job(a.job_params, a.J, j);
+    const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
+    if constexpr (MODE == kPrepSampledMemo) {
+        for (int r = 0; r < ROWS; ++r) {
+            const Best best = sweep_sampled(q, m_row, a.Gm, a.Gs, K0 + r, one_node ? 1 : 2);
+            if (lane == 0) a.memo[row0 + r] = MemoEntry{best.goodput, best.m, best.s};
+        }
+        return;
+    }
+    const GridParams gp = load_grid_params(a.job_params, a.J, j);
+    // lane r prepares T_sync and its logarithm, and 1/K, for the r-th row
+    const int my_K = K0 + (lane < ROWS ? lane : 0);
+    const SyncTerm mine = sync_term(q, my_K, one_node);
+    const double my_rK = 1.0 / (double)my_K;
+    SyncTerm t[ROWS];
+    double rK[ROWS], kbest[ROWS];
+    int where[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        t[r].ts = wave_read(mine.ts, r);
+        t[r].lnts = wave_read(mine.lnts, r);
+        t[r].gamma = mine.gamma;
+        t[r].inv_gamma = mine.inv_gamma;
+        t[r].mode = __builtin_amdgcn_readlane(mine.mode, r);
+        rK[r] = wave_read(my_rK, r);
+        kbest[r] = __builtin_inf();
+        where[r] = 0;
+    }
+    int32_t *__restrict__ ranges = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
+    for (int i = lane; i < a.Gm; i += kWave) {
+        const GridPoint g = grid_point(gp, m_row[i]);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const double last = last_pass(t[r], g.tg, g.lntg);
+            if constexpr (MODE == kPrepMemo) {
+                int s_c;
+                const double h = best_count(g, last, rK[r], a.Gs, true, s_c);
+                if (h < kbest[r]) {
+                    kbest[r] = h;
+                    where[r] = s_c | ((i / kWave) << 16);
+                }
+            } else {
+                a.lt[(row0 + r) * a.Gm + i] = last;
+                int s_lo, s_hi;
+                feasible_range(g.ql5, g.qh5, rK[r], a.Gs, s_lo, s_hi);
+                const bool none = s_lo > s_hi || s_hi < 0;
+                if (none) { s_lo = 1; s_hi = 0; }
+                if (!one_node) ranges[(size_t)r * a.Gm + i] = s_lo | (s_hi << 16);
+                // what the sweep needs of (job, class, K, i): h(m_i, s) = A0 + T_grad (s + C / (s+1))
+                const double u = g.pu * rK[r];
+                const double A0 = px_fma(u, g.tg, last);
+                const double B0 = (last - g.tg) * u;
+                a.ca[(row0 + r) * a.Gm + i] = double2{B0 * g.rtg, none ? __builtin_inf() : A0};
+            }
+        }
+    }
+    if constexpr (MODE == kPrepMemo) {
+        // lane r prices the point elected for row r
+        int my_i = -1, my_s = -1;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const Pick pick = elect(kbest[r], where[r], 0ull, a.Gs);
+            my_i = lane == r ? pick.i : my_i;
+            my_s = lane == r ? pick.s : my_s;
+        }
+        if (lane < ROWS) {
+            MemoEntry e = {0.0, -1, -1};
+            if (my_i >= 0) {
+                e.m = m_row[my_i];
+                e.s = my_s;
+                e.goodput = price_in_place(q, gp, mine, my_K, e.m, e.s);
+            }
+            a.memo[row0 + lane] = e;
+        }
+    }
+}
+
+template <int ROWS, int MODE>
+__global__ void __launch_bounds__(256) prepare_kernel(FitnessArgs a)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, threads = (size_t)gridDim.x * blockDim.x;
+    if (tid == 0) *a.status = 0;
+    if (a.clear_counters) {
+        // the per-candidate, per-node counters of the constraint check start the call at zero
+        const size_t n = (size_t)a.P * a.N;
+        for (size_t i = tid; i < n; i += threads) a.colpack[i] = 0ull;
+    }
+    if constexpr (prep_has_tables(MODE)) {
+        for (size_t i = tid; i < (size_t)a.gs_pad; i += threads) {
+            a.rs[i] = 1.0 / (double)(int)(i + 1);
+            a.rsf[i] = 1.0f / (float)(int)(i + 1);
+        }
+        if (tid < kRecipTable) a.rk[tid] = tid > 0 ? 1.0 / (double)(int)tid : 0.0;
+    }
+    if (blockIdx.x == 0 && wave == 0) {
+        int c = 0;
+        for (int n = lane_id(); n < a.N; n += kWave) {
+            const int v = a.node_capacity[n];
+            c = v > c ? v : c;
+        }
+        c = (int)wave_max((unsigned)c);
+        if (lane_id() == 0) *a.k1 = c < kTableK ? c : kTableK;
+    }
+    constexpr int kTasks = prep_tasks(MODE, ROWS);
+    const int slot = (int)(blockIdx.x >> 3) * kWavesPerBlock + wave;
+    const int j = (slot / kTasks) * 8 + (int)(blockIdx.x & 7);
+    const int task = slot % kTasks;
+    if (j >= a.J) return;
+    if (task == 0) {
+        prepare_job<MODE>(a, j);
+    } else if constexpr (MODE != kPrepSampled) {
+        constexpr int kPerClass = kTableK / ROWS;
+        const bool one_node = task - 1 >= kPerClass;
+        const int K0 = ((task - 1) % kPerClass) * ROWS + 1;
+        if (one_node && !node_holds(a, K0)) return;       // no row of this wavefront is ever looked up
+        prepare_rows<ROWS, MODE>(a, j, K0, one_node);
+    }
+}
+
+// ---- fp32 variant: fair shares and memo table, from the tables --------------------------------------
+
+template <int CH>
+__global__ void __launch_bounds__(256) jobs_kernel_f32(FitnessArgs a)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int j = blockIdx.x * kWavesPerBlock + wave;
     if (j >= a.J) return;
     const int lane = lane_id();
-    const Job q = load_job(a.job_params, a.J, j);
-    const SyncParams y = load_sync(q);
     const double *__restrict__ jp = a.job_params;
-    const double alpha_g = jp[(size_t)PX_ALPHA_G * a.J + j], beta_g = jp[(size_t)PX_BETA_G * a.J + j];
-    const double M0 = jp[(size_t)PX_M0 * a.J + j], Mmax = jp[(size_t)PX_MMAX * a.J + j];
-    const double w = jp[(size_t)PX_WEIGHT * a.J + j];
     const double T = jp[(size_t)PX_AGE_T * a.J + j];
     const double R = jp[(size_t)PX_RESTARTS_R * a.J + j];
-    int st = 0;
-    if (!(y.gamma >= 1.0 && y.gamma <= 10.0) || !(alpha_g >= 0.0) || !(beta_g >= 0.0) || !(y.alpha_sl >= 0.0) ||
-        !(y.beta_sl >= 0.0) || !(y.alpha_sn >= 0.0) || !(y.beta_sn >= 0.0) || !(q.phi > 0.0) || !(M0 >= 1.0) ||
-        !(Mmax >= M0) || !(w >= 0.0) || !(Mmax <= 4503599627370496.0) || !(alpha_g + beta_g > 0.0))
-        st |= PX_ST_BAD_PARAM;
-    if constexpr (CH == 0) {
-        const double m_mem = jp[(size_t)PX_M_MEM * a.J + j];
-        if (!(m_mem >= 1.0 && m_mem <= 2147483647.0)) st |= PX_ST_BAD_PARAM;
-    }
+    int st = job_status(load_grid_params(jp, a.J, j), load_sync(load_job(jp, a.J, j)), jp[(size_t)PX_WEIGHT * a.J + j]);
     // re-allocation penalty factor of Sec. 4.2
-    double factor = (T - R * a.delta) / (T + a.delta);
-    if constexpr (F32) factor = (double)(((float)T - (float)R * (float)a.delta) / ((float)T + (float)a.delta));
+    const double factor = (double)(((float)T - (float)R * (float)a.delta) / ((float)T + (float)a.delta));
     if (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
-    // does the job hold GPUs now?
-    long long csum = 0;
-    int neg = 0;
-    for (int n = lane; n < a.N; n += kWave) {
-        const int c = a.current_alloc[(size_t)j * a.N + n];
-        csum += c;
-        neg |= c < 0;
-    }
-    const long long total = wave_sum(csum);
-    if (__ballot(neg) != 0) st |= PX_ST_NEG_ALLOC;
-    // which 16-byte groups of the current row hold anything (rows that one 16-byte load per lane covers)
-    unsigned long long groups = 0ull;
-    if ((a.N & 3) == 0 && a.N <= 4 * kWave) {
-        bool any = false;
-        if (lane < (a.N >> 2)) {
-            const int32_t *g = a.current_alloc + (size_t)j * a.N + 4 * lane;
-            any = (g[0] | g[1] | g[2] | g[3]) != 0;
-        }
-        groups = __ballot(any);
-    }
-    // denominator of Eq. 15: the same sweep at the fair-share allocation
-    Best fair;
-    if constexpr (CH == 0)
-        fair = sweep_sampled(q, a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, a.fair_share[2 * j], a.fair_share[2 * j + 1]);
-    else if constexpr (F32)
-        fair = sweep_any_f32<CH>(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rsf, a.rk, a.Gm, a.Gs,
-                                 a.fair_share[2 * j], a.fair_share[2 * j + 1]);
-    else
-        fair = sweep<CH>(q, job_tables(a, j), a.rs, a.rk, a.Gm, a.Gs, a.fair_share[2 * j], a.fair_share[2 * j + 1]);
+    const CurrentRow cur = current_row(a, j);
+    if (cur.negative) st |= PX_ST_NEG_ALLOC;
+    const Best fair = sweep_any_f32<CH>(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rsf, a.rk, a.Gm, a.Gs,
+                                        a.fair_share[2 * j], a.fair_share[2 * j + 1]);
     if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
     if (lane == 0) {
         a.denom[j] = fair.goodput;
-        a.factor[j] = (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && total > 0) ? factor : 1.0;
-        a.running[j] = total > 0;
-        a.curmask[j] = groups;
-        if (st) atomicOr(a.status, st);
+        a.factor[j] = (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && cur.total > 0) ? factor : 1.0;
+        a.curmask[j] = cur.groups;
+        a.jobstat[j] = st;
     }
     if (j == 0 && lane < 16) a.zeros[lane] = 0;
 }
 
-// ---- memoised mode ---------------------------------------------------------------
-// The goodput model sees an allocation row only through K and through whether the job
-// sits on one node (Eq. 9), so the sweep of a pair equals the sweep of its (job, class, K).
-// One wavefront per (job, class, K <= kTableK) runs the sweep once; the population pass
-// then looks the result up (pairs_kernel with MEMO) and is bound by reading the
-// population.  Rows with K > kTableK are swept in place.  Results are identical.
-template <int CH, bool F32>
-__global__ void __launch_bounds__(256) memo_kernel(FitnessArgs a)
+// One wavefront per (job, class, K <= kTableK).
+template <int CH>
+__global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const long long row = (long long)blockIdx.x * kWavesPerBlock + wave;
@@ -1305,15 +1479,8 @@ __global__ void __launch_bounds__(256) memo_kernel(FitnessArgs a)
     const int nodes = ((row / kTableK) & 1) ? 1 : 2;
     const int j = (int)(row / (2 * kTableK));
     if (nodes == 1 && K > *a.k1) return;            // never looked up (tabled_row)
-    Best best;
-    if constexpr (CH == 0) best = sweep_sampled(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
-    else if constexpr (F32) best = sweep_any_f32<CH>(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rsf, a.rk, a.Gm, a.Gs, K, nodes);
-    else best = sweep<CH>(load_job(a.job_params, a.J, j), job_tables(a, j), a.rs, a.rk, a.Gm, a.Gs, K, nodes);
-    if (lane_id() == 0) {
-        MemoEntry e;
-        e.goodput = best.goodput; e.m = best.m; e.s = best.s;
-        a.memo[row] = e;
-    }
+    const Best best = sweep_any_f32<CH>(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rsf, a.rk, a.Gm, a.Gs, K, nodes);
+    if (lane_id() == 0) a.memo[row] = MemoEntry{best.goodput, best.m, best.s};
 }
 
 // ---- per (candidate, job) ------------------------------------------------------
@@ -1373,7 +1540,7 @@ pairs_kernel(FitnessArgs a)
     bool has_near = false;
     // (the instances whose rows fit one 16-byte load per lane fill the table after they have requested their first rows)
     constexpr bool kRowsFirst = CH != 0 && ROW1;
-    // every thread brings one entry, formed by the same division as the entry of a.rs (tables_kernel): no load, so
+    // every thread brings one entry, formed by the same division as the entry of a.rs (prepare_kernel): no load, so
     // storing it waits for nothing that is on its way from memory
     static_assert(kNearRecips <= kWavesPerBlock * kWave, "one entry per thread");
     const bool near_fits = CH != 0 && !MEMO && a.gs_pad <= kNearRecips;
@@ -1847,6 +2014,8 @@ pairs_kernel(FitnessArgs a)
             Best found;
             if constexpr (F32) {
                 found = sweep_f32(qf, tbb, b.rk, b.Gm, b.Gs, K, nodes);
+            } else if constexpr (MEMO) {
+                found = row_best(qb, load_grid_params(b.job_params, b.J, j), tbb.m, b.Gm, b.Gs, K, nodes == 1, false);
             } else {
                 const Pick pick = sweep_pick<CH, false>(qb, tbb, X, b.rs, b.rk, b.Gm, b.Gs, K, nodes);
                 found = price_point(qb, tbb, b.Gm, K, nodes == 1, pick.i, pick.s);
@@ -1887,7 +2056,8 @@ pairs_kernel(FitnessArgs a)
 }
 
 // ---- the argmax alone, for the consumers outside the search ----------------------------
-// One wavefront per query (job, K, nodes): the same sweep and pricing as a (candidate, job) pair.
+// One wavefront per query (job, K, nodes), found in place (row_best): the job tables would cost a call 72 rows per job
+// where it asks for one (or max_nodes + 1), and two launches (200 jobs, 17 queries each: 28 us with them).
 //   per_gpu mode   query (j, n), n = 0..max_nodes: column 0 is the job on one GPU, column n >= 1
 //                  the job on n full nodes of gpus_per_node GPUs; the goodput is divided by the
 //                  GPUs held (auto-scaling rule of Sec. 5.3.3)
@@ -1904,7 +2074,6 @@ struct QueryArgs {
     int32_t *finished;
 };
 
-template <int CH>
 __global__ void __launch_bounds__(256) queries_kernel(FitnessArgs a, QueryArgs q)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1924,7 +2093,9 @@ __global__ void __launch_bounds__(256) queries_kernel(FitnessArgs a, QueryArgs q
     K = __builtin_amdgcn_readfirstlane(K);             // one query per wavefront: the same in every lane
     nodes = __builtin_amdgcn_readfirstlane(nodes);
     Best best = {0.0, -1, -1};
-    if (K > 0) best = sweep<CH>(load_job(a.job_params, a.J, j), job_tables(a, j), a.rs, a.rk, a.Gm, a.Gs, K, nodes);
+    if (K > 0)
+        best = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs,
+                        K, nodes == 1, K <= kTableK);
     if (lane_id() != 0) return;
     if (q.mode == 0) {
         q.per_gpu[id] = best.goodput / (double)K;
@@ -1981,6 +2152,15 @@ __device__ __forceinline__ double pmean_finish(double mean, double p)
 }
 __device__ __forceinline__ float pmean_finish(float mean, float p) { return p == 0.0f ? expf(mean) : powf(mean, 1.0f / p); }
 
+// The status bits prepare_kernel has left per job go into the status word here: that kernel also clears the word, so no
+// wavefront of it may add to it.  Called by one workgroup of the call's last kernel.
+__device__ __forceinline__ void or_job_status(const FitnessArgs &a)
+{
+    int st = 0;
+    for (int j = threadIdx.x; j < a.J; j += blockDim.x) st |= a.jobstat[j];
+    if (st) atomicOr(a.status, st);
+}
+
 // REAL = double, or float for the fp32 variant (SPEEDUP, the penalty and the mean are then formed in fp32).
 template <typename REAL>
 __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
@@ -1994,6 +2174,7 @@ __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
     const int32_t *__restrict__ meta = a.meta + (size_t)c * a.J;
     const double *__restrict__ wt = a.job_params + (size_t)PX_WEIGHT * a.J;
 
+    if (a.or_job_status && blockIdx.x == 0) or_job_status(a);
     // SPEEDUP (Eq. 15) with the re-allocation penalty, then the generalized mean (Eq. 14):
     // each thread sums its jobs in ascending order, then a fixed tree
     REAL acc = 0, wsum = 0;
@@ -2148,6 +2329,7 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
     const int k1 = __builtin_amdgcn_readfirstlane(*a.k1);
     node_lds[t] = 0ull;
     if (t == 0) found_beyond = 0;
+    if (!BEYOND && a.or_job_status && blockIdx.x == 0) or_job_status(a);
     __syncthreads();
 
     double acc = 0.0, wsum = 0.0;
@@ -2259,7 +2441,8 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
                             const int K = __builtin_amdgcn_readlane(d_K, l);
                             const int nodes = __builtin_amdgcn_readlane(d_meta, l) & ~kMetaChanged;
                             const int j = jc + place(first) + l;
-                            const Best b = sweep<CH>(load_job(a.job_params, a.J, j), job_tables(a, j), a.rs, a.rk, a.Gm, a.Gs, K, nodes);
+                            const Best b = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
+                                                    a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
                             if (lane == l) {
                                 MemoEntry e;
                                 e.goodput = b.goodput; e.m = b.m; e.s = b.s;
@@ -2383,38 +2566,45 @@ static FitnessArgs job_level_args(const pollux_dims *d, const double *job_params
     return a;
 }
 
-// tables_kernel and, for the grid sweeps (not the sampling argmax), last_kernel: everything the sweep of a (job, K, nodes) needs
-static void launch_job_tables(const pollux_dims *d, const FitnessArgs &a, bool last_pass_tables, hipStream_t stream)
+// Rows (placement class, K) one wavefront of prepare_kernel takes.  Below 128 jobs eight rows each would leave SIMDs without
+// a wavefront (72 rows a job on nodes of 8 GPUs: 1152 wavefronts at 128 jobs), and the kernel lasts as long as one
+// wavefront's chain: two rows (30 jobs, memoised: 7.1 us against 10.9; 8 jobs: 6.2 against 7.3).  From there on the terms of
+// a batch size are formed once for eight rows (200 jobs: 14.8 us against 15.7; 1000 jobs: 70 against 91).
+template <int MODE>
+static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
 {
-    long long table_items = (long long)d->J * d->Gm;
-    if (table_items < a.gs_pad) table_items = a.gs_pad;
-    if (table_items < kRecipTable) table_items = kRecipTable;
-    hipLaunchKernelGGL(tables_kernel, dim3((unsigned)((table_items + 255) / 256)), dim3(256), 0, stream, a);
-    const long long lt_rows = (long long)d->J * 2 * kTableK;
-    if (last_pass_tables)
-        hipLaunchKernelGGL(last_kernel, dim3((unsigned)((lt_rows / kLastRows + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(256), 0, stream, a);
+    auto blocks = [&](int rows) {
+        const long long slots = ((long long)(a.J + 7) / 8) * prep_tasks(MODE, rows);
+        long long n = (slots + kWavesPerBlock - 1) / kWavesPerBlock * 8;
+        // a few jobs with many candidates: enough workgroups to clear the counters
+        const long long clear = a.clear_counters ? ((long long)a.P * a.N + 4095) / 4096 : 0;
+        return dim3((unsigned)(n < clear ? (clear < 1024 ? clear : 1024) : n));
+    };
+    if constexpr (MODE == kPrepSampled || MODE == kPrepSampledMemo) {
+        hipLaunchKernelGGL((prepare_kernel<1, MODE>), blocks(1), dim3(256), 0, stream, a);
+    } else {
+        if (a.J < 128) hipLaunchKernelGGL((prepare_kernel<2, MODE>), blocks(2), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((prepare_kernel<8, MODE>), blocks(8), dim3(256), 0, stream, a);
+    }
 }
 
-static int launch_queries(const pollux_dims *d, const double *job_params, const int32_t *m_grid, void *workspace,
-                          const QueryArgs &q, hipStream_t stream)
+static int launch_queries(const pollux_dims *d, const double *job_params, const int32_t *m_grid, const QueryArgs &q, hipStream_t stream)
 {
-    const FitnessArgs a = job_level_args(d, job_params, m_grid, workspace);
-    launch_job_tables(d, a, true, stream);
+    FitnessArgs a = {};
+    a.J = d->J; a.Gm = d->Gm; a.Gs = d->Gs;
+    a.m_grid = m_grid; a.job_params = job_params;
     const long long queries = (long long)d->J * (q.mode == 0 ? q.max_nodes + 1 : 1);
     const dim3 grid((unsigned)((queries + kWavesPerBlock - 1) / kWavesPerBlock));
-    const int ch = d->Gs <= 8 ? 8 : (d->Gs <= 16 ? 16 : 32);
-    if (ch == 8) hipLaunchKernelGGL((queries_kernel<8>), grid, dim3(256), 0, stream, a, q);
-    else if (ch == 16) hipLaunchKernelGGL((queries_kernel<16>), grid, dim3(256), 0, stream, a, q);
-    else hipLaunchKernelGGL((queries_kernel<32>), grid, dim3(256), 0, stream, a, q);
+    hipLaunchKernelGGL(queries_kernel, grid, dim3(256), 0, stream, a, q);
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
 }
 
 int launch_goodput_per_gpu(const pollux_dims *d, const double *job_params, const int32_t *m_grid, int gpus_per_node,
-                           int max_nodes, void *workspace, double *per_gpu, hipStream_t stream)
+                           int max_nodes, double *per_gpu, hipStream_t stream)
 {
     QueryArgs q = {};
     q.mode = 0; q.gpus_per_node = gpus_per_node; q.max_nodes = max_nodes; q.per_gpu = per_gpu;
-    return launch_queries(d, job_params, m_grid, workspace, q, stream);
+    return launch_queries(d, job_params, m_grid, q, stream);
 }
 
 int launch_autoscale(int J, int max_nodes, const double *per_gpu, const int32_t *nodes_now, double U, double L,
@@ -2427,12 +2617,12 @@ int launch_autoscale(int J, int max_nodes, const double *per_gpu, const int32_t 
 
 int launch_sim_tick(const pollux_dims *d, const double *job_params, const int32_t *m_grid, const int32_t *K,
                     const int32_t *nodes, const int32_t *changed, const double *target, double dt, double restart_delay,
-                    void *workspace, double *progress, double *goodput, int32_t *finished, hipStream_t stream)
+                    double *progress, double *goodput, int32_t *finished, hipStream_t stream)
 {
     QueryArgs q = {};
     q.mode = 1; q.K = K; q.nodes = nodes; q.changed = changed; q.target = target; q.dt = dt;
     q.restart_delay = restart_delay; q.progress = progress; q.goodput = goodput; q.finished = finished;
-    return launch_queries(d, job_params, m_grid, workspace, q, stream);
+    return launch_queries(d, job_params, m_grid, q, stream);
 }
 
 __global__ void copy_status_kernel(const int32_t *__restrict__ from, int32_t *__restrict__ to)
@@ -2460,10 +2650,9 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     a.population = population; a.fair_share = fair_share; a.current_alloc = current_alloc;
     a.node_capacity = node_capacity;
     a.p = p; a.delta = delta;
-    a.clear_status = 1;
     a.denom = (double *)(ws + L.denom);
     a.factor = (double *)(ws + L.factor);
-    a.running = (int32_t *)(ws + L.running);
+    a.jobstat = (int32_t *)(ws + L.jobstat);
     a.G = (double *)(ws + L.G);
     a.meta = (int32_t *)(ws + L.meta);
     a.memo = (MemoEntry *)(ws + L.memo);
@@ -2493,7 +2682,6 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     a.cand_groups = (int)((P_eff + per_wave * kWavesPerBlock - 1) / (per_wave * kWavesPerBlock));
     const unsigned pair_blocks = (unsigned)(8 * ((d->J + 7) / 8) * a.cand_groups);
 
-    const long long lt_rows = (long long)d->J * 2 * kTableK;
     const bool f32 = d->precision == 1;
     const bool memo = (d->flags & PX_FLAG_MEMOISE) != 0;
     const bool sampled = (d->flags & PX_FLAG_SAMPLE_M) != 0;       // fp64 only (checked by the caller)
@@ -2515,27 +2703,26 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         a.dirty = (int32_t *)(ws + L.dirty);
         hipLaunchKernelGGL(inherit_kernel, dim3((unsigned)P_eff), dim3(256), 0, stream, a);
     }
-    // done by tables_kernel, i.e. not by a call that keeps the job tables; the candidate pass keeps its counters on chip
+    // done by prepare_kernel, i.e. not by a call that keeps the job tables; the candidate pass keeps its counters on chip
     // and leaves those in memory alone, unless generations that inherit rows (and read them) are to follow
     a.clear_counters = (candidate_pass && !(d->flags & PX_FLAG_PAIR_RESULTS)) ? 0 : 1;
     if (!(d->flags & PX_FLAG_KEEP_JOB_TABLES)) {
         // everything that depends on the jobs only (not on the population)
-        launch_job_tables(d, a, !sampled, stream);
-        const dim3 job_grid((unsigned)((d->J + kWavesPerBlock - 1) / kWavesPerBlock));
-        if (sampled) hipLaunchKernelGGL((jobs_kernel<0, false>), job_grid, dim3(256), 0, stream, a);
-        else if (f32 && ch == 8) hipLaunchKernelGGL((jobs_kernel<8, true>), job_grid, dim3(256), 0, stream, a);
-        else if (f32) hipLaunchKernelGGL((jobs_kernel<16, true>), job_grid, dim3(256), 0, stream, a);
-        else if (ch == 8) hipLaunchKernelGGL((jobs_kernel<8, false>), job_grid, dim3(256), 0, stream, a);
-        else if (ch == 16) hipLaunchKernelGGL((jobs_kernel<16, false>), job_grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((jobs_kernel<32, false>), job_grid, dim3(256), 0, stream, a);
-        if (memo) {
-            const dim3 memo_grid((unsigned)((lt_rows + kWavesPerBlock - 1) / kWavesPerBlock));
-            if (sampled) hipLaunchKernelGGL((memo_kernel<0, false>), memo_grid, dim3(256), 0, stream, a);
-            else if (f32 && ch == 8) hipLaunchKernelGGL((memo_kernel<8, true>), memo_grid, dim3(256), 0, stream, a);
-            else if (f32) hipLaunchKernelGGL((memo_kernel<16, true>), memo_grid, dim3(256), 0, stream, a);
-            else if (ch == 8) hipLaunchKernelGGL((memo_kernel<8, false>), memo_grid, dim3(256), 0, stream, a);
-            else if (ch == 16) hipLaunchKernelGGL((memo_kernel<16, false>), memo_grid, dim3(256), 0, stream, a);
-            else hipLaunchKernelGGL((memo_kernel<32, false>), memo_grid, dim3(256), 0, stream, a);
+        a.or_job_status = 1;
+        if (sampled && memo) launch_prepare_rows<kPrepSampledMemo>(a, stream);
+        else if (sampled) launch_prepare_rows<kPrepSampled>(a, stream);
+        else if (f32) launch_prepare_rows<kPrepTables>(a, stream);
+        else if (memo) launch_prepare_rows<kPrepMemo>(a, stream);
+        else launch_prepare_rows<kPrepPlain>(a, stream);
+        if (f32) {
+            const dim3 job_grid((unsigned)((d->J + kWavesPerBlock - 1) / kWavesPerBlock));
+            if (ch == 8) hipLaunchKernelGGL((jobs_kernel_f32<8>), job_grid, dim3(256), 0, stream, a);
+            else hipLaunchKernelGGL((jobs_kernel_f32<16>), job_grid, dim3(256), 0, stream, a);
+            if (memo) {
+                const dim3 memo_grid((unsigned)(((long long)d->J * 2 * kTableK + kWavesPerBlock - 1) / kWavesPerBlock));
+                if (ch == 8) hipLaunchKernelGGL((memo_kernel_f32<8>), memo_grid, dim3(256), 0, stream, a);
+                else hipLaunchKernelGGL((memo_kernel_f32<16>), memo_grid, dim3(256), 0, stream, a);
+            }
         }
     }
     if (sweep_start) (void)hipEventRecord(sweep_start, stream);

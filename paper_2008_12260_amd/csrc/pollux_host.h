@@ -27,7 +27,7 @@ struct WorkspaceLayout {
     size_t rk;        // double [256]     1/K
     size_t denom;     // double [J]       fair-share goodput
     size_t factor;    // double [J]       re-allocation factor
-    size_t running;   // int32  [J]       job holds GPUs in current_alloc
+    size_t jobstat;   // int32  [J]       status bits of the job's parameters
     size_t G;         // double [P,J]     best goodput of the pair
     size_t meta;      // int32  [P,J]     nodes occupied by the row | changed flag
     size_t memo;      // 16 bytes [J,2,kTableK]  best point per (job, one node?, K) in memoised mode
@@ -67,7 +67,7 @@ inline WorkspaceLayout workspace_layout(const pollux_dims &d)
     L.rk = o;      o = up(o + 8 * 256);
     L.denom = o;   o = up(o + 8 * J);
     L.factor = o;  o = up(o + 8 * J);
-    L.running = o; o = up(o + 4 * J);
+    L.jobstat = o; o = up(o + 4 * J);
     L.G = o;       o = up(o + 8 * P * J);
     L.meta = o;    o = up(o + 4 * P * J);
     L.memo = o;    o = up(o + 16 * J * 2 * kTableK);
@@ -115,14 +115,14 @@ int launch_apply_best(const pollux_dims *d, const int32_t *population, const dou
                       int32_t *best, int32_t *K, int32_t *nodes, int32_t *changed, hipStream_t stream);
 
 int launch_goodput_per_gpu(const pollux_dims *d, const double *job_params, const int32_t *m_grid, int gpus_per_node,
-                           int max_nodes, void *workspace, double *per_gpu, hipStream_t stream);
+                           int max_nodes, double *per_gpu, hipStream_t stream);
 
 int launch_autoscale(int J, int max_nodes, const double *per_gpu, const int32_t *nodes_now, double U, double L,
                      int32_t *nodes_new, hipStream_t stream);
 
 int launch_sim_tick(const pollux_dims *d, const double *job_params, const int32_t *m_grid, const int32_t *K,
                     const int32_t *nodes, const int32_t *changed, const double *target, double dt, double restart_delay,
-                    void *workspace, double *progress, double *goodput, int32_t *finished, hipStream_t stream);
+                    double *progress, double *goodput, int32_t *finished, hipStream_t stream);
 
 int launch_fit_theta(int J, int max_obs, int max_iter, int n_starts, const int32_t *count, const int32_t *K, const int32_t *nodes,
                      const int32_t *m, const int32_t *s, const double *T, const double *init, double *theta,
