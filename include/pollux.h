@@ -50,7 +50,7 @@ typedef struct {
 enum {
     PX_FLAG_NO_REALLOC_PENALTY = 1,   /* skip the re-allocation penalty of Sec. 4.2         */
     PX_FLAG_NO_CONSTRAINT_CHECK = 2,  /* fitness is Eq. 14 even for infeasible candidates  */
-    PX_FLAG_MEMOISE = 4,              /* sweep the (m, s) grid once per (job, K, one node or several) instead of
+    PX_FLAG_MEMOISE = 4,              /* take the argmax over the (m, s) grid once per (job, K, one node or several) instead of
                                          once per (candidate, job): the goodput model (Eq. 4, 9) sees a row only
                                          through those; identical results, the population pass becomes a gather */
     PX_FLAG_KEEP_JOB_TABLES = 8,      /* reuse what the previous pollux_fitness call on this workspace derived from
@@ -67,7 +67,7 @@ enum {
     PX_FLAG_PAIR_RESULTS = 32         /* with PX_FLAG_MEMOISE: the call also leaves the goodput and the node count of
                                          every (candidate, job) pair in the workspace, which pollux_generation with
                                          PX_GA_INHERIT_ROWS reads (calls without PX_FLAG_MEMOISE leave them anyway;
-                                         a memoised call on rows of 65 to 256 nodes otherwise keeps them on chip,
+                                         a memoised call on rows of 4 to 256 nodes otherwise keeps them on chip,
                                          and the 12 bytes per pair cost it about a twentieth of its time). */
 };
 

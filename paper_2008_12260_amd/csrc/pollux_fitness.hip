@@ -98,9 +98,8 @@ struct FitnessArgs {
     int32_t *jobstat;             // [J] status bits of each job (prepare_kernel), OR-ed into the status word by the call's last kernel
     int32_t *meta;
     MemoEntry *memo;              // [J,2,kTableK] best point per (job, one node?, K), memoised mode only
-    int32_t *redo;                // [P] memoised mode: candidates left to the second instance of memo_candidates_kernel
-    unsigned long long *curmask;  // [J] rows of at most 256 entries in 16-byte groups: bit g set when group g of the job's
-                                  // current row holds a non-zero entry (prepare_kernel)
+    unsigned long long *curmask;  // [J] rows of at most 256 entries: bit g set when one of entries 4 g .. 4 g + 3 of the job's
+                                  // current row is not zero (prepare_kernel)
     int32_t *zeros;               // 64 zero bytes (prepare_kernel): what lanes read where the current row holds nothing
     unsigned long long *colpack;  // [P,N] per node: GPUs asked (low 40 bits, signed) + multi-node jobs present << 40
     int need_constraints;
@@ -133,6 +132,26 @@ constexpr int kStageBase = kNearU + kNearRecips + 8;
 constexpr int kStageDoubles = 2 * kStageGm + kStageRows * kStageRowDoubles;
 constexpr int kPending = -2;             // pairs kernel: grid index of a row whose sweep is still to be done
 constexpr int kMetaChanged = 1 << 30;   // meta[pair] = nodes | (row differs from current ? kMetaChanged : 0)
+
+// Four entries of a row in one 16-byte load; the hardware asks for the alignment of an entry only.
+typedef int Entries __attribute__((ext_vector_type(4), aligned(4)));
+
+// What lane l holds of a row of N >= 4 entries: entries base .. base + 3, of which the mask (all ones or zero per entry) keeps
+// those from 4 l on.  Lanes beyond the row load its last entries and keep none.
+struct RowLane {
+    int base;
+    Entries mask;
+};
+
+__device__ __forceinline__ RowLane row_lane(int l, int N)
+{
+    RowLane r;
+    const int first = 4 * l;
+    r.base = first < N - 4 ? first : N - 4;
+    const int skip = first < N ? first - r.base : 4;             // entries that belong to the lane before
+    r.mask = Entries{skip > 0 ? 0 : -1, skip > 1 ? 0 : -1, skip > 2 ? 0 : -1, skip > 3 ? 0 : -1};
+    return r;
+}
 
 // Parameters of one job (uniform across the wavefront).  The sweep itself needs only
 // phi and a = phi + M0; the synchronisation parameters are read where T_sync is formed.
@@ -1135,7 +1154,7 @@ __device__ __forceinline__ int job_status(const GridParams &g, const SyncParams 
 struct CurrentRow {
     long long total;                // GPUs the job holds now
     bool negative;                  // the row has a negative entry
-    unsigned long long groups;      // 16-byte groups that hold a non-zero entry (rows that one 16-byte load per lane covers)
+    unsigned long long groups;      // groups of four entries that hold a non-zero one (rows that one 16-byte load per lane covers)
 };
 
 __device__ __forceinline__ CurrentRow current_row(const FitnessArgs &a, int j)
@@ -1152,12 +1171,9 @@ __device__ __forceinline__ CurrentRow current_row(const FitnessArgs &a, int j)
     }
     out.total = wave_sum(sum);
     out.negative = __ballot(neg) != 0ull;
-    if ((a.N & 3) == 0 && a.N <= 4 * kWave) {
+    if (a.N <= 4 * kWave) {
         bool any = false;
-        if (lane < (a.N >> 2)) {
-            const int32_t *g = row + 4 * lane;
-            any = (g[0] | g[1] | g[2] | g[3]) != 0;
-        }
+        for (int n = 4 * lane; n < 4 * lane + 4 && n < a.N; ++n) any |= row[n] != 0;
         out.groups = __ballot(any);
     }
     return out;
@@ -2283,199 +2299,284 @@ __global__ void __launch_bounds__(256) inherit_kernel(FitnessArgs a)
 }
 
 // ---- memoised mode, one workgroup per candidate ---------------------------------------------------
-// With the sweeps looked up a candidate costs the reading of its matrix and little else, so one workgroup
+// With the argmaxes looked up a candidate costs the reading of its matrix and little else, so one workgroup
 // takes the whole candidate: it walks the matrix in memory order (four wavefronts, 64 consecutive rows each
-// per round of 256 jobs, four rows and the matching rows of the current allocation requested at a time, the
-// next four before the current ones are worked on, from one round straight into the next), keeps the per-node
-// counters of the constraint check in LDS (integer atomics: order-independent) and K, nodes and the changed flag
-// of every row in LDS as well.  After up to 1024 jobs the workgroup stops reading, and thread t finishes the
-// pairs of jobs t, t + 256, ... of those: looks the sweep's result up, forms SPEEDUP (Eq. 15) with the penalty
-// and its term of the generalized mean (Eq. 14).  (Finishing per round instead, between the requests, left the
-// memory system idle a tenth of the time.)  The terms are summed exactly as candidates_kernel sums them (thread
-// t over its jobs in ascending order, then the same tree), so the fitness is bit-identical to the plain mode's.
-// Nothing but the results leaves the chip.  For rows of 16-byte groups of at most 256 nodes, fp64, grid sweeps
-// (not the sampling argmax).
-// BEYOND = false: the instance for the common case.  A candidate with a row of more GPUs than the memo table
-// covers is left alone and flagged in a.redo[c]; the instance with BEYOND = true is launched after it, returns at
-// once for the candidates that are done and treats the flagged ones in full, such rows swept by their wavefront.
-// Split because the sweep costs the kernel twice the registers of everything else in it.
+// per round of 256 jobs), keeps the per-node counters of the constraint check in LDS (integer atomics:
+// order-independent) and K, nodes and the changed flag of every row in LDS as well.  After up to 1024 jobs the
+// workgroup stops reading, and thread t finishes the pairs of jobs t, t + 256, ... of those: looks the result up, forms
+// SPEEDUP (Eq. 15) with the penalty and its term of the generalized mean (Eq. 14).  (Finishing per round instead,
+// between the requests, left the memory system idle a tenth of the time.)  The terms are summed exactly as
+// candidates_kernel sums them (thread t over its jobs in ascending order, then the same tree), so the fitness is
+// bit-identical to the plain mode's.  Nothing but the results leaves the chip.
+// Rows of 4 to 256 entries, of any length and alignment: a lane's 16-byte load needs no more than the alignment of its
+// entries, the lane of a row's last entries takes the last four and masks those its neighbour has, and lanes beyond mask
+// all.  Rows of at most 64 entries (SHORT) come four to a load, 16 lanes each.
+//   2048 candidates of 900 jobs on 250 nodes: 1169 us with a wavefront per (candidate, job) reading entry by entry, 0.34 ms so.
+// KIND: the fp64 grid, the fp32 variant, or the sampling argmax.
+// CHILD: the children of a search step that inherits rows (see inherit_kernel for the rule): a row held unchanged takes over
+// the results of the row it was copied from, only the others are read back and looked up.  One launch in place of three
+// (inherit_kernel, pairs_kernel over the listed rows, candidates_kernel: 14 us a generation at 30 jobs, 15 at 200).  A child
+// that satisfies both constraints by construction has no violations; any other is evaluated in full, counters included.
+// Rows of more GPUs than the memo table covers are found in place by their wavefront when the chunk is finished.  (An instance
+// without that code, with a second launch for the candidates that need it, was no faster at any size: 4096 candidates of 1000
+// jobs on 256 nodes 957 us a call with the pair of launches, 856 with the one.)
+// PAIRS: the goodput and the node count of every pair are also left in the workspace (PX_FLAG_PAIR_RESULTS; CHILD does so).
 constexpr int kMemoChunkJobs = 4 * kCandThreads;    // jobs between two finishing steps
+constexpr int kMemoNodes = 4 * kWave;               // the longest row
+constexpr int kInherited = -1;                      // row_lds: the row takes over the results of candidate x
+enum MemoKind { kMemoGrid, kMemoF32, kMemoSampled };
 
-// PAIRS: the goodput and the node count of every pair are also left in the workspace (PX_FLAG_PAIR_RESULTS).
-template <int CH, bool BEYOND, bool PAIRS>
+template <int KIND, bool SHORT, bool CHILD, bool PAIRS>
 __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessArgs a)
 {
     static_assert(kCandThreads == 4 * kWave, "thread t of the workgroup is lane t % 64 of wavefront t / 64");
-    constexpr int kAhead = 4;
-    static_assert(kWave % (2 * kAhead) == 0, "a pass of the request loop never straddles two rounds");
-    __shared__ unsigned long long node_lds[4 * kWave];       // per node: GPUs asked + multi-node jobs << 40, as colpack
-    __shared__ int2 row_lds[kMemoChunkJobs];                  // per job of the chunk: K, nodes | changed flag
-    __shared__ MemoEntry beyond_lds[BEYOND ? kMemoChunkJobs : 1];   // per job of the chunk with K beyond the table: its sweep
-    __shared__ double red_acc[kCandThreads];
-    __shared__ double red_w[kCandThreads];
+    static_assert(!CHILD || PAIRS, "children: per-pair results kept");
+    using Real = typename std::conditional<KIND == kMemoF32, float, double>::type;
+    __shared__ unsigned long long node_lds[kMemoNodes];      // per node: GPUs asked + multi-node jobs << 40, as colpack
+    __shared__ int2 row_lds[kMemoChunkJobs];                 // per job of the chunk: K, nodes | changed flag; or candidate, kInherited
+    __shared__ uint16_t list_lds[CHILD ? kMemoChunkJobs : 1]; // positions in the chunk of the rows to read
+    __shared__ Real red_acc[kCandThreads];
+    __shared__ Real red_w[kCandThreads];
     __shared__ long long red_v[kCandThreads];
-    __shared__ int found_beyond;
+    __shared__ int listed;
     const int c = a.sel ? a.sel[blockIdx.x] : (int)blockIdx.x;
-    if constexpr (BEYOND) {
-        if (!a.redo[c]) return;
-    }
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
-    const int n4 = a.N >> 2;
-    const int lane4 = lane < n4 ? lane : n4 - 1;          // lanes past the end of a row load its last 16 bytes again
-    const unsigned long long in_row = __ballot(lane < n4);
     const double *__restrict__ wt = a.job_params + (size_t)PX_WEIGHT * a.J;
     const int k1 = __builtin_amdgcn_readfirstlane(*a.k1);
+    bool odd = true;                                         // CHILD: to be evaluated in full
+    const int32_t *__restrict__ src = nullptr;
+    if constexpr (CHILD) {
+        odd = __builtin_amdgcn_readfirstlane(a.odd[blockIdx.x]) != 0;
+        src = a.src_row + (size_t)blockIdx.x * a.J;
+    }
+    const bool count_nodes = a.need_constraints && odd;
     node_lds[t] = 0ull;
-    if (t == 0) found_beyond = 0;
-    if (!BEYOND && a.or_job_status && blockIdx.x == 0) or_job_status(a);
+    if (t == 0) listed = 0;
+    if (a.or_job_status && blockIdx.x == 0) or_job_status(a);
     __syncthreads();
 
-    double acc = 0.0, wsum = 0.0;
+    // what this lane holds of a row
+    const RowLane at_row = row_lane(SHORT ? (lane & 15) : lane, a.N);
+    auto load = [&](const int32_t *row) { return *(const Entries *)(row + at_row.base); };
+    // a row's share of the constraint counters: the few lanes that hold a non-zero entry (a job sits on few nodes) add
+    // their four entries, zeros included (a negative entry as it is): one branch per row instead of one per entry
+    auto add_to_nodes = [&](const Entries &w, int nodes) {
+        if (count_nodes && (w.x | w.y | w.z | w.w) != 0) {
+            const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
+            unsigned long long *to = node_lds + at_row.base;
+            atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
+            atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
+            atomicAdd(&to[2], (unsigned long long)(long long)w.z + (w.z > 0 ? one_job : 0ull));
+            atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
+        }
+    };
     bool any_neg = false;
+    // One row per load: K and nodes | changed of the row the wavefront holds, the same in every lane.
+    auto reduce_row = [&](const Entries &v, const Entries &was) {
+        const Entries w = v & at_row.mask, differs = (v ^ was) & at_row.mask;
+        const int K = wave_sum((w.x + w.y) + (w.z + w.w));
+        const int nodes = __popcll(__ballot(w.x > 0)) + __popcll(__ballot(w.y > 0)) + __popcll(__ballot(w.z > 0)) + __popcll(__ballot(w.w > 0));
+        const bool changed = __ballot((differs.x | differs.y | differs.z | differs.w) != 0) != 0;
+        any_neg |= __ballot((w.x | w.y | w.z | w.w) < 0) != 0;
+        add_to_nodes(w, nodes);
+        return make_int2(K, nodes | (changed ? kMetaChanged : 0));
+    };
+    // Four rows per load: the same for the row the lane's group of 16 lanes holds (live: it holds one).
+    auto reduce_rows = [&](const Entries &v, const Entries &was, bool live) {
+        const Entries mask = live ? at_row.mask : Entries{0, 0, 0, 0};
+        const Entries w = v & mask, differs = (v ^ was) & mask;
+        const int positive = (w.x > 0 ? 1 : 0) + (w.y > 0 ? 1 : 0) + (w.z > 0 ? 1 : 0) + (w.w > 0 ? 1 : 0);
+        // one word carries two small counts: positive entries (at most 64) and lanes that differ
+        const int counts = row16_sum(positive | ((differs.x | differs.y | differs.z | differs.w) != 0 ? 1 << 12 : 0));
+        const int K = row16_sum((w.x + w.y) + (w.z + w.w));
+        any_neg |= __ballot((w.x | w.y | w.z | w.w) < 0) != 0;
+        add_to_nodes(w, counts & 0xFFF);
+        return make_int2(K, (counts & 0xFFF) | ((counts >> 12) != 0 ? kMetaChanged : 0));
+    };
+
+    Real acc = 0, wsum = 0;
+    const Real p = (Real)a.p;
     for (int jc = 0; jc < a.J; jc += kMemoChunkJobs) {
         const int chunk_jobs = a.J - jc < kMemoChunkJobs ? a.J - jc : kMemoChunkJobs;
-        // Row q of this wavefront in the chunk is job  jc + (q / 64) * 256 + 64 * wave + q % 64  (position in the
-        // chunk: the same without jc); the wavefront has `rows` of them.
-        int tail = chunk_jobs % kCandThreads - kWave * wave;
-        tail = tail < 0 ? 0 : (tail > kWave ? kWave : tail);
-        const int rows = kWave * (chunk_jobs / kCandThreads) + tail;
-        auto place = [&](int q) { return (q >> 6) * kCandThreads + kWave * wave + (q & (kWave - 1)); };
-        if (rows > 0) {
-            const int4 *__restrict__ rowp = (const int4 *)(a.population + ((size_t)c * a.J + jc) * a.N) + lane4;
-            const int4 *__restrict__ curp = (const int4 *)(a.current_alloc + (size_t)jc * a.N) + lane4;
-            auto request = [&](int q0, int4 (&v)[kAhead]) {
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int q = q0 + u < rows ? q0 + u : rows - 1;               // the tail reads the last row again
-                    v[u] = rowp[(size_t)place(q) * n4];
+        const int32_t *__restrict__ pop = a.population + ((size_t)c * a.J + jc) * a.N;
+        const int32_t *__restrict__ cur = a.current_alloc + (size_t)jc * a.N;
+        if constexpr (CHILD) {
+            for (int at = t; at < chunk_jobs; at += kCandThreads) {
+                const int from = odd ? -1 : src[jc + at];
+                if (from >= 0) row_lds[at] = make_int2(from, kInherited);
+                else list_lds[atomicAdd(&listed, 1)] = (uint16_t)at;
+            }
+            __syncthreads();
+            const int rows = __builtin_amdgcn_readfirstlane(listed);
+            if constexpr (SHORT) {
+                for (int q0 = 4 * wave; q0 < rows; q0 += 4 * kWavesPerBlock) {
+                    const int q = q0 + (lane >> 4);
+                    const int at = list_lds[q < rows ? q : rows - 1];
+                    const int2 row = reduce_rows(load(pop + (size_t)at * a.N), load(cur + (size_t)at * a.N), q < rows);
+                    if (q < rows && (lane & 15) == 0) row_lds[at] = row;
                 }
-            };
-            // The rows of the current allocation come from L2 (shared by all candidates), and only the lanes whose
-            // 16-byte group of the current row holds anything read it (a.curmask, a scalar per row: a job sits on few
-            // nodes, so that is a lane or two); all other lanes read one block of zeros, which is what the current
-            // row holds there: a few cache lines per row through the vector cache instead of 1 KB.  Every lane
-            // loads either way, so the number of loads in flight is the same on every path and the waits can be
-            // exact.  The rows are requested when their batch is about to be worked on, not a batch ahead, which
-            // saves the registers of a second buffer, but BEFORE the next batch of the population is requested:
-            // loads complete in order, so waiting for them then leaves that next batch in flight.
-            // (the masks through the scalar cache: a vector load would make every use wait for all loads in flight)
-            typedef const unsigned long long __attribute__((address_space(4))) *ScalarMasks;
-            const ScalarMasks maskp = (ScalarMasks)a.curmask + jc;
-            const int4 *__restrict__ zerop = (const int4 *)a.zeros;
-            auto request_current = [&](int q0, int4 (&cv)[kAhead]) {
+            } else {
+                constexpr int kAhead = 4;
+                for (int q0 = wave; q0 < rows; q0 += kAhead * kWavesPerBlock) {
+                    Entries v[kAhead], was[kAhead];
+                    int at[kAhead];
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int at = place(q0 + u < rows ? q0 + u : rows - 1);
-                    cv[u] = *(((maskp[at] >> lane) & 1ull) ? curp + (size_t)at * n4 : zerop);
-                }
-            };
-            int d_K = 0, d_meta = 0;                        // lane r: K and nodes | changed of row q with q % 64 = r
-            auto work = [&](int q0, const int4 (&v)[kAhead], const int4 (&cv)[kAhead]) {
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int q = q0 + u * kWavesPerBlock;
+                        at[u] = __builtin_amdgcn_readfirstlane((int)list_lds[q < rows ? q : rows - 1]);
+                        v[u] = load(pop + (size_t)at[u] * a.N);
+                        was[u] = load(cur + (size_t)at[u] * a.N);
+                    }
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    if (q0 + u < rows) {
-                        const int4 w = v[u], was = cv[u];
-                        const int part = (w.x + w.y) + (w.z + w.w);
-                        const int K = wave_sum(lane < n4 ? part : 0);
-                        const int nodes = __popcll(__ballot(w.x > 0) & in_row) + __popcll(__ballot(w.y > 0) & in_row) +
-                                          __popcll(__ballot(w.z > 0) & in_row) + __popcll(__ballot(w.w > 0) & in_row);
-                        const bool changed = ((__ballot(w.x != was.x) | __ballot(w.y != was.y) | __ballot(w.z != was.z) | __ballot(w.w != was.w)) & in_row) != 0;
-                        any_neg |= (__ballot((w.x | w.y | w.z | w.w) < 0) & in_row) != 0;
-                        if (a.need_constraints && lane < n4 && (w.x | w.y | w.z | w.w) != 0) {
-                            // The few lanes that hold a non-zero entry (a job sits on few nodes) add their four
-                            // entries to the per-node counters, zeros included (a negative entry as it is): one
-                            // branch per row instead of one per entry.
-                            const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
-                            unsigned long long *to = node_lds + 4 * lane;
-                            atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
-                            atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
-                            atomicAdd(&to[2], (unsigned long long)(long long)w.z + (w.z > 0 ? one_job : 0ull));
-                            atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
-                        }
-                        if (lane == ((q0 + u) & (kWave - 1))) {
-                            d_K = K;
-                            d_meta = nodes | (changed ? kMetaChanged : 0);
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (q0 + u * kWavesPerBlock < rows) {
+                            const int2 row = reduce_row(v[u], was[u]);
+                            if (lane == 0) row_lds[at[u]] = row;
                         }
                     }
                 }
-            };
-            // Two buffers of kAhead rows: requests are in flight all the time.  A request past the end of the
-            // wavefront's rows reads its last row again (nothing works on it), so that every pass through the
-            // loop issues the same loads in the same order and each wait leaves exactly the next batch in flight.
-            int4 v0[kAhead], v1[kAhead], cv[kAhead];
-            request(0, v0);
-            // (the fences keep the compiler from issuing the requests in another order)
-            auto fence = [] {
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            for (int q0 = 0; q0 < rows; q0 += 2 * kAhead) {
-                request_current(q0, cv);
-                fence();
-                request(q0 + kAhead, v1);
-                fence();
-                work(q0, v0, cv);
-                fence();
-                request_current(q0 + kAhead, cv);
-                fence();
-                request(q0 + 2 * kAhead, v0);
-                fence();
-                work(q0 + kAhead, v1, cv);
-                fence();
-                // a round of 64 rows (or the last, shorter one) is complete: lane r puts its row's figures away
-                const int next = q0 + 2 * kAhead;
-                if ((next & (kWave - 1)) == 0 || next >= rows) {
-                    const int first = q0 & ~(kWave - 1);
-                    const int in_round = rows - first < kWave ? rows - first : kWave;
-                    const int at = place(first) + lane;
-                    if (lane < in_round) row_lds[at] = make_int2(d_K, d_meta);
-                    // rows beyond the memo table: swept and priced by the whole wavefront (BEYOND), or the candidate
-                    // is left to the instance that can
-                    unsigned long long pending = __ballot(lane < in_round && !tabled_row(d_K, (d_meta & ~kMetaChanged) == 1, k1));
-                    if constexpr (BEYOND) {
-                        while (pending) {
-                            const int l = __ffsll(pending) - 1;
-                            pending &= pending - 1;
-                            const int K = __builtin_amdgcn_readlane(d_K, l);
-                            const int nodes = __builtin_amdgcn_readlane(d_meta, l) & ~kMetaChanged;
-                            const int j = jc + place(first) + l;
-                            const Best b = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
-                                                    a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
-                            if (lane == l) {
-                                MemoEntry e;
-                                e.goodput = b.goodput; e.m = b.m; e.s = b.s;
-                                beyond_lds[at] = e;
+            }
+        } else {
+            // Row q of this wavefront in the chunk is job  jc + (q / 64) * 256 + 64 * wave + q % 64  (position in the
+            // chunk: the same without jc); the wavefront has `rows` of them.
+            int tail = chunk_jobs % kCandThreads - kWave * wave;
+            tail = tail < 0 ? 0 : (tail > kWave ? kWave : tail);
+            const int rows = kWave * (chunk_jobs / kCandThreads) + tail;
+            auto place = [&](int q) { return (q >> 6) * kCandThreads + kWave * wave + (q & (kWave - 1)); };
+            if constexpr (SHORT) {
+                constexpr int kAhead = 4;                   // loads in flight, of four rows each
+                for (int q0 = 0; q0 < rows; q0 += 4 * kAhead) {
+                    Entries v[kAhead], was[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int q = q0 + 4 * u + (lane >> 4);
+                        const int at = place(q < rows ? q : rows - 1);
+                        v[u] = load(pop + (size_t)at * a.N);
+                        was[u] = load(cur + (size_t)at * a.N);
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (q0 + 4 * u < rows) {
+                            const int q = q0 + 4 * u + (lane >> 4);
+                            const int2 row = reduce_rows(v[u], was[u], q < rows);
+                            if (q < rows && (lane & 15) == 0) row_lds[place(q)] = row;
+                        }
+                    }
+                }
+            } else if (rows > 0) {
+                constexpr int kAhead = 4;
+                static_assert(kWave % (2 * kAhead) == 0, "a pass of the request loop never straddles two rounds");
+                const int32_t *__restrict__ rowp = pop + at_row.base;
+                const int32_t *__restrict__ curp = cur + at_row.base;
+                auto request = [&](int q0, Entries (&v)[kAhead]) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int q = q0 + u < rows ? q0 + u : rows - 1;               // the tail reads the last row again
+                        v[u] = *(const Entries *)(rowp + (size_t)place(q) * a.N);
+                    }
+                };
+                // The rows of the current allocation come from L2 (shared by all candidates), and only the lanes whose
+                // group of four entries of the current row holds anything read it (a.curmask, a scalar per row: a job sits
+                // on few nodes, so that is a lane or two); all other lanes read one block of zeros, which is what the
+                // current row holds there: a few cache lines per row through the vector cache instead of 1 KB.  Every lane
+                // loads either way, so the number of loads in flight is the same on every path and the waits can be
+                // exact.  The rows are requested when their batch is about to be worked on, not a batch ahead, which
+                // saves the registers of a second buffer, but BEFORE the next batch of the population is requested:
+                // loads complete in order, so waiting for them then leaves that next batch in flight.
+                // (the masks through the scalar cache: a vector load would make every use wait for all loads in flight)
+                typedef const unsigned long long __attribute__((address_space(4))) *ScalarMasks;
+                const ScalarMasks maskp = (ScalarMasks)a.curmask + jc;
+                auto request_current = [&](int q0, Entries (&cv)[kAhead]) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int at = place(q0 + u < rows ? q0 + u : rows - 1);
+                        cv[u] = *(const Entries *)(((maskp[at] >> lane) & 1ull) ? curp + (size_t)at * a.N : a.zeros);
+                    }
+                };
+                int d_K = 0, d_meta = 0;                        // lane r: K and nodes | changed of row q with q % 64 = r
+                auto work = [&](int q0, const Entries (&v)[kAhead], const Entries (&cv)[kAhead]) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (q0 + u < rows) {
+                            const int2 row = reduce_row(v[u], cv[u]);
+                            if (lane == ((q0 + u) & (kWave - 1))) {
+                                d_K = row.x;
+                                d_meta = row.y;
                             }
                         }
-                    } else if (pending) {
-                        if (lane == 0) found_beyond = 1;
+                    }
+                };
+                // Two buffers of kAhead rows: requests are in flight all the time.  A request past the end of the
+                // wavefront's rows reads its last row again (nothing works on it), so that every pass through the
+                // loop issues the same loads in the same order and each wait leaves exactly the next batch in flight.
+                Entries v0[kAhead], v1[kAhead], cv[kAhead];
+                request(0, v0);
+                // (the fences keep the compiler from issuing the requests in another order)
+                auto fence = [] {
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                for (int q0 = 0; q0 < rows; q0 += 2 * kAhead) {
+                    request_current(q0, cv);
+                    fence();
+                    request(q0 + kAhead, v1);
+                    fence();
+                    work(q0, v0, cv);
+                    fence();
+                    request_current(q0 + kAhead, cv);
+                    fence();
+                    request(q0 + 2 * kAhead, v0);
+                    fence();
+                    work(q0 + kAhead, v1, cv);
+                    fence();
+                    // a round of 64 rows (or the last, shorter one) is complete: lane r puts its row's figures away
+                    const int next = q0 + 2 * kAhead;
+                    if ((next & (kWave - 1)) == 0 || next >= rows) {
+                        const int first = q0 & ~(kWave - 1);
+                        const int in_round = rows - first < kWave ? rows - first : kWave;
+                        if (lane < in_round) row_lds[place(first) + lane] = make_int2(d_K, d_meta);
                     }
                 }
             }
         }
         __syncthreads();                                    // the chunk's rows are all put away
-        if constexpr (!BEYOND) {
-            // (the outputs written so far for a flagged candidate are written again, in full, by the other instance)
-            if (found_beyond) {
-                if (t == 0) a.redo[c] = 1;
-                return;
-            }
-        }
         // thread t finishes the pairs of jobs jc + t, jc + t + 256, ...
-        for (int at = t; at < chunk_jobs; at += kCandThreads) {
+        for (int at0 = kWave * wave; at0 < chunk_jobs; at0 += kCandThreads) {
+            const int at = at0 + lane;
+            const bool mine = at < chunk_jobs;
+            const int2 row = mine ? row_lds[at] : make_int2(0, 0);
+            Best best = {0.0, -1, -1};
+            // rows beyond the memo table: found and priced by the whole wavefront, one after the other
+            unsigned long long pending = __ballot(row.y != kInherited && !tabled_row(row.x, (row.y & ~kMetaChanged) == 1, k1));
+            while (pending) {
+                const int l = __ffsll(pending) - 1;
+                pending &= pending - 1;
+                const int K = __builtin_amdgcn_readlane(row.x, l);
+                const int nodes = __builtin_amdgcn_readlane(row.y, l) & ~kMetaChanged;
+                const int j = jc + at0 + l;
+                Best found;
+                if constexpr (KIND == kMemoF32) found = sweep_f32(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rk, a.Gm, a.Gs, K, nodes);
+                else if constexpr (KIND == kMemoSampled) found = sweep_sampled(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
+                else found = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
+                                      a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
+                if (lane == l) best = found;
+            }
+            if (!mine) continue;
             const int j = jc + at;
             const size_t pair = (size_t)c * a.J + j;
-            const int2 row = row_lds[at];
-            const int d_K = row.x, d_meta = row.y;
-            const int nodes = d_meta & ~kMetaChanged;
-            Best best = {0.0, -1, -1};
-            if (d_K >= 1 && tabled_row(d_K, nodes == 1, k1)) {
-                const MemoEntry e = a.memo[((size_t)j * 2 + (nodes == 1 ? 1 : 0)) * kTableK + (d_K - 1)];
-                best.goodput = e.goodput; best.m = e.m; best.s = e.s;
-            } else if (BEYOND && d_K >= 1) {
-                const MemoEntry e = beyond_lds[at];
+            int d_meta = row.y;
+            if (CHILD && row.y == kInherited) {
+                const size_t from = (size_t)row.x * a.J + j;
+                best.goodput = a.G[from];
+                d_meta = a.meta[from];
+                if (a.best_m) {
+                    best.m = a.best_m[from];
+                    best.s = a.best_s[from];
+                }
+            } else if (row.x >= 1 && tabled_row(row.x, (d_meta & ~kMetaChanged) == 1, k1)) {
+                const MemoEntry e = a.memo[((size_t)j * 2 + ((d_meta & ~kMetaChanged) == 1 ? 1 : 0)) * kTableK + (row.x - 1)];
                 best.goodput = e.goodput; best.m = e.m; best.s = e.s;
             }
             if (a.best_m) {
@@ -2489,25 +2590,23 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
                 a.meta[pair] = d_meta;
             }
             // SPEEDUP (Eq. 15) with the re-allocation penalty, and the job's term of Eq. 14
-            const double d = a.denom[j];
-            double s_j = d > 0 ? best.goodput / d : 0.0;
-            if (d_meta & kMetaChanged) s_j = s_j * a.factor[j];
-            if (a.speedup) a.speedup[pair] = s_j;
-            acc += pmean_term(s_j, wt[j], a.p);
-            wsum += wt[j];
+            const Real d = (Real)a.denom[j];
+            Real s_j = d > 0 ? (Real)best.goodput / d : (Real)0;
+            if (d_meta & kMetaChanged) s_j = s_j * (Real)a.factor[j];
+            if (a.speedup) a.speedup[pair] = (double)s_j;
+            acc += pmean_term(s_j, (Real)wt[j], p);
+            wsum += (Real)wt[j];
         }
+        if (CHILD && t == 0) listed = 0;
         __syncthreads();                                    // before the next chunk's rows take their places
     }
     red_acc[t] = acc;
     red_w[t] = wsum;
-    if constexpr (!BEYOND) {
-        if (t == 0) a.redo[c] = 0;
-    }
     if (__ballot(any_neg) != 0ull && lane == 0) atomicOr(a.status, PX_ST_NEG_ALLOC);
 
     // constraint check: per node, multi-node jobs beyond the first and GPUs beyond capacity
     long long v = 0;
-    if (a.need_constraints && t < a.N) {
+    if (count_nodes && t < a.N) {
         const long long x = (long long)node_lds[t];
         const long long asked = (x << 24) >> 24;              // low 40 bits, sign-extended
         const long long distributed = (x - asked) >> 40;
@@ -2526,8 +2625,8 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
         __syncthreads();
     }
     if (t == 0) {
-        const double mean = red_acc[0] / red_w[0];
-        double f = pmean_finish(mean, a.p);
+        const Real mean = red_acc[0] / red_w[0];
+        double f = (double)pmean_finish(mean, p);
         const long long V = red_v[0];
         if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
         if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
@@ -2586,6 +2685,23 @@ static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
         if (a.J < 128) hipLaunchKernelGGL((prepare_kernel<2, MODE>), blocks(2), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((prepare_kernel<8, MODE>), blocks(8), dim3(256), 0, stream, a);
     }
+}
+
+// The population pass of memoised mode, P_eff workgroups.
+template <int KIND>
+static void launch_memo_candidates(const FitnessArgs &a, int P_eff, bool child, bool pairs_kept, hipStream_t stream)
+{
+    const dim3 grid((unsigned)P_eff), block(kCandThreads);
+    const bool short_rows = a.N <= kWave;
+#define PX_LAUNCH_MEMO(CHILD, PAIRS)                                                                                      \
+    do {                                                                                                                  \
+        if (short_rows) hipLaunchKernelGGL((memo_candidates_kernel<KIND, true, CHILD, PAIRS>), grid, block, 0, stream, a); \
+        else hipLaunchKernelGGL((memo_candidates_kernel<KIND, false, CHILD, PAIRS>), grid, block, 0, stream, a);          \
+    } while (0)
+    if (child) PX_LAUNCH_MEMO(true, true);
+    else if (pairs_kept) PX_LAUNCH_MEMO(false, true);
+    else PX_LAUNCH_MEMO(false, false);
+#undef PX_LAUNCH_MEMO
 }
 
 static int launch_queries(const pollux_dims *d, const double *job_params, const int32_t *m_grid, const QueryArgs &q, hipStream_t stream)
@@ -2656,7 +2772,6 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     a.G = (double *)(ws + L.G);
     a.meta = (int32_t *)(ws + L.meta);
     a.memo = (MemoEntry *)(ws + L.memo);
-    a.redo = (int32_t *)(ws + L.redo);
     a.curmask = (unsigned long long *)(ws + L.curmask);
     a.zeros = (int32_t *)(ws + L.zeros);
     a.colpack = (unsigned long long *)(ws + L.colpack);
@@ -2690,22 +2805,22 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     // untouched workspace and unchanged dimensions, does not clear them once more.
     const bool row1 = d->N <= 4 * kWave && (d->N & 3) == 0 && (((uintptr_t)population | (uintptr_t)current_alloc) & 15) == 0;
     const bool row4 = row1 && d->N <= kWave;        // four rows per load of a wavefront (cand_per_wave <= 16 holds)
-    // memoised pass over rows of 65 to 256 entries: one workgroup per candidate, counters in LDS, fitness included
     const bool inherit = inherit_rows && first_rank > 0;
-    // (not with row inheritance, whose rows to evaluate are listed per job, not per candidate)
-    const bool candidate_pass = memo && !sampled && !f32 && row1 && !row4 && !inherit;
+    // memoised pass over rows of 4 to 256 entries: one workgroup per candidate, counters in LDS, fitness included
+    const bool candidate_pass = memo && d->N >= 4 && d->N <= kMemoNodes;
     if (inherit) {
-        // the children of the step that has just run: unchanged rows take over their source's results; the others are
-        // listed per job and go through the population pass below like any pair
+        // the children of the step that has just run: unchanged rows take over their source's results
         a.src_row = (const int32_t *)(ws + L.src_row);
         a.odd = (const int32_t *)(ws + L.odd);
+    }
+    if (inherit && !candidate_pass) {
+        // the other rows are listed per job and go through the population pass below like any pair
         a.dirty_count = (int32_t *)(ws + L.dirty_count);
         a.dirty = (int32_t *)(ws + L.dirty);
         hipLaunchKernelGGL(inherit_kernel, dim3((unsigned)P_eff), dim3(256), 0, stream, a);
     }
     // done by prepare_kernel, i.e. not by a call that keeps the job tables; the candidate pass keeps its counters on chip
-    // and leaves those in memory alone, unless generations that inherit rows (and read them) are to follow
-    a.clear_counters = (candidate_pass && !(d->flags & PX_FLAG_PAIR_RESULTS)) ? 0 : 1;
+    a.clear_counters = candidate_pass ? 0 : 1;
     if (!(d->flags & PX_FLAG_KEEP_JOB_TABLES)) {
         // everything that depends on the jobs only (not on the population)
         a.or_job_status = 1;
@@ -2737,30 +2852,17 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     // the instance for the row length (four rows per load, one row per load, any) and the grid (whole groups of 64 batch sizes or not)
 #define PX_LAUNCH_PAIRS_GRID(CH, F32)                                          \
     do {                                                                       \
-        if (memo && row4) PX_LAUNCH_PAIRS(CH, F32, true, true, false, true);   \
-        else if (memo && row1) PX_LAUNCH_PAIRS(CH, F32, true, true, false, false); \
-        else if (memo) PX_LAUNCH_PAIRS(CH, F32, true, false, false, false);    \
+        if (memo) PX_LAUNCH_PAIRS(16, F32, true, false, false, false);         \
         else if (row4 && whole && near) PX_LAUNCH_PAIRS(CH, F32, false, true, true, true); \
         else if (row1 && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, false); \
         else if (row1) PX_LAUNCH_PAIRS(CH, F32, false, true, false, false);    \
         else PX_LAUNCH_PAIRS(CH, F32, false, false, false, false);             \
     } while (0)
     if (candidate_pass) {
-        const dim3 memo_grid((unsigned)P_eff);
-#define PX_LAUNCH_MEMO_CANDIDATES(CH)                                                                                 \
-    do {                                                                                                              \
-        if (d->flags & PX_FLAG_PAIR_RESULTS) {                                                                        \
-            hipLaunchKernelGGL((memo_candidates_kernel<CH, false, true>), memo_grid, dim3(kCandThreads), 0, stream, a); \
-            hipLaunchKernelGGL((memo_candidates_kernel<CH, true, true>), memo_grid, dim3(kCandThreads), 0, stream, a); \
-        } else {                                                                                                      \
-            hipLaunchKernelGGL((memo_candidates_kernel<CH, false, false>), memo_grid, dim3(kCandThreads), 0, stream, a); \
-            hipLaunchKernelGGL((memo_candidates_kernel<CH, true, false>), memo_grid, dim3(kCandThreads), 0, stream, a); \
-        }                                                                                                             \
-    } while (0)
-        if (ch == 8) PX_LAUNCH_MEMO_CANDIDATES(8);
-        else if (ch == 16) PX_LAUNCH_MEMO_CANDIDATES(16);
-        else PX_LAUNCH_MEMO_CANDIDATES(32);
-#undef PX_LAUNCH_MEMO_CANDIDATES
+        const bool pairs_kept = (d->flags & PX_FLAG_PAIR_RESULTS) != 0;
+        if (sampled) launch_memo_candidates<kMemoSampled>(a, P_eff, inherit, pairs_kept, stream);
+        else if (f32) launch_memo_candidates<kMemoF32>(a, P_eff, inherit, pairs_kept, stream);
+        else launch_memo_candidates<kMemoGrid>(a, P_eff, inherit, pairs_kept, stream);
         if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     } else if (sampled) {
