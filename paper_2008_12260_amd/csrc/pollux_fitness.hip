@@ -1505,8 +1505,11 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 // of one job then run on one XCD and its tables stay in that XCD's L2.  Each of the
 // four wavefronts walks cand_per_wave candidates of that job.
 
-// ROW1: the host has checked that a row is at most 256 entries, a multiple of four, and that
-// population and current_alloc are 16-byte aligned, so one 16-byte load per lane covers a row.
+// ROW1: the host has checked that a row has 4 to 256 entries, so one 16-byte load per lane covers it.
+// RAG: rows of any length and alignment (row_lane: the lane of a row's last entries takes the last four and masks those its
+// neighbour has).  Without it the host has checked that a row is whole 16-byte groups and that population and current_alloc
+// are 16-byte aligned: the masks cost an instruction per entry (200 jobs on 64 nodes: 53.6 us against 52.4), so whole grids
+// keep an instance without them.  (1021 candidates of 331 jobs on 130 nodes: 207 us entry by entry, 134 so.)
 // WHOLE: the host has checked that Gm is a multiple of 64 (tabled sweeps then skip the test for the end of the grid).
 // ROW4: ROW1 and a row is at most 64 entries, so one load of the wavefront covers the rows of four candidates
 // (16 lanes each); cand_per_wave is at most 16.
@@ -1528,7 +1531,7 @@ constexpr bool rows_at_a_time(int CH, bool F32, bool MEMO, bool ROW4) { return R
 
 // SEL = 2: per job, the candidates listed in a.dirty[j, 0 .. a.dirty_count[j]) (row inheritance: the rows of job j that a
 // move or a repair of the search step has changed); workgroups beyond a job's list return at once.
-template <int CH, bool F32, bool MEMO, bool ROW1, bool WHOLE = false, bool ROW4 = false, int SEL = 0>
+template <int CH, bool F32, bool MEMO, bool ROW1, bool WHOLE, bool ROW4, bool RAG, int SEL>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rows_at_a_time(CH, F32, MEMO, ROW4) ? 6 : 8)))
 pairs_kernel(FitnessArgs a)
 {
@@ -1589,11 +1592,27 @@ pairs_kernel(FitnessArgs a)
     const JobTables tb = job_tables(a, j);
     const int32_t *__restrict__ cur = a.current_alloc + (size_t)j * a.N;
     const bool vec4 = ROW1 || ((a.N & 3) == 0 && (((uintptr_t)a.population | (uintptr_t)a.current_alloc) & 15) == 0);
-    const int n4 = a.N >> 2;
-    int4 cur0 = {0, 0, 0, 0};                         // the lane's share of the job's current row (its first 256 entries)
-    if (vec4) cur0 = ((const int4 *)cur)[lane < n4 ? lane : n4 - 1];
-    const int lane4 = lane < n4 ? lane : n4 - 1;      // ROW1: lanes past the end of the row load its last 16 bytes again
+    const int n4 = RAG ? (a.N + 3) >> 2 : a.N >> 2;   // lanes that hold entries of a row (ROW1), 16-byte groups of a row
+    const int lane4 = lane < n4 ? lane : n4 - 1;      // lanes past the end of the row load its last 16 bytes again
     const unsigned long long in_row = __ballot(lane < n4);
+    // RAG: the lane's first entry of a row and which of the four it keeps; such a lane's loads take any alignment
+    const RowLane ragged = row_lane(ROW4 ? (lane & 15) : lane, RAG ? a.N : 4);
+    auto kept = [&](const int4 &v) {
+        if constexpr (RAG) return int4{v.x & ragged.mask.x, v.y & ragged.mask.y, v.z & ragged.mask.z, v.w & ragged.mask.w};
+        else return v;
+    };
+    // the lane's entries of a row of ROW1 as they are in memory; `kept` of them when they are used
+    auto load_entries = [&](const int32_t *from) {
+        if constexpr (RAG) {
+            const Entries e = *(const Entries *)(from + ragged.base);
+            return int4{e.x, e.y, e.z, e.w};
+        } else {
+            return ((const int4 *)from)[ROW4 ? ((lane & 15) < n4 ? (lane & 15) : n4 - 1) : lane4];
+        }
+    };
+    int4 cur0 = {0, 0, 0, 0};                         // the lane's share of the job's current row (its first 256 entries)
+    if constexpr (ROW1) cur0 = kept(load_entries(cur));
+    else if (vec4) cur0 = ((const int4 *)cur)[lane4];
     constexpr bool kDeferred = CH != 0;               // the grid sweeps of both precisions (not the sampling argmax)
     constexpr int kPriced = -3;                       // a row beyond the tables whose result lane r already holds (see below)
     int d_K = 0, d_meta = 0, d_i = -1, d_s = -1;      // lane r: what candidate r of this wavefront needs at the end
@@ -1638,7 +1657,7 @@ pairs_kernel(FitnessArgs a)
         bool changed = false, neg = false;
         int4 v0 = {0, 0, 0, 0};       // the lane's first four entries (the whole row when N <= 256)
         if constexpr (ROW1) {
-            const int4 v = have ? *have : ((const int4 *)row)[lane4];
+            const int4 v = have ? *have : kept(load_entries(row));
             v0 = v;
             if (!K_have) {
                 const int part = (v.x + v.y) + (v.z + v.w);
@@ -1690,7 +1709,7 @@ pairs_kernel(FitnessArgs a)
             const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
             if ((ROW1 || (vec4 && a.N <= 4 * kWave)) && !neg) {
                 // the row is still in registers and has no negative entry
-                const int nb = lane * 4;
+                const int nb = RAG ? ragged.base : lane * 4;
                 if (lane < n4) {
                     if (v0.x > 0) atomicAdd(&cp[nb + 0], (unsigned long long)v0.x + one_job);
                     if (v0.y > 0) atomicAdd(&cp[nb + 1], (unsigned long long)v0.y + one_job);
@@ -1720,10 +1739,10 @@ pairs_kernel(FitnessArgs a)
             static_assert(ROW1, "rows of 16-byte groups");
             const int g = lane >> 4, l16 = lane & 15;
             const bool in_row16 = l16 < n4;
-            const int lane_off = in_row16 ? l16 : n4 - 1;
-            const int4 *__restrict__ row1 = (const int4 *)(row + row_step) + lane_off;
-            unsigned long long *__restrict__ cp1 = cp + (size_t)kWavesPerBlock * a.N + 4 * l16;
-            const int4 curg = ((const int4 *)cur)[lane_off];
+            const int at16 = RAG ? ragged.base : 4 * l16;
+            const int32_t *__restrict__ row1 = row + row_step;
+            unsigned long long *__restrict__ cp1 = cp + (size_t)kWavesPerBlock * a.N + at16;
+            const int4 curg = cur0;
             constexpr int kBatches = kMaxCandPerWave / 4;
             int4 v[kBatches];
             int kb[kBatches] = {}, mb[kBatches] = {};
@@ -1734,9 +1753,9 @@ pairs_kernel(FitnessArgs a)
                     const int r = 4 * b + g < rows ? 4 * b + g : rows - 1;             // the tail reads the last row again
                     if constexpr (SEL != 0) {
                         cb[b] = __builtin_amdgcn_ds_bpermute(r << 2, d_c);
-                        v[b] = ((const int4 *)(a.population + ((size_t)cb[b] * a.J + j) * a.N))[lane_off];
+                        v[b] = load_entries(a.population + ((size_t)cb[b] * a.J + j) * a.N);
                     } else {
-                        v[b] = *(const int4 *)((const int32_t *)row1 + (size_t)r * row_step);
+                        v[b] = load_entries(row1 + (size_t)r * row_step);
                     }
                 }
             }
@@ -1746,7 +1765,7 @@ pairs_kernel(FitnessArgs a)
                 if (4 * b < rows) {
                     const int r = 4 * b + g;
                     const bool live = in_row16 && r < rows;
-                    const int4 w = v[b];
+                    const int4 w = kept(v[b]);
                     const int part = (w.x + w.y) + (w.z + w.w);
                     const int positive = (w.x > 0 ? 1 : 0) + (w.y > 0 ? 1 : 0) + (w.z > 0 ? 1 : 0) + (w.w > 0 ? 1 : 0);
                     const int differs = ((w.x != curg.x) | (w.y != curg.y) | (w.z != curg.z) | (w.w != curg.w)) ? 1 : 0;
@@ -1761,7 +1780,7 @@ pairs_kernel(FitnessArgs a)
                     if (a.need_constraints && live) {
                         // every non-zero entry goes to the candidate's per-node counters (a negative one as it is)
                         const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
-                        unsigned long long *__restrict__ to = SEL != 0 ? a.colpack + (size_t)cb[b] * a.N + 4 * l16
+                        unsigned long long *__restrict__ to = SEL != 0 ? a.colpack + (size_t)cb[b] * a.N + at16
                                                                   : cp1 + (size_t)r * kWavesPerBlock * a.N;
                         if (w.x != 0) atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
                         if (w.y != 0) atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
@@ -1791,8 +1810,8 @@ pairs_kernel(FitnessArgs a)
             const int32_t *__restrict__ row_first = row + row_step;       // the row of the wavefront's candidate 0 (SEL == 0)
             auto request = [&](int r, int4 &to) {
                 const int ru = r < rows ? r : rows - 1;                   // the tail reads the last row again
-                if constexpr (SEL != 0) to = ((const int4 *)row_of(ru))[lane4];
-                else to = ((const int4 *)(row_first + (size_t)ru * row_step))[lane4];
+                if constexpr (SEL != 0) to = load_entries(row_of(ru));
+                else to = load_entries(row_first + (size_t)ru * row_step);
             };
             // the rows of the first stretch are on their way while the workgroup fills its table in LDS
             if (r_last >= 0) {
@@ -1816,6 +1835,10 @@ pairs_kernel(FitnessArgs a)
 #pragma unroll
                 for (int u = 0; u < kAhead; u += 2) {
                     if (r0 + u < rows) {
+                        if constexpr (RAG) {
+                            v[u] = kept(v[u]);
+                            v[u + 1] = kept(v[u + 1]);
+                        }
                         const int4 &va = v[u], &vb = v[u + 1];
                         int wide = (__ballot((unsigned)(((va.x | va.y) | (va.z | va.w)) | ((vb.x | vb.y) | (vb.z | vb.w))) > 255u) & in_row) != 0 ? 1 : 0;
                         wide = __builtin_amdgcn_readfirstlane(wide);
@@ -2803,7 +2826,8 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     // The per-node counters start every call at zero.  A call that uses them leaves them at zero again
     // (candidates_kernel clears what it reads), so a call that keeps the job tables, whose caller guarantees an
     // untouched workspace and unchanged dimensions, does not clear them once more.
-    const bool row1 = d->N <= 4 * kWave && (d->N & 3) == 0 && (((uintptr_t)population | (uintptr_t)current_alloc) & 15) == 0;
+    const bool row1 = d->N >= 4 && d->N <= 4 * kWave;
+    const bool aligned = row1 && (d->N & 3) == 0 && (((uintptr_t)population | (uintptr_t)current_alloc) & 15) == 0;
     const bool row4 = row1 && d->N <= kWave;        // four rows per load of a wavefront (cand_per_wave <= 16 holds)
     const bool inherit = inherit_rows && first_rank > 0;
     // memoised pass over rows of 4 to 256 entries: one workgroup per candidate, counters in LDS, fitness included
@@ -2843,20 +2867,22 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     if (sweep_start) (void)hipEventRecord(sweep_start, stream);
     const bool whole = d->Gm % kWave == 0;
     const bool near = a.gs_pad <= kNearRecips;      // the kernels keep reciprocals and thresholds of all counts in LDS
-#define PX_LAUNCH_PAIRS(CH, F32, MEMO, ROW1, WHOLE, ROW4)                                                               \
-    do {                                                                                                                \
-        if (a.dirty) hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, 2>), dim3(pair_blocks), dim3(256), 0, stream, a); \
-        else if (a.sel) hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, 1>), dim3(pair_blocks), dim3(256), 0, stream, a); \
-        else hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, 0>), dim3(pair_blocks), dim3(256), 0, stream, a); \
+#define PX_LAUNCH_PAIRS(CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG)                                                               \
+    do {                                                                                                                     \
+        if (a.dirty) hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG, 2>), dim3(pair_blocks), dim3(256), 0, stream, a); \
+        else if (a.sel) hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG, 1>), dim3(pair_blocks), dim3(256), 0, stream, a); \
+        else hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG, 0>), dim3(pair_blocks), dim3(256), 0, stream, a); \
     } while (0)
     // the instance for the row length (four rows per load, one row per load, any) and the grid (whole groups of 64 batch sizes or not)
-#define PX_LAUNCH_PAIRS_GRID(CH, F32)                                          \
-    do {                                                                       \
-        if (memo) PX_LAUNCH_PAIRS(16, F32, true, false, false, false);         \
-        else if (row4 && whole && near) PX_LAUNCH_PAIRS(CH, F32, false, true, true, true); \
-        else if (row1 && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, false); \
-        else if (row1) PX_LAUNCH_PAIRS(CH, F32, false, true, false, false);    \
-        else PX_LAUNCH_PAIRS(CH, F32, false, false, false, false);             \
+#define PX_LAUNCH_PAIRS_GRID(CH, F32)                                                       \
+    do {                                                                                    \
+        if (memo) PX_LAUNCH_PAIRS(16, F32, true, false, false, false, false);               \
+        else if (row4 && aligned && whole && near) PX_LAUNCH_PAIRS(CH, F32, false, true, true, true, false);  \
+        else if (row4 && near) PX_LAUNCH_PAIRS(CH, F32, false, true, false, true, true);    \
+        else if (aligned && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, false, false); \
+        else if (row1 && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, false, true);   \
+        else if (row1) PX_LAUNCH_PAIRS(CH, F32, false, true, false, false, true);           \
+        else PX_LAUNCH_PAIRS(CH, F32, false, false, false, false, false);                   \
     } while (0)
     if (candidate_pass) {
         const bool pairs_kept = (d->flags & PX_FLAG_PAIR_RESULTS) != 0;
@@ -2866,8 +2892,8 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     } else if (sampled) {
-        if (memo) PX_LAUNCH_PAIRS(0, false, true, false, false, false);
-        else PX_LAUNCH_PAIRS(0, false, false, false, false, false);
+        if (memo) PX_LAUNCH_PAIRS(0, false, true, false, false, false, false);
+        else PX_LAUNCH_PAIRS(0, false, false, false, false, false, false);
     } else if (f32) {
         if (ch == 8) PX_LAUNCH_PAIRS_GRID(8, true);
         else PX_LAUNCH_PAIRS_GRID(16, true);
