@@ -6,11 +6,12 @@
 // at zero.
 //
 // One workgroup per job, one wavefront per starting point.  The lanes of a wavefront share the
-// job's records; everything about the seven unknowns is the same in every lane.  The error is a sum of squares of
+// job's records; of the seven unknowns lane i < 7 holds the i-th (value, scale, bounds, gradient, its row of the
+// matrix to factorise), and what all lanes need of them travels through scalar registers.  The error is a sum of squares of
 //     r_o = ln T_iter(theta; K_o, nodes_o, m_o, s_o) - ln T_o,
 // so the minimiser is a damped Gauss-Newton (Levenberg-Marquardt) iteration on the box:
 // per iteration the lanes form r_o and its seven partial derivatives, the wave reduces
-// SUM r^2, J^T r (7 sums) and J^T J (28 sums) in a fixed butterfly order, every lane
+// SUM r^2, J^T r (7 sums) and J^T J (28 sums) in a fixed binary tree (sum_terms),
 // solves the damped 7 x 7 system on the variables that are free (not held by a prior,
 // not at a bound with the gradient pointing outwards) by Cholesky factorisation, clips
 // the step to the box and accepts it if SUM r^2 went down.  The unknowns are scaled by
@@ -46,12 +47,70 @@ struct FitArgs {
     int32_t *iterations;
 };
 
-template <int STEP = 0>
-__device__ __forceinline__ double wave_sum_f64(double v)
+// The 36 sums over a wavefront, through LDS.  Sixteen at a time: every lane puts its terms into a row of its own, then lane
+// 16 q + k adds term k of the sixteen lanes of quarter q, and the quarters are added across lanes.  A butterfly per sum was
+// 648 vector instructions (six steps of two moves and an addition, 36 times) of an iteration's 1600; this is 120, in the same
+// binary tree ((0+1)+(2+3)) + ..., so every sum has the same bits.  Rows of 17 doubles keep writes and reads off each other's
+// banks.  The sums stay in LDS, where the solver reads them, and the unknowns are spread over lanes, so that four wavefronts fit
+// a SIMD, not two, and the 3000 chains of 1000 jobs with three starts run side by side: 2.44 ms a call before, 1.15 so.  What is
+// left is a chain of 3.5 us per iteration (100 jobs, 200 iterations: 0.70 ms), half of it the seven pivots of the solver.
+constexpr int kSums = 1 + 7 + 28;                       // SUM r^2, J^T r, J^T J
+constexpr int kSumRow = 17;
+constexpr int kSumTable = 64 * kSumRow;                 // doubles of one wavefront's table of terms
+constexpr int kWaveDoubles = kSumTable + 2 * kSums;     // and two sets of sums: of the iterate and of the trial
+
+// What the lanes of a wavefront write becomes visible to all of them: the LDS serves a wavefront's accesses in order, so only
+// the compiler has to keep them so.
+__device__ __forceinline__ void wave_fence()
 {
-    v += exchange<STEP>(v);
-    if constexpr (STEP < 5) return wave_sum_f64<STEP + 1>(v);
-    return v;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Lane 16 q + k: the sum of term FIRST + k over the lanes of quarter q (sixteen terms, or up to the last).
+template <int FIRST>
+__device__ __forceinline__ double sum_quarter(double *table, const double (&term)[kSums])
+{
+    constexpr int kCount = kSums - FIRST < 16 ? kSums - FIRST : 16;
+    const int lane = lane_id();
+    wave_fence();
+#pragma unroll
+    for (int k = 0; k < kCount; ++k) table[lane * kSumRow + k] = term[FIRST + k];
+    wave_fence();
+    const int k = lane & 15;
+    const double *column = table + (lane & 48) * kSumRow + (k < kCount ? k : 0);
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = column[i * kSumRow];
+#pragma unroll
+    for (int width = 1; width < 16; width *= 2) {
+#pragma unroll
+        for (int i = 0; i < 16; i += 2 * width) v[i] += v[i + width];
+    }
+    return v[0];
+}
+
+// All sums, to out[0 .. kSums-1].
+__device__ __forceinline__ void sum_terms(double *table, const double (&term)[kSums], double *out)
+{
+    static_assert(kSums > 32 && kSums <= 48, "three passes of sixteen");
+    double s0 = sum_quarter<0>(table, term), s1 = sum_quarter<16>(table, term), s2 = sum_quarter<32>(table, term);
+    // the quarters, all three together so that their exchanges overlap
+    s0 += exchange<4>(s0); s1 += exchange<4>(s1); s2 += exchange<4>(s2);
+    s0 += exchange<5>(s0); s1 += exchange<5>(s1); s2 += exchange<5>(s2);
+    const int lane = lane_id();
+    if (lane < 16) {
+        out[lane] = s0;
+        out[16 + lane] = s1;
+        if (lane < kSums - 32) out[32 + lane] = s2;
+    }
+    wave_fence();
+}
+
+// The value lane `src` holds, in every lane.
+__device__ __forceinline__ double wave_read(double v, int src)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src), __builtin_amdgcn_readlane(__double2loint(v), src));
 }
 
 __device__ __forceinline__ double uniform_f64(double v)
@@ -75,34 +134,25 @@ __device__ __forceinline__ Record load_record(const FitArgs &f, size_t at)
     return r;
 }
 
-// SUM r^2, J^T r and J^T J of one job at theta = z * scale.
-struct Normal {
-    double sse;
-    double g[kTheta];
-    double a[kPacked];
-};
-
-// mine: the record of lane l when the job has at most 64 of them (held: read once per job, kept in registers
-// over all iterations); otherwise the records are read from memory in every evaluation.
-__device__ __forceinline__ Normal normal_equations(const FitArgs &f, int j, int n, const double (&z)[kTheta],
-                                                   const double (&scale)[kTheta], const Record &mine, bool held_records)
+// The sums of one job at theta = z * scale (lane i < 7 holds the i-th of each), in `out` (LDS): SUM r^2, then J^T r, then J^T J as a packed lower triangle.
+// HELD: the job has at most 64 records and `mine` is lane l's (read once per job, kept in registers over all iterations);
+// otherwise the records are read from memory in every evaluation.
+template <bool HELD>
+__device__ __forceinline__ void normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale, const Record &mine,
+                                                 double *table, double *out)
 {
     const int lane = lane_id();
-    double th[kTheta];
+    const double my_th = my_z * my_scale;
+    double th[kTheta], scale[kTheta];
 #pragma unroll
-    for (int i = 0; i < kTheta; ++i) th[i] = z[i] * scale[i];
+    for (int i = 0; i < kTheta; ++i) {
+        th[i] = wave_read(my_th, i);
+        scale[i] = wave_read(my_scale, i);
+    }
     const double gamma = th[PX_GAMMA], inv_gamma = 1.0 / gamma;
 
-    Normal acc;
-    acc.sse = 0.0;
-#pragma unroll
-    for (int i = 0; i < kTheta; ++i) acc.g[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < kPacked; ++i) acc.a[i] = 0.0;
-
-    const size_t base = (size_t)j * f.max_obs;
-    for (int o = lane; o < n; o += kWave) {
-        const Record rec = held_records ? mine : load_record(f, base + o);
+    // the residual of one record and its derivatives with respect to z
+    auto evaluate = [&](const Record &rec, double &r, double (&d)[kTheta]) {
         const int K = rec.K, nodes = rec.nodes;
         const double md = rec.md, sd = rec.sd;
         const double lnT = rec.lnT;
@@ -129,9 +179,8 @@ __device__ __forceinline__ Normal normal_equations(const FitArgs &f, int j, int 
             dlnl_dg = (w_g * lntg + w_s * lnts) * inv_gamma - lnsum * inv_gamma * inv_gamma;
         }
         const double pred = sd * tg + last;                                               // Eq. 11
-        const double r = px_log(pred) - lnT;
+        r = px_log(pred) - lnT;
         const double inv_pred = px_div(1.0, pred);
-        double d[kTheta];
         d[PX_ALPHA_G] = (sd + dl_dtg) * inv_pred;
         d[PX_BETA_G] = d[PX_ALPHA_G] * md;
         const double dts = dl_dts * inv_pred;
@@ -142,79 +191,92 @@ __device__ __forceinline__ Normal normal_equations(const FitArgs &f, int j, int 
         d[PX_GAMMA] = last * dlnl_dg * inv_pred;
 #pragma unroll
         for (int i = 0; i < kTheta; ++i) d[i] *= scale[i];
-        acc.sse = px_fma(r, r, acc.sse);
+    };
+    double term[kSums];
+    // the record's terms: r^2; d_i r; d_i d_k, k <= i, row by row
+    auto add = [&](double r, const double (&d)[kTheta]) {
+        term[0] = px_fma(r, r, term[0]);
 #pragma unroll
         for (int i = 0; i < kTheta; ++i) {
-            acc.g[i] = px_fma(d[i], r, acc.g[i]);
+            term[1 + i] = px_fma(d[i], r, term[1 + i]);
 #pragma unroll
-            for (int k = 0; k <= i; ++k) acc.a[i * (i + 1) / 2 + k] = px_fma(d[i], d[k], acc.a[i * (i + 1) / 2 + k]);
+            for (int k = 0; k <= i; ++k) term[1 + kTheta + i * (i + 1) / 2 + k] = px_fma(d[i], d[k], term[1 + kTheta + i * (i + 1) / 2 + k]);
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < kSums; ++t) term[t] = 0.0;
+    if constexpr (HELD) {
+        double r, d[kTheta];
+        evaluate(mine, r, d);
+        if (lane >= n) {
+            r = 0.0;
+#pragma unroll
+            for (int i = 0; i < kTheta; ++i) d[i] = 0.0;
+        }
+        add(r, d);
+    } else {
+        const size_t base = (size_t)j * f.max_obs;
+        for (int o = lane; o < n; o += kWave) {
+            double r, d[kTheta];
+            evaluate(load_record(f, base + o), r, d);
+            add(r, d);
         }
     }
-    Normal out;
-    out.sse = uniform_f64(wave_sum_f64(acc.sse));
-#pragma unroll
-    for (int i = 0; i < kTheta; ++i) out.g[i] = uniform_f64(wave_sum_f64(acc.g[i]));
-#pragma unroll
-    for (int i = 0; i < kPacked; ++i) out.a[i] = uniform_f64(wave_sum_f64(acc.a[i]));
-    return out;
+    sum_terms(table, term, out);
 }
 
-// Solves (A + lambda diag(A)) x = -g on the free variables (bit i of `held` set: x_i = 0) by Cholesky
-// factorisation of the packed lower triangle.  Returns false if a pivot is not positive.
-__device__ __forceinline__ bool damped_step(const Normal &q, double lambda, unsigned held, double (&x)[kTheta])
+// Solves (A + lambda diag(A)) x = -g on the free variables (bit i of `held` set: x_i = 0) by Cholesky factorisation.
+// Lane i < 7 holds row i and returns x_i; per column the pivot, its reciprocal (one division; the entries below it and both
+// substitutions multiply by it) and the column's entries are known to all lanes.  Every entry takes its subtractions in
+// ascending order of the column, as in the textbook's row-by-row form.  Returns false if a pivot is not positive.
+__device__ __forceinline__ bool damped_step(const double *sums, double lambda, unsigned held, double &x)
 {
-    double l[kPacked];
-    double b[kTheta];
+    const int lane = lane_id();
+    const int row = lane < kTheta ? lane : kTheta - 1;                  // (the lanes beyond repeat the last row)
+    const double *g = sums + 1, *a = sums + 1 + kTheta;
+    const bool mine_held = (held >> row) & 1u;
+    const double dii = a[row * (row + 3) / 2];
+    const double diagonal = mine_held ? 1.0 : dii + lambda * (dii > 1e-300 ? dii : 1e-300);
+    double w[kTheta];
 #pragma unroll
-    for (int i = 0; i < kTheta; ++i) {
-        const bool hi = (held >> i) & 1u;
-#pragma unroll
-        for (int k = 0; k < i; ++k) l[i * (i + 1) / 2 + k] = (hi || ((held >> k) & 1u)) ? 0.0 : q.a[i * (i + 1) / 2 + k];
-        const double dii = q.a[i * (i + 1) / 2 + i];
-        l[i * (i + 1) / 2 + i] = hi ? 1.0 : dii + lambda * (dii > 1e-300 ? dii : 1e-300);
-        b[i] = hi ? 0.0 : -q.g[i];
+    for (int k = 0; k < kTheta; ++k) {
+        const double entry = a[row * (row + 1) / 2 + k];                // (right of the diagonal: some other entry, never used)
+        w[k] = row == k ? diagonal : ((mine_held || ((held >> k) & 1u)) ? 0.0 : entry);
     }
-    // (one division per pivot: the entries below it and both substitutions multiply by its reciprocal)
-    double inv[kTheta];
-    bool ok = true;
+    double b = mine_held ? 0.0 : -g[row];
+    double l[kPacked], inv[kTheta], y[kTheta];
 #pragma unroll
-    for (int i = 0; i < kTheta; ++i) {
+    for (int k = 0; k < kTheta; ++k) {
+        const double pivot = wave_read(w[k], k);
+        if (!(pivot > 0.0)) return false;
+        inv[k] = 1.0 / sqrt(pivot);
+        const double column = w[k] * inv[k];
+        y[k] = wave_read(b, k) * inv[k];
+        b = px_fma(-column, y[k], b);
 #pragma unroll
-        for (int k = 0; k <= i; ++k) {
-            double s = l[i * (i + 1) / 2 + k];
-#pragma unroll
-            for (int t = 0; t < k; ++t) s = px_fma(-l[i * (i + 1) / 2 + t], l[k * (k + 1) / 2 + t], s);
-            if (k == i) {
-                if (!(s > 0.0)) { ok = false; s = 1.0; }
-                l[i * (i + 1) / 2 + i] = sqrt(s);
-                inv[i] = 1.0 / l[i * (i + 1) / 2 + i];
-            } else {
-                l[i * (i + 1) / 2 + k] = s * inv[k];
-            }
+        for (int i = k + 1; i < kTheta; ++i) {
+            l[i * (i + 1) / 2 + k] = wave_read(column, i);
+            w[i] = px_fma(-column, l[i * (i + 1) / 2 + k], w[i]);
         }
-    }
-    // forward then backward substitution
-#pragma unroll
-    for (int i = 0; i < kTheta; ++i) {
-        double s = b[i];
-#pragma unroll
-        for (int t = 0; t < i; ++t) s = px_fma(-l[i * (i + 1) / 2 + t], b[t], s);
-        b[i] = s * inv[i];
     }
 #pragma unroll
     for (int i = kTheta - 1; i >= 0; --i) {
-        double s = b[i];
+        double s = y[i];
 #pragma unroll
-        for (int t = i + 1; t < kTheta; ++t) s = px_fma(-l[t * (t + 1) / 2 + i], x[t], s);
-        x[i] = s * inv[i];
+        for (int t = i + 1; t < kTheta; ++t) s = px_fma(-l[t * (t + 1) / 2 + i], y[t], s);
+        y[i] = s * inv[i];
+        x = lane == i ? y[i] : x;
     }
-    return ok;
+    return true;
 }
 
 constexpr int kMaxStarts = 5;
 
-__global__ void __launch_bounds__(64 * kMaxStarts) fit_theta_kernel(FitArgs f)
+// Dynamic LDS: kWaveDoubles doubles per wavefront.  HELD: no job has more than 64 records.
+template <bool HELD>
+__global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_per_eu(3, 8))) fit_theta_kernel(FitArgs f)
 {
+    extern __shared__ __align__(16) double fit_lds[];
     __shared__ double end_sse[kMaxStarts];
     __shared__ double end_z[kMaxStarts][kTheta];
     __shared__ int end_it[kMaxStarts];
@@ -255,9 +317,8 @@ __global__ void __launch_bounds__(64 * kMaxStarts) fit_theta_kernel(FitArgs f)
     }
     const double t_min = uniform_f64(best);
     // the usual case, at most one record per lane: each lane keeps its record for the whole fit
-    const bool held_records = n <= kWave;
     Record mine = {1, 1, 1.0, 0.0, 0.0};
-    if (held_records && lane < n) mine = load_record(f, base + lane);
+    if (HELD && lane < n) mine = load_record(f, base + lane);
     const double m_at = (double)f.m[base + (size_t)__builtin_amdgcn_readfirstlane(best_o)];
 
     // priors (Sec. 4.1, "Prior-driven exploration"): parameters without evidence are held at zero
@@ -265,23 +326,18 @@ __global__ void __launch_bounds__(64 * kMaxStarts) fit_theta_kernel(FitArgs f)
     if (max_k <= 1) prior |= (1u << PX_ALPHA_SL) | (1u << PX_BETA_SL) | (1u << PX_ALPHA_SN) | (1u << PX_BETA_SN);
     if (max_nodes <= 1) prior |= (1u << PX_ALPHA_SN) | (1u << PX_BETA_SN);
     if (max_k <= 2) prior |= (1u << PX_BETA_SL) | (1u << PX_BETA_SN);
-    // Held in a vector register on purpose: everything derived from it (the active set, the iterate) then lives in
-    // vector registers, which this kernel has to spare, instead of in scalar registers, which it would spill.
-    asm("" : "+v"(prior));
-
-    double start[kTheta] = {t_min * 0.5, t_min / (2.0 * m_at), t_min / 10.0, t_min / 100.0, t_min / 10.0, t_min / 100.0, 2.0};
-    if (f.init) {
-#pragma unroll
-        for (int i = 0; i < kTheta; ++i) start[i] = f.init[(size_t)i * f.J + j];
-    }
-    double scale[kTheta], lo[kTheta], hi[kTheta];
-#pragma unroll
-    for (int i = 0; i < kTheta; ++i) {
-        if ((prior >> i) & 1u) start[i] = 0.0;
-        scale[i] = (i != PX_GAMMA && start[i] > 0.0) ? start[i] : 1.0;
-        lo[i] = i == PX_GAMMA ? 1.0 : 0.0;
-        hi[i] = i == PX_GAMMA ? 10.0 : __builtin_inf();
-    }
+    prior = (unsigned)__builtin_amdgcn_readfirstlane((int)prior);
+    // lane i < 7: what the iteration keeps of unknown i (the lanes beyond hold nothing that is read)
+    const bool is_sync = lane >= PX_ALPHA_SL && lane <= PX_BETA_SN, is_gamma = lane == PX_GAMMA;
+    const bool my_prior = lane < kTheta && ((prior >> lane) & 1u);
+    // the default starting value of this lane's sync parameter
+    const double sync_default = (lane == PX_ALPHA_SL || lane == PX_ALPHA_SN) ? t_min / 10.0 : t_min / 100.0;
+    double start = is_gamma ? 2.0 : (is_sync ? sync_default : (lane == PX_ALPHA_G ? t_min * 0.5 : t_min / (2.0 * m_at)));
+    if (f.init && lane < kTheta) start = f.init[(size_t)lane * f.J + j];
+    if (my_prior) start = 0.0;
+    const double scale = (!is_gamma && start > 0.0) ? start : 1.0;
+    const double lo = is_gamma ? 1.0 : 0.0, hi = is_gamma ? 10.0 : __builtin_inf();
+    constexpr unsigned kAll = (1u << kTheta) - 1u;
 
     // The error has several local minima (and a flat spot at T_sync = 0 when gamma > 1), so the iteration is
     // run from a few starting points, one per wavefront, and the best end point is kept (the first one on
@@ -292,115 +348,111 @@ __global__ void __launch_bounds__(64 * kMaxStarts) fit_theta_kernel(FitArgs f)
     {
         const bool two_phase = k == 1 || k == 2;
         const double sync_factor = (k == 3) ? 3.0 : (k == 4 ? 0.3 : 1.0);
-        const double gamma0 = (k == 0) ? start[PX_GAMMA] : (k == 1 ? 2.0 : (k == 3 ? 1.2 : 5.0));
-        // the default starting values of the sync parameters, in the units of z (used where one has to leave zero)
-        const double sync_a = (t_min / 10.0), sync_b = (t_min / 100.0);
-        double z[kTheta];
-#pragma unroll
-        for (int i = 0; i < kTheta; ++i) {
-            double v = start[i];
-            if (i >= PX_ALPHA_SL && i <= PX_BETA_SN) v *= sync_factor;
-            if (i == PX_GAMMA) v = two_phase ? 1.0 : gamma0;
-            v /= scale[i];
-            z[i] = v < lo[i] ? lo[i] : (v > hi[i] ? hi[i] : v);
+        const double gamma0 = (k == 0) ? wave_read(start, PX_GAMMA) : (k == 1 ? 2.0 : (k == 3 ? 1.2 : 5.0));
+        double z;
+        {
+            double v = start;
+            if (is_sync) v *= sync_factor;
+            if (is_gamma) v = two_phase ? 1.0 : gamma0;
+            v /= scale;
+            z = v < lo ? lo : (v > hi ? hi : v);
         }
 
-        Normal cur;
+        double *table = fit_lds + k * kWaveDoubles, *cur = table + kSumTable, *trial = cur + kSums;
+        double cur_sse = 0.0;
         int it = 0;
-        // The damped Gauss-Newton iteration from z, until it converges or the budget of steps is spent;
-        // the variables in `hold` stay where they are.  Leaves the end point in z and its sums in cur.
-        auto descend = [&](unsigned hold) {
-            cur = normal_equations(f, j, n, z, scale, mine, held_records);
-            double lambda = 1e-3;
-            while (it < f.max_iter && cur.sse > 0.0) {
-                ++it;
-                unsigned held = hold;
-#pragma unroll
-                for (int i = 0; i < kTheta; ++i) {
-                    if ((z[i] <= lo[i] && cur.g[i] > 0.0) || (z[i] >= hi[i] && cur.g[i] < 0.0)) held |= 1u << i;
-                }
-                // a free variable that sits on a bound and would be pushed across it joins the held set
-                double step[kTheta];
-                bool solved = false;
-                for (int pass = 0; pass < kTheta + 1; ++pass) {
-                    solved = damped_step(cur, lambda, held, step);
-                    if (!solved) break;
-                    unsigned more = 0u;
-#pragma unroll
-                    for (int i = 0; i < kTheta; ++i) {
-                        if (!((held >> i) & 1u) && ((z[i] <= lo[i] && step[i] < 0.0) || (z[i] >= hi[i] && step[i] > 0.0))) more |= 1u << i;
-                    }
-                    if (!more) break;
-                    held |= more;
-                }
-                if (!solved) {
-                    lambda *= 10.0;
-                    if (lambda > 1e15) break;
-                    continue;
-                }
-                double zn[kTheta];
-                double moved = 0.0;
-#pragma unroll
-                for (int i = 0; i < kTheta; ++i) {
-                    double v = ((held >> i) & 1u) ? z[i] : z[i] + step[i];
-                    v = v < lo[i] ? lo[i] : (v > hi[i] ? hi[i] : v);
-                    zn[i] = v;
-                    const double rel = fabs(v - z[i]) / (fabs(z[i]) + 1e-12);
-                    moved = rel > moved ? rel : moved;
-                }
-                if (moved == 0.0) break;
-                const Normal trial = normal_equations(f, j, n, zn, scale, mine, held_records);
-                if (trial.sse < cur.sse) {
-                    const double gain = (cur.sse - trial.sse) / cur.sse;
-#pragma unroll
-                    for (int i = 0; i < kTheta; ++i) z[i] = zn[i];
+        // Up to four descents, written as one loop so that the iteration is in the code once (inlined four times it was 110 KB,
+        // more than the instruction cache, and the wavefronts of a compute unit are all somewhere else in it): with gamma
+        // held at 1 (two-phase starts), the descent proper, and one more for either sync pair that has ended at zero.
+#pragma unroll 1
+        for (int phase = two_phase ? 0 : 1; phase < 4; ++phase) {
+            const double z_before = z, sse_before = cur_sse;
+            if (phase >= 2) {
+                // A sync pair that has ended at zero may only be stuck there: with T_sync = 0 and gamma > 1 the error
+                // does not feel the pair at all (the flat spot).  It is put back to its default starting value once, the
+                // others staying where they are, and the iteration is continued; the better end point is kept.
+                const int ia = phase == 2 ? PX_ALPHA_SL : PX_ALPHA_SN, ib = ia + 1;
+                const unsigned zero = (unsigned)__ballot(z == 0.0);
+                const bool stuck = !((prior >> ia) & 1u) && ((zero >> ia) & 1u) && (((prior | zero) >> ib) & 1u);
+                if (!(stuck && it < f.max_iter && cur_sse > 0.0)) continue;
+                if (lane == ia) z = sync_default / scale;
+            }
+            // The damped Gauss-Newton iteration from z, until it converges or the budget of steps is spent; the
+            // variables in `hold` stay where they are.  Leaves the end point in z and its error in cur_sse.
+            const unsigned hold = phase == 0 ? prior | (1u << PX_GAMMA) : prior;
+            double lambda = 1e-3, moved = 0.0, zn = z;
+            bool first = true;
+            for (;;) {
+                normal_equations<HELD>(f, j, n, zn, scale, mine, table, trial);
+                const double trial_sse = uniform_f64(trial[0]);
+                if (first || trial_sse < cur_sse) {
+                    const double gain = (cur_sse - trial_sse) / cur_sse;
+                    z = zn;
+                    double *sums = cur;
                     cur = trial;
-                    lambda = lambda * 0.2 > 1e-15 ? lambda * 0.2 : 1e-15;
-                    if (gain < 1e-13 && moved < 1e-9) break;
+                    trial = sums;
+                    cur_sse = trial_sse;
+                    if (!first) {
+                        lambda = lambda * 0.2 > 1e-15 ? lambda * 0.2 : 1e-15;
+                        if (gain < 1e-13 && moved < 1e-9) break;
+                    }
+                    first = false;
                 } else {
                     lambda *= 5.0;
                     if (lambda > 1e15 || moved < 1e-15) break;
                 }
-            }
-        };
-
-        if (two_phase) {
-            descend(prior | (1u << PX_GAMMA));
-            z[PX_GAMMA] = gamma0;
-#pragma unroll
-            for (int i = PX_ALPHA_SL; i <= PX_BETA_SN; ++i) {
-                const double least = 0.1 * ((i == PX_ALPHA_SL || i == PX_ALPHA_SN) ? sync_a : sync_b) / scale[i];
-                if (!((prior >> i) & 1u) && z[i] < least) z[i] = least;
-            }
-        }
-        descend(prior);
-        // A sync pair that has ended at zero may only be stuck there: with T_sync = 0 and gamma > 1 the error
-        // does not feel the pair at all (the flat spot).  It is put back to its default starting value once, the
-        // others staying where they are, and the iteration is continued; the better end point is kept.
-#pragma unroll
-        for (int pair = 0; pair < 2; ++pair) {
-            const int ia = pair == 0 ? PX_ALPHA_SL : PX_ALPHA_SN, ib = ia + 1;
-            const bool stuck = !((prior >> ia) & 1u) && z[ia] == 0.0 && (((prior >> ib) & 1u) || z[ib] == 0.0);
-            if (stuck && it < f.max_iter && cur.sse > 0.0) {
-                double z_before[kTheta];
-#pragma unroll
-                for (int i = 0; i < kTheta; ++i) z_before[i] = z[i];
-                const double sse_before = cur.sse;
-                z[ia] = sync_a / scale[ia];
-                descend(prior);
-                if (!(cur.sse < sse_before)) {
-#pragma unroll
-                    for (int i = 0; i < kTheta; ++i) z[i] = z_before[i];
-                    cur.sse = sse_before;
+                // the next trial point
+                bool found = false;
+                while (!found && it < f.max_iter && cur_sse > 0.0) {
+                    ++it;
+                    const double g = cur[1 + (lane < kTheta ? lane : 0)];
+                    unsigned held = hold | ((unsigned)__ballot((z <= lo && g > 0.0) || (z >= hi && g < 0.0)) & kAll);
+                    // a free variable that sits on a bound and would be pushed across it joins the held set
+                    double step = 0.0;
+                    bool solved = false;
+#pragma unroll 1
+                    for (int pass = 0; pass < kTheta + 1; ++pass) {
+                        solved = damped_step(cur, lambda, held, step);
+                        if (!solved) break;
+                        const unsigned more = (unsigned)__ballot((z <= lo && step < 0.0) || (z >= hi && step > 0.0)) & kAll & ~held;
+                        if (!more) break;
+                        held |= more;
+                    }
+                    if (!solved) {
+                        lambda *= 10.0;
+                        if (lambda > 1e15) break;
+                        continue;
+                    }
+                    const double v = ((held >> (lane & 31)) & 1u) ? z : z + step;
+                    zn = v < lo ? lo : (v > hi ? hi : v);
+                    // the largest relative change of an unknown (lanes 0 .. 7 among themselves)
+                    const double rel = lane < kTheta ? fabs(zn - z) / (fabs(z) + 1e-12) : 0.0;
+                    double most = rel > 0.0 ? rel : 0.0, other = exchange<0>(most);
+                    most = other > most ? other : most;
+                    other = exchange<1>(most);
+                    most = other > most ? other : most;
+                    other = exchange<2>(most);
+                    most = other > most ? other : most;
+                    moved = wave_read(most, 0);
+                    if (moved == 0.0) break;
+                    found = true;
                 }
+                if (!found) break;
+            }
+            if (phase == 0) {
+                if (is_gamma) z = gamma0;
+                const double least = 0.1 * sync_default / scale;
+                if (is_sync && !my_prior && z < least) z = least;
+            } else if (phase >= 2 && !(cur_sse < sse_before)) {
+                z = z_before;
+                cur_sse = sse_before;
             }
         }
         if (lane == 0) {
-            end_sse[k] = cur.sse;
+            end_sse[k] = cur_sse;
             end_it[k] = it;
-#pragma unroll
-            for (int i = 0; i < kTheta; ++i) end_z[k][i] = z[i];
         }
+        if (lane < kTheta) end_z[k][lane] = z;
     }
     __syncthreads();
     if (k != 0) return;
@@ -411,14 +463,7 @@ __global__ void __launch_bounds__(64 * kMaxStarts) fit_theta_kernel(FitArgs f)
         if (end_sse[c] < end_sse[best_k]) best_k = c;
     }
     const double best_sse = end_sse[best_k];
-    if (lane < kTheta) {
-        double sc = 1.0;
-#pragma unroll
-        for (int i = 0; i < kTheta; ++i) {
-            if (lane == i) sc = scale[i];
-        }
-        f.theta[(size_t)lane * f.J + j] = end_z[best_k][lane] * sc;
-    }
+    if (lane < kTheta) f.theta[(size_t)lane * f.J + j] = end_z[best_k][lane] * scale;
     if (lane == 0) {
         f.rmsle[j] = sqrt(best_sse / (double)n);
         if (f.iterations) f.iterations[j] = total_it;
@@ -433,7 +478,10 @@ int launch_fit_theta(int J, int max_obs, int max_iter, int n_starts, const int32
     f.J = J; f.max_obs = max_obs; f.max_iter = max_iter; f.n_starts = n_starts;
     f.count = count; f.K = K; f.nodes = nodes; f.m = m; f.s = s; f.T = T; f.init = init;
     f.theta = theta; f.rmsle = rmsle; f.iterations = iterations;
-    hipLaunchKernelGGL(fit_theta_kernel, dim3((unsigned)J), dim3(64 * (unsigned)n_starts), 0, stream, f);
+    const size_t lds = sizeof(double) * kWaveDoubles * (size_t)n_starts;
+    const dim3 grid((unsigned)J), block(64 * (unsigned)n_starts);
+    if (max_obs <= kWave) hipLaunchKernelGGL(fit_theta_kernel<true>, grid, block, lds, stream, f);
+    else hipLaunchKernelGGL(fit_theta_kernel<false>, grid, block, lds, stream, f);
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
 }
 

@@ -1,0 +1,33 @@
+"""The fit at the record counts where its lanes, quarters of a wavefront and launch instances end: records held in registers
+(at most 64 per job) and records read in every evaluation give the same bits, and both reach the checker's error."""
+import numpy as np
+import pytest
+
+import oracle.theta as TH
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_starts", [1, 2, 3, 5])
+@pytest.mark.parametrize("counts", [[1], [2, 15, 16, 17], [31, 32, 33, 47, 48, 49], [63, 64, 1]])
+def test_records_in_registers_and_in_memory(counts, n_starts):
+    import paper_2008_12260_amd as px
+    J = len(counts)
+    ob = W.observations(W.custom("records", P=1, J=J, N=4, cap=4, Gm=8, Gs=4, index=800 + counts[0]), max_obs=64)
+    rng = np.random.default_rng(counts[0])
+    for j, n in enumerate(counts):                     # every slot a real record, however many the generator drew
+        have = int(ob["count"][j])
+        for k in ("K", "nodes", "m", "s", "T"):
+            ob[k][j, have:] = ob[k][j, rng.integers(0, have, 64 - have)]
+        ob["count"][j] = n
+    held = px.fit_theta(ob, n_starts=n_starts)
+    wider = {k: (v if k == "count" else np.concatenate([v, np.ones((J, 7), v.dtype)], axis=1)) for k, v in ob.items()}
+    read = px.fit_theta(wider, n_starts=n_starts)
+    for k in held:
+        assert np.array_equal(held[k], read[k]), k
+    for j, n in enumerate(counts):
+        rec = tuple(ob[k][j, :n] for k in ("K", "nodes", "m", "s", "T"))
+        want = TH.rmsle(held["theta"][:, j], *rec)
+        assert abs(held["rmsle"][j] - want) <= 1e-12 * want + 1e-13     # residuals are differences of logarithms of size 1
+        assert np.all(held["theta"][:6, j] >= 0.0) and 1.0 <= held["theta"][6, j] <= 10.0
