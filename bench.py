@@ -260,7 +260,7 @@ def main():
     extra["memoised_population_bytes_per_s"] = 4.0 * cfg.P * cfg.J * cfg.N / (extra["memoised_fitness_call_ms"] * 1e-3)
     del mcall_memo
 
-    # the argmax by sampling total batch sizes (Sec. 4.3): Gm evaluations of Eq. 4 per pair instead of Gm x Gs; its
+    # the argmax by sampling total batch sizes (Sec. 4.3): Gm evaluations of Eq. 4 per argmax instead of Gm x Gs; its
     # own figure, not part of the headline (the grid row of a job then lists total batch sizes)
     swl = W.sampled(wl)
     scall = px.FitnessCall(cfg.P, cfg.J, cfg.N, cfg.Gm, cfg.Gs, swl.job_params, swl.m_grid, swl.fair_share,
@@ -275,7 +275,8 @@ def main():
     s1.record(stream)
     torch.cuda.synchronize()
     extra["sampled_fitness_call_ms"] = s0.elapsed_time(s1) / 5
-    extra["sampled_evals_per_s"] = cfg.P * cfg.J * cfg.Gm / (extra["sampled_fitness_call_ms"] * 1e-3)
+    # evaluations made: the argmax is taken once per (job, GPU count up to 64 or the largest node's, placement)
+    extra["sampled_evals_per_s"] = cfg.J * (64 + cfg.cap) * cfg.Gm / (extra["sampled_fitness_call_ms"] * 1e-3)
     del scall, swl
 
     if not args.no_ga_loop:

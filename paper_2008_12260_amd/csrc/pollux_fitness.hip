@@ -2821,8 +2821,14 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const unsigned pair_blocks = (unsigned)(8 * ((d->J + 7) / 8) * a.cand_groups);
 
     const bool f32 = d->precision == 1;
-    const bool memo = (d->flags & PX_FLAG_MEMOISE) != 0;
     const bool sampled = (d->flags & PX_FLAG_SAMPLE_M) != 0;       // fp64 only (checked by the caller)
+    // The sampling argmax of a pair depends on (job, K, one node or several) only, as the grid's does, and each of its list
+    // entries takes a last pass of Eq. 10 (no table holds it): from as many candidates on as a job has rows to take the argmax
+    // of (64, and one per GPU of the largest node), the call takes them once per row whether PX_FLAG_MEMOISE asks for it or
+    // not (200 jobs, 1000 candidates: 165 us a call with an argmax per pair, 30 so).  P is the same in all calls that
+    // share a workspace, so a generation finds the rows its fitness call has left.
+    const bool sampled_rows = sampled && d->P >= 2 * kTableK && d->N >= 4 && d->N <= kMemoNodes;
+    const bool memo = (d->flags & PX_FLAG_MEMOISE) != 0 || sampled_rows;
     // The per-node counters start every call at zero.  A call that uses them leaves them at zero again
     // (candidates_kernel clears what it reads), so a call that keeps the job tables, whose caller guarantees an
     // untouched workspace and unchanged dimensions, does not clear them once more.
@@ -2885,7 +2891,7 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         else PX_LAUNCH_PAIRS(CH, F32, false, false, false, false, false);                   \
     } while (0)
     if (candidate_pass) {
-        const bool pairs_kept = (d->flags & PX_FLAG_PAIR_RESULTS) != 0;
+        const bool pairs_kept = (d->flags & PX_FLAG_PAIR_RESULTS) != 0 || !(d->flags & PX_FLAG_MEMOISE);
         if (sampled) launch_memo_candidates<kMemoSampled>(a, P_eff, inherit, pairs_kept, stream);
         else if (f32) launch_memo_candidates<kMemoF32>(a, P_eff, inherit, pairs_kept, stream);
         else launch_memo_candidates<kMemoGrid>(a, P_eff, inherit, pairs_kept, stream);
