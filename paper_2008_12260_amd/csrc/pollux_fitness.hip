@@ -1023,6 +1023,32 @@ __device__ __forceinline__ void scan_chunk_f32(float &kmin, float C, ScalarFloat
     }
 }
 
+// The accumulation count with the smallest w(s) among all counts of the grid, equal values to the lower count.
+template <int CH>
+__device__ __forceinline__ int scan_argmin_f32(float C, const RunStepsF32 &X, ScalarFloats rsc, int Gs)
+{
+    // argmin of w over all counts: chunk by chunk, values relative to the chunk's first count
+    float wmin;
+    scan_chunk_f32<CH>(wmin, C, rsc, X);
+    int s_star = __float_as_int(wmin) & 15;
+    for (int s0 = CH; s0 < Gs; s0 += CH) {
+        float w;
+        scan_chunk_f32<CH>(w, C, rsc + s0, X);
+        const float moved = w + (float)s0;                               // strictly smaller only: ties keep the smaller s
+        if (moved < wmin) {
+            wmin = moved;
+            s_star = s0 + (__float_as_int(w) & 15);
+        }
+    }
+    // neighbours in their exact order (the tags may have swapped two that agree to 2^-19)
+    {
+        const float sd = (float)s_star;
+        const float t_lo = s_star > 0 ? fmaf(sd, sd, sd) : -1.0f, t_hi = fmaf(sd, sd, fmaf(3.0f, sd, 2.0f));
+        s_star = C <= t_lo ? s_star - 1 : (C > t_hi ? s_star + 1 : s_star);
+    }
+    return s_star;
+}
+
 // All 64 lanes call this with the same (job, 1 <= K <= kTableK, nodes); every lane returns the same result.
 // rsf: 1/(s+1) in fp32, padded to a multiple of 32 counts; near: a copy of it in LDS when has_near.
 template <int CH, bool WHOLE>
@@ -1061,25 +1087,7 @@ __device__ __forceinline__ Pick sweep_pick_f32(const JobF32 &q, const JobTables 
         const int bounds = srow[il];
         const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
         const bool feasible = active && s_lo <= s_hi;
-        // argmin of w over all counts: chunk by chunk, values relative to the chunk's first count
-        float wmin;
-        scan_chunk_f32<CH>(wmin, C, rsc, X);
-        int s_star = __float_as_int(wmin) & 15;
-        for (int s0 = CH; s0 < Gs; s0 += CH) {
-            float w;
-            scan_chunk_f32<CH>(w, C, rsc + s0, X);
-            const float moved = w + (float)s0;                               // strictly smaller only: ties keep the smaller s
-            if (moved < wmin) {
-                wmin = moved;
-                s_star = s0 + (__float_as_int(w) & 15);
-            }
-        }
-        // neighbours in their exact order (the tags may have swapped two that agree to 2^-19)
-        {
-            const float sd = (float)s_star;
-            const float t_lo = s_star > 0 ? fmaf(sd, sd, sd) : -1.0f, t_hi = fmaf(sd, sd, fmaf(3.0f, sd, 2.0f));
-            s_star = C <= t_lo ? s_star - 1 : (C > t_hi ? s_star + 1 : s_star);
-        }
+        const int s_star = scan_argmin_f32<CH>(C, X, rsc, Gs);
         int s_c = s_star < s_hi ? s_star : s_hi;
         s_c = s_c > s_lo ? s_c : s_lo;
         const float r_c = has_near ? near[s_c] : rsf[s_c];
@@ -1104,6 +1112,54 @@ __device__ __forceinline__ Pick sweep_pick_f32(const JobF32 &q, const JobTables 
     const int wl = __ffsll(winners) - 1;
     const int wwhere = __builtin_amdgcn_readlane(where, wl);
     return Pick{(wwhere >> 16) * kWave + wl, wwhere & 0xFFFF};
+}
+
+// The same election for four (job, K, placement) at once, one per row of 16 lanes, as sweep_pick_rows does in fp64: lane l of
+// a row takes batch sizes l, l + 16, ...; every lane of a row returns (i << 16) | s of the row's point, or -1.  Per (K, batch
+// size) the arithmetic is that of sweep_pick_f32.
+template <int CH, bool WHOLE>
+__device__ __forceinline__ int sweep_pick_rows_f32(const JobF32 &q, const JobTables &tb, const RunStepsF32 &X, const float *__restrict__ rsf,
+                                                   int Gm, int Gs, int K, bool one_node, LdsFloats near, bool has_near)
+{
+    const int l16 = lane_id() & 15;
+    const float Kf = (float)K;
+    float ts = 0.0f;                                                          // Eq. 9
+    if (K > 1) ts = one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
+    // byte offsets inside one job's tables, 32 bits each (see sweep_pick_rows)
+    const unsigned l_row = (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm * 8u;
+    const unsigned s_row = (unsigned)(K - 1) * (unsigned)Gm * 4u;
+    const ScalarFloats rsc = (ScalarFloats)rsf;
+    float kbest = __builtin_inff();
+    int where = 0x7FFFFFFF;
+    for (int i0 = 0; i0 < Gm; i0 += 16) {
+        const int i = i0 + l16;
+        const bool active = WHOLE || i < Gm;
+        const unsigned il = (unsigned)(active ? i : Gm - 1);
+        const float mf = (float)tb.m[il];
+        const float tg = q.alpha_g + q.beta_g * mf;                           // Eq. 8
+        float last = (float)*(const double *)((const char *)tb.lt + (l_row + 8u * il));     // Eq. 10
+        last = ts == 0.0f ? tg : (q.gamma == 1.0f ? tg + ts : last);
+        const float u = q.phi * __builtin_amdgcn_rcpf(Kf * mf);
+        const float A0 = fmaf(u, tg, last);
+        const float C = (last - tg) * u * __builtin_amdgcn_rcpf(tg);
+        const int bounds = *(const int32_t *)((const char *)tb.srange + (s_row + 4u * il));
+        const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
+        const bool feasible = active && s_lo <= s_hi;
+        const int s_star = scan_argmin_f32<CH>(C, X, rsc, Gs);
+        int s_c = s_star < s_hi ? s_star : s_hi;
+        s_c = s_c > s_lo ? s_c : s_lo;
+        const float r_c = has_near ? near[s_c] : rsf[s_c];
+        const float key = fmaf(tg, fmaf(C, r_c, (float)s_c), A0);
+        if (feasible && key < kbest) {
+            kbest = key;
+            where = (i << 16) | s_c;
+        }
+    }
+    // positive floats order like their bit patterns; equal values: the lowest (i, s)
+    const unsigned bits = (unsigned)__float_as_int(kbest);
+    const unsigned bmin = row16_min(bits);
+    const unsigned first = row16_min(bits == bmin ? (unsigned)where : 0x7FFFFFFFu);
+    return bmin >= 0x7F800000u ? -1 : (int)first;
 }
 
 // Eq. 4 at grid point (i, s) in the plain form, in fp32, for a GPU count within the tables.  Arguments may
@@ -1527,7 +1583,7 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 // its row, the rows with two votes or more (four at most) are copied to LDS once, and the sweeps of those pairs
 // read (C, A0), T_grad and the feasible range from there.  Three vector-memory loads per lane and group of 64
 // batch sizes were what kept the texture addresser two thirds busy and the vector ALU waiting.
-constexpr bool rows_at_a_time(int CH, bool F32, bool MEMO, bool ROW4) { return ROW4 && !F32 && !MEMO && CH != 0 && CH <= 16; }
+constexpr bool rows_at_a_time(int CH, bool F32, bool MEMO, bool ROW4) { return ROW4 && !MEMO && CH != 0 && CH <= 16; }
 
 // SEL = 2: per job, the candidates listed in a.dirty[j, 0 .. a.dirty_count[j]) (row inheritance: the rows of job j that a
 // move or a repair of the search step has changed); workgroups beyond a job's list return at once.
@@ -1968,7 +2024,9 @@ pairs_kernel(FitnessArgs a)
                 const bool within = tabled_row(K, nodes == 1, tb.k1);
                 const int K_in = (K < 1 || !within) ? 1 : K;
                 // (this instance is launched only for grids whose tables of reciprocals and thresholds fit LDS)
-                const int found = sweep_pick_rows<CH, WHOLE>(tb, X, a.rs, a.Gm, a.Gs, K_in, nodes == 1 && within, (LdsDoubles)r_lds, WHOLE || has_near);
+                int found;
+                if constexpr (F32) found = sweep_pick_rows_f32<CH, WHOLE>(qf, tb, XF, a.rsf, a.Gm, a.Gs, K_in, nodes == 1 && within, (LdsFloats)(const float *)r_lds, WHOLE || has_near);
+                else found = sweep_pick_rows<CH, WHOLE>(tb, X, a.rs, a.Gm, a.Gs, K_in, nodes == 1 && within, (LdsDoubles)r_lds, WHOLE || has_near);
                 int pi = found < 0 ? -1 : found >> 16, ps = found < 0 ? -1 : found & 0xFFFF;
                 if (K >= 1 && !within) {                     // rare: swept after the loop, outside the hot path
                     pi = kPending;
@@ -2834,7 +2892,8 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     // untouched workspace and unchanged dimensions, does not clear them once more.
     const bool row1 = d->N >= 4 && d->N <= 4 * kWave;
     const bool aligned = row1 && (d->N & 3) == 0 && (((uintptr_t)population | (uintptr_t)current_alloc) & 15) == 0;
-    const bool row4 = row1 && d->N <= kWave;        // four rows per load of a wavefront (cand_per_wave <= 16 holds)
+    // four rows per load of a wavefront (cand_per_wave <= 16 holds); its sweeps pack a batch size's index into 15 bits
+    const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF;
     const bool inherit = inherit_rows && first_rank > 0;
     // memoised pass over rows of 4 to 256 entries: one workgroup per candidate, counters in LDS, fitness included
     const bool candidate_pass = memo && d->N >= 4 && d->N <= kMemoNodes;

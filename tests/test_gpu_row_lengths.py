@@ -47,3 +47,30 @@ def test_matrices_at_any_address(N, P, off, precision):
     got = call.results()
     for k in want:
         assert np.array_equal(got[k], want[k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("Gm", [0x7FFF, 0x8000, 0x8001, 0x10040])
+def test_more_batch_sizes_than_a_packed_index_holds(Gm):
+    wl = W.make(W.custom("long", P=5, J=1, N=6, cap=4, Gm=Gm, Gs=2, index=750))
+    wl.m_grid[0] = np.arange(1, Gm + 1)                      # the best batch sizes anywhere in the grid
+    wl.param("M0")[0], wl.param("M_max")[0], wl.param("phi")[0] = 0.9 * Gm, 1e7, 1e9
+    ref = run_oracle(wl)
+    assert ref["best_m"].max() >= 0.8 * Gm
+    assert compare(wl, run_gpu(wl), ref) == 0
+
+
+@pytest.mark.parametrize("Gm,Gs", [(5, 3), (33, 8), (64, 16), (65, 20), (128, 40)])
+@pytest.mark.parametrize("N", [5, 64])
+def test_fp32_four_rows_at_a_time_elects_what_one_row_at_a_time_elects(N, Gm, Gs):
+    """A population in rows of N nodes, and the same one with empty nodes appended until rows are longer than 64."""
+    wl = W.make(W.custom("f32", P=30, J=6, N=N, cap=4, Gm=Gm, Gs=Gs, index=760 + N))
+    pad = lambda x: np.concatenate([x, np.zeros(x.shape[:-1] + (68 - N,), x.dtype)], axis=-1)
+    short = run_gpu(wl, precision=1)
+    c = wl.cfg
+    long = W.make(W.custom("f32 long", P=c.P, J=c.J, N=68, cap=4, Gm=Gm, Gs=Gs, index=760 + N), with_population=False)
+    long.job_params, long.m_grid, long.fair_share = wl.job_params, wl.m_grid, wl.fair_share
+    long.current_alloc, long.population = pad(wl.current_alloc), pad(wl.population)
+    long.node_capacity = np.concatenate([wl.node_capacity, np.full(68 - N, 4, np.int32)])
+    want = run_gpu(long, precision=1)
+    for k in want:
+        assert np.array_equal(short[k], want[k], equal_nan=True), k
