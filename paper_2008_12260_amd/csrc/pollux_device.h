@@ -43,6 +43,31 @@ __device__ __forceinline__ long long exchange(long long v)
     return ((long long)exchange<STEP>(hi) << 32) | (long long)(unsigned)exchange<STEP>(lo);
 }
 
+template <int STEP>
+__device__ __forceinline__ float exchange(float v)
+{
+    return __int_as_float(exchange<STEP>(__float_as_int(v)));
+}
+
+// Every lane receives the value of the lane N below it in its row of 16 lanes, cyclically.
+template <int N>
+__device__ __forceinline__ int rotate16(int v) { return __builtin_amdgcn_mov_dpp(v, 0x120 + N, 0xF, 0xF, false); }   // row_ror:N
+
+template <int N>
+__device__ __forceinline__ float rotate16(float v) { return __int_as_float(rotate16<N>(__float_as_int(v))); }
+
+template <int N>
+__device__ __forceinline__ double rotate16(double v)
+{
+    return __hiloint2double(rotate16<N>(__double2hiint(v)), rotate16<N>(__double2loint(v)));
+}
+
+template <int N>
+__device__ __forceinline__ long long rotate16(long long v)
+{
+    return ((long long)rotate16<N>((int)(v >> 32)) << 32) | (long long)(unsigned)rotate16<N>((int)(v & 0xFFFFFFFFll));
+}
+
 // The value lane `src` holds (src the same in every lane).
 __device__ __forceinline__ long long wave_broadcast(long long v, int src)
 {

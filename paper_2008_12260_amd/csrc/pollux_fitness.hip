@@ -2226,6 +2226,23 @@ __global__ void __launch_bounds__(256) autoscale_kernel(int J, int max_nodes, co
 
 constexpr int kCandThreads = 256;
 
+// The sum of red[0 .. kCandThreads-1] in lane 0 of the first wavefront, which alone calls this: the tree that adds the upper half
+// to the lower one again and again, its last six levels across lanes (a barrier per level took 0.6 us of a 5 us kernel).
+template <typename T>
+__device__ __forceinline__ T tree_sum(const T *red)
+{
+    static_assert(kCandThreads == 4 * kWave, "two levels before one wavefront holds the rest");
+    const int l = lane_id();
+    T s = (red[l] + red[l + 2 * kWave]) + (red[l + kWave] + red[l + 3 * kWave]);
+    s += exchange<5>(s);                     // lane ^ 32
+    s += exchange<4>(s);                     // lane ^ 16
+    s += rotate16<8>(s);                     // lane ^ 8, and from here on lanes 2^k apart hold the same
+    s += rotate16<4>(s);
+    s += rotate16<2>(s);
+    s += rotate16<1>(s);
+    return s;
+}
+
 __device__ __forceinline__ double pmean_term(double s, double w, double p)
 {
     if (p == 0.0) return w * log(s);      // log(0) = -inf
@@ -2304,18 +2321,12 @@ __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
     }
     red_v[t] = v;
     __syncthreads();
-    for (int half = kCandThreads / 2; half > 0; half >>= 1) {
-        if (t < half) {
-            red_acc[t] += red_acc[t + half];
-            red_w[t] += red_w[t + half];
-            red_v[t] += red_v[t + half];
-        }
-        __syncthreads();
-    }
+    if (t >= kWave) return;
+    const REAL total = tree_sum(red_acc), weight = tree_sum(red_w);
+    const long long V = tree_sum(red_v);
     if (t == 0) {
-        const REAL mean = red_acc[0] / red_w[0];
+        const REAL mean = total / weight;
         double f = (double)pmean_finish(mean, (REAL)a.p);
-        const long long V = red_v[0];
         if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
         if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
         a.fitness[c] = f;
@@ -2697,18 +2708,12 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
     }
     red_v[t] = v;
     __syncthreads();
-    for (int half = kCandThreads / 2; half > 0; half >>= 1) {
-        if (t < half) {
-            red_acc[t] += red_acc[t + half];
-            red_w[t] += red_w[t + half];
-            red_v[t] += red_v[t + half];
-        }
-        __syncthreads();
-    }
+    if (wave != 0) return;
+    const Real total = tree_sum(red_acc), weight = tree_sum(red_w);
+    const long long V = tree_sum(red_v);
     if (t == 0) {
-        const Real mean = red_acc[0] / red_w[0];
+        const Real mean = total / weight;
         double f = (double)pmean_finish(mean, p);
-        const long long V = red_v[0];
         if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
         if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
         a.fitness[c] = f;

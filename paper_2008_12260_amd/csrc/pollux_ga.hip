@@ -269,6 +269,14 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
     int32_t *__restrict__ src_row = INHERIT ? a.src_row + (size_t)(c - (int)a.elite_k) * a.J : nullptr;
 
     // ---- step A ----
+    // FOUR: the parents are asked for before the decisions are drawn; those workgroups all run at once and the kernel lasts as
+    // long as one of them.  (Long rows are bound by the copy; drawn here the parents cost that instance registers and 1.6 %.)
+    int early_a = 0, early_b = 0;
+    if constexpr (FOUR) {
+        const U4 pr = philox4x32_10(a.generation, (uint32_t)c, 0u, kTagParent, a.key0, a.key1);
+        early_a = a.order[below(pr.x, a.elite_k)];
+        early_b = (pr.z & 1u) ? early_a : a.order[below(pr.y, a.elite_k)];
+    }
     // decisions of every row, one thread per job: dec[j] = source parent | (move + 1) << 1, decx[j] = the
     // second word of the mutation draw (which node)
     for (int j = tid; j < a.J; j += kGaThreads) {
@@ -284,13 +292,14 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
         sh.dec[j] = d;
         sh.decx[j] = (int32_t)x;
     }
-    const U4 pr = philox4x32_10(a.generation, (uint32_t)c, 0u, kTagParent, a.key0, a.key1);
-    const int32_t *__restrict__ pa = a.parents + (size_t)a.order[below(pr.x, a.elite_k)] * JN;
+    const U4 pr = FOUR ? U4{0u, 0u, 0u, 0u} : philox4x32_10(a.generation, (uint32_t)c, 0u, kTagParent, a.key0, a.key1);
+    const int32_t *__restrict__ pa = a.parents + (size_t)(FOUR ? early_a : a.order[below(pr.x, a.elite_k)]) * JN;
     // half of the children have a single parent (mutation only)
-    const int32_t *__restrict__ pb = (pr.z & 1u) ? pa : a.parents + (size_t)a.order[below(pr.y, a.elite_k)] * JN;
+    const int32_t *__restrict__ pb = FOUR ? a.parents + (size_t)early_b * JN
+                                          : ((pr.z & 1u) ? pa : a.parents + (size_t)a.order[below(pr.y, a.elite_k)] * JN);
     // the two parents as candidates (what src_row names)
-    int cand_a = 0, cand_b = 0;
-    if constexpr (INHERIT) {
+    int cand_a = early_a, cand_b = early_b;
+    if constexpr (INHERIT && !FOUR) {
         cand_a = a.order[below(pr.x, a.elite_k)];
         cand_b = (pr.z & 1u) ? cand_a : a.order[below(pr.y, a.elite_k)];
     }
@@ -324,27 +333,41 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
     // Rows of at most 64 nodes that are copied unchanged (no move drawn, no GPU limit to apply): four rows per
     // load of the wavefront, 16 lanes each.  The loop after this one then takes only the rows with a move.
     if constexpr (FOUR) {
+        // kAhead loads are requested before the first is worked on: one after the other, each with its store and its
+        // bookkeeping, the seven loads of a wavefront at 200 jobs took longest in the kernel (19.0 us in all, 17.1 so; what is left of it is the copy, at 7 TB/s out of the caches).
         const int n4 = a.N >> 2;
         const int g = lane >> 4, l16 = lane & 15;
-        for (int j0 = 4 * wave; j0 < a.J; j0 += 4 * waves) {
-            const int j = j0 + g;
-            const int d = j < a.J ? sh.dec[j] : 2;
-            const bool plain = (d >> 1) == 0;
-            int4 v = {0, 0, 0, 0};
-            if (plain && l16 < n4) {
-                v = ((const int4 *)(((d & 1) ? pb : pa) + (size_t)j * a.N))[l16];
-                ((int4 *)(child + (size_t)j * a.N))[l16] = v;
-                const int n = 4 * l16;
-                if (v.x != 0) record(j, n, v.x);
-                if (v.y != 0) record(j, n + 1, v.y);
-                if (v.z != 0) record(j, n + 2, v.z);
-                if (v.w != 0) record(j, n + 3, v.w);
+        constexpr int kAhead = 4;
+        for (int j0 = 4 * wave; j0 < a.J; j0 += 4 * waves * kAhead) {
+            int d[kAhead];
+            int4 v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int j = j0 + 4 * waves * u + g;
+                d[u] = j < a.J ? sh.dec[j] : 2;
+                v[u] = int4{0, 0, 0, 0};
+                if ((d[u] >> 1) == 0 && l16 < n4) v[u] = ((const int4 *)(((d[u] & 1) ? pb : pa) + (size_t)j * a.N))[l16];
             }
-            const int nodes = row16_sum((v.x > 0 ? 1 : 0) + (v.y > 0 ? 1 : 0) + (v.z > 0 ? 1 : 0) + (v.w > 0 ? 1 : 0));
-            if (plain && l16 == 0) {
-                sh.nodes_of[j] = nodes;
-                if (nodes >= 2) sh.dist[atomicAdd(&n_dist, 1)] = j;
-                if (INHERIT) src_row[j] = (d & 1) ? cand_b : cand_a;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (j0 + 4 * waves * u >= a.J) break;
+                const int j = j0 + 4 * waves * u + g;
+                const bool plain = (d[u] >> 1) == 0;
+                const int4 w = v[u];
+                if (plain && l16 < n4) {
+                    ((int4 *)(child + (size_t)j * a.N))[l16] = w;
+                    const int n = 4 * l16;
+                    if (w.x != 0) record(j, n, w.x);
+                    if (w.y != 0) record(j, n + 1, w.y);
+                    if (w.z != 0) record(j, n + 2, w.z);
+                    if (w.w != 0) record(j, n + 3, w.w);
+                }
+                const int nodes = row16_sum((w.x > 0 ? 1 : 0) + (w.y > 0 ? 1 : 0) + (w.z > 0 ? 1 : 0) + (w.w > 0 ? 1 : 0));
+                if (plain && l16 == 0) {
+                    sh.nodes_of[j] = nodes;
+                    if (nodes >= 2) sh.dist[atomicAdd(&n_dist, 1)] = j;
+                    if (INHERIT) src_row[j] = (d[u] & 1) ? cand_b : cand_a;
+                }
             }
         }
     }
@@ -455,6 +478,44 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
         if (nodes >= 2 && lane == 0) sh.dist[atomicAdd(&n_dist, 1)] = j;
         if (INHERIT && lane == 0) src_row[j] = (move < 0 && !over_limit) ? ((d & 1) ? cand_b : cand_a) : -1;
     };
+    // The same for a row of at most 64 nodes without a GPU limit: lane n holds entry n, so the one load serves the move, the
+    // copy and the bookkeeping (three dependent trips to memory otherwise).
+    auto short_row_by_wavefront = [&](int j, int d) {
+        const int32_t *__restrict__ src = ((d & 1) ? pb : pa) + (size_t)j * a.N;
+        const int move = ((d >> 1) & 3) - 1;
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readfirstlane(sh.decx[j]);
+        int32_t v = lane < a.N ? src[lane] : 0;
+        const int drawn = (int)below(x, (uint32_t)a.N);
+        if (move == 2) {
+            // re-pack: the whole row goes to one drawn node, as far as that node's capacity allows
+            const long long cap = a.node_capacity[drawn];
+            long long k = wave_sum((long long)v);
+            if (k < 0) k = 0;
+            v = lane == drawn ? (int32_t)(k < cap ? k : cap) : 0;
+        } else {
+            // grow / shrink by one GPU on one of the nodes the job occupies (a job without GPUs grows on a drawn node)
+            unsigned long long on = __ballot(v > 0);
+            const int occupied = __popcll(on);
+            int target = -1;
+            if (occupied > 0) {
+                for (int skip = (int)below(x, (uint32_t)occupied); skip > 0; --skip) on &= on - 1ull;
+                target = __builtin_ctzll(on);
+            } else if (move == 0) {
+                target = drawn;
+            }
+            if (lane == target) v += move == 0 ? 1 : -1;
+        }
+        if (lane < a.N) {
+            child[(size_t)j * a.N + lane] = v;
+            if (v != 0) record(j, lane, v);
+        }
+        const int nodes = __popcll(__ballot(v > 0));
+        if (lane == 0) {
+            sh.nodes_of[j] = nodes;
+            if (nodes >= 2) sh.dist[atomicAdd(&n_dist, 1)] = j;
+            if (INHERIT) src_row[j] = -1;
+        }
+    };
     if constexpr (FOUR) {
         // only the rows with a move are left: every wavefront reads the decisions 64 at a time and takes, of the rows
         // that have one, those whose number is its own modulo the number of wavefronts (a few per child: walking
@@ -467,7 +528,7 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
             while (mine != 0ull) {
                 const int b = __builtin_ctzll(mine);
                 mine &= mine - 1ull;
-                row_by_wavefront(jb + b, __builtin_amdgcn_readlane(dd, b));
+                short_row_by_wavefront(jb + b, __builtin_amdgcn_readlane(dd, b));
             }
         }
     } else {
