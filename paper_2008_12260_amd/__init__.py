@@ -104,14 +104,26 @@ def workspace_size(dims: Dims) -> int:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()       # (the argument types turn integers into pointers)
+
+
+_raw_stream = None
 
 
 def _stream_handle(stream):
-    if stream is None:
+    if stream is not None:
+        return stream.cuda_stream
+    # the current stream's handle without the torch.cuda.Stream object around it (3 us of a call of 15), where torch has it
+    global _raw_stream
+    if _raw_stream is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None:
+            torch.cuda.init()
+            _raw_stream = lambda: raw(device())
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _raw_stream()
 
 
 def pollux_fitness(dims: Dims, population, job_params, m_grid, fair_share, current_alloc, node_capacity,
