@@ -319,9 +319,13 @@ int pollux_last_status(const void *workspace, void *hip_stream, int32_t *host_ou
     const char *ws = (const char *)workspace;
     pollux_dims d = {1, 1, 1, 1, 1, 0, 0};
     const size_t off = px::workspace_layout(d).status;    // the status word sits at a fixed offset
-    if (hipMemcpyAsync(host_out, ws + off, sizeof(int32_t), hipMemcpyDeviceToHost, (hipStream_t)hip_stream) != hipSuccess)
-        return PX_E_HIP;
+    int32_t words[px::kStatusWords];
+    if (hipMemcpyAsync(words, ws + off, sizeof(words), hipMemcpyDeviceToHost, (hipStream_t)hip_stream) != hipSuccess) return PX_E_HIP;
     if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess) return PX_E_HIP;
+    *host_out = words[0];
+    for (int i = 1; i < px::kStatusWords; ++i) {
+        if (words[i] != 0) *host_out |= PX_ST_NEG_ALLOC;
+    }
     return PX_OK;
 }
 

@@ -87,7 +87,7 @@ struct FitnessArgs {
     const double *job_params;
     double p, delta;
     // workspace
-    int32_t *status;
+    int32_t *status;              // the status word; in the 252 bytes behind it, per candidate of a small call, whether it met a negative entry
     double *rs, *rk, *lntg, *pu, *qh5, *ql5, *lt, *denom, *factor, *G;
     float *rsf;                   // 1/(s+1) in fp32, as long as rs
     double2 *tg;                  // [J,Gm] (T_grad, 1 / T_grad)
@@ -1251,10 +1251,12 @@ __device__ __forceinline__ int argmin_count(double C)
     return C <= t_lo ? t - 1 : (C > t_hi ? t + 1 : t);
 }
 
-// h of one batch size at its best feasible count s_c (+inf when no count is feasible).  tabled: h in the form the tables
+// h of one batch size at its best feasible count s_c (+inf when no count is feasible).  argmin: the best count of all, given C.
+// tabled: h in the form the tables
 // give it (C and A0), else in the form of the untabled sweep: rounding decides elections between equal points, so a row
 // keeps the form its sweep has.
-__device__ __forceinline__ double best_count(const GridPoint &g, double last, double rK, int Gs, bool tabled, int &s_c)
+template <typename ARGMIN>
+__device__ __forceinline__ double best_count(const GridPoint &g, double last, double rK, int Gs, bool tabled, const ARGMIN &argmin, int &s_c)
 {
     int s_lo, s_hi;
     feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
@@ -1262,7 +1264,7 @@ __device__ __forceinline__ double best_count(const GridPoint &g, double last, do
     const double A0 = px_fma(u, g.tg, last);
     const double B0 = (last - g.tg) * u;
     const double C = B0 * g.rtg;
-    int s = argmin_count(C);
+    int s = argmin(C);
     s = s < s_hi ? s : s_hi;
     s = s > s_lo ? s : s_lo;
     s_c = s;
@@ -1278,18 +1280,33 @@ __device__ __forceinline__ double price_in_place(const Job &q, const GridParams 
     return goodput_point(q, (double)K * (double)m, tg, last_pass(st, tg, px_log(tg)), s);
 }
 
+// Reciprocals of the counts of a grid of at most 32, for the scan of calls that have no table of them.
+constexpr int kSmallGs = 32;
+#define PX_R4(n) 1.0 / (n), 1.0 / (n + 1), 1.0 / (n + 2), 1.0 / (n + 3)
+__constant__ double small_recips[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R4(13), PX_R4(17), PX_R4(21), PX_R4(25), PX_R4(29)};
+#undef PX_R4
+
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
+// CH > 0: each batch size's count is found by the scan over all of them (Gs <= kSmallGs), as in the population pass; the same
+// count either way.
+template <int CH = 0>
 __device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs,
                                          int K, bool one_node, bool tabled)
 {
     const SyncTerm st = sync_term(q, K, one_node);
+    RunSteps X = {};
+    if constexpr (CH > 0) X = make_run_steps();
+    auto argmin = [&](double C) {
+        if constexpr (CH > 0) return scan_argmin<CH>(C, X, (ScalarDoubles)small_recips, Gs, nullptr, false);
+        else return argmin_count(C);
+    };
     const double rK = 1.0 / (double)K;
     double kbest = __builtin_inf();
     int where = 0;
     for (int i = lane_id(); i < Gm; i += kWave) {
         const GridPoint g = grid_point(gp, m_row[i]);
         int s_c;
-        const double h = best_count(g, last_pass(st, g.tg, g.lntg), rK, Gs, tabled, s_c);
+        const double h = best_count(g, last_pass(st, g.tg, g.lntg), rK, Gs, tabled, argmin, s_c);
         if (h < kbest) {
             kbest = h;
             where = s_c | ((i / kWave) << 16);
@@ -1426,7 +1443,7 @@ __device__ __forceinline__ void prepare_rows(const FitnessArgs &a, int j, int K0
             const double last = last_pass(t[r], g.tg, g.lntg);
             if constexpr (MODE == kPrepMemo) {
                 int s_c;
-                const double h = best_count(g, last, rK[r], a.Gs, true, s_c);
+                const double h = best_count(g, last, rK[r], a.Gs, true, argmin_count, s_c);
                 if (h < kbest[r]) {
                     kbest[r] = h;
                     where[r] = s_c | ((i / kWave) << 16);
@@ -1472,7 +1489,7 @@ __global__ void __launch_bounds__(256) prepare_kernel(FitnessArgs a)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, threads = (size_t)gridDim.x * blockDim.x;
-    if (tid == 0) *a.status = 0;
+    if (tid < kStatusWords) a.status[tid] = 0;
     if (a.clear_counters) {
         // the per-candidate, per-node counters of the constraint check start the call at zero
         const size_t n = (size_t)a.P * a.N;
@@ -2226,14 +2243,10 @@ __global__ void __launch_bounds__(256) autoscale_kernel(int J, int max_nodes, co
 
 constexpr int kCandThreads = 256;
 
-// The sum of red[0 .. kCandThreads-1] in lane 0 of the first wavefront, which alone calls this: the tree that adds the upper half
-// to the lower one again and again, its last six levels across lanes (a barrier per level took 0.6 us of a 5 us kernel).
+// The last six levels of that tree, across the lanes of a wavefront; lane 0 holds the sum.
 template <typename T>
-__device__ __forceinline__ T tree_sum(const T *red)
+__device__ __forceinline__ T wave_tree_sum(T s)
 {
-    static_assert(kCandThreads == 4 * kWave, "two levels before one wavefront holds the rest");
-    const int l = lane_id();
-    T s = (red[l] + red[l + 2 * kWave]) + (red[l + kWave] + red[l + 3 * kWave]);
     s += exchange<5>(s);                     // lane ^ 32
     s += exchange<4>(s);                     // lane ^ 16
     s += rotate16<8>(s);                     // lane ^ 8, and from here on lanes 2^k apart hold the same
@@ -2241,6 +2254,16 @@ __device__ __forceinline__ T tree_sum(const T *red)
     s += rotate16<2>(s);
     s += rotate16<1>(s);
     return s;
+}
+
+// The sum of red[0 .. kCandThreads-1] in lane 0 of the first wavefront, which alone calls this: the tree that adds the upper half
+// to the lower one again and again, its last six levels across lanes (a barrier per level took 0.6 us of a 5 us kernel).
+template <typename T>
+__device__ __forceinline__ T tree_sum(const T *red)
+{
+    static_assert(kCandThreads == 4 * kWave, "two levels before one wavefront holds the rest");
+    const int l = lane_id();
+    return wave_tree_sum((red[l] + red[l + 2 * kWave]) + (red[l + kWave] + red[l + 3 * kWave]));
 }
 
 __device__ __forceinline__ double pmean_term(double s, double w, double p)
@@ -2330,6 +2353,146 @@ __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
         if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
         if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
         a.fitness[c] = f;
+    }
+}
+
+// ---- small calls: one launch -----------------------------------------------------------------------
+// A few hundred candidates of a dozen jobs are less work than the tables their sweeps would share (72 rows a job), and the call
+// lasts as long as its launches follow one another: three of 5 to 7 us each.  Here one workgroup of sixteen wavefronts takes
+// a candidate: each wavefront finds the fair-share goodput of some jobs and reduces, sweeps and prices some of the candidate's
+// rows, forming the terms of its batch sizes itself (row_best, with the scan over all counts for the rows); the node counters
+// are in LDS, and the first wavefront forms SPEEDUP and the mean, term by term and in the tree of candidates_kernel.  The same
+// results, bit by bit.  Nothing of the workspace is read, and only the status section is written: every call of such dimensions
+// comes here, those that keep job tables and the children of a generation included.
+// The line (small_call) is drawn where a wavefront has two rows of 64 batch sizes to take, fair shares included, at 3 to 4 us a
+// row (a chain of dependent steps): 8 jobs 9.5 us a call against 15.9 in three launches, 12 jobs 11.9 against 17.5, 16 jobs 15.2
+// against 16.5, 24 jobs 20.7 against 19.3; 8 jobs with 128 batch sizes 12.3 against 17.6.  The status section holds a byte per
+// candidate.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallJobs = 16;
+constexpr int kSmallCandidates = 4 * (kStatusWords - 1);
+
+static bool small_call(const pollux_dims &d)
+{
+    return d.precision == 0 && (d.flags & (PX_FLAG_MEMOISE | PX_FLAG_SAMPLE_M)) == 0 && d.P <= kSmallCandidates && d.J <= kSmallJobs &&
+           d.N >= 4 && d.N <= 4 * kWave && d.Gs <= kSmallGs && d.J * ((d.Gm + kWave - 1) / kWave) <= kSmallJobs;
+}
+
+template <int CH>
+__global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
+{
+    __shared__ unsigned long long node_lds[4 * kWave];       // per node: GPUs asked + multi-node jobs << 40, as colpack
+    __shared__ double fair_lds[kSmallJobs], factor_lds[kSmallJobs], goodput_lds[kSmallJobs];
+    __shared__ int meta_lds[kSmallJobs], m_lds[kSmallJobs], s_lds[kSmallJobs];
+    __shared__ int status_lds, negative;
+    const int c = a.sel ? a.sel[blockIdx.x] : (int)blockIdx.x;
+    const int t = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (t < 4 * kWave) node_lds[t] = 0ull;
+    if (t == 0) status_lds = negative = 0;
+    // the largest node capacity (rows of the "one node" class beyond it take the form of the untabled sweep)
+    const RowLane at_row = row_lane(lane, a.N);
+    const Entries caps = *(const Entries *)(a.node_capacity + at_row.base);
+    int k1 = caps.x > caps.y ? caps.x : caps.y;
+    k1 = k1 > caps.z ? k1 : caps.z;
+    k1 = k1 > caps.w ? k1 : caps.w;
+    k1 = (int)wave_max((unsigned)(k1 > 0 ? k1 : 0));
+    k1 = k1 < kTableK ? k1 : kTableK;
+    __syncthreads();
+    for (int task = wave; task < 2 * a.J; task += kSmallThreads / kWave) {
+        const bool is_row = task >= a.J;
+        const int j = is_row ? task - a.J : task;
+        const Job q = load_job(a.job_params, a.J, j);
+        const GridParams gp = load_grid_params(a.job_params, a.J, j);
+        const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
+        const Entries was = *(const Entries *)(a.current_alloc + (size_t)j * a.N + at_row.base) & at_row.mask;
+        if (is_row) {
+            const Entries w = *(const Entries *)(a.population + ((size_t)c * a.J + j) * a.N + at_row.base) & at_row.mask;
+            const int K = wave_sum((w.x + w.y) + (w.z + w.w));
+            const int nodes = __popcll(__ballot(w.x > 0)) + __popcll(__ballot(w.y > 0)) + __popcll(__ballot(w.z > 0)) + __popcll(__ballot(w.w > 0));
+            const bool changed = __ballot(((w.x ^ was.x) | (w.y ^ was.y) | (w.z ^ was.z) | (w.w ^ was.w)) != 0) != 0;
+            if (__ballot((w.x | w.y | w.z | w.w) < 0) != 0 && lane == 0) negative = 1;
+            if ((w.x | w.y | w.z | w.w) != 0) {
+                const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
+                unsigned long long *to = node_lds + at_row.base;
+                atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
+                atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
+                atomicAdd(&to[2], (unsigned long long)(long long)w.z + (w.z > 0 ? one_job : 0ull));
+                atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
+            }
+            Best best = {0.0, -1, -1};
+            if (K >= 1) best = row_best<CH>(q, gp, m_row, a.Gm, a.Gs, K, nodes == 1, tabled_row(K, nodes == 1, k1));
+            if (lane == 0) {
+                goodput_lds[j] = best.goodput;
+                meta_lds[j] = nodes | (changed ? kMetaChanged : 0);
+                m_lds[j] = best.m;
+                s_lds[j] = best.s;
+            }
+        } else {
+            const int K = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j]);
+            const bool one_node = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j + 1]) == 1;
+            const double T = a.job_params[(size_t)PX_AGE_T * a.J + j], R = a.job_params[(size_t)PX_RESTARTS_R * a.J + j];
+            int st = job_status(gp, load_sync(q), a.job_params[(size_t)PX_WEIGHT * a.J + j]);
+            // re-allocation penalty factor of Sec. 4.2
+            const bool penalty = !(a.flags & PX_FLAG_NO_REALLOC_PENALTY);
+            if (penalty && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
+            const long long held = wave_sum((long long)was.x + was.y + was.z + was.w);
+            if (__ballot((was.x | was.y | was.z | was.w) < 0) != 0) st |= PX_ST_NEG_ALLOC;
+            Best fair = {0.0, -1, -1};
+            if (K > 0) fair = row_best(q, gp, m_row, a.Gm, a.Gs, K, one_node, tabled_row(K, one_node, k1));
+            if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
+            if (lane == 0) {
+                fair_lds[j] = fair.goodput;
+                factor_lds[j] = penalty && held > 0 ? (T - R * a.delta) / (T + a.delta) : 1.0;
+                if (st) atomicOr(&status_lds, st);
+            }
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    // one job per lane: SPEEDUP (Eq. 15) with the penalty, its term of Eq. 14
+    const bool mine = lane < a.J;
+    double acc = 0.0, wsum = 0.0;
+    if (mine) {
+        const size_t pair = (size_t)c * a.J + lane;
+        const double w = a.job_params[(size_t)PX_WEIGHT * a.J + lane], d = fair_lds[lane];
+        double s_j = d > 0 ? goodput_lds[lane] / d : 0.0;
+        if (meta_lds[lane] & kMetaChanged) s_j = s_j * factor_lds[lane];
+        if (a.best_m) {
+            a.best_m[pair] = m_lds[lane];
+            a.best_s[pair] = s_lds[lane];
+        }
+        if (a.best_goodput) a.best_goodput[pair] = goodput_lds[lane];
+        if (a.speedup) a.speedup[pair] = s_j;
+        acc += pmean_term(s_j, w, a.p);
+        wsum += w;
+    }
+    long long v = 0;
+    if (a.need_constraints) {
+        for (int n = lane; n < a.N; n += kWave) {
+            const long long x = (long long)node_lds[n];
+            const long long asked = (x << 24) >> 24;              // low 40 bits, sign-extended
+            const long long distributed = (x - asked) >> 40;
+            if (distributed > 1) v += distributed - 1;
+            const long long over = asked - (long long)a.node_capacity[n];
+            if (over > 0) v += over;
+        }
+    }
+    const long long V = wave_sum(v);
+    const double mean = wave_tree_sum(acc) / wave_tree_sum(wsum);
+    const bool fresh = !(a.flags & PX_FLAG_KEEP_JOB_TABLES);
+    if (lane == 0) {
+        double f = pmean_finish(mean, a.p);
+        if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
+        if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
+        a.fitness[c] = f;
+        uint8_t *negatives = (uint8_t *)(a.status + 1);
+        if (fresh || negative) negatives[c] = (uint8_t)negative;
+    }
+    // a fresh call starts the status section anew; the jobs' bits are the same in every workgroup
+    if (fresh && blockIdx.x == 0) {
+        if (lane == 0) *a.status = status_lds;
+        for (int i = a.P + lane; i < kSmallCandidates; i += kWave) ((uint8_t *)(a.status + 1))[i] = 0;
     }
 }
 
@@ -2829,14 +2992,16 @@ int launch_sim_tick(const pollux_dims *d, const double *job_params, const int32_
 
 __global__ void copy_status_kernel(const int32_t *__restrict__ from, int32_t *__restrict__ to)
 {
-    if (threadIdx.x == 0) *to = *from;
+    const bool negative = threadIdx.x > 0 && from[threadIdx.x] != 0;
+    const int bits = __ballot(negative) != 0ull ? PX_ST_NEG_ALLOC : 0;
+    if (threadIdx.x == 0) *to = from[0] | bits;
 }
 
 int launch_copy_status(const void *workspace, int32_t *status_out, hipStream_t stream)
 {
     pollux_dims d = {1, 1, 1, 1, 1, 0, 0};
     const int32_t *word = (const int32_t *)((const char *)workspace + workspace_layout(d).status);
-    hipLaunchKernelGGL(copy_status_kernel, dim3(1), dim3(64), 0, stream, word, status_out);
+    hipLaunchKernelGGL(copy_status_kernel, dim3(1), dim3(kStatusWords), 0, stream, word, status_out);
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
 }
 
@@ -2884,6 +3049,14 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const unsigned pair_blocks = (unsigned)(8 * ((d->J + 7) / 8) * a.cand_groups);
 
     const bool f32 = d->precision == 1;
+    if (small_call(*d)) {
+        if (sweep_start) (void)hipEventRecord(sweep_start, stream);
+        if (ch == 8) hipLaunchKernelGGL(small_kernel<8>, dim3((unsigned)P_eff), dim3(kSmallThreads), 0, stream, a);
+        else if (ch == 16) hipLaunchKernelGGL(small_kernel<16>, dim3((unsigned)P_eff), dim3(kSmallThreads), 0, stream, a);
+        else hipLaunchKernelGGL(small_kernel<32>, dim3((unsigned)P_eff), dim3(kSmallThreads), 0, stream, a);
+        if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
+        return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
+    }
     const bool sampled = (d->flags & PX_FLAG_SAMPLE_M) != 0;       // fp64 only (checked by the caller)
     // The sampling argmax of a pair depends on (job, K, one node or several) only, as the grid's does, and each of its list
     // entries takes a last pass of Eq. 10 (no table holds it): from as many candidates on as a job has rows to take the argmax

@@ -13,12 +13,15 @@ namespace px {
 // The last pass of Eq. 10 is tabled for GPU counts K = 1..kTableK; larger K are computed in place.
 constexpr int kTableK = 64;
 
+constexpr int kStatusWords = 64;
+
 // Byte offsets of the sections of the caller's workspace (each 256-byte aligned).  The sections whose size
 // depends on P, J and N only come first, so that their offsets are the same for every grid: the search step
 // (which ignores Gm and Gs) and a fitness call that keeps the job tables may then share one workspace
 // whatever grid dimensions the former is given.
 struct WorkspaceLayout {
-    size_t status;    // int32 status word
+    size_t status;    // int32 [kStatusWords]: the status word; the other words are non-zero where a candidate of a small call
+                      //                  met a negative entry (PX_ST_NEG_ALLOC)
     size_t k1;        // int32            the tables of the "one node" class cover K <= this (largest node capacity)
     size_t order;     // int32  [P]       candidates by rank (search step)
     size_t curmask;   // uint64 [J]       groups of four entries of the job's current row that hold a non-zero one
@@ -57,7 +60,7 @@ inline WorkspaceLayout workspace_layout(const pollux_dims &d)
     WorkspaceLayout L;
     size_t o = 0;
     const size_t P = (size_t)d.P, J = (size_t)d.J, Gm = (size_t)(d.Gm > 0 ? d.Gm : 1), Gs = (size_t)(d.Gs > 0 ? d.Gs : 1);
-    L.status = o;  o = up(o + 256);
+    L.status = o;  o = up(o + 4 * kStatusWords);
     L.k1 = o;      o = up(o + 256);
     L.order = o;   o = up(o + 4 * P);
     L.curmask = o; o = up(o + 8 * J);
