@@ -2581,11 +2581,14 @@ constexpr int kMemoNodes = 4 * kWave;               // the longest row
 constexpr int kInherited = -1;                      // row_lds: the row takes over the results of candidate x
 enum MemoKind { kMemoGrid, kMemoF32, kMemoSampled };
 
-template <int KIND, bool SHORT, bool CHILD, bool PAIRS>
-__global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessArgs a)
+// WAVES: four wavefronts, or sixteen where the candidates are too few to fill the chip and their jobs many (see
+// launch_memo_candidates).
+template <int KIND, bool SHORT, bool CHILD, bool PAIRS, int WAVES>
+__global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessArgs a)
 {
-    static_assert(kCandThreads == 4 * kWave, "thread t of the workgroup is lane t % 64 of wavefront t / 64");
+    static_assert(kCandThreads == 4 * kWave && WAVES >= 4, "thread t < kCandThreads is lane t % 64 of wavefront t / 64");
     static_assert(!CHILD || PAIRS, "children: per-pair results kept");
+    constexpr int kThreads = WAVES * kWave;
     using Real = typename std::conditional<KIND == kMemoF32, float, double>::type;
     __shared__ unsigned long long node_lds[kMemoNodes];      // per node: GPUs asked + multi-node jobs << 40, as colpack
     __shared__ int2 row_lds[kMemoChunkJobs];                 // per job of the chunk: K, nodes | changed flag; or candidate, kInherited
@@ -2607,7 +2610,7 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
         src = a.src_row + (size_t)blockIdx.x * a.J;
     }
     const bool count_nodes = a.need_constraints && odd;
-    node_lds[t] = 0ull;
+    if (t < kMemoNodes) node_lds[t] = 0ull;
     if (t == 0) listed = 0;
     if (a.or_job_status && blockIdx.x == 0) or_job_status(a);
     __syncthreads();
@@ -2658,7 +2661,7 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
         const int32_t *__restrict__ pop = a.population + ((size_t)c * a.J + jc) * a.N;
         const int32_t *__restrict__ cur = a.current_alloc + (size_t)jc * a.N;
         if constexpr (CHILD) {
-            for (int at = t; at < chunk_jobs; at += kCandThreads) {
+            for (int at = t; at < chunk_jobs; at += kThreads) {
                 const int from = odd ? -1 : src[jc + at];
                 if (from >= 0) row_lds[at] = make_int2(from, kInherited);
                 else list_lds[atomicAdd(&listed, 1)] = (uint16_t)at;
@@ -2666,7 +2669,7 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
             __syncthreads();
             const int rows = __builtin_amdgcn_readfirstlane(listed);
             if constexpr (SHORT) {
-                for (int q0 = 4 * wave; q0 < rows; q0 += 4 * kWavesPerBlock) {
+                for (int q0 = 4 * wave; q0 < rows; q0 += 4 * WAVES) {
                     const int q = q0 + (lane >> 4);
                     const int at = list_lds[q < rows ? q : rows - 1];
                     const int2 row = reduce_rows(load(pop + (size_t)at * a.N), load(cur + (size_t)at * a.N), q < rows);
@@ -2674,19 +2677,19 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
                 }
             } else {
                 constexpr int kAhead = 4;
-                for (int q0 = wave; q0 < rows; q0 += kAhead * kWavesPerBlock) {
+                for (int q0 = wave; q0 < rows; q0 += kAhead * WAVES) {
                     Entries v[kAhead], was[kAhead];
                     int at[kAhead];
 #pragma unroll
                     for (int u = 0; u < kAhead; ++u) {
-                        const int q = q0 + u * kWavesPerBlock;
+                        const int q = q0 + u * WAVES;
                         at[u] = __builtin_amdgcn_readfirstlane((int)list_lds[q < rows ? q : rows - 1]);
                         v[u] = load(pop + (size_t)at[u] * a.N);
                         was[u] = load(cur + (size_t)at[u] * a.N);
                     }
 #pragma unroll
                     for (int u = 0; u < kAhead; ++u) {
-                        if (q0 + u * kWavesPerBlock < rows) {
+                        if (q0 + u * WAVES < rows) {
                             const int2 row = reduce_row(v[u], was[u]);
                             if (lane == 0) row_lds[at[u]] = row;
                         }
@@ -2694,12 +2697,22 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
                 }
             }
         } else {
-            // Row q of this wavefront in the chunk is job  jc + (q / 64) * 256 + 64 * wave + q % 64  (position in the
-            // chunk: the same without jc); the wavefront has `rows` of them.
-            int tail = chunk_jobs % kCandThreads - kWave * wave;
-            tail = tail < 0 ? 0 : (tail > kWave ? kWave : tail);
-            const int rows = kWave * (chunk_jobs / kCandThreads) + tail;
-            auto place = [&](int q) { return (q >> 6) * kCandThreads + kWave * wave + (q & (kWave - 1)); };
+            // Row q of this wavefront in the chunk (position: the job's number less jc) of the `rows` it has: with four
+            // wavefronts 64 consecutive rows of every round of 256 each, with more of them a stretch of its own.
+            int rows, first_row = 0;
+            if constexpr (WAVES == 4) {
+                int tail = chunk_jobs % kCandThreads - kWave * wave;
+                tail = tail < 0 ? 0 : (tail > kWave ? kWave : tail);
+                rows = kWave * (chunk_jobs / kCandThreads) + tail;
+            } else {
+                const int share = ((chunk_jobs + WAVES - 1) / WAVES + 3) & ~3;
+                first_row = share * wave;
+                rows = chunk_jobs - first_row < share ? chunk_jobs - first_row : share;
+            }
+            auto place = [&](int q) {
+                if constexpr (WAVES == 4) return (q >> 6) * kCandThreads + kWave * wave + (q & (kWave - 1));
+                else return first_row + q;
+            };
             if constexpr (SHORT) {
                 constexpr int kAhead = 4;                   // loads in flight, of four rows each
                 for (int q0 = 0; q0 < rows; q0 += 4 * kAhead) {
@@ -2798,7 +2811,7 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
         }
         __syncthreads();                                    // the chunk's rows are all put away
         // thread t finishes the pairs of jobs jc + t, jc + t + 256, ...
-        for (int at0 = kWave * wave; at0 < chunk_jobs; at0 += kCandThreads) {
+        for (int at0 = kWave * wave; wave < 4 && at0 < chunk_jobs; at0 += kCandThreads) {
             const int at = at0 + lane;
             const bool mine = at < chunk_jobs;
             const int2 row = mine ? row_lds[at] : make_int2(0, 0);
@@ -2855,8 +2868,10 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
         if (CHILD && t == 0) listed = 0;
         __syncthreads();                                    // before the next chunk's rows take their places
     }
-    red_acc[t] = acc;
-    red_w[t] = wsum;
+    if (t < kCandThreads) {
+        red_acc[t] = acc;
+        red_w[t] = wsum;
+    }
     if (__ballot(any_neg) != 0ull && lane == 0) atomicOr(a.status, PX_ST_NEG_ALLOC);
 
     // constraint check: per node, multi-node jobs beyond the first and GPUs beyond capacity
@@ -2869,7 +2884,7 @@ __global__ void __launch_bounds__(kCandThreads) memo_candidates_kernel(FitnessAr
         const long long over = asked - (long long)a.node_capacity[t];
         if (over > 0) v += over;
     }
-    red_v[t] = v;
+    if (t < kCandThreads) red_v[t] = v;
     __syncthreads();
     if (wave != 0) return;
     const Real total = tree_sum(red_acc), weight = tree_sum(red_w);
@@ -2936,20 +2951,24 @@ static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
     }
 }
 
-// The population pass of memoised mode, P_eff workgroups.
+// The population pass of memoised mode, P_eff workgroups.  Up to 256 candidates leave most of a compute unit idle with four
+// wavefronts each; from 64 jobs on (a load of rows per wavefront) they get sixteen.  19 candidates of 552 jobs on 138 nodes:
+// 89 us a call with four, 54 with sixteen.
 template <int KIND>
 static void launch_memo_candidates(const FitnessArgs &a, int P_eff, bool child, bool pairs_kept, hipStream_t stream)
 {
-    const dim3 grid((unsigned)P_eff), block(kCandThreads);
-    const bool short_rows = a.N <= kWave;
-#define PX_LAUNCH_MEMO(CHILD, PAIRS)                                                                                      \
-    do {                                                                                                                  \
-        if (short_rows) hipLaunchKernelGGL((memo_candidates_kernel<KIND, true, CHILD, PAIRS>), grid, block, 0, stream, a); \
-        else hipLaunchKernelGGL((memo_candidates_kernel<KIND, false, CHILD, PAIRS>), grid, block, 0, stream, a);          \
+    const dim3 grid((unsigned)P_eff);
+    const bool short_rows = a.N <= kWave, few = P_eff <= 256 && a.J >= kWave;
+#define PX_LAUNCH_MEMO(CHILD, PAIRS, WAVES)                                                                                                \
+    do {                                                                                                                                   \
+        if (short_rows) hipLaunchKernelGGL((memo_candidates_kernel<KIND, true, CHILD, PAIRS, WAVES>), grid, dim3(WAVES * kWave), 0, stream, a); \
+        else hipLaunchKernelGGL((memo_candidates_kernel<KIND, false, CHILD, PAIRS, WAVES>), grid, dim3(WAVES * kWave), 0, stream, a);      \
     } while (0)
-    if (child) PX_LAUNCH_MEMO(true, true);
-    else if (pairs_kept) PX_LAUNCH_MEMO(false, true);
-    else PX_LAUNCH_MEMO(false, false);
+    if (child) PX_LAUNCH_MEMO(true, true, 4);
+    else if (pairs_kept && few) PX_LAUNCH_MEMO(false, true, 16);
+    else if (pairs_kept) PX_LAUNCH_MEMO(false, true, 4);
+    else if (few) PX_LAUNCH_MEMO(false, false, 16);
+    else PX_LAUNCH_MEMO(false, false, 4);
 #undef PX_LAUNCH_MEMO
 }
 

@@ -34,10 +34,10 @@ def test_rows_of_any_length(N):
         assert np.array_equal(plain[k], memo[k], equal_nan=True), k
 
 
-@pytest.mark.parametrize("J", [1, 255, 257, 1025, 1300])
+@pytest.mark.parametrize("P,J", [(4, 1), (4, 63), (4, 64), (4, 255), (4, 257), (256, 70), (257, 70), (4, 1025), (4, 1300)])
 @pytest.mark.parametrize("N", [6, 70])
-def test_more_jobs_than_a_chunk_of_the_pass(J, N):
-    wl = W.make(W.custom("chunks", P=4, J=J, N=N, cap=max(4, -(-J // N)), Gm=8, Gs=4, index=300 + J))
+def test_more_jobs_than_a_chunk_of_the_pass_and_few_candidates(P, J, N):
+    wl = W.make(W.custom("chunks", P=P, J=J, N=N, cap=max(4, -(-J // N)), Gm=8, Gs=4, index=300 + J))
     plain, memo = run_gpu(wl), run_gpu(wl, flags=MEMO)
     for k in NAMES + ("status",):
         assert np.array_equal(plain[k], memo[k], equal_nan=True), k
