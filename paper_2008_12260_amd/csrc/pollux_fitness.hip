@@ -358,7 +358,7 @@ typedef const double __attribute__((address_space(3))) *LdsDoubles;
 typedef double Double2 __attribute__((ext_vector_type(2)));
 
 constexpr int kRun = 16;
-constexpr int runs_of(int CH) { return CH > kRun ? CH / kRun : 1; }
+constexpr int runs_of(int CH) { return (CH + kRun - 1) / kRun; }
 // Chunks of 16 and 32 tag per group of four positions; chunks of 8 tag every position (twelve instructions per
 // four points, and less to find afterwards: quicker for very few counts per batch size).
 constexpr bool grouped_tags(int CH) { return CH >= 16; }
@@ -490,7 +490,7 @@ __device__ __forceinline__ double merge_runs(double lower, double upper)
 template <int CH>
 __device__ __forceinline__ double scan_chunk(double C, const RunSteps &X, ScalarDoubles rs)
 {
-    static_assert(CH == 8 || CH == 16 || CH == 32, "one or two runs");
+    static_assert(CH == 8 || CH == 16 || CH == 24 || CH == 32, "one or two runs");
     double kmin[runs_of(CH)];
     scan_groups<CH>(kmin, C, X, rs, load_group<0>(rs));
     if constexpr (runs_of(CH) == 1) return kmin[0];
@@ -628,13 +628,13 @@ __device__ __forceinline__ Pick elect(double kbest, int where, unsigned long lon
 // lowest flat index i * Gs + s).
 // TABLED: last pass and feasible ranges come from the job's tables (K <= kTableK), else they are formed here.
 // WHOLE: the caller has checked that Gm is a multiple of 64, so no lane runs past the grid of batch sizes.
-template <int CH, bool TABLED, bool WHOLE = false>
+template <int CH, bool TABLED, bool WHOLE = false, bool STAGED = false>
 __device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, const RunSteps &X, const double *__restrict__ rs,
                                            const double *__restrict__ rk, int Gm, int Gs, int K, int nodes,
                                            LdsDoubles near = nullptr, bool has_near = false, int staged_row = -1)
 {
     // near: a copy of rs in LDS (quicker to read per lane) when has_near
-    // staged_row: where in `near` the terms of this (class, K) are staged (TABLED and WHOLE; see kStageBase), or -1;
+    // staged_row: where in `near` the terms of this (class, K) are staged (TABLED and STAGED; see kStageBase), or -1;
     // rows are staged only together with has_near
     const int lane = lane_id();
     K = __builtin_amdgcn_readfirstlane(K);        // the same in every lane (see above): kept in scalar registers
@@ -757,7 +757,7 @@ __device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, co
             where = s_c | ((i0 / kWave) << 16);
         }
     };
-    if (TABLED && WHOLE && staged_row >= 0) {
+    if (TABLED && STAGED && staged_row >= 0) {
         group(0, std::integral_constant<int, 0>());
         if (Gm > kWave) group(kWave, std::integral_constant<int, 1>());
     } else {
@@ -1624,7 +1624,7 @@ pairs_kernel(FitnessArgs a)
     // behind them U[t] = t (t+1), U[0] = -1: what decides the order of neighbouring counts (sweep_pick)
     // kStage: behind them the table rows most of the workgroup's pairs read (see kStageBase); stage_votes counts, per
     // (class, K), the pairs of the workgroup that read the row
-    constexpr bool kStage = CH != 0 && !F32 && !MEMO && ROW1 && !ROW4 && WHOLE;
+    constexpr bool kStage = CH != 0 && !F32 && !MEMO && ROW1 && !ROW4;
     __shared__ __align__(16) double r_lds[kNearU + kNearRecips + 8 + (kStage ? kStageDoubles : 0)];
     __shared__ int stage_votes[kStage ? 2 * kTableK : 1];
     // (only where the table of reciprocals and thresholds is in LDS as well: sweep_pick's staged path reads both)
@@ -1990,9 +1990,13 @@ pairs_kernel(FitnessArgs a)
                 int range_in[kStageRows];
                 double2 tg_in = {0.0, 0.0};
                 if (t < a.Gm) tg_in = tb.tg[t];
+                // lanes past the end of a grid that is no whole group of 64 find a batch size without a feasible count
+                const int whole_gm = WHOLE ? a.Gm : (a.Gm <= kWave ? kWave : kStageGm);
 #pragma unroll
                 for (int e = 0; e < kStageRows; ++e) {
                     staged[e] = -1;
+                    ca_in[e] = double2{0.0, __builtin_inf()};
+                    range_in[e] = 0;
                     if (one != 0ull) {
                         staged[e] = kTableK + __builtin_ctzll(one);
                         one &= one - 1ull;
@@ -2001,13 +2005,13 @@ pairs_kernel(FitnessArgs a)
                         several &= several - 1ull;
                     }
                     if (staged[e] >= 0) {
-                        // threads 0 .. Gm-1 bring the (C, A0) pairs of the row, threads Gm .. 2 Gm - 1 its feasible ranges
+                        // threads 0 .. Gm-1 bring the (C, A0) pairs of the row, as many from whole_gm on its feasible ranges
                         if (t < a.Gm) ca_in[e] = tb.ca[(size_t)staged[e] * a.Gm + t];
-                        else if (t < 2 * a.Gm) range_in[e] = tb.srange[(size_t)(staged[e] & (kTableK - 1)) * a.Gm + (t - a.Gm)];
+                        else if (t >= whole_gm && t < whole_gm + a.Gm) range_in[e] = tb.srange[(size_t)(staged[e] & (kTableK - 1)) * a.Gm + (t - whole_gm)];
                         if (votes && my_row == staged[e]) d_s = kStageBase + 2 * kStageGm + e * kStageRowDoubles;
                     }
                 }
-                if (t < a.Gm) {
+                if (t < whole_gm) {
                     r_lds[kStageBase + 2 * t] = tg_in.x;
                     r_lds[kStageBase + 2 * t + 1] = tg_in.y;
                 }
@@ -2015,11 +2019,11 @@ pairs_kernel(FitnessArgs a)
                 for (int e = 0; e < kStageRows; ++e) {
                     if (staged[e] >= 0) {
                         double *row_lds = r_lds + kStageBase + 2 * kStageGm + e * kStageRowDoubles;
-                        if (t < a.Gm) {
+                        if (t < whole_gm) {
                             row_lds[2 * t] = ca_in[e].x;
                             row_lds[2 * t + 1] = ca_in[e].y;
-                        } else if (t < 2 * a.Gm) {
-                            ((int *)(row_lds + 2 * kStageGm))[t - a.Gm] = range_in[e];
+                        } else if (t < 2 * whole_gm) {
+                            ((int *)(row_lds + 2 * kStageGm))[t - whole_gm] = range_in[e];
                         }
                     }
                 }
@@ -2068,7 +2072,7 @@ pairs_kernel(FitnessArgs a)
             if (K >= 1 && !tabled_row(K, nodes == 1, tb.k1)) pick.i = kPending;   // rare: swept after the loop, outside the hot path
             else if (!MEMO && K >= 1) {
                 if constexpr (F32) pick = sweep_pick_f32<CH, WHOLE>(qf, tb, XF, a.rsf, a.Gm, a.Gs, K, nodes, (LdsFloats)(const float *)r_lds, has_near);
-                else pick = sweep_pick<CH, true, WHOLE>(q, tb, X, a.rs, a.rk, a.Gm, a.Gs, K, nodes, (LdsDoubles)r_lds, has_near,
+                else pick = sweep_pick<CH, true, WHOLE, kStage>(q, tb, X, a.rs, a.rk, a.Gm, a.Gs, K, nodes, (LdsDoubles)r_lds, has_near,
                                                         kStage ? __builtin_amdgcn_readlane(d_s, r) : -1);
             }
             if (lane == r) {
@@ -3057,8 +3061,10 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     a.fitness = fitness; a.best_goodput = best_goodput; a.speedup = speedup;
     a.best_m = best_m; a.best_s = best_s; a.violations = violations;
 
-    // unrolled s-chunk: the smallest of 8, 16, 32 that covers Gs (32 with several chunks beyond that)
-    const int ch = d->Gs <= 8 ? 8 : (d->Gs <= 16 ? 16 : 32);
+    // unrolled s-chunk: the smallest of 8, 16, 24, 32 that covers Gs (32 with several chunks beyond that).  (21 counts in a chunk
+    // of 24, and table rows staged in LDS on grids that are no whole groups of 64 too: 1021 candidates of 331 jobs with 50
+    // batch sizes 140 us a call, 159 without either.)
+    const int ch = d->Gs <= 8 ? 8 : (d->Gs <= 16 ? 16 : (d->Gs <= 24 ? 24 : 32));
     const long long pairs = (long long)P_eff * d->J;
     // candidates per wavefront: enough wavefronts to fill the chip several times over
     long long per_wave = pairs / 25000;
@@ -3163,6 +3169,8 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         PX_LAUNCH_PAIRS_GRID(8, false);
     } else if (ch == 16) {
         PX_LAUNCH_PAIRS_GRID(16, false);
+    } else if (ch == 24) {
+        PX_LAUNCH_PAIRS_GRID(24, false);
     } else {
         PX_LAUNCH_PAIRS_GRID(32, false);
     }
