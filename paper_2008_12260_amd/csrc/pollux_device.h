@@ -171,4 +171,25 @@ __device__ __forceinline__ unsigned wave_max(unsigned v)
     return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// ---- rows of any length and alignment ------------------------------------------
+// Four entries of a row in one 16-byte load; the hardware asks for the alignment of an entry only.
+typedef int Entries __attribute__((ext_vector_type(4), aligned(4)));
+
+// What lane l holds of a row of N >= 4 entries: entries base .. base + 3, of which the mask (all ones or zero per entry) keeps
+// those from 4 l on.  Lanes beyond the row load its last entries and keep none.
+struct RowLane {
+    int base;
+    Entries mask;
+};
+
+__device__ __forceinline__ RowLane row_lane(int l, int N)
+{
+    RowLane r;
+    const int first = 4 * l;
+    r.base = first < N - 4 ? first : N - 4;
+    const int skip = first < N ? first - r.base : 4;             // entries that belong to the lane before
+    r.mask = Entries{skip > 0 ? 0 : -1, skip > 1 ? 0 : -1, skip > 2 ? 0 : -1, skip > 3 ? 0 : -1};
+    return r;
+}
+
 }  // namespace px

@@ -226,12 +226,20 @@ __device__ __forceinline__ unsigned long long holder_key(int32_t v, int j)
     return ((unsigned long long)(uint32_t)v << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)j);
 }
 
-// FOUR: the host has checked that rows are 16-byte groups of at most 64 nodes and no per-job GPU limit is given.
+// ROWS (see launch_ga_step):
+//   kRowsAny      any rows, a per-job GPU limit or not
+//   kRowsAhead    rows of 4 to 256 nodes, no GPU limit, and too few children to hide one row's trip to memory behind the others':
+//                 rows copied unchanged are requested four at a time
+//   kRows64       (FOUR) rows of 4 to 64 nodes, no GPU limit; of any length and alignment (row_lane)
+//   kRows64Whole  (FOUR) and of whole 16-byte groups at 16-byte boundaries: without the masks (200 jobs on 64 nodes: 4 % of an interval)
 // INHERIT: the step also records where every row of the child comes from (GaArgs::src_row, odd); an instance of its
 // own, so that the plain step pays nothing for it (a few scalar registers more would cost it a workgroup per CU).
-template <bool FOUR, bool INHERIT>
+enum GaRows { kRowsAny, kRowsAhead, kRows64, kRows64Whole };
+
+template <int ROWS, bool INHERIT>
 __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96))) generation_kernel(GaArgs a)
 {
+    constexpr bool FOUR = ROWS >= kRows64;
     extern __shared__ __align__(16) unsigned char ga_lds[];
     __shared__ int count, n_dist, n_ent;
     __shared__ int odd;             // see GaArgs::odd
@@ -335,28 +343,31 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
     if constexpr (FOUR) {
         // kAhead loads are requested before the first is worked on: one after the other, each with its store and its
         // bookkeeping, the seven loads of a wavefront at 200 jobs took longest in the kernel (19.0 us in all, 17.1 so; what is left of it is the copy, at 7 TB/s out of the caches).
-        const int n4 = a.N >> 2;
         const int g = lane >> 4, l16 = lane & 15;
+        RowLane at_row = {4 * l16, Entries{-1, -1, -1, -1}};
+        if constexpr (ROWS == kRows64) at_row = row_lane(l16, a.N);
+        const bool in_row = 4 * l16 < a.N;
         constexpr int kAhead = 4;
         for (int j0 = 4 * wave; j0 < a.J; j0 += 4 * waves * kAhead) {
             int d[kAhead];
-            int4 v[kAhead];
+            Entries v[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 const int j = j0 + 4 * waves * u + g;
                 d[u] = j < a.J ? sh.dec[j] : 2;
-                v[u] = int4{0, 0, 0, 0};
-                if ((d[u] >> 1) == 0 && l16 < n4) v[u] = ((const int4 *)(((d[u] & 1) ? pb : pa) + (size_t)j * a.N))[l16];
+                v[u] = Entries{0, 0, 0, 0};
+                if ((d[u] >> 1) == 0 && in_row) v[u] = *(const Entries *)(((d[u] & 1) ? pb : pa) + (size_t)j * a.N + at_row.base);
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 if (j0 + 4 * waves * u >= a.J) break;
                 const int j = j0 + 4 * waves * u + g;
                 const bool plain = (d[u] >> 1) == 0;
-                const int4 w = v[u];
-                if (plain && l16 < n4) {
-                    ((int4 *)(child + (size_t)j * a.N))[l16] = w;
-                    const int n = 4 * l16;
+                // (the lane of a row's last entries writes some of its neighbour's again, the same)
+                if (plain && in_row) *(Entries *)(child + (size_t)j * a.N + at_row.base) = v[u];
+                const Entries w = v[u] & at_row.mask;
+                if (plain && in_row) {
+                    const int n = at_row.base;
                     if (w.x != 0) record(j, n, w.x);
                     if (w.y != 0) record(j, n + 1, w.y);
                     if (w.z != 0) record(j, n + 2, w.z);
@@ -530,6 +541,45 @@ __global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_num_sgpr(96)
                 mine &= mine - 1ull;
                 short_row_by_wavefront(jb + b, __builtin_amdgcn_readlane(dd, b));
             }
+        }
+    } else if constexpr (ROWS == kRowsAhead) {
+        // Rows that are copied unchanged, four requested before the first is worked on; then the rows with a move.
+        constexpr int kAhead = 4;
+        const RowLane at_row = row_lane(lane, a.N);
+        const bool in_row = 4 * lane < a.N;
+        for (int j0 = wave; j0 < a.J; j0 += waves * kAhead) {
+            int d[kAhead];
+            Entries v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int j = j0 + waves * u;
+                d[u] = j < a.J ? __builtin_amdgcn_readfirstlane(sh.dec[j]) : 2;
+                v[u] = Entries{0, 0, 0, 0};
+                if ((d[u] >> 1) == 0 && in_row) v[u] = *(const Entries *)(((d[u] & 1) ? pb : pa) + (size_t)j * a.N + at_row.base);
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int j = j0 + waves * u;
+                if ((d[u] >> 1) != 0) continue;
+                // (the lane of a row's last entries writes some of its neighbour's again, the same)
+                if (in_row) *(Entries *)(child + (size_t)j * a.N + at_row.base) = v[u];
+                const Entries w = v[u] & at_row.mask;
+                const int n = at_row.base;
+                if (w.x != 0) record(j, n, w.x);
+                if (w.y != 0) record(j, n + 1, w.y);
+                if (w.z != 0) record(j, n + 2, w.z);
+                if (w.w != 0) record(j, n + 3, w.w);
+                const int nodes = __popcll(__ballot(w.x > 0)) + __popcll(__ballot(w.y > 0)) + __popcll(__ballot(w.z > 0)) + __popcll(__ballot(w.w > 0));
+                if (lane == 0) {
+                    sh.nodes_of[j] = nodes;
+                    if (nodes >= 2) sh.dist[atomicAdd(&n_dist, 1)] = j;
+                    if (INHERIT) src_row[j] = (d[u] & 1) ? cand_b : cand_a;
+                }
+            }
+        }
+        for (int j = wave; j < a.J; j += waves) {
+            const int d = __builtin_amdgcn_readfirstlane(sh.dec[j]);
+            if ((d >> 1) != 0) row_by_wavefront(j, d);
         }
     } else {
         for (int j = wave; j < a.J; j += waves) row_by_wavefront(j, __builtin_amdgcn_readfirstlane(sh.dec[j]));
@@ -931,16 +981,26 @@ int launch_ga_step(const pollux_dims *d, const int32_t *parents, const double *f
 
     hipLaunchKernelGGL(rank_kernel, dim3((unsigned)((d->P + 3) / 4)), dim3(256), 0, stream, a);
     const size_t lds = ga_shared_bytes(d->J, d->N);
-    const bool four = (d->N & 3) == 0 && d->N <= kWave && !a.job_gpu_cap && (((uintptr_t)a.parents | (uintptr_t)a.children) & 15) == 0;
+    const unsigned children_formed = a.in_place ? (unsigned)d->P - ga->elite_k : (unsigned)d->P;
+    const bool four = d->N >= 4 && d->N <= kWave && !a.job_gpu_cap;
+    // Rows of 65 to 256 nodes: four requested at a time up to 1 GiB of children, where a wavefront otherwise waits for one row after
+    // the other (128 x 1000 x 256: 161 -> 137 us, 326 x 201 x 88: 49 -> 44, 1024 x 1000 x 256: 489 -> 473); beyond, the copy runs at
+    // the memory's rate without it (2048 x 1000 x 256: 881 us against 889).
+    const bool ahead = !four && d->N >= 4 && d->N <= 4 * kWave && !a.job_gpu_cap &&
+                       4ull * children_formed * (unsigned long long)d->J * d->N <= (1ull << 30);
     const bool inherit = a.src_row != nullptr;
-    const int instance = (four ? 1 : 0) + (inherit ? 2 : 0);
-    const void *kernels[4] = {(const void *)generation_kernel<false, false>, (const void *)generation_kernel<true, false>,
-                              (const void *)generation_kernel<false, true>, (const void *)generation_kernel<true, true>};
+    const bool whole = four && (d->N & 3) == 0 && (((uintptr_t)a.parents | (uintptr_t)a.children) & 15) == 0;
+    constexpr int kInstances = 8;
+    const void *kernels[kInstances] = {(const void *)generation_kernel<kRowsAny, false>, (const void *)generation_kernel<kRowsAhead, false>,
+                                       (const void *)generation_kernel<kRows64, false>, (const void *)generation_kernel<kRows64Whole, false>,
+                                       (const void *)generation_kernel<kRowsAny, true>, (const void *)generation_kernel<kRowsAhead, true>,
+                                       (const void *)generation_kernel<kRows64, true>, (const void *)generation_kernel<kRows64Whole, true>};
+    const int instance = (whole ? kRows64Whole : (four ? kRows64 : (ahead ? kRowsAhead : kRowsAny))) + (inherit ? 4 : 0);
     if (lds > 48 * 1024) {
         // Beyond 48 KB a kernel must be allowed its dynamic LDS explicitly.  The allowance is raised per kernel
         // instance and device, and only when a call needs more than any earlier one did.
         static std::mutex lock;
-        static size_t allowed[4][kGaDevices];
+        static size_t allowed[kInstances][kGaDevices];
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kGaDevices) return PX_E_HIP;
         std::lock_guard<std::mutex> hold(lock);
@@ -949,13 +1009,9 @@ int launch_ga_step(const pollux_dims *d, const int32_t *parents, const double *f
             allowed[instance][dev] = lds;
         }
     }
-    const unsigned children_formed = a.in_place ? (unsigned)d->P - ga->elite_k : (unsigned)d->P;
     if (children_formed > 0) {
-        const dim3 grid(children_formed), block(kGaThreads);
-        if (instance == 0) hipLaunchKernelGGL((generation_kernel<false, false>), grid, block, lds, stream, a);
-        else if (instance == 1) hipLaunchKernelGGL((generation_kernel<true, false>), grid, block, lds, stream, a);
-        else if (instance == 2) hipLaunchKernelGGL((generation_kernel<false, true>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((generation_kernel<true, true>), grid, block, lds, stream, a);
+        void *args[] = {&a};
+        if (hipLaunchKernel(kernels[instance], dim3(children_formed), dim3(kGaThreads), args, lds, stream) != hipSuccess) return PX_E_HIP;
     }
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
 }
