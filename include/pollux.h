@@ -460,8 +460,7 @@ int pollux_apply_best(const pollux_dims *dims,           /* host */
 
 /* Copies the status word of the last pollux_fitness (or pollux_fitness_timed) call that used `workspace`
  * to *host_out.  Synchronises `hip_stream`.  pollux_goodput_per_gpu and pollux_sim_tick neither clear nor
- * set the word; they do rewrite the job tables of the workspace, so a pollux_fitness call with
- * PX_FLAG_KEEP_JOB_TABLES may follow them only if they were given the same job_params, m_grid and grid. */
+ * set the word; they leave the workspace as it is. */
 int pollux_last_status(const void *workspace, void *hip_stream, int32_t *host_out /* host */);
 
 /* Text for a PX_* return code (static storage, never NULL). */
