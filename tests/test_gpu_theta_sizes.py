@@ -1,5 +1,5 @@
 """The fit at the record counts where its lanes, quarters of a wavefront and launch instances end: records held in registers
-(at most 64 per job) and records read in every evaluation give the same bits, and both reach the checker's error."""
+(at most 64 per job) and records read in every evaluation give the same bits, and both report the oracle's error."""
 import numpy as np
 import pytest
 
