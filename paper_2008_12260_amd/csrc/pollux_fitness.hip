@@ -66,11 +66,11 @@
 #include "../../include/pollux.h"
 #include "pollux_device.h"
 #include "pollux_host.h"
+#include "pollux_launch.h"
 #include "pollux_math.h"
 
 namespace px {
 
-constexpr int kWavesPerBlock = 4;
 constexpr int kMaxCandPerWave = 16;   // pairs kernel: candidates one wavefront walks at most (lane r keeps what candidate r needs)
 constexpr int kRecipTable = 256;      // 1/K is tabled for K below this
 
@@ -1492,9 +1492,8 @@ __global__ void __launch_bounds__(256) prepare_kernel(FitnessArgs a)
         if (lane_id() == 0) *a.k1 = c < kTableK ? c : kTableK;
     }
     constexpr int kTasks = prep_tasks(MODE, ROWS);
-    const int slot = (int)(blockIdx.x >> 3) * kWavesPerBlock + wave;
-    const int j = (slot / kTasks) * 8 + (int)(blockIdx.x & 7);
-    const int task = slot % kTasks;
+    const PrepSlot slot = prep_slot(blockIdx.x, wave, kTasks);
+    const int j = slot.job, task = slot.task;
     if (j >= a.J) return;
     if (task == 0) {
         prepare_job<MODE>(a, j);
@@ -2921,11 +2920,7 @@ template <int MODE>
 static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
 {
     auto blocks = [&](int rows) {
-        const long long slots = ((long long)(a.J + 7) / 8) * prep_tasks(MODE, rows);
-        long long n = (slots + kWavesPerBlock - 1) / kWavesPerBlock * 8;
-        // a few jobs with many candidates: enough workgroups to clear the counters
-        const long long clear = a.clear_counters ? ((long long)a.P * a.N + 4095) / 4096 : 0;
-        return dim3((unsigned)(n < clear ? (clear < 1024 ? clear : 1024) : n));
+        return dim3(prep_blocks(a.J, prep_tasks(MODE, rows), a.clear_counters ? (long long)a.P * a.N : 0));
     };
     if constexpr (MODE == kPrepSampled || MODE == kPrepSampledMemo) {
         hipLaunchKernelGGL((prepare_kernel<1, MODE>), blocks(1), dim3(256), 0, stream, a);

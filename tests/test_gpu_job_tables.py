@@ -37,3 +37,23 @@ def test_goodput_per_gpu_on_grids_of_any_size(Gm, Gs):
     px.pollux_goodput_per_gpu(dims, torch.as_tensor(wl.job_params).cuda(), torch.as_tensor(wl.m_grid).cuda(), 8, 12, ws, out)
     want = LP.goodput_per_gpu(wl.job_params, wl.m_grid, Gs, 8, 12)
     assert rel_err(out.cpu().numpy(), want).max() <= RTOL
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_every_job_is_prepared_beside_many_counters(precision):
+    """72 jobs need 1176 workgroups, the counters of 22000 candidates on 256 nodes would like 1375: copies of four candidates
+    get the four's results, those of the last jobs too."""
+    import torch
+    import paper_2008_12260_amd as px
+    wl = W.make(W.custom("many", P=4, J=72, N=256, cap=4, Gm=5, Gs=3, index=130))
+    want = run_gpu(wl, precision=precision)
+    if precision == 0:
+        assert compare(wl, want, run_oracle(wl)) == 0
+    c, copies = wl.cfg, 5500
+    call = px.FitnessCall(4 * copies, c.J, c.N, c.Gm, c.Gs, wl.job_params, wl.m_grid, wl.fair_share, wl.current_alloc, wl.node_capacity,
+                          p=c.p, delta=c.delta, precision=precision)
+    call.run(torch.as_tensor(wl.population).cuda().repeat(copies, 1, 1))
+    got = call.results()
+    assert got.pop("status") == want.pop("status")
+    for k, v in want.items():
+        assert np.array_equal(got[k], np.tile(v, (copies,) + (1,) * (v.ndim - 1)), equal_nan=True), k

@@ -1,0 +1,34 @@
+"""The job-level launch gives every (job, task) one wavefront, whatever else it is asked to clear: the arithmetic the kernel and
+its launch share, compiled for the host."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def launch(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("pxlaunch") / "libpxlaunch.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "launch_host.cpp")], check=True)
+    L = ctypes.CDLL(so)
+    L.px_host_prep_covers.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
+    L.px_host_prep_blocks.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
+    L.px_host_prep_blocks.restype = ctypes.c_uint
+    return L
+
+
+# wavefronts a job: itself alone; with 128 table rows eight, two or one at a time
+@pytest.mark.parametrize("tasks", [1, 17, 65, 129])
+def test_every_job_is_prepared(launch, tasks):
+    for jobs in (1, 7, 8, 9, 64, 65, 72, 100, 127, 128, 129, 241, 400, 1000, 4001):
+        for counters in (0, 1, 4096, 4096 * 1023, 4096 * 1024 + 1, 4096 * 1025, 16 * 4096, 20000 * 256, 30000 * 256, 1800 * 4096, 32000 * 256, 1 << 34):
+            assert launch.px_host_prep_covers(jobs, tasks, counters), (jobs, tasks, counters)
+
+
+def test_few_jobs_get_workgroups_to_clear_with(launch):
+    assert launch.px_host_prep_blocks(1, 17, 1 << 34) == 1024
+    assert launch.px_host_prep_blocks(1, 17, 4096 * 100) == 100
+    assert launch.px_host_prep_blocks(1000, 17, 0) == launch.px_host_prep_blocks(1000, 17, 4096) == 4256
