@@ -1,4 +1,5 @@
-// How the job-level launch divides its work: plain arithmetic, shared by the kernel, its launch and a host test.
+// Plain arithmetic shared by the kernels, their launches and a host test: how the job-level launch divides its work, and which
+// record a fit starts from.
 #pragma once
 
 #if defined(__HIPCC__)
@@ -33,5 +34,8 @@ inline unsigned prep_blocks(int jobs, int tasks, long long counters)
     const long long clear = (counters + 4095) / 4096, clearing = clear < 1024 ? clear : 1024;
     return (unsigned)(needed > clearing ? needed : clearing);
 }
+
+// The record a search over a job's records has found, or the first where it has found none (no time below infinity).
+PX_HOST_DEVICE int record_or_first(int found, int records) { return found < records ? found : 0; }
 
 }  // namespace px

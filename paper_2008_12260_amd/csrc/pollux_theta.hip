@@ -31,6 +31,7 @@
 #include "../../include/pollux.h"
 #include "pollux_device.h"
 #include "pollux_host.h"
+#include "pollux_launch.h"
 #include "pollux_math.h"
 
 namespace px {
@@ -319,7 +320,8 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
     // the usual case, at most one record per lane: each lane keeps its record for the whole fit
     Record mine = {1, 1, 1.0, 0.0, 0.0};
     if (HELD && lane < n) mine = load_record(f, base + lane);
-    const double m_at = (double)f.m[base + (size_t)__builtin_amdgcn_readfirstlane(best_o)];
+    // (a job whose times are all infinite, NaN or negative has no such record: what is fitted to it is unspecified, what is read is its own)
+    const double m_at = (double)f.m[base + (size_t)record_or_first(__builtin_amdgcn_readfirstlane(best_o), n)];
 
     // priors (Sec. 4.1, "Prior-driven exploration"): parameters without evidence are held at zero
     unsigned prior = 0u;

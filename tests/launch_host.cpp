@@ -1,4 +1,4 @@
-// Host build of the arithmetic that divides the job-level launch.
+// Host build of the arithmetic that kernels and launches share.
 #include "../paper_2008_12260_amd/csrc/pollux_launch.h"
 
 #include <stddef.h>
@@ -23,4 +23,5 @@ int px_host_prep_covers(int jobs, int tasks, long long counters)
     return 1;
 }
 unsigned px_host_prep_blocks(int jobs, int tasks, long long counters) { return px::prep_blocks(jobs, tasks, counters); }
+int px_host_record_or_first(int found, int records) { return px::record_or_first(found, records); }
 }

@@ -31,3 +31,21 @@ def test_records_in_registers_and_in_memory(counts, n_starts):
         want = TH.rmsle(held["theta"][:, j], *rec)
         assert abs(held["rmsle"][j] - want) <= 1e-12 * want + 1e-13     # residuals are differences of logarithms of size 1
         assert np.all(held["theta"][:6, j] >= 0.0) and 1.0 <= held["theta"][6, j] <= 10.0
+
+
+@pytest.mark.parametrize("slots", [64, 71])
+@pytest.mark.parametrize("n_starts", [1, 3, 5])
+def test_a_job_without_a_usable_time_does_not_touch_the_others(n_starts, slots):
+    """Times that are all infinite, NaN, zero or negative: the call ends, and every other job is fitted as without them."""
+    import paper_2008_12260_amd as px
+    J = 9
+    ob = W.observations(W.custom("records", P=1, J=J, N=4, cap=4, Gm=8, Gs=4, index=830), max_obs=slots)
+    want = px.fit_theta(ob, n_starts=n_starts)
+    bad = {1: np.inf, 3: np.nan, 5: -1.0, 6: 0.0, J - 1: np.inf}
+    for j, value in bad.items():
+        ob["T"][j] = value
+    ob["count"][J - 1] = slots
+    got = px.fit_theta(ob, n_starts=n_starts)
+    good = [j for j in range(J) if j not in bad]
+    for k in want:
+        assert np.array_equal(want[k][..., good], got[k][..., good]), k

@@ -1,5 +1,5 @@
-"""The job-level launch gives every (job, task) one wavefront, whatever else it is asked to clear: the arithmetic the kernel and
-its launch share, compiled for the host."""
+"""The arithmetic that kernels and launches share, compiled for the host: the job-level launch gives every (job, task) one
+wavefront, whatever else it is asked to clear; a fit starts from a record its job has."""
 import ctypes
 import os
 import subprocess
@@ -32,3 +32,10 @@ def test_few_jobs_get_workgroups_to_clear_with(launch):
     assert launch.px_host_prep_blocks(1, 17, 1 << 34) == 1024
     assert launch.px_host_prep_blocks(1, 17, 4096 * 100) == 100
     assert launch.px_host_prep_blocks(1000, 17, 0) == launch.px_host_prep_blocks(1000, 17, 4096) == 4256
+
+
+def test_a_fit_starts_from_a_record_its_job_has(launch):
+    for records in (1, 2, 64, 65, 1000):
+        for found in (0, 1, records - 1, records, 1 << 20, 0x7FFFFFFF):        # the last: no record had a time below infinity
+            at = launch.px_host_record_or_first(found, records)
+            assert at == (found if found < records else 0)
