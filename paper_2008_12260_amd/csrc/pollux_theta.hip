@@ -136,8 +136,8 @@ __device__ __forceinline__ Record load_record(const FitArgs &f, size_t at)
 }
 
 // The sums of one job at theta = z * scale (lane i < 7 holds the i-th of each), in `out` (LDS): SUM r^2, then J^T r, then J^T J as a packed lower triangle.
-// HELD: the job has at most 64 records and `mine` is lane l's (read once per job, kept in registers over all iterations);
-// otherwise the records are read from memory in every evaluation.
+// mine: the l-th record of the job, read once and kept in lane l's registers over all iterations.  HELD: the job has no more than
+// these 64; otherwise those beyond are read from memory in every evaluation.
 template <bool HELD>
 __device__ __forceinline__ void normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale, const Record &mine,
                                                  double *table, double *out)
@@ -206,22 +206,19 @@ __device__ __forceinline__ void normal_equations(const FitArgs &f, int j, int n,
     };
 #pragma unroll
     for (int t = 0; t < kSums; ++t) term[t] = 0.0;
-    if constexpr (HELD) {
+    const size_t base = (size_t)j * f.max_obs;
+    for (int o0 = 0; o0 < (HELD ? 1 : n); o0 += kWave) {
+        const int o = o0 + lane;
+        Record rec = mine;
+        if (!HELD && o0 > 0) rec = load_record(f, base + (size_t)(o < n ? o : n - 1));
         double r, d[kTheta];
-        evaluate(mine, r, d);
-        if (lane >= n) {
+        evaluate(rec, r, d);
+        if (o >= n) {
             r = 0.0;
 #pragma unroll
             for (int i = 0; i < kTheta; ++i) d[i] = 0.0;
         }
         add(r, d);
-    } else {
-        const size_t base = (size_t)j * f.max_obs;
-        for (int o = lane; o < n; o += kWave) {
-            double r, d[kTheta];
-            evaluate(load_record(f, base + o), r, d);
-            add(r, d);
-        }
     }
     sum_terms(table, term, out);
 }
@@ -317,9 +314,9 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
         best = __hiloint2double((int)hmin, (int)lmin);
     }
     const double t_min = uniform_f64(best);
-    // the usual case, at most one record per lane: each lane keeps its record for the whole fit
+    // each lane keeps one record for the whole fit; usually there are no more
     Record mine = {1, 1, 1.0, 0.0, 0.0};
-    if (HELD && lane < n) mine = load_record(f, base + lane);
+    if (lane < n) mine = load_record(f, base + lane);
     // (a job whose times are all infinite, NaN or negative has no such record: what is fitted to it is unspecified, what is read is its own)
     const double m_at = (double)f.m[base + (size_t)record_or_first(__builtin_amdgcn_readfirstlane(best_o), n)];
 
@@ -482,6 +479,9 @@ int launch_fit_theta(int J, int max_obs, int max_iter, int n_starts, const int32
     f.theta = theta; f.rmsle = rmsle; f.iterations = iterations;
     const size_t lds = sizeof(double) * kWaveDoubles * (size_t)n_starts;
     const dim3 grid((unsigned)J), block(64 * (unsigned)n_starts);
+    // The instance without the loop over further records needs 128 registers, not 162, so four wavefronts fit a SIMD: 1000 jobs of
+    // up to 48 records in 48 slots 1062 us, in 65 slots 1148 with the other (1213 while that read every record in every
+    // evaluation; 1000 jobs of up to 128 records 1345).
     if (max_obs <= kWave) hipLaunchKernelGGL(fit_theta_kernel<true>, grid, block, lds, stream, f);
     else hipLaunchKernelGGL(fit_theta_kernel<false>, grid, block, lds, stream, f);
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;

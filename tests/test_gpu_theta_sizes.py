@@ -1,5 +1,5 @@
-"""The fit at the record counts where its lanes, quarters of a wavefront and launch instances end: records held in registers
-(at most 64 per job) and records read in every evaluation give the same bits, and both report the oracle's error."""
+"""The fit at the record counts where its lanes, quarters of a wavefront and launch instances end: the instance for at most 64
+record slots and the one for more give the same bits, and both report the oracle's error."""
 import numpy as np
 import pytest
 
@@ -31,6 +31,29 @@ def test_records_in_registers_and_in_memory(counts, n_starts):
         want = TH.rmsle(held["theta"][:, j], *rec)
         assert abs(held["rmsle"][j] - want) <= 1e-12 * want + 1e-13     # residuals are differences of logarithms of size 1
         assert np.all(held["theta"][:6, j] >= 0.0) and 1.0 <= held["theta"][6, j] <= 10.0
+
+
+@pytest.mark.parametrize("n_starts", [1, 3])
+@pytest.mark.parametrize("counts", [[65, 64, 63, 127], [128, 129, 1, 200]])
+def test_more_records_than_lanes(counts, n_starts):
+    """The record a lane keeps and those it reads: the oracle's error, and the same bits however many slots the arrays have."""
+    import paper_2008_12260_amd as px
+    J = len(counts)
+    ob = W.observations(W.custom("records", P=1, J=J, N=4, cap=4, Gm=8, Gs=4, index=820 + counts[0]), max_obs=200)
+    rng = np.random.default_rng(counts[0])
+    for j, n in enumerate(counts):
+        have = int(ob["count"][j])
+        for k in ("K", "nodes", "m", "s", "T"):
+            ob[k][j, have:] = ob[k][j, rng.integers(0, have, 200 - have)]
+        ob["count"][j] = n
+    got = px.fit_theta(ob, n_starts=n_starts)
+    wider = {k: (v if k == "count" else np.concatenate([v, np.ones((J, 57), v.dtype)], axis=1)) for k, v in ob.items()}
+    again = px.fit_theta(wider, n_starts=n_starts)
+    for k in got:
+        assert np.array_equal(got[k], again[k]), k
+    for j, n in enumerate(counts):
+        want = TH.rmsle(got["theta"][:, j], *(ob[k][j, :n] for k in ("K", "nodes", "m", "s", "T")))
+        assert abs(got["rmsle"][j] - want) <= 1e-12 * want + 1e-13
 
 
 @pytest.mark.parametrize("slots", [64, 71])
