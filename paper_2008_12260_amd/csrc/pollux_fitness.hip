@@ -2345,23 +2345,30 @@ __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
 // a candidate: each wavefront finds the fair-share goodput of some jobs and reduces, sweeps and prices some of the candidate's
 // rows, forming the terms of its batch sizes itself (row_best, with the scan over all counts for the rows); the node counters
 // are in LDS, and the first wavefront forms SPEEDUP and the mean, term by term and in the tree of candidates_kernel.  The same
-// results, bit by bit.  Nothing of the workspace is read, and only the status section is written: every call of such dimensions
-// comes here, those that keep job tables and the children of a generation included.
+// results, bit by bit.  A call that starts anew leaves its fair shares and re-allocation factors in the workspace, beside the
+// status section; one that keeps the job tables (the children of a generation are such) takes them from there, which leaves a
+// wavefront one row to find.
 // The line (small_call) is drawn where a wavefront has two rows of 64 batch sizes to take, fair shares included, at 3 to 4 us a
-// row (a chain of dependent steps): 8 jobs 9.5 us a call against 15.9 in three launches, 12 jobs 11.9 against 17.5, 16 jobs 15.2
-// against 16.5, 24 jobs 20.7 against 19.3; 8 jobs with 128 batch sizes 12.3 against 17.6.  The status section holds a byte per
-// candidate.
+// row (a chain of dependent steps): 8 jobs 9.4 us a call against 15.9 in three launches, 12 jobs 11.5 against 17.5, 16 jobs 15.2
+// against 16.5, 24 jobs 20.7 against 19.3; 8 jobs with 128 batch sizes 12.1 against 17.6.  Calls that keep their tables are two
+// launches on the other side: 8 jobs 6.7 against 9.4, 16 jobs 8.9 against 9.6, and a generation of 16 jobs 17.4 against 18.5.
+// With more than 16 counts the scan weighs more: there 16 jobs take 15.5 against 15.0 and, keeping their tables, 9.1 against 8.2,
+// and one job with 512 batch sizes (eight groups one after the other) 13.5 against 11.9 keeping them, so the line lies at 14 jobs
+// (9.0 against 12.3) and four groups a row (4 jobs 9.3 against 23.8).  The status section holds a byte per candidate.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallJobs = 16;
 constexpr int kSmallCandidates = 4 * (kStatusWords - 1);
 
 static bool small_call(const pollux_dims &d)
 {
+    const int groups = (d.Gm + kWave - 1) / kWave;             // of 64 batch sizes, a row
     return d.precision == 0 && (d.flags & (PX_FLAG_MEMOISE | PX_FLAG_SAMPLE_M)) == 0 && d.P <= kSmallCandidates && d.J <= kSmallJobs &&
-           d.N >= 4 && d.N <= 4 * kWave && d.Gs <= kSmallGs && d.J * ((d.Gm + kWave - 1) / kWave) <= kSmallJobs;
+           d.N >= 4 && d.N <= 4 * kWave && d.Gs <= kSmallGs &&
+           d.J * groups <= kSmallJobs && (d.Gs <= 16 || (groups <= 4 && d.J <= kSmallJobs - 2));
 }
 
-template <int CH>
+// KEPT: the call keeps the job tables.
+template <int CH, bool KEPT>
 __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
 {
     __shared__ unsigned long long node_lds[4 * kWave];       // per node: GPUs asked + multi-node jobs << 40, as colpack
@@ -2382,9 +2389,16 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
     k1 = (int)wave_max((unsigned)(k1 > 0 ? k1 : 0));
     k1 = k1 < kTableK ? k1 : kTableK;
     __syncthreads();
-    for (int task = wave; task < 2 * a.J; task += kSmallThreads / kWave) {
-        const bool is_row = task >= a.J;
-        const int j = is_row ? task - a.J : task;
+    // (asked for here, so that the trip to memory is over when the first wavefront needs them)
+    double kept_fair = 0.0, kept_factor = 1.0;
+    if (KEPT && t < a.J) {
+        kept_fair = a.denom[t];
+        kept_factor = a.factor[t];
+    }
+    const int shares = KEPT ? 0 : a.J;                       // fair shares to find, before the rows
+    for (int task = wave; task < shares + a.J; task += kSmallThreads / kWave) {
+        const bool is_row = KEPT || task >= shares;
+        const int j = is_row ? task - shares : task;
         const Job q = load_job(a.job_params, a.J, j);
         const GridParams gp = load_grid_params(a.job_params, a.J, j);
         const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
@@ -2438,9 +2452,10 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
     double acc = 0.0, wsum = 0.0;
     if (mine) {
         const size_t pair = (size_t)c * a.J + lane;
-        const double w = a.job_params[(size_t)PX_WEIGHT * a.J + lane], d = fair_lds[lane];
+        const double w = a.job_params[(size_t)PX_WEIGHT * a.J + lane];
+        const double d = KEPT ? kept_fair : fair_lds[lane], factor = KEPT ? kept_factor : factor_lds[lane];
         double s_j = d > 0 ? goodput_lds[lane] / d : 0.0;
-        if (meta_lds[lane] & kMetaChanged) s_j = s_j * factor_lds[lane];
+        if (meta_lds[lane] & kMetaChanged) s_j = s_j * factor;
         if (a.best_m) {
             a.best_m[pair] = m_lds[lane];
             a.best_s[pair] = s_lds[lane];
@@ -2463,18 +2478,21 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
     }
     const long long V = wave_sum(v);
     const double mean = wave_tree_sum(acc) / wave_tree_sum(wsum);
-    const bool fresh = !(a.flags & PX_FLAG_KEEP_JOB_TABLES);
     if (lane == 0) {
         double f = pmean_finish(mean, a.p);
         if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
         if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
         a.fitness[c] = f;
         uint8_t *negatives = (uint8_t *)(a.status + 1);
-        if (fresh || negative) negatives[c] = (uint8_t)negative;
+        if (!KEPT || negative) negatives[c] = (uint8_t)negative;
     }
-    // a fresh call starts the status section anew; the jobs' bits are the same in every workgroup
-    if (fresh && blockIdx.x == 0) {
+    // a call that starts anew starts the status section anew; what it finds of the jobs is the same in every workgroup
+    if (!KEPT && blockIdx.x == 0) {
         if (lane == 0) *a.status = status_lds;
+        if (mine) {
+            a.denom[lane] = fair_lds[lane];
+            a.factor[lane] = factor_lds[lane];
+        }
         for (int i = a.P + lane; i < kSmallCandidates; i += kWave) ((uint8_t *)(a.status + 1))[i] = 0;
     }
 }
@@ -3051,9 +3069,17 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const bool f32 = d->precision == 1;
     if (small_call(*d)) {
         if (sweep_start) (void)hipEventRecord(sweep_start, stream);
-        if (ch == 8) hipLaunchKernelGGL(small_kernel<8>, dim3((unsigned)P_eff), dim3(kSmallThreads), 0, stream, a);
-        else if (ch == 16) hipLaunchKernelGGL(small_kernel<16>, dim3((unsigned)P_eff), dim3(kSmallThreads), 0, stream, a);
-        else hipLaunchKernelGGL(small_kernel<32>, dim3((unsigned)P_eff), dim3(kSmallThreads), 0, stream, a);
+        const dim3 grid((unsigned)P_eff), block(kSmallThreads);
+        const bool kept = (d->flags & PX_FLAG_KEEP_JOB_TABLES) != 0;
+#define PX_LAUNCH_SMALL(CH)                                                                    \
+    do {                                                                                       \
+        if (kept) hipLaunchKernelGGL((small_kernel<CH, true>), grid, block, 0, stream, a);     \
+        else hipLaunchKernelGGL((small_kernel<CH, false>), grid, block, 0, stream, a);         \
+    } while (0)
+        if (ch == 8) PX_LAUNCH_SMALL(8);
+        else if (ch == 16) PX_LAUNCH_SMALL(16);
+        else PX_LAUNCH_SMALL(32);
+#undef PX_LAUNCH_SMALL
         if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     }

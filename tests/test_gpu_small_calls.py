@@ -32,6 +32,26 @@ def test_either_side_of_the_line(P, J, N, Gm, Gs, p):
         assert compare(wl, run_gpu(wl, p=p, flags=flags), run_oracle(wl, p=p, flags=flags)) == 0
 
 
+@pytest.mark.parametrize("P,J,N,Gm,Gs", [(6, 1, 4, 1, 1), (252, 5, 6, 33, 8), (253, 5, 6, 33, 8), (6, 16, 9, 64, 16), (6, 17, 9, 64, 16),
+                                         (6, 14, 9, 64, 17), (6, 15, 9, 64, 17), (5, 4, 9, 256, 32), (5, 3, 9, 257, 17), (5, 1, 7, 1024, 16)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_calls_that_keep_their_tables(P, J, N, Gm, Gs, flags):
+    """Another population, the fair shares and re-allocation factors of the call before: the oracle's results."""
+    import torch
+    import paper_2008_12260_amd as px
+    wl = workload(P, J, N, Gm, Gs, 1500 + N)
+    wl.fair_share[::2, 0] = 66
+    c = wl.cfg
+    call = px.FitnessCall(P, J, N, Gm, Gs, wl.job_params, wl.m_grid, wl.fair_share, wl.current_alloc, wl.node_capacity, p=c.p,
+                          delta=c.delta, flags=flags)
+    call.run(torch.as_tensor(wl.population).cuda())
+    assert compare(wl, call.results(), run_oracle(wl, flags=flags)) == 0
+    for seed in (1, 2):
+        pop = wl.population[np.random.default_rng(seed).permutation(P)][:, :, ::-1].copy()
+        call.run(torch.as_tensor(pop).cuda(), keep_job_tables=True)
+        assert compare(wl, call.results(), run_oracle(wl, population=pop, flags=flags), population=pop) == 0
+
+
 @pytest.mark.parametrize("P", [40, 260])                     # one launch, and the general path
 def test_status_word_is_started_by_a_call_and_kept_by_the_next(P):
     import torch
