@@ -71,7 +71,6 @@
 
 namespace px {
 
-constexpr int kMaxCandPerWave = 16;   // pairs kernel: candidates one wavefront walks at most (lane r keeps what candidate r needs)
 constexpr int kRecipTable = 256;      // 1/K is tabled for K below this
 
 // Result of the sweep for one (job, placement class, K); filled and used only in memoised mode.
@@ -127,6 +126,10 @@ constexpr int kNearU = 2 * kNearRecips;
 // (or times 4 for the ranges) plus a uniform offset, as they are for the tables in memory.
 constexpr int kStageGm = 128;             // staged rows hold grids of at most this many batch sizes
 constexpr int kStageRows = 4;             // rows staged at most (16.6 KB of LDS per workgroup with the rest: eight workgroups per CU)
+// Candidates per wavefront from which staging pays for its two barriers; the children of a generation resemble each other, so more
+// of their pairs share a row.  Kept calls on 128 nodes, us without, with: 50 x 16, 200 candidates of 100 jobs (one each) 23.0, 25.4;
+// 500 of 200 (four each) 46.5, 48.1; 100 x 8, 1000 of 200 (eight each) 83.4, 80.9; its 500 children (four each) 89.5, 86.4.
+constexpr int stage_candidates(int SEL) { return SEL == 0 ? 5 : 4; }
 constexpr int kStageRowDoubles = 2 * kStageGm + kStageGm / 2;
 constexpr int kStageBase = kNearU + kNearRecips + 8;
 constexpr int kStageDoubles = 2 * kStageGm + kStageRows * kStageRowDoubles;
@@ -1564,7 +1567,7 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 // keep an instance without them.  (1021 candidates of 331 jobs on 130 nodes: 207 us entry by entry, 134 so.)
 // WHOLE: the host has checked that Gm is a multiple of 64 (tabled sweeps then skip the test for the end of the grid).
 // ROW4: ROW1 and a row is at most 64 entries, so one load of the wavefront covers the rows of four candidates
-// (16 lanes each); cand_per_wave is at most 16.
+// (16 lanes each); cand_per_wave is at most 16.  kFourRowsSwept: the candidates are also swept four at a time (see split_pairs).
 // SEL: only the candidates listed in a.sel are evaluated (the children a search step has just formed); the
 // wavefronts then walk positions of that list and look the candidate up where an address is formed.
 // Eight wavefronts per SIMD (64 registers); the instances that sweep four candidates at a time (rows_at_a_time)
@@ -1574,17 +1577,18 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 // hand the registers of each finished pair to the rows of the next stretch of eight; then the sweeps of its
 // candidates, one after the other; then prices and stores.  What a wavefront spends waiting at its start is
 // time the vector ALU has one wavefront fewer to draw on, so memory is asked as early as the addresses are known.
-// Between row pass and sweeps (grids of at most 128 batch sizes, whole groups of 64): the workgroup's 64 pairs
+// Between row pass and sweeps (grids of at most 128 batch sizes, stage_candidates or more a wavefront): the workgroup's 64 pairs
 // share one job and mostly a handful of (placement class, GPU count) rows of its tables, so each pair votes for
 // its row, the rows with two votes or more (four at most) are copied to LDS once, and the sweeps of those pairs
 // read (C, A0), T_grad and the feasible range from there.  Three vector-memory loads per lane and group of 64
 // batch sizes were what kept the texture addresser two thirds busy and the vector ALU waiting.
-constexpr bool rows_at_a_time(int CH, bool F32, bool MEMO, bool ROW4) { return ROW4 && !MEMO && CH != 0 && CH <= 16; }
+enum { kRowAtATime, kFourRowsLoaded, kFourRowsSwept };      // ROW4
+constexpr bool rows_at_a_time(int ROW4) { return ROW4 == kFourRowsSwept; }
 
 // SEL = 2: per job, the candidates listed in a.dirty[j, 0 .. a.dirty_count[j]) (row inheritance: the rows of job j that a
 // move or a repair of the search step has changed); workgroups beyond a job's list return at once.
-template <int CH, bool F32, bool MEMO, bool ROW1, bool WHOLE, bool ROW4, bool RAG, int SEL>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rows_at_a_time(CH, F32, MEMO, ROW4) ? 6 : 8)))
+template <int CH, bool F32, bool MEMO, bool ROW1, bool WHOLE, int ROW4, bool RAG, int SEL>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rows_at_a_time(ROW4) ? 6 : 8)))
 pairs_kernel(FitnessArgs a)
 {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -1607,7 +1611,7 @@ pairs_kernel(FitnessArgs a)
     __shared__ __align__(16) double r_lds[kNearU + kNearRecips + 8 + (kStage ? kStageDoubles : 0)];
     __shared__ int stage_votes[kStage ? 2 * kTableK : 1];
     // (only where the table of reciprocals and thresholds is in LDS as well: sweep_pick's staged path reads both)
-    const bool stage_on = kStage && a.Gm <= kStageGm && a.gs_pad <= kNearRecips;
+    const bool stage_on = kStage && a.Gm <= kStageGm && a.gs_pad <= kNearRecips && a.cand_per_wave >= stage_candidates(SEL);
     bool has_near = false;
     // (the instances whose rows fit one 16-byte load per lane fill the table after they have requested their first rows)
     constexpr bool kRowsFirst = CH != 0 && ROW1;
@@ -2013,7 +2017,7 @@ pairs_kernel(FitnessArgs a)
         if constexpr (F32) XF = make_run_steps_f32();
         else X = make_run_steps();
         // Short rows come with small grids: there the sweeps go four candidates at a time, one per row of 16 lanes.
-        constexpr bool kRows = rows_at_a_time(CH, F32, MEMO, ROW4);
+        constexpr bool kRows = rows_at_a_time(ROW4);
         if constexpr (kRows) {
             const int g = lane >> 4;
             for (int b = 0; 4 * b < rows; ++b) {
@@ -3058,12 +3062,16 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     // of 24, and table rows staged in LDS on grids that are no whole groups of 64 too: 1021 candidates of 331 jobs with 50
     // batch sizes 140 us a call, 159 without either.)
     const int ch = d->Gs <= 8 ? 8 : (d->Gs <= 16 ? 16 : (d->Gs <= 24 ? 24 : 32));
-    const long long pairs = (long long)P_eff * d->J;
-    // candidates per wavefront: enough wavefronts to fill the chip several times over
-    long long per_wave = pairs / 25000;
-    per_wave = per_wave < 1 ? 1 : (per_wave > kMaxCandPerWave ? kMaxCandPerWave : per_wave);
-    a.cand_per_wave = (int)per_wave;
-    a.cand_groups = (int)((P_eff + per_wave * kWavesPerBlock - 1) / (per_wave * kWavesPerBlock));
+    const bool inherit = inherit_rows && first_rank > 0;
+    const bool row1 = d->N >= 4 && d->N <= 4 * kWave;
+    const bool aligned = row1 && (d->N & 3) == 0 && (((uintptr_t)population | (uintptr_t)current_alloc) & 15) == 0;
+    const bool whole = d->Gm % kWave == 0;
+    const bool near = a.gs_pad <= kNearRecips;      // the kernels keep reciprocals and thresholds of all counts in LDS
+    // four rows per load of a wavefront (cand_per_wave <= 16 holds); its sweeps pack a batch size's index into 15 bits
+    const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF && near;
+    const PairSplit split = split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit);
+    a.cand_per_wave = split.per_wave;
+    a.cand_groups = pair_groups(P_eff, split.per_wave);
     const unsigned pair_blocks = (unsigned)(8 * ((d->J + 7) / 8) * a.cand_groups);
 
     const bool f32 = d->precision == 1;
@@ -3094,11 +3102,6 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     // The per-node counters start every call at zero.  A call that uses them leaves them at zero again
     // (candidates_kernel clears what it reads), so a call that keeps the job tables, whose caller guarantees an
     // untouched workspace and unchanged dimensions, does not clear them once more.
-    const bool row1 = d->N >= 4 && d->N <= 4 * kWave;
-    const bool aligned = row1 && (d->N & 3) == 0 && (((uintptr_t)population | (uintptr_t)current_alloc) & 15) == 0;
-    // four rows per load of a wavefront (cand_per_wave <= 16 holds); its sweeps pack a batch size's index into 15 bits
-    const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF;
-    const bool inherit = inherit_rows && first_rank > 0;
     // memoised pass over rows of 4 to 256 entries: one workgroup per candidate, counters in LDS, fitness included
     const bool candidate_pass = memo && d->N >= 4 && d->N <= kMemoNodes;
     if (inherit) {
@@ -3134,24 +3137,27 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         }
     }
     if (sweep_start) (void)hipEventRecord(sweep_start, stream);
-    const bool whole = d->Gm % kWave == 0;
-    const bool near = a.gs_pad <= kNearRecips;      // the kernels keep reciprocals and thresholds of all counts in LDS
 #define PX_LAUNCH_PAIRS(CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG)                                                               \
     do {                                                                                                                     \
         if (a.dirty) hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG, 2>), dim3(pair_blocks), dim3(256), 0, stream, a); \
         else if (a.sel) hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG, 1>), dim3(pair_blocks), dim3(256), 0, stream, a); \
         else hipLaunchKernelGGL((pairs_kernel<CH, F32, MEMO, ROW1, WHOLE, ROW4, RAG, 0>), dim3(pair_blocks), dim3(256), 0, stream, a); \
     } while (0)
-    // the instance for the row length (four rows per load, one row per load, any) and the grid (whole groups of 64 batch sizes or not)
-#define PX_LAUNCH_PAIRS_GRID(CH, F32)                                                       \
-    do {                                                                                    \
-        if (memo) PX_LAUNCH_PAIRS(16, F32, true, false, false, false, false);               \
-        else if (row4 && aligned && whole && near) PX_LAUNCH_PAIRS(CH, F32, false, true, true, true, false);  \
-        else if (row4 && near) PX_LAUNCH_PAIRS(CH, F32, false, true, false, true, true);    \
-        else if (aligned && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, false, false); \
-        else if (row1 && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, false, true);   \
-        else if (row1) PX_LAUNCH_PAIRS(CH, F32, false, true, false, false, true);           \
-        else PX_LAUNCH_PAIRS(CH, F32, false, false, false, false, false);                   \
+    // the instance for the row length (four rows per load, one row per load, any) and the grid (whole groups of 64 batch sizes or not).
+    // Ragged rows of at most 64 nodes with fewer than four candidates a wavefront go entry by entry, a lane each (64 x 500 x 17 with
+    // 500 batch sizes 47.0 us against 51.2 in 16-byte loads), but for the children of a generation (76 against 44).
+    constexpr int kSwept = kFourRowsSwept, kLoaded = kFourRowsLoaded, kOne = kRowAtATime;
+    const bool entries = !row1 || (row4 && !aligned && split.entry_by_entry && !a.sel);
+#define PX_LAUNCH_PAIRS_GRID(CH, F32, FOUR)                                                          \
+    do {                                                                                             \
+        if (memo) PX_LAUNCH_PAIRS(16, F32, true, false, false, kOne, false);                         \
+        else if (entries) PX_LAUNCH_PAIRS(CH, F32, false, false, false, kOne, false);                \
+        else if (split.four && aligned && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, FOUR, false);  \
+        else if (split.four) PX_LAUNCH_PAIRS(CH, F32, false, true, false, FOUR, true);               \
+        else if (aligned && whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, kOne, false);         \
+        else if (aligned) PX_LAUNCH_PAIRS(CH, F32, false, true, false, kOne, false);                 \
+        else if (whole) PX_LAUNCH_PAIRS(CH, F32, false, true, true, kOne, true);                     \
+        else PX_LAUNCH_PAIRS(CH, F32, false, true, false, kOne, true);                               \
     } while (0)
     if (candidate_pass) {
         const bool pairs_kept = (d->flags & PX_FLAG_PAIR_RESULTS) != 0 || !(d->flags & PX_FLAG_MEMOISE);
@@ -3161,19 +3167,22 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     } else if (sampled) {
-        if (memo) PX_LAUNCH_PAIRS(0, false, true, false, false, false, false);
-        else PX_LAUNCH_PAIRS(0, false, false, false, false, false, false);
+        if (memo) PX_LAUNCH_PAIRS(0, false, true, false, false, kOne, false);
+        else PX_LAUNCH_PAIRS(0, false, false, false, false, kOne, false);
+    } else if (f32 && row4 && aligned && whole && !split.four && !memo) {
+        if (ch == 8) PX_LAUNCH_PAIRS(8, true, false, true, true, kLoaded, false);
+        else PX_LAUNCH_PAIRS(16, true, false, true, true, kLoaded, false);
     } else if (f32) {
-        if (ch == 8) PX_LAUNCH_PAIRS_GRID(8, true);
-        else PX_LAUNCH_PAIRS_GRID(16, true);
+        if (ch == 8) PX_LAUNCH_PAIRS_GRID(8, true, kSwept);
+        else PX_LAUNCH_PAIRS_GRID(16, true, kSwept);
     } else if (ch == 8) {
-        PX_LAUNCH_PAIRS_GRID(8, false);
+        PX_LAUNCH_PAIRS_GRID(8, false, kSwept);
     } else if (ch == 16) {
-        PX_LAUNCH_PAIRS_GRID(16, false);
+        PX_LAUNCH_PAIRS_GRID(16, false, kSwept);
     } else if (ch == 24) {
-        PX_LAUNCH_PAIRS_GRID(24, false);
+        PX_LAUNCH_PAIRS_GRID(24, false, kLoaded);
     } else {
-        PX_LAUNCH_PAIRS_GRID(32, false);
+        PX_LAUNCH_PAIRS_GRID(32, false, kLoaded);
     }
 #undef PX_LAUNCH_PAIRS_GRID
 #undef PX_LAUNCH_PAIRS

@@ -23,5 +23,12 @@ int px_host_prep_covers(int jobs, int tasks, long long counters)
     return 1;
 }
 unsigned px_host_prep_blocks(int jobs, int tasks, long long counters) { return px::prep_blocks(jobs, tasks, counters); }
+// Candidates a wavefront takes, | 16 swept in fours, | 32 read entry by entry.
+int px_host_split(int candidates, int jobs, int Gm, int Gs, int f32, int row4, int whole_rows, int inherit)
+{
+    const px::PairSplit p = px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row4 != 0, whole_rows != 0, inherit != 0);
+    return (p.per_wave - 1) | (p.four ? 16 : 0) | (p.entry_by_entry ? 32 : 0);
+}
+int px_host_pair_groups(int candidates, int per_wave) { return px::pair_groups(candidates, per_wave); }
 int px_host_record_or_first(int found, int records) { return px::record_or_first(found, records); }
 }

@@ -74,3 +74,47 @@ def test_fp32_four_rows_at_a_time_elects_what_one_row_at_a_time_elects(N, Gm, Gs
     want = run_gpu(long, precision=1)
     for k in want:
         assert np.array_equal(short[k], want[k], equal_nan=True), k
+
+
+# either side of every line of split_pairs (candidates in whole fours, grid width, counts, pairs, candidates a wavefront) and of the
+# staging of table rows (five candidates a wavefront)
+SPLITS = [(12, 7, 5, 64, 16), (13, 7, 5, 64, 16), (13, 7, 8, 50, 16), (12, 7, 8, 65, 8), (13, 455, 5, 65, 16), (13, 465, 5, 65, 16),
+          (16, 380, 9, 128, 12), (16, 380, 9, 129, 12), (16, 380, 8, 64, 17), (16, 380, 9, 64, 17), (40, 30, 64, 128, 16),
+          (2260, 100, 4, 64, 16), (2510, 100, 4, 64, 8), (2510, 100, 5, 65, 8), (2510, 100, 5, 33, 8), (1010, 100, 66, 33, 8), (1260, 100, 66, 33, 8),
+          (1010, 100, 68, 65, 16), (1260, 100, 68, 65, 16)]
+
+
+@pytest.mark.parametrize("P,J,N,Gm,Gs", SPLITS)
+@pytest.mark.parametrize("precision", [0, 1])
+def test_either_side_of_the_lines_of_the_split(P, J, N, Gm, Gs, precision):
+    """The same population with empty nodes appended gives the same bits (and fp64 the oracle's results); the children of a
+    generation get what a call on the new population gives them, row by row inherited or not."""
+    import torch
+    import paper_2008_12260_amd as px
+    wl = W.make(W.custom("split", P=P, J=J, N=N, cap=4, Gm=Gm, Gs=Gs, index=780 + N))
+    wl.population[1 % P, J - 1, 0] = 70                       # beyond the tables
+    c = wl.cfg
+    got = run_gpu(wl, precision=precision)
+    if precision == 0 and P * J * Gm * Gs <= 2 ** 28:
+        assert compare(wl, got, run_oracle(wl)) == 0
+    extra = 131 - N
+    pad = lambda x: np.concatenate([x, np.zeros(x.shape[:-1] + (extra,), x.dtype)], axis=-1)
+    long = W.make(W.custom("split long", P=P, J=J, N=131, cap=4, Gm=Gm, Gs=Gs, index=780 + N), with_population=False)
+    long.job_params, long.m_grid, long.fair_share = wl.job_params, wl.m_grid, wl.fair_share
+    long.current_alloc, long.population = pad(wl.current_alloc), pad(wl.population)
+    long.node_capacity = np.concatenate([wl.node_capacity, np.full(extra, 4, np.int32)])
+    want = run_gpu(long, precision=precision)
+    for k in want:
+        assert np.array_equal(got[k], want[k], equal_nan=True), k
+    for inherit in (False, True):
+        call = px.FitnessCall(P, J, N, Gm, Gs, wl.job_params, wl.m_grid, wl.fair_share, wl.current_alloc, wl.node_capacity,
+                              p=c.p, delta=c.delta, precision=precision)
+        pop = torch.as_tensor(wl.population).cuda()
+        call.run(pop)
+        for g in (1, 2):
+            call.generation(pop, 5, g, max(1, P // 3), (1 << 32) // 8, inherit_rows=inherit)
+        got_g = call.results()
+        want_g = run_gpu(wl, population=pop.cpu().numpy(), precision=precision)
+        for k in want_g:
+            if k != "status":                                 # (the first call's population had more in it)
+                assert np.array_equal(got_g[k], want_g[k], equal_nan=True), (inherit, k)

@@ -34,6 +34,28 @@ def test_few_jobs_get_workgroups_to_clear_with(launch):
     assert launch.px_host_prep_blocks(1000, 17, 0) == launch.px_host_prep_blocks(1000, 17, 4096) == 4256
 
 
+@pytest.mark.parametrize("f32", [0, 1])
+@pytest.mark.parametrize("inherit", [0, 1])
+def test_the_population_pass_takes_every_candidate(launch, f32, inherit):
+    """1 to 16 candidates a wavefront, four wavefronts a workgroup, as many workgroups as the candidates need and no more; a sweep
+    of four is not asked to find fewer than four candidates when the split is rounded for it."""
+    for candidates in (1, 3, 4, 12, 13, 16, 64, 100, 1000, 4096, 22000, 0x7FFFFFFF):
+        for jobs in (1, 8, 30, 200, 1000, 100000):
+            if candidates * jobs > 0x7FFFFFFF:
+                continue
+            for Gm, Gs in ((1, 1), (64, 16), (65, 16), (128, 8), (129, 8), (64, 17), (64, 32), (4096, 4)):
+                for row4, whole in ((0, 0), (0, 1), (1, 0), (1, 1)):
+                    got = launch.px_host_split(candidates, jobs, Gm, Gs, f32, row4, whole, inherit)
+                    n, four = (got & 15) + 1, bool(got & 16)
+                    groups = launch.px_host_pair_groups(candidates, n)
+                    assert (groups - 1) * 4 * n < candidates <= groups * 4 * n
+                    assert row4 or not got & 48
+                    if four and not inherit and (f32 or not whole) and Gs <= 16:
+                        assert n % 4 == 0 and candidates > 12
+                    if got & 32:
+                        assert not four and n < 4
+
+
 def test_a_fit_starts_from_a_record_its_job_has(launch):
     for records in (1, 2, 64, 65, 1000):
         for found in (0, 1, records - 1, records, 1 << 20, 0x7FFFFFFF):        # the last: no record had a time below infinity
