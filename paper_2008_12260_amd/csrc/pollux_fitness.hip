@@ -2019,34 +2019,35 @@ pairs_kernel(FitnessArgs a)
         // Short rows come with small grids: there the sweeps go four candidates at a time, one per row of 16 lanes.
         constexpr bool kRows = rows_at_a_time(ROW4);
         if constexpr (kRows) {
-            const int g = lane >> 4;
-            for (int b = 0; 4 * b < rows; ++b) {
-                // lane r holds K and nodes of candidate r; this lane's row works on candidate 4 b + g
-                const int r = 4 * b + g;
-                const int K = __builtin_amdgcn_ds_bpermute(r << 2, d_K);
-                const int nodes = __builtin_amdgcn_ds_bpermute(r << 2, d_meta) & ~kMetaChanged;
-                const bool within = tabled_row(K, nodes == 1, tb.k1);
-                const int K_in = (K < 1 || !within) ? 1 : K;
+            // Lane r holds K and nodes of candidate r.  A sweep lasts as long with empty rows as with others: where it saves a
+            // sweep, the rows that want one (not those beyond the tables, swept after the loop, either) move up to the first slots.
+            const bool one = (d_meta & ~kMetaChanged) == 1, tabled = tabled_row(d_K, one, tb.k1);
+            const bool wanted = lane < rows && d_K >= 1 && tabled;
+            const unsigned live = (unsigned)__ballot(wanted);
+            const int live_sweeps = (__builtin_popcount(live) + 3) >> 2;
+            const bool packed = live_sweeps < ((rows + 3) >> 2);
+            const int sweeps = packed ? live_sweeps : (rows + 3) >> 2;
+            int in_slot = wanted ? d_K | (one ? 1 << 8 : 0) : 0, found_in_slot = -1;
+            const int slot = wanted ? __builtin_popcount(live & ((1u << (lane & 15)) - 1u)) : kWave - 1;
+            if (packed) in_slot = __builtin_amdgcn_ds_permute(slot << 2, in_slot);
+            for (int b = 0; b < sweeps; ++b) {
+                // this lane's row works on slot 4 b + (its number)
+                const int K_one = __builtin_amdgcn_ds_bpermute((4 * b + (lane >> 4)) << 2, in_slot);
+                const int K = K_one & 0xFF, K_in = K < 1 ? 1 : K;
+                const bool one_node = (K_one >> 8) != 0;
                 // (this instance is launched only for grids whose tables of reciprocals and thresholds fit LDS)
                 int found;
-                if constexpr (F32) found = sweep_pick_rows_f32<CH, WHOLE>(qf, tb, XF, a.rsf, a.Gm, a.Gs, K_in, nodes == 1 && within, (LdsFloats)(const float *)r_lds, WHOLE || has_near);
-                else found = sweep_pick_rows<CH, WHOLE>(tb, X, a.rs, a.Gm, a.Gs, K_in, nodes == 1 && within, (LdsDoubles)r_lds, WHOLE || has_near);
-                int pi = found < 0 ? -1 : found >> 16, ps = found < 0 ? -1 : found & 0xFFFF;
-                if (K >= 1 && !within) {                     // rare: swept after the loop, outside the hot path
-                    pi = kPending;
-                    ps = -1;
-                } else if (K < 1 || r >= rows) {
-                    pi = -1;
-                    ps = -1;
-                }
-                // lane 4 b + g' takes over what row g' has found
-                const int from = ((lane & 3) * 16) << 2;
-                const int ti = __builtin_amdgcn_ds_bpermute(from, pi), ts = __builtin_amdgcn_ds_bpermute(from, ps);
-                if ((lane >> 2) == b) {
-                    d_i = ti;
-                    d_s = ts;
-                }
+                if constexpr (F32) found = sweep_pick_rows_f32<CH, WHOLE>(qf, tb, XF, a.rsf, a.Gm, a.Gs, K_in, one_node, (LdsFloats)(const float *)r_lds, WHOLE || has_near);
+                else found = sweep_pick_rows<CH, WHOLE>(tb, X, a.rs, a.Gm, a.Gs, K_in, one_node, (LdsDoubles)r_lds, WHOLE || has_near);
+                found = K < 1 ? -1 : found;
+                // lane 4 b + g takes over what row g has found
+                const int taken = __builtin_amdgcn_ds_bpermute(((lane & 3) * 16) << 2, found);
+                if ((lane >> 2) == b) found_in_slot = taken;
             }
+            const int found = packed ? __builtin_amdgcn_ds_bpermute(slot << 2, found_in_slot) : found_in_slot;
+            d_i = found < 0 ? -1 : found >> 16;
+            d_s = found < 0 ? -1 : found & 0xFFFF;
+            if (lane < rows && d_K >= 1 && !tabled) d_i = kPending;
         }
         for (int r = 0; !kRows && r < rows; ++r) {
             const int K = __builtin_amdgcn_readlane(d_K, r);

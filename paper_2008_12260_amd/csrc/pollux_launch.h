@@ -40,19 +40,18 @@ constexpr int kMaxCandPerWave = 16;   // candidates one wavefront of pairs_kerne
 // How many candidates a wavefront of pairs_kernel takes: enough wavefronts to fill the chip several times over.  And, for rows of at
 // most 64 nodes whose count tables are on chip (row4), whether one load covers the rows of four candidates, which with chunks of up
 // to 16 counts also sweeps the four, a row of 16 lanes each.
-// A sweep of four saves three elections and lasts as long with one candidate as with four: it wants candidates in whole fours and
-// narrow grids.  In fp32 on whole rows and grids the instance that sweeps one at a time has eight wavefronts a SIMD against six, and
-// is quicker from nine candidates a wavefront on.  fp64 on whole rows and grids takes four always.  Calls that keep their tables,
-// us, 16 nodes (whole rows) and 17: one at a time, four at a time in whole fours (in brackets: one candidate a wavefront)
-//   fp32, 16 nodes,  64 x 16   64 candidates of 500 jobs 25.6, 16.6 (33.7); 1000 of 200 49.0, 48.7; 2000 of 300 92.9, 113.6
-//   fp32, 16 nodes, 512 x 16   64 of 500 30.2, 42.7 (119)
-//   fp32, 16 nodes,  64 x 32   1000 of 200 56.4, 59.1
-//   fp64, 17 nodes,  64 x 16   64 of 500 25.7, 17.6 (38.2); 2000 of 300 157, 129
-//   fp64, 17 nodes, 100 x 16   100 of 30 10.0, 11.0; 64 of 500 27.5, 22.3 (48.7); 1200 of 200 104, 86.5
-//   fp64, 16 nodes, 100 x 16   2000 of 300 162, 181
-//   fp64, 17 nodes, 500 x 12   64 of 500 47.0, 59.8 (144)
-// With row inheritance a job's list is shorter than the candidates, of no length known here, and the split is not rounded to fours
-// (128 children of 1000 jobs, 64 x 8: 60.5 us, 67.3 in fours).
+// A sweep of four saves three elections and lasts as long with one candidate as with four: it wants candidates in whole fours,
+// enough pairs to fill the chip with so few wavefronts, and narrow grids (chunk: batch sizes x chunks of 16 counts).
+// fp64 on whole rows and grids takes four always.  Calls that keep their tables, at 1.3 to 10 GPUs a job, us one at a time and
+// four at a time:
+//   17 nodes, 50 x 16, fp64    66 candidates of 30 jobs 9.1, 9.7; 166 of 30 11.5, 10.1; 300 of 100 30.9, 16.8
+//   16 nodes, 64 x 16, fp32    66 of 30 9.2, 10.0; 166 of 30 11.2, 10.5; 300 of 100 26.5, 16.4; 1300 of 100 48.0, 43.1
+// over the 16 to 64 nodes and 6 grids tried: 2000 pairs 1.04 to 1.19 times as long in fours, 5000 0.93 to 1.03, 10000 0.79 to 0.91,
+// from there on 0.65 to 0.98.  Grids of 300 take 1.4 times as long at 2000 pairs and 0.9 from 12000 on, but more again where most
+// rows are empty and fours cannot be filled (1000 candidates of 200 jobs on 128 GPUs, 500 x 12: 228 and 175): wide grids go one at a time.
+// With row inheritance a job's list is shorter than the candidates, of no length known here: its split is not rounded to fours (128
+// children of 1000 jobs, 64 x 8: 60.5 us, 67.3 in fours), and four at a time pay from 80000 pairs on (1000 children of 200 jobs on
+// 61 nodes, 64 x 16: 60.1 and 65.6; 100 children of 200 jobs 1.03 times as long), in fp32 on whole rows not at all (1.02 to 1.06).
 // entry_by_entry: ragged rows with fewer than four candidates a wavefront, none of them a generation's child (see launch_fitness).
 struct PairSplit {
     int per_wave;
@@ -68,12 +67,9 @@ inline PairSplit split_pairs(int candidates, int jobs, int Gm, int Gs, bool f32,
     n = n > 1 ? n : 1;
     if (!row4) return PairSplit{n, false, false};
     if (!f32 && (whole_rows || Gs > 16)) return PairSplit{n, true, false};
-    const bool narrow = Gm <= 64 && (Gs <= 16 || !whole_rows);
-    bool four;
-    if (inherit) four = narrow;
-    else if (narrow && Gs <= 16) four = share >= 4 && !(whole_rows && n > 9);
-    else four = share >= 4 && Gm <= 128 && !whole_rows && pairs >= 6000 && n <= 9;
-    if (four && !inherit) n = n < 4 ? 4 : n & ~3;
+    const int chunk = Gm * ((Gs + 15) / 16);
+    const bool four = inherit ? chunk <= 64 && pairs >= 80000 && !whole_rows : chunk <= 128 && pairs >= 8000 && share >= 4;
+    if (four && !inherit) n = n < 4 ? 4 : (n + 2) & ~3;
     return PairSplit{n, four, !four && n < 4};
 }
 

@@ -78,10 +78,10 @@ def test_fp32_four_rows_at_a_time_elects_what_one_row_at_a_time_elects(N, Gm, Gs
 
 # either side of every line of split_pairs (candidates in whole fours, grid width, counts, pairs, candidates a wavefront) and of the
 # staging of table rows (five candidates a wavefront)
-SPLITS = [(12, 7, 5, 64, 16), (13, 7, 5, 64, 16), (13, 7, 8, 50, 16), (12, 7, 8, 65, 8), (13, 455, 5, 65, 16), (13, 465, 5, 65, 16),
-          (16, 380, 9, 128, 12), (16, 380, 9, 129, 12), (16, 380, 8, 64, 17), (16, 380, 9, 64, 17), (40, 30, 64, 128, 16),
-          (2260, 100, 4, 64, 16), (2510, 100, 4, 64, 8), (2510, 100, 5, 65, 8), (2510, 100, 5, 33, 8), (1010, 100, 66, 33, 8), (1260, 100, 66, 33, 8),
-          (1010, 100, 68, 65, 16), (1260, 100, 68, 65, 16)]
+SPLITS = [(12, 7, 5, 64, 16), (13, 7, 5, 64, 16), (12, 700, 5, 64, 16), (13, 615, 8, 50, 16), (13, 616, 8, 50, 16), (16, 499, 5, 65, 16), (16, 500, 5, 65, 16),
+          (16, 500, 8, 64, 8), (16, 499, 8, 64, 16), (16, 500, 9, 128, 12), (16, 500, 9, 129, 12), (16, 500, 8, 64, 17), (16, 500, 9, 64, 17),
+          (200, 40, 64, 128, 16), (200, 600, 9, 64, 16), (202, 600, 9, 50, 16), (1300, 100, 4, 64, 16), (1510, 100, 4, 64, 8), (1510, 100, 5, 65, 8), (2510, 100, 5, 33, 8),
+          (1010, 100, 66, 33, 8), (1260, 100, 66, 33, 8), (1010, 100, 68, 65, 16), (1260, 100, 68, 65, 16), (2010, 100, 68, 65, 16)]
 
 
 @pytest.mark.parametrize("P,J,N,Gm,Gs", SPLITS)
@@ -92,7 +92,11 @@ def test_either_side_of_the_lines_of_the_split(P, J, N, Gm, Gs, precision):
     import torch
     import paper_2008_12260_amd as px
     wl = W.make(W.custom("split", P=P, J=J, N=N, cap=4, Gm=Gm, Gs=Gs, index=780 + N))
-    wl.population[1 % P, J - 1, 0] = 70                       # beyond the tables
+    wl.population[1, J - 1, 0] = 70                           # beyond the tables
+    empty = np.random.default_rng(P + N).random((3, P))       # rows that need no sweep between those that do: some, most, nearly all
+    for j, share in enumerate((0.3, 0.7, 0.95)):
+        wl.population[empty[j] < share, j] = 0
+    wl.population[empty[1] > 0.95, 1, 0] = 66
     c = wl.cfg
     got = run_gpu(wl, precision=precision)
     if precision == 0 and P * J * Gm * Gs <= 2 ** 28:

@@ -50,7 +50,7 @@ def test_the_population_pass_takes_every_candidate(launch, f32, inherit):
                     groups = launch.px_host_pair_groups(candidates, n)
                     assert (groups - 1) * 4 * n < candidates <= groups * 4 * n
                     assert row4 or not got & 48
-                    if four and not inherit and (f32 or not whole) and Gs <= 16:
+                    if four and not inherit and (f32 or not whole) and (f32 or Gs <= 16):
                         assert n % 4 == 0 and candidates > 12
                     if got & 32:
                         assert not four and n < 4
