@@ -3069,7 +3069,7 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const bool whole = d->Gm % kWave == 0;
     const bool near = a.gs_pad <= kNearRecips;      // the kernels keep reciprocals and thresholds of all counts in LDS
     // four rows per load of a wavefront (cand_per_wave <= 16 holds); its sweeps pack a batch size's index into 15 bits
-    const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF && near;
+    const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF && near && !(d->flags & PX_FLAG_SAMPLE_M);
     const PairSplit split = split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit);
     a.cand_per_wave = split.per_wave;
     a.cand_groups = pair_groups(P_eff, split.per_wave);
