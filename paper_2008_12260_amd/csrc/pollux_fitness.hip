@@ -2357,9 +2357,10 @@ __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
 // row (a chain of dependent steps): 8 jobs 9.4 us a call against 15.9 in three launches, 12 jobs 11.5 against 17.5, 16 jobs 15.2
 // against 16.5, 24 jobs 20.7 against 19.3; 8 jobs with 128 batch sizes 12.1 against 17.6.  Calls that keep their tables are two
 // launches on the other side: 8 jobs 6.7 against 9.4, 16 jobs 8.9 against 9.6, and a generation of 16 jobs 17.4 against 18.5.
-// With more than 16 counts the scan weighs more: there 16 jobs take 15.5 against 15.0 and, keeping their tables, 9.1 against 8.2,
-// and one job with 512 batch sizes (eight groups one after the other) 13.5 against 11.9 keeping them, so the line lies at 14 jobs
-// (9.0 against 12.3) and four groups a row (4 jobs 9.3 against 23.8).  The status section holds a byte per candidate.
+// With more than 16 counts 16 jobs take 12.2 to 15.9 us against 18.4 to 19.4, but 9.1 against 8.2 keeping their tables.  Long grids
+// are groups of 64 one after the other: one job with 512 batch sizes takes 13.6 against 52 to 102 and, keeping its tables, 13.5 against
+// 12.2 on 4 GPUs a node and 38.9 on 8; one with 1024 and more than 16 counts 22.6 against 42 to 95 and, keeping them, 22.6 against
+// 16.4 and 69, so there the line lies at eight groups.  The status section holds a byte per candidate.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallJobs = 16;
 constexpr int kSmallCandidates = 4 * (kStatusWords - 1);
@@ -2369,7 +2370,7 @@ static bool small_call(const pollux_dims &d)
     const int groups = (d.Gm + kWave - 1) / kWave;             // of 64 batch sizes, a row
     return d.precision == 0 && (d.flags & (PX_FLAG_MEMOISE | PX_FLAG_SAMPLE_M)) == 0 && d.P <= kSmallCandidates && d.J <= kSmallJobs &&
            d.N >= 4 && d.N <= 4 * kWave && d.Gs <= kSmallGs &&
-           d.J * groups <= kSmallJobs && (d.Gs <= 16 || (groups <= 4 && d.J <= kSmallJobs - 2));
+           d.J * groups <= kSmallJobs && (d.Gs <= 16 || groups <= 8);
 }
 
 // KEPT: the call keeps the job tables.
