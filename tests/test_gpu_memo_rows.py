@@ -58,6 +58,33 @@ def test_other_precisions_and_the_sampling_argmax(kind, N):
 
 
 @pytest.mark.parametrize("kind", [dict(), dict(precision=1), dict(flags=SAMPLE)])
+@pytest.mark.parametrize("P,J,N", [(7, 63, 7), (7, 64, 7), (9, 67, 66), (256, 64, 5), (257, 64, 5), (5, 1090, 64), (5, 1029, 70)])
+@pytest.mark.parametrize("kept", [0, PAIRS])
+def test_sixteen_wavefronts_a_candidate(P, J, N, kind, kept):
+    """Few candidates of 64 jobs and more, and their neighbours: rows beyond the table, negative entries, empty rows, in every
+    kind of call, the per-pair results left or not."""
+    wl = W.make(W.custom("few", P=P, J=J, N=N, cap=max(4, -(-2 * J // N)), Gm=17, Gs=5, index=450 + J))
+    flags, precision = kind.get("flags", 0), kind.get("precision", 0)
+    if flags:
+        wl = W.sampled(wl)
+    pop = spoiled(wl, J)
+    rng = np.random.default_rng(J)
+    for c in range(P):                                        # in the first rows, the last, and between, whichever wavefront has them
+        for j in {0, J - 1, int(rng.integers(J))}:
+            pop[c, j] = 0
+            pop[c, j, rng.integers(N)] = rng.choice([0, 3, 65, 70])
+    if P > 5:
+        pop[P - 1, J - 1, N - 1] = -1
+    memo = run_gpu(wl, population=pop, flags=flags | MEMO | kept, precision=precision)
+    if precision == 0:
+        assert compare(wl, memo, run_oracle(wl, population=pop, flags=flags), population=pop, sampled=bool(flags)) == 0
+    if not (flags and P >= 128):                              # (sampling calls of that size take the same pass either way)
+        plain = run_gpu(wl, population=pop, flags=flags, precision=precision)
+        for k in NAMES + ("status",):
+            assert np.array_equal(plain[k], memo[k], equal_nan=True), k
+
+
+@pytest.mark.parametrize("kind", [dict(), dict(precision=1), dict(flags=SAMPLE)])
 @pytest.mark.parametrize("J,N,off", [(9, 4, 0), (30, 5, 1), (40, 64, 0), (40, 67, 3), (1030, 6, 0)])
 def test_children_that_inherit_rows(J, N, off, kind):
     """Generations that look changed rows up leave what the plain call on the same matrices leaves, misaligned buffers too."""

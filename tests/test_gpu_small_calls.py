@@ -33,7 +33,8 @@ def test_either_side_of_the_line(P, J, N, Gm, Gs, p):
 
 
 @pytest.mark.parametrize("P,J,N,Gm,Gs", [(6, 1, 4, 1, 1), (252, 5, 6, 33, 8), (253, 5, 6, 33, 8), (6, 16, 9, 64, 16), (6, 17, 9, 64, 16),
-                                         (6, 14, 9, 64, 17), (6, 15, 9, 64, 17), (5, 4, 9, 256, 32), (5, 3, 9, 257, 17), (5, 1, 7, 1024, 16)])
+                                         (6, 14, 9, 64, 17), (6, 15, 9, 64, 17), (6, 16, 9, 64, 17), (6, 17, 9, 64, 17), (5, 4, 9, 256, 32),
+                                         (5, 3, 9, 257, 17), (5, 1, 7, 512, 17), (5, 1, 7, 513, 17), (5, 1, 7, 1024, 16)])
 @pytest.mark.parametrize("flags", [0, 1])
 def test_calls_that_keep_their_tables(P, J, N, Gm, Gs, flags):
     """Another population, the fair shares and re-allocation factors of the call before: the oracle's results."""
