@@ -984,12 +984,14 @@ int launch_ga_step(const pollux_dims *d, const int32_t *parents, const double *f
     const unsigned children_formed = a.in_place ? (unsigned)d->P - ga->elite_k : (unsigned)d->P;
     const bool four = d->N >= 4 && d->N <= kWave && !a.job_gpu_cap;
     // Rows of 65 to 256 nodes: four requested at a time up to 1 GiB of children, where a wavefront otherwise waits for one row after
-    // the other (128 x 1000 x 256: 161 -> 137 us, 326 x 201 x 88: 49 -> 44, 1024 x 1000 x 256: 489 -> 473); beyond, the copy runs at
-    // the memory's rate without it (2048 x 1000 x 256: 881 us against 889).
+    // the other (128 x 1000 x 256: 161 -> 137 us, 326 x 201 x 88: 49 -> 44, 1024 x 1000 x 256: 489 -> 473); beyond, the copy of whole
+    // 16-byte groups runs at the memory's rate without it (2048 x 1000 x 256: 881 us against 889).  Other rows would go entry by entry
+    // there, so they come this way at any size (2048 x 1000 x 250: 1247 -> 911 us, 2048 x 900 x 254: 1151 -> 850).
+    const bool groups16 = (d->N & 3) == 0 && (((uintptr_t)a.parents | (uintptr_t)a.children) & 15) == 0;
     const bool ahead = !four && d->N >= 4 && d->N <= 4 * kWave && !a.job_gpu_cap &&
-                       4ull * children_formed * (unsigned long long)d->J * d->N <= (1ull << 30);
+                       (!groups16 || 4ull * children_formed * (unsigned long long)d->J * d->N <= (1ull << 30));
     const bool inherit = a.src_row != nullptr;
-    const bool whole = four && (d->N & 3) == 0 && (((uintptr_t)a.parents | (uintptr_t)a.children) & 15) == 0;
+    const bool whole = four && groups16;
     constexpr int kInstances = 8;
     const void *kernels[kInstances] = {(const void *)generation_kernel<kRowsAny, false>, (const void *)generation_kernel<kRowsAhead, false>,
                                        (const void *)generation_kernel<kRows64, false>, (const void *)generation_kernel<kRows64Whole, false>,
