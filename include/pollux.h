@@ -66,9 +66,10 @@ enum {
                                          PX_M_MEM; see pollux_fitness.  fp64 only. */
     PX_FLAG_PAIR_RESULTS = 32         /* with PX_FLAG_MEMOISE: the call also leaves the goodput and the node count of
                                          every (candidate, job) pair in the workspace, which pollux_generation with
-                                         PX_GA_INHERIT_ROWS reads (calls without PX_FLAG_MEMOISE leave them anyway;
-                                         a memoised call on rows of 4 to 256 nodes otherwise keeps them on chip,
-                                         and the 12 bytes per pair cost it about a twentieth of its time). */
+                                         PX_GA_INHERIT_ROWS reads (calls without PX_FLAG_MEMOISE need no flag: they
+                                         leave them where such a call reads them; a memoised call on rows of 4 to
+                                         256 nodes otherwise keeps them on chip, and the 12 bytes per pair cost it
+                                         about a twentieth of its time). */
 };
 
 /* Rows of job_params[PX_NPARAM][J] (structure of arrays, fp64).

@@ -5,7 +5,7 @@
 // Sec. 4.1 (Eq. 13), SPEEDUP / FITNESS_p, re-allocation penalty and
 // interference avoidance Sec. 4.2 (Eq. 14-15).
 //
-// Kernels (one call = three launches on the caller's stream)
+// Kernels of a call with the dense grid in fp64 (three launches on the caller's stream)
 //   prepare_kernel    everything that depends on the jobs only.  Per job, placement class and GPU count K <= 64
 //                     (the "one node" class only up to the largest node capacity): T_sync (Eq. 9) and, for every
 //                     batch size of the grid, T_grad(m) (Eq. 8), the last pass of Eq. 10,
@@ -19,14 +19,19 @@
 //                     per-candidate, per-node counters with integer atomics
 //   candidates_kernel per candidate (one workgroup): SPEEDUP, penalty, constraint
 //                     check from those counters and the generalized mean
-// With PX_FLAG_MEMOISE, prepare_kernel takes the argmax once per (job, placement class, K <= 64) and the population pass
-// looks the result up: pairs_kernel, or for rows of 65 to 256 nodes memo_candidates_kernel, which takes a whole candidate
-// per workgroup and finishes its fitness as well (no per-pair scratch, no candidates_kernel).
-// With PX_FLAG_SAMPLE_M the sweep is replaced by sweep_sampled (Sec. 4.3), the kernels
-// instantiated with CH = 0.
-// For pollux_generation the population pass takes a list of candidates (the children of the search step), or,
-// with PX_GA_INHERIT_ROWS, per job the list of rows the step has changed, after inherit_kernel has given every
-// unchanged row the results of the row it was copied from.
+// Other calls (launch_fitness decides; a call that keeps the job tables leaves out what makes them):
+//   fp32              jobs_kernel_f32 finds the fair shares from prepare_kernel's tables, memoised memo_kernel_f32 the argmaxes
+//   PX_FLAG_MEMOISE   prepare_kernel takes the argmax once per (job, placement class, K <= 64) and the population pass looks it
+//                     up: memo_candidates_kernel for rows of 4 to 256 nodes, which takes a whole candidate per workgroup and
+//                     finishes its fitness as well (no per-pair scratch, no candidates_kernel); other rows in pairs_kernel
+//   PX_FLAG_SAMPLE_M  sweep_sampled (Sec. 4.3) replaces the sweep, the kernels instantiated with CH = 0; from 128 candidates
+//                     on rows of 4 to 256 nodes take the memoised pass
+//   small calls       small_kernel does everything in one launch: up to 252 candidates and 16 groups of 64 batch sizes over all
+//                     jobs (small_call)
+// For pollux_generation the population pass takes a list of candidates, the children of the search step.  With
+// PX_GA_INHERIT_ROWS an unchanged row takes over the results of the row it was copied from: in the children's instance of
+// memo_candidates_kernel where that is the pass, not at all in small_kernel (a row there costs no launch), and otherwise in
+// inherit_kernel, which also lists the rows the step has changed per job for pairs_kernel.
 //
 // How one wavefront sweeps the grid of a (candidate, job) pair.  Lane l owns
 // the batch sizes m_i, i = l, l+64, ...; it walks s = 0..Gs-1.  Dividing Eq. 4
@@ -2706,7 +2711,7 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
         } else {
             // Row q of this wavefront in the chunk (position: the job's number less jc) of the `rows` it has: with four
             // wavefronts 64 consecutive rows of every round of 256 each, or where there is no such round an even share in
-            // whole passes of the loops below (63 jobs on 138 nodes, 19 candidates: 23.0 us in one wavefront, 10.2 so; 200
+            // whole passes of the loops below (63 jobs on 138 nodes, 19 candidates: 23.0 us in one wavefront, 9.6 so; 200
             // jobs in other shares than 64, 64, 64, 8 only add passes); with more of them a stretch of its own.
             constexpr int kPass = SHORT ? 16 : 8;
             const int full = WAVES == 4 ? chunk_jobs / kCandThreads : 0, tail = chunk_jobs - full * kCandThreads;
@@ -2953,8 +2958,9 @@ static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
 }
 
 // The population pass of memoised mode, P_eff workgroups.  Up to 256 candidates leave most of a compute unit idle with four
-// wavefronts each; from 64 jobs on (a load of rows per wavefront) they get sixteen.  19 candidates of 552 jobs on 138 nodes:
-// 89 us a call with four, 54 with sixteen.
+// wavefronts each; from 64 jobs on (a load of rows per wavefront) they get sixteen.  Calls that keep their tables, us, 256
+// candidates with sixteen and 257 with four: 64 jobs on 138 nodes 8.3, 10.3; 200 on 64 8.6, 11.1; 200 on 256 15.9, 26.5; 1000 on 64
+// 21.9, 34.4; 1000 on 256 52, 105.  19 candidates, 63 jobs with four and 64 with sixteen: on 64 nodes 5.6, 5.6, on 138 9.6, 8.0.
 template <int KIND>
 static void launch_memo_candidates(const FitnessArgs &a, int P_eff, bool child, bool pairs_kept, hipStream_t stream)
 {
