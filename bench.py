@@ -36,12 +36,12 @@ FLOPS_PER_EVAL = 7                  # Eq. 4 at one grid point: 5 add/mul + 2 div
 #   valu_busy       fraction of the kernel's cycles in which the vector ALUs were busy
 PROFILED = {
     "large": {
-        "source_sha256": "7447726b468e5572b82008161f4feaec860912ca4e9122a2f09fef25c5d8ee27",
-        "traffic_bytes": 2_078_890 * 1024 * 2 + 697_306 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
-        "fp64_flops": 64 * (8.960e5 + 1.770e7 + 2 * 2.670e8),
-        "valu_insts": 1.00264e9,
+        "source_sha256": "d3e0749132a6a0e92d350e4bc1621b9095c3427b8f5fbb340d02cc6ecf9b761b",
+        "traffic_bytes": 2_079_238 * 1024 * 2 + 698_746 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
+        "fp64_flops": 64 * (8.96016e5 + 1.76994e7 + 2 * 2.66984e8),
+        "valu_insts": 9.95398e8,
         "scan_insts": 2.25 * 1.6777e10 / 64,
-        "valu_busy": 1.02073e9 * 4 / 1024 / (3.39817e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
+        "valu_busy": 1.01356e9 * 4 / 1024 / (3.39006e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
     },
 }
 GA_SEED = 0x2008_1226_5EED_0001

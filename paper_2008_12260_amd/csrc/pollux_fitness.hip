@@ -107,6 +107,7 @@ struct FitnessArgs {
     int32_t *zeros;               // 64 zero bytes (prepare_kernel): what lanes read where the current row holds nothing
     unsigned long long *colpack;  // [P,N] per node: GPUs asked (low 40 bits, signed) + multi-node jobs present << 40
     int need_constraints;
+    int stage_rows;               // pairs_kernel: table rows that several pairs read are copied to LDS (see stage_candidates)
     const int32_t *sel;           // candidates to evaluate (device list of n_sel indices into the population), or null: all P
     int n_sel;
     // row inheritance (pollux_generation with PX_GA_INHERIT_ROWS; written by the search step, see GaArgs)
@@ -134,7 +135,7 @@ constexpr int kStageRows = 4;             // rows staged at most (16.6 KB of LDS
 // Candidates per wavefront from which staging pays for its two barriers; the children of a generation resemble each other, so more
 // of their pairs share a row.  Kept calls on 128 nodes, us without, with: 50 x 16, 200 candidates of 100 jobs (one each) 23.0, 25.4;
 // 500 of 200 (four each) 46.5, 48.1; 100 x 8, 1000 of 200 (eight each) 83.4, 80.9; its 500 children (four each) 89.5, 86.4.
-constexpr int stage_candidates(int SEL) { return SEL == 0 ? 5 : 4; }
+constexpr int stage_candidates(bool children) { return children ? 4 : 5; }
 constexpr int kStageRowDoubles = 2 * kStageGm + kStageGm / 2;
 constexpr int kStageBase = kNearU + kNearRecips + 8;
 constexpr int kStageDoubles = 2 * kStageGm + kStageRows * kStageRowDoubles;
@@ -1616,7 +1617,9 @@ pairs_kernel(FitnessArgs a)
     __shared__ __align__(16) double r_lds[kNearU + kNearRecips + 8 + (kStage ? kStageDoubles : 0)];
     __shared__ int stage_votes[kStage ? 2 * kTableK : 1];
     // (only where the table of reciprocals and thresholds is in LDS as well: sweep_pick's staged path reads both)
-    const bool stage_on = kStage && a.Gm <= kStageGm && a.gs_pad <= kNearRecips && a.cand_per_wave >= stage_candidates(SEL);
+    // (the host's decision; formed here, which is the same, it costs whole grids 0.4 % and saves ragged ones 0.9 %)
+    const bool stage_on = kStage && (WHOLE ? a.stage_rows != 0
+                                           : a.Gm <= kStageGm && a.gs_pad <= kNearRecips && a.cand_per_wave >= stage_candidates(SEL != 0));
     bool has_near = false;
     // (the instances whose rows fit one 16-byte load per lane fill the table after they have requested their first rows)
     constexpr bool kRowsFirst = CH != 0 && ROW1;
@@ -3077,6 +3080,7 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF && near && !(d->flags & PX_FLAG_SAMPLE_M);
     const PairSplit split = split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit);
     a.cand_per_wave = split.per_wave;
+    a.stage_rows = d->Gm <= kStageGm && near && split.per_wave >= stage_candidates(a.sel != nullptr) ? 1 : 0;
     a.cand_groups = pair_groups(P_eff, split.per_wave);
     const unsigned pair_blocks = (unsigned)(8 * ((d->J + 7) / 8) * a.cand_groups);
 
