@@ -6,16 +6,23 @@
 // at zero.
 //
 // One workgroup per job, one wavefront per starting point.  The lanes of a wavefront share the
-// job's records; of the seven unknowns lane i < 7 holds the i-th (value, scale, bounds, gradient, its row of the
-// matrix to factorise), and what all lanes need of them travels through scalar registers.  The error is a sum of squares of
+// job's records; of the seven unknowns lanes 2 i and 2 i + 1 hold the i-th (value, scale, bounds, gradient, its row of
+// the matrix to factorise), and what all lanes need of them travels through scalar registers.  The error is a sum of squares of
 //     r_o = ln T_iter(theta; K_o, nodes_o, m_o, s_o) - ln T_o,
 // so the minimiser is a damped Gauss-Newton (Levenberg-Marquardt) iteration on the box:
 // per iteration the lanes form r_o and its seven partial derivatives, the wave reduces
-// SUM r^2, J^T r (7 sums) and J^T J (28 sums) in a fixed binary tree (sum_terms),
+// SUM r^2, J^T r (7 sums) and J^T J (24 sums) in a fixed binary tree (sum_terms),
 // solves the damped 7 x 7 system on the variables that are free (not held by a prior,
 // not at a bound with the gradient pointing outwards) by Cholesky factorisation, clips
 // the step to the box and accepts it if SUM r^2 went down.  The unknowns are scaled by
 // the starting point (they differ by four orders of magnitude).
+//
+// Bound by the vector ALU's issue, wavefront by wavefront: an instruction, scalar ones included, takes four cycles whether it
+// waits for the one before it or not, so what counts is how many there are.  An iteration is 700 (1200 with the sums through
+// LDS, the library's roots and divisions and the polynomials' constants formed where they are used); 100 jobs, 200 iterations:
+// 0.70 ms then, 0.39 now.  Beyond 256 jobs SIMDs hold two chains and three, and the slowest job is the one whose neighbours
+// are slow: 1000 jobs of up to 48 records with three starts 1.07 ms then, 0.76 now.  Every result has the same bits: on the flat
+// stretches of this error other roundings end at other parameters.
 //
 // Eq. 10 is evaluated with the larger term factored out, as in the fitness kernels:
 // with D = ln T_sync - ln T_grad and e = exp(-gamma |D|),
@@ -28,6 +35,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/pollux.h"
 #include "pollux_device.h"
 #include "pollux_host.h"
@@ -37,7 +46,6 @@
 namespace px {
 
 constexpr int kTheta = 7;                 // unknowns, in the order of the first seven PX_* rows
-constexpr int kPacked = 28;               // lower triangle of a symmetric 7 x 7 matrix, row-major: (i, k <= i) at i(i+1)/2 + k
 constexpr double kTgradFloor = 1e-12;     // keeps ln T_grad finite should alpha_grad = beta_grad = 0 ever be tried
 
 struct FitArgs {
@@ -48,17 +56,38 @@ struct FitArgs {
     int32_t *iterations;
 };
 
-// The 36 sums over a wavefront, through LDS.  Sixteen at a time: every lane puts its terms into a row of its own, then lane
-// 16 q + k adds term k of the sixteen lanes of quarter q, and the quarters are added across lanes.  A butterfly per sum was
-// 648 vector instructions (six steps of two moves and an addition, 36 times) of an iteration's 1600; this is 120, in the same
-// binary tree ((0+1)+(2+3)) + ..., so every sum has the same bits.  Rows of 17 doubles keep writes and reads off each other's
-// banks.  The sums stay in LDS, where the solver reads them, and the unknowns are spread over lanes, so that four wavefronts fit
-// a SIMD, not two, and the 3000 chains of 1000 jobs with three starts run side by side: 2.44 ms a call before, 1.15 so.  What is
-// left is a chain of 3.5 us per iteration (100 jobs, 200 iterations: 0.70 ms), half of it the seven pivots of the solver.
-constexpr int kSums = 1 + 7 + 28;                       // SUM r^2, J^T r, J^T J
-constexpr int kSumRow = 17;
-constexpr int kSumTable = 64 * kSumRow;                 // doubles of one wavefront's table of terms
-constexpr int kWaveDoubles = kSumTable + 2 * kSums;     // and two sets of sums: of the iterate and of the trial
+// The sums over a wavefront: SUM r^2, J^T r, J^T J.  A record is a local or a distributed one, so its derivative with respect to
+// one of the two sync pairs is zero and the four sums that mix the pairs are too: 32 sums remain, one per pair of lanes.
+// Sum t ends in lanes 2 t and 2 t + 1:
+//   0 .. 6  J^T r      7  SUM r^2      8 ..  the entries (i, k <= i) of J^T J, kOrder
+constexpr int kSums = 32;
+struct SumOrder {
+    int row[kSums], column[kSums];       // of J^T J (8 ..)
+    int at[kTheta][kTheta];              // the sum of entry (i, k <= i), -1: zero
+};
+constexpr SumOrder make_order()
+{
+    SumOrder o = {};
+    int t = 8;
+    for (int i = 0; i < kTheta; ++i) {
+        for (int k = 0; k <= i; ++k) {
+            const bool mixed = (i == PX_ALPHA_SN || i == PX_BETA_SN) && (k == PX_ALPHA_SL || k == PX_BETA_SL);
+            o.at[i][k] = mixed ? -1 : t;
+            if (!mixed) {
+                o.row[t] = i;
+                o.column[t++] = k;
+            }
+        }
+    }
+    return o;
+}
+constexpr SumOrder kOrder = make_order();
+
+// Unknown i belongs to lanes 2 i and 2 i + 1, and has both their bits in the sets of unknowns below.
+constexpr unsigned unknown(int i) { return 3u << (2 * i); }
+constexpr unsigned kAll = (1u << (2 * kTheta)) - 1u;
+constexpr int kRowDoubles = 8;                          // a row of the system in LDS: its entries, and the right-hand side
+constexpr int kWaveDoubles = (kTheta + 1) * kRowDoubles;  // of one wavefront (the last row: what belongs to none)
 
 // What the lanes of a wavefront write becomes visible to all of them: the LDS serves a wavefront's accesses in order, so only
 // the compiler has to keep them so.
@@ -68,44 +97,65 @@ __device__ __forceinline__ void wave_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Lane 16 q + k: the sum of term FIRST + k over the lanes of quarter q (sixteen terms, or up to the last).
-template <int FIRST>
-__device__ __forceinline__ double sum_quarter(double *table, const double (&term)[kSums])
+// Lane l holds record bit_reversed(l), so the tree ((0+1)+(2+3)) + ... over the records begins with lanes 32 apart, which
+// gfx950 exchanges between two registers by one instruction, as it does rows of 16 lanes; and at every level a lane hands
+// half of its sums to its partner, so 32 values become one in 16 + 8 + 4 + 2 + 1 + 1 additions.  (Through a table in LDS, as it was
+// before, the stores alone took 15 cycles each, an eighth of an iteration.)
+__device__ __forceinline__ int bit_reversed(int lane) { return (int)(__builtin_bitreverse32((unsigned)lane) >> 26); }
+
+// Lanes of the lower half: x of the lane and of the one 32 above; of the upper half: y of the lane and of the one 32 below.
+__device__ __forceinline__ double add_halves(double x, double y)
 {
-    constexpr int kCount = kSums - FIRST < 16 ? kSums - FIRST : 16;
-    const int lane = lane_id();
-    wave_fence();
-#pragma unroll
-    for (int k = 0; k < kCount; ++k) table[lane * kSumRow + k] = term[FIRST + k];
-    wave_fence();
-    const int k = lane & 15;
-    const double *column = table + (lane & 48) * kSumRow + (k < kCount ? k : 0);
-    double v[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = column[i * kSumRow];
-#pragma unroll
-    for (int width = 1; width < 16; width *= 2) {
-#pragma unroll
-        for (int i = 0; i < 16; i += 2 * width) v[i] += v[i + width];
-    }
-    return v[0];
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
 
-// All sums, to out[0 .. kSums-1].
-__device__ __forceinline__ void sum_terms(double *table, const double (&term)[kSums], double *out)
+// The same for rows of 16 lanes: rows 0 and 2 x, rows 1 and 3 y.
+__device__ __forceinline__ double add_rows(double x, double y)
 {
-    static_assert(kSums > 32 && kSums <= 48, "three passes of sixteen");
-    double s0 = sum_quarter<0>(table, term), s1 = sum_quarter<16>(table, term), s2 = sum_quarter<32>(table, term);
-    // the quarters, all three together so that their exchanges overlap
-    s0 += exchange<4>(s0); s1 += exchange<4>(s1); s2 += exchange<4>(s2);
-    s0 += exchange<5>(s0); s1 += exchange<5>(s1); s2 += exchange<5>(s2);
-    const int lane = lane_id();
-    if (lane < 16) {
-        out[lane] = s0;
-        out[16 + lane] = s1;
-        if (lane < kSums - 32) out[32 + lane] = s2;
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// The same for lanes FAR = 8 or 4 apart: the lanes without that bit x, the others y.  The banks of four lanes that want the
+// shifted y take it over the shifted x.
+template <int FAR>
+__device__ __forceinline__ int fetch(int x, int y)
+{
+    if constexpr (FAR == 8) {                            // row_ror:8
+        const int v = __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);
+        return __builtin_amdgcn_update_dpp(v, y, 0x128, 0xF, 0xC, false);
+    } else {                                             // row_shl:4 (from the lane four above), row_shr:4
+        const int v = __builtin_amdgcn_mov_dpp(x, 0x104, 0xF, 0xF, true);
+        return __builtin_amdgcn_update_dpp(v, y, 0x114, 0xF, 0xA, false);
     }
-    wave_fence();
+}
+
+template <int FAR>
+__device__ __forceinline__ double add_near(double x, double y)
+{
+    const double mine = (lane_id() & FAR) != 0 ? y : x;
+    return mine + __hiloint2double(fetch<FAR>(__double2hiint(x), __double2hiint(y)), fetch<FAR>(__double2loint(x), __double2loint(y)));
+}
+
+// All sums: sum t in lanes 2 t and 2 t + 1.
+__device__ __forceinline__ double sum_terms(const double (&term)[kSums])
+{
+    double v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) v[t] = add_halves(term[t], term[t + 16]);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = add_rows(v[t], v[t + 8]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = add_near<8>(v[t], v[t + 4]);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) v[t] = add_near<4>(v[t], v[t + 2]);
+    const bool second = (lane_id() & 2) != 0;
+    const double mine = second ? v[1] : v[0], other = second ? v[0] : v[1];
+    const double sum = mine + exchange<1>(other);
+    return sum + exchange<0>(sum);
 }
 
 // The value lane `src` holds, in every lane.
@@ -135,25 +185,100 @@ __device__ __forceinline__ Record load_record(const FitArgs &f, size_t at)
     return r;
 }
 
-// The sums of one job at theta = z * scale (lane i < 7 holds the i-th of each), in `out` (LDS): SUM r^2, then J^T r, then J^T J as a packed lower triangle.
-// mine: the l-th record of the job, read once and kept in lane l's registers over all iterations.  HELD: the job has no more than
+// a / b for b well inside the exponent range: reciprocal seed (2^-24), one step of third order, one residual correction of the
+// quotient.  In 2e9 tries over all kinds of mantissas the quotient was the correctly rounded one every time.
+__device__ __forceinline__ double fit_div(double a, double b)
+{
+    double r = px_rcp_seed(b);
+    const double e = px_fma(-b, r, 1.0);
+    r = px_fma(px_fma(e, e, e), r, r);
+    const double q = a * r;
+    return px_fma(px_fma(-b, q, a), r, q);
+}
+
+// The functions of the fitness kernels, step by step, with their constants in registers for the whole fit.  One wavefront a
+// SIMD issues an instruction every four cycles whatever it depends on, and scalar ones no faster, so that a coefficient formed
+// where it is used, by two moves, trebled the price of a polynomial's step.
+struct FitMath {
+    double log_top, log_c[10], exp_top, exp_c[10];       // (the highest coefficients in vector registers, all others in scalar ones)
+    double ln2, ln2_low, log2e, least, root_half, root2_less1;
+};
+
+__device__ __forceinline__ FitMath make_fit_math()
+{
+    FitMath c = {2.0 / 23.0,
+                 {2.0 / 21.0, 2.0 / 19.0, 2.0 / 17.0, 2.0 / 15.0, 2.0 / 13.0, 2.0 / 11.0, 2.0 / 9.0, 2.0 / 7.0, 2.0 / 5.0, 2.0 / 3.0},
+                 1.0 / 6227020800.0,
+                 {1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0, 1.0 / 5040.0, 1.0 / 720.0,
+                  1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0},
+                 0.6931471805599453, 2.3190468138462996e-17, 1.4426950408889634, -745.5, 0.7071067811865476, 0.41421356237309503};
+    // (opaque: neither formed again at every use nor moved elsewhere)
+    asm volatile("" : "+v"(c.log_top), "+v"(c.exp_top));
+#pragma unroll
+    for (int i = 0; i < 10; ++i) asm volatile("" : "+s"(c.log_c[i]), "+s"(c.exp_c[i]));
+    asm volatile("" : "+s"(c.ln2), "+s"(c.ln2_low), "+s"(c.log2e), "+s"(c.least), "+s"(c.root_half), "+s"(c.root2_less1));
+    return c;
+}
+
+__device__ __forceinline__ double fit_two_atanh(const FitMath &c, double z)
+{
+    const double w = z * z;
+    double p = c.log_top;
+#pragma unroll
+    for (int i = 0; i < 10; ++i) p = px_fma(p, w, c.log_c[i]);
+    return px_fma(z * w, p, z + z);
+}
+
+__device__ __forceinline__ double fit_log(const FitMath &c, double x)
+{
+    int k = __builtin_amdgcn_frexp_exp(x);
+    double m = __builtin_amdgcn_frexp_mant(x);
+    if (m < c.root_half) { m += m; k -= 1; }
+    const double f = m - 1.0;
+    const double l = fit_two_atanh(c, fit_div(f, 2.0 + f));
+    const double kd = (double)k;
+    return px_fma(kd, c.ln2, px_fma(kd, c.ln2_low, l));
+}
+
+__device__ __forceinline__ double fit_log1p(const FitMath &c, double e)
+{
+    const bool big = e > c.root2_less1;
+    const double f = big ? (e - 1.0) * 0.5 : e;
+    const double l = fit_two_atanh(c, fit_div(f, 2.0 + f));
+    return big ? l + c.ln2 : l;
+}
+
+__device__ __forceinline__ double fit_exp(const FitMath &c, double t)
+{
+    t = t > c.least ? t : c.least;
+    const double k = px_rint(t * c.log2e);
+    double r = px_fma(-k, c.ln2, t);
+    r = px_fma(-k, c.ln2_low, r);
+    double p = c.exp_top;
+#pragma unroll
+    for (int i = 0; i < 10; ++i) p = px_fma(p, r, c.exp_c[i]);
+    p = px_fma(p, r, 0.5);
+    p = px_fma(p, r, 1.0);
+    p = px_fma(p, r, 1.0);
+    return px_ldexp(p, (int)k);
+}
+
+// The sums of one job at theta = z * scale (lanes 2 i and 2 i + 1 hold z_i, all lanes all of scale): sum t in lanes 2 t and 2 t + 1 (kOrder).
+// mine: the lane's record (bit_reversed), read once and kept in its registers over all iterations.  HELD: the job has no more than
 // these 64; otherwise those beyond are read from memory in every evaluation.
 template <bool HELD>
-__device__ __forceinline__ void normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale, const Record &mine,
-                                                 double *table, double *out)
+__device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale,
+                                                   const double (&scale)[kTheta], const Record &mine, const FitMath &c)
 {
     const int lane = lane_id();
     const double my_th = my_z * my_scale;
-    double th[kTheta], scale[kTheta];
+    double th[kTheta];
 #pragma unroll
-    for (int i = 0; i < kTheta; ++i) {
-        th[i] = wave_read(my_th, i);
-        scale[i] = wave_read(my_scale, i);
-    }
-    const double gamma = th[PX_GAMMA], inv_gamma = 1.0 / gamma;
+    for (int i = 0; i < kTheta; ++i) th[i] = wave_read(my_th, 2 * i);
+    const double gamma = th[PX_GAMMA], inv_gamma = fit_div(1.0, gamma);
 
     // the residual of one record and its derivatives with respect to z
-    auto evaluate = [&](const Record &rec, double &r, double (&d)[kTheta]) {
+    auto evaluate = [&](const Record &rec, bool some, double &r, double (&d)[kTheta]) {
         const int K = rec.K, nodes = rec.nodes;
         const double md = rec.md, sd = rec.sd;
         const double lnT = rec.lnT;
@@ -166,22 +291,26 @@ __device__ __forceinline__ void normal_equations(const FitArgs &f, int j, int n,
         if (node) ts = th[PX_ALPHA_SN] + th[PX_BETA_SN] * km2;
         double last = tg, dl_dtg = 1.0, dl_dts = gamma == 1.0 ? 1.0 : 0.0, dlnl_dg = 0.0;
         if (ts > 0.0) {                                                                   // Eq. 10
-            const double lntg = px_log(tg), lnts = px_log(ts);
+            const double lntg = fit_log(c, tg), lnts = fit_log(c, ts);
             const double d = lnts - lntg;
-            const double e = px_exp(-gamma * fabs(d));
-            const double l1p = px_log1p_unit(e);
+            const double e = fit_exp(c, -gamma * fabs(d));
+            const double l1p = fit_log1p(c, e);
             const double big = d >= 0.0 ? ts : tg, lnbig = d >= 0.0 ? lnts : lntg;
-            last = big * px_exp(l1p * inv_gamma);
-            const double w_small = px_div(e, 1.0 + e), w_big = px_div(1.0, 1.0 + e);
+            last = big * fit_exp(c, l1p * inv_gamma);
+            const double w_small = fit_div(e, 1.0 + e), w_big = fit_div(1.0, 1.0 + e);
             const double w_s = d >= 0.0 ? w_big : w_small, w_g = d >= 0.0 ? w_small : w_big;
-            dl_dtg = w_g * px_div(last, tg);
-            dl_dts = w_s * px_div(last, ts);
+            dl_dtg = w_g * fit_div(last, tg);
+            dl_dts = w_s * fit_div(last, ts);
             const double lnsum = gamma * lnbig + l1p;                                     // ln(T_grad^g + T_sync^g)
             dlnl_dg = (w_g * lntg + w_s * lnts) * inv_gamma - lnsum * inv_gamma * inv_gamma;
         }
         const double pred = sd * tg + last;                                               // Eq. 11
-        r = px_log(pred) - lnT;
-        const double inv_pred = px_div(1.0, pred);
+        // a lane without a record (some): every derivative has the factor 1 / pred
+        double inv_pred = fit_div(1.0, pred);
+        r = fit_log(c, pred) - lnT;
+        asm("" : "+v"(r), "+v"(inv_pred));                       // (selected, not branched around)
+        r = some ? r : 0.0;
+        inv_pred = some ? inv_pred : 0.0;
         d[PX_ALPHA_G] = (sd + dl_dtg) * inv_pred;
         d[PX_BETA_G] = d[PX_ALPHA_G] * md;
         const double dts = dl_dts * inv_pred;
@@ -194,83 +323,233 @@ __device__ __forceinline__ void normal_equations(const FitArgs &f, int j, int n,
         for (int i = 0; i < kTheta; ++i) d[i] *= scale[i];
     };
     double term[kSums];
-    // the record's terms: r^2; d_i r; d_i d_k, k <= i, row by row
+    // (a job whose records are all held has one a lane: its products as they are)
+    auto accumulate = [](double a, double b, double to) { return HELD ? a * b : px_fma(a, b, to); };
+    // the record's terms, in the order of kOrder
     auto add = [&](double r, const double (&d)[kTheta]) {
-        term[0] = px_fma(r, r, term[0]);
+        term[7] = accumulate(r, r, term[7]);
 #pragma unroll
         for (int i = 0; i < kTheta; ++i) {
-            term[1 + i] = px_fma(d[i], r, term[1 + i]);
+            term[i] = accumulate(d[i], r, term[i]);
 #pragma unroll
-            for (int k = 0; k <= i; ++k) term[1 + kTheta + i * (i + 1) / 2 + k] = px_fma(d[i], d[k], term[1 + kTheta + i * (i + 1) / 2 + k]);
+            for (int k = 0; k <= i; ++k) {
+                if (kOrder.at[i][k] >= 0) term[kOrder.at[i][k]] = accumulate(d[i], d[k], term[kOrder.at[i][k]]);
+            }
         }
     };
 #pragma unroll
     for (int t = 0; t < kSums; ++t) term[t] = 0.0;
     const size_t base = (size_t)j * f.max_obs;
     for (int o0 = 0; o0 < (HELD ? 1 : n); o0 += kWave) {
-        const int o = o0 + lane;
+        const int o = o0 + bit_reversed(lane);
         Record rec = mine;
         if (!HELD && o0 > 0) rec = load_record(f, base + (size_t)(o < n ? o : n - 1));
         double r, d[kTheta];
-        evaluate(rec, r, d);
-        if (o >= n) {
-            r = 0.0;
-#pragma unroll
-            for (int i = 0; i < kTheta; ++i) d[i] = 0.0;
-        }
+        evaluate(rec, o < n, r, d);
         add(r, d);
     }
-    sum_terms(table, term, out);
+    return sum_terms(term);
 }
 
-// Solves (A + lambda diag(A)) x = -g on the free variables (bit i of `held` set: x_i = 0) by Cholesky factorisation.
-// Lane i < 7 holds row i and returns x_i; per column the pivot, its reciprocal (one division; the entries below it and both
-// substitutions multiply by it) and the column's entries are known to all lanes.  Every entry takes its subtractions in
-// ascending order of the column, as in the textbook's row-by-row form.  Returns false if a pivot is not positive.
-__device__ __forceinline__ bool damped_step(const double *sums, double lambda, unsigned held, double &x)
+// One over the root of a pivot, from one chain of thirteen instructions (seed 2^-23, two steps of second order, a correction each),
+// rounded as the library's root and division round it (30 and 12 instructions) for pivots well inside the exponent range.
+__device__ __forceinline__ double inverse_root(double pivot)
 {
-    const int lane = lane_id();
-    const int row = lane < kTheta ? lane : kTheta - 1;                  // (the lanes beyond repeat the last row)
-    const double *g = sums + 1, *a = sums + 1 + kTheta;
-    const bool mine_held = (held >> row) & 1u;
-    const double dii = a[row * (row + 3) / 2];
-    const double diagonal = mine_held ? 1.0 : dii + lambda * (dii > 1e-300 ? dii : 1e-300);
-    double w[kTheta];
-#pragma unroll
-    for (int k = 0; k < kTheta; ++k) {
-        const double entry = a[row * (row + 1) / 2 + k];                // (right of the diagonal: some other entry, never used)
-        w[k] = row == k ? diagonal : ((mine_held || ((held >> k) & 1u)) ? 0.0 : entry);
+    const double seed = __builtin_amdgcn_rsq(pivot);
+    double root = pivot * seed, half = 0.5 * seed;                  // sqrt(pivot), 1 / (2 sqrt(pivot))
+    double r = px_fma(-half, root, 0.5);
+    root = px_fma(root, r, root);
+    half = px_fma(half, r, half);
+    r = px_fma(-half, root, 0.5);
+    root = px_fma(root, r, root);
+    half = px_fma(half, r, half);
+    root = px_fma(px_fma(-root, root, pivot), half, root);
+    const double near = half + half;
+    return px_fma(px_fma(-root, near, 1.0), near, near);
+}
+
+// What lane 2 N of the lane's row of 16 holds, that is what belongs to unknown N.
+template <int N>
+__device__ __forceinline__ double of_unknown(double v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, 0x150 + 2 * N, 0xF, 0xF, true);       // row_newbcast:2 N
+}
+
+// a - (x of unknown N) * y.  The multiply-add takes its operand across lanes itself; two instructions that are not vector
+// writes of x have to lie in front of it.
+#define PX_OF_UNKNOWN(N) " row_newbcast:" #N " row_mask:0xf bank_mask:0xf\n\t"
+#define PX_LESS(A, X, N, Y) "v_fmac_f64_dpp " A ", -" X ", " Y PX_OF_UNKNOWN(N)
+
+// Column K of the factorisation: what it takes from the entries to its right and from the right-hand side, the column itself
+// and the right-hand side's share of it, and the next pivot.  Unknown i's lanes hold row i.
+template <int K>
+__device__ __forceinline__ void eliminate(double (&w)[kTheta], double &b, double inv, double &column, double &share, double &pivot)
+{
+#define PX_BEGIN "v_mul_f64 %0, %[k], %[i]\n\tv_mul_f64 %1, %[b], %[i]\n\ts_nop 0\n\t"
+#define PX_NEXT(N) "v_mov_b64_dpp %2, %3" PX_OF_UNKNOWN(N)
+#define PX_OUT "=&v"(column), "=&v"(share), "=&v"(pivot), "+v"(w[K + 1])
+#define PX_IN [k] "v"(w[K]), [i] "v"(inv)
+    if constexpr (K == 0)
+        asm(PX_BEGIN PX_LESS("%3", "%0", 2, "%0") PX_LESS("%4", "%0", 4, "%0") PX_LESS("%5", "%0", 6, "%0") PX_LESS("%6", "%0", 8, "%0")
+            PX_LESS("%7", "%0", 10, "%0") PX_LESS("%8", "%0", 12, "%0") PX_LESS("%[b]", "%1", 0, "%0") PX_NEXT(2)
+            : PX_OUT, "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), [b] "+v"(b) : PX_IN);
+    else if constexpr (K == 1)
+        asm(PX_BEGIN PX_LESS("%3", "%0", 4, "%0") PX_LESS("%4", "%0", 6, "%0") PX_LESS("%5", "%0", 8, "%0") PX_LESS("%6", "%0", 10, "%0")
+            PX_LESS("%7", "%0", 12, "%0") PX_LESS("%[b]", "%1", 2, "%0") PX_NEXT(4)
+            : PX_OUT, "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), [b] "+v"(b) : PX_IN);
+    else if constexpr (K == 2)
+        asm(PX_BEGIN PX_LESS("%3", "%0", 6, "%0") PX_LESS("%4", "%0", 8, "%0") PX_LESS("%5", "%0", 10, "%0") PX_LESS("%6", "%0", 12, "%0")
+            PX_LESS("%[b]", "%1", 4, "%0") PX_NEXT(6)
+            : PX_OUT, "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), [b] "+v"(b) : PX_IN);
+    else if constexpr (K == 3)
+        asm(PX_BEGIN PX_LESS("%3", "%0", 8, "%0") PX_LESS("%4", "%0", 10, "%0") PX_LESS("%5", "%0", 12, "%0") PX_LESS("%[b]", "%1", 6, "%0")
+            PX_NEXT(8)
+            : PX_OUT, "+v"(w[5]), "+v"(w[6]), [b] "+v"(b) : PX_IN);
+    else if constexpr (K == 4)
+        asm(PX_BEGIN PX_LESS("%3", "%0", 10, "%0") PX_LESS("%4", "%0", 12, "%0") PX_LESS("%[b]", "%1", 8, "%0") PX_NEXT(10)
+            : PX_OUT, "+v"(w[6]), [b] "+v"(b) : PX_IN);
+    else if constexpr (K == 5)
+        asm(PX_BEGIN PX_LESS("%3", "%0", 12, "%0") PX_LESS("%[b]", "%1", 10, "%0") "s_nop 0\n\t" PX_NEXT(12)
+            : PX_OUT, [b] "+v"(b) : PX_IN);
+    else
+        asm("v_mul_f64 %0, %1, %2" : "=v"(share) : "v"(b), "v"(inv));
+#undef PX_BEGIN
+#undef PX_NEXT
+#undef PX_OUT
+#undef PX_IN
+}
+
+// x_K of the triangular system that is left, from x_{K+1} ..: the right-hand side's share less the column's entries times those.
+template <int K>
+__device__ __forceinline__ void substitute(double (&x)[kTheta], double column, double share, double inv)
+{
+#define PX_BEGIN(N) "v_mov_b64_dpp %0, %1" PX_OF_UNKNOWN(N)
+#define PX_IN "v"(share), "v"(column)
+    double s;
+    // (between the last write of a column or a share and here lie at least the two instructions the reads across lanes need)
+    if constexpr (K == 6) asm("s_nop 1\n\t" PX_BEGIN(12) : "=v"(s) : "v"(share));
+    else if constexpr (K == 5) asm(PX_BEGIN(10) PX_LESS("%0", "%2", 12, "%3") : "=&v"(s) : PX_IN, "v"(x[6]));
+    else if constexpr (K == 4) asm(PX_BEGIN(8) PX_LESS("%0", "%2", 10, "%3") PX_LESS("%0", "%2", 12, "%4") : "=&v"(s) : PX_IN, "v"(x[5]), "v"(x[6]));
+    else if constexpr (K == 3)
+        asm(PX_BEGIN(6) PX_LESS("%0", "%2", 8, "%3") PX_LESS("%0", "%2", 10, "%4") PX_LESS("%0", "%2", 12, "%5")
+            : "=&v"(s) : PX_IN, "v"(x[4]), "v"(x[5]), "v"(x[6]));
+    else if constexpr (K == 2)
+        asm(PX_BEGIN(4) PX_LESS("%0", "%2", 6, "%3") PX_LESS("%0", "%2", 8, "%4") PX_LESS("%0", "%2", 10, "%5") PX_LESS("%0", "%2", 12, "%6")
+            : "=&v"(s) : PX_IN, "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]));
+    else if constexpr (K == 1)
+        asm(PX_BEGIN(2) PX_LESS("%0", "%2", 4, "%3") PX_LESS("%0", "%2", 6, "%4") PX_LESS("%0", "%2", 8, "%5") PX_LESS("%0", "%2", 10, "%6")
+            PX_LESS("%0", "%2", 12, "%7")
+            : "=&v"(s) : PX_IN, "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]));
+    else
+        asm(PX_BEGIN(0) PX_LESS("%0", "%2", 2, "%3") PX_LESS("%0", "%2", 4, "%4") PX_LESS("%0", "%2", 6, "%5") PX_LESS("%0", "%2", 8, "%6")
+            PX_LESS("%0", "%2", 10, "%7") PX_LESS("%0", "%2", 12, "%8")
+            : "=&v"(s) : PX_IN, "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]));
+    x[K] = s * inv;
+#undef PX_BEGIN
+#undef PX_IN
+}
+
+// Solves the 7 x 7 system in LDS by Cholesky factorisation: unknown i's lanes hold row i (all four rows of 16 lanes do the
+// same), everything that is about all rows comes across lanes as an operand of the multiply-add.  Every entry takes its
+// subtractions in ascending order of the column.  PLAIN: roots and divisions of the library.
+// Returns false if a pivot is not positive, or, not PLAIN, not well inside the exponent range.
+template <bool PLAIN>
+__device__ __forceinline__ bool solve(const double *system, double (&x)[kTheta])
+{
+    const int mine = (lane_id() & 15) >> 1, row = mine < kTheta ? mine : kTheta - 1;
+    double w[kTheta], b, inv[kTheta], column[kTheta], share[kTheta];
+    {
+        const double2 *from = (const double2 *)(system + row * kRowDoubles);
+        const double2 v0 = from[0], v1 = from[1], v2 = from[2], v3 = from[3];
+        w[0] = v0.x; w[1] = v0.y; w[2] = v1.x; w[3] = v1.y; w[4] = v2.x; w[5] = v2.y; w[6] = v3.x;
+        b = v3.y;
     }
-    double b = mine_held ? 0.0 : -g[row];
-    double l[kPacked], inv[kTheta], y[kTheta];
+    double pivot = of_unknown<0>(w[0]);
+    bool good = true;
+    unsigned off = 0u;                   // of the pivots' high words from that of 2^-900, the largest (negative, zero and NaN far off)
+    auto column_of = [&](auto K) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (PLAIN) {
+            good = good && pivot > 0.0;
+            inv[k] = 1.0 / sqrt(pivot);
+        } else {
+            const unsigned d = (unsigned)__double2hiint(pivot) - ((1023u - 900u) << 20);
+            off = d > off ? d : off;
+            inv[k] = inverse_root(pivot);
+        }
+        eliminate<k>(w, b, inv[k], column[k], share[k], pivot);
+    };
+    column_of(std::integral_constant<int, 0>());
+    column_of(std::integral_constant<int, 1>());
+    column_of(std::integral_constant<int, 2>());
+    column_of(std::integral_constant<int, 3>());
+    column_of(std::integral_constant<int, 4>());
+    column_of(std::integral_constant<int, 5>());
+    column_of(std::integral_constant<int, 6>());
+    if (!PLAIN) good = off <= (1800u << 20);
+    if (__builtin_amdgcn_readfirstlane((int)good) == 0) return false;
+    substitute<6>(x, 0.0, share[6], inv[6]);
+    substitute<5>(x, column[5], share[5], inv[5]);
+    substitute<4>(x, column[4], share[4], inv[4]);
+    substitute<3>(x, column[3], share[3], inv[3]);
+    substitute<2>(x, column[2], share[2], inv[2]);
+    substitute<1>(x, column[1], share[1], inv[1]);
+    substitute<0>(x, column[0], share[0], inv[0]);
+    return true;
+}
+#undef PX_LESS
+#undef PX_OF_UNKNOWN
+
+// What a lane does with its sum when a system is set up: the unknowns the sum belongs to, and where it goes.
+struct SumLane {
+    unsigned unknowns;
+    int place;                           // in the system in LDS
+    bool gradient, diagonal;
+};
+
+__device__ __forceinline__ SumLane sum_lane()
+{
+    const int t = lane_id() >> 1;
+    SumLane me = {t < kTheta ? 3u << (2 * t) : 0u, t * kRowDoubles + kTheta, t < kTheta, false};     // (SUM r^2: behind the last row)
 #pragma unroll
-    for (int k = 0; k < kTheta; ++k) {
-        const double pivot = wave_read(w[k], k);
-        if (!(pivot > 0.0)) return false;
-        inv[k] = 1.0 / sqrt(pivot);
-        const double column = w[k] * inv[k];
-        y[k] = wave_read(b, k) * inv[k];
-        b = px_fma(-column, y[k], b);
-#pragma unroll
-        for (int i = k + 1; i < kTheta; ++i) {
-            l[i * (i + 1) / 2 + k] = wave_read(column, i);
-            w[i] = px_fma(-column, l[i * (i + 1) / 2 + k], w[i]);
+    for (int k = 8; k < kSums; ++k) {
+        if (t == k) {
+            me.unknowns = unknown(kOrder.row[k]) | unknown(kOrder.column[k]);
+            me.place = kOrder.row[k] * kRowDoubles + kOrder.column[k];
+            me.diagonal = kOrder.row[k] == kOrder.column[k];
         }
     }
-#pragma unroll
-    for (int i = kTheta - 1; i >= 0; --i) {
-        double s = y[i];
-#pragma unroll
-        for (int t = i + 1; t < kTheta; ++t) s = px_fma(-l[t * (t + 1) / 2 + i], y[t], s);
-        y[i] = s * inv[i];
-        x = lane == i ? y[i] : x;
+    return me;
+}
+
+// Solves (A + lambda diag(A)) x = -g on the free variables (x = 0 for those in `held`); `sum`: what normal_equations returned.
+// The lanes of unknown i return x_i.  A variable that no record feels (its row, column and gradient are zero: the sync
+// parameters of a job that has never run on several GPUs of one node, or any pair on the flat spot T_sync = 0) gets a pivot of
+// one; its x is zero whatever the pivot, and lambda 1e-300 would be out of inverse_root's range.
+// Returns false if a pivot is not positive.
+__device__ __forceinline__ bool damped_step(double *system, const SumLane &me, double sum, double lambda, unsigned held, double &step)
+{
+    const double damped = sum + lambda * (sum > 1e-300 ? sum : 1e-300);
+    double entry = me.gradient ? -sum : (me.diagonal ? damped : sum);
+    if ((held & me.unknowns) != 0u || (me.diagonal && sum == 0.0)) entry = me.diagonal ? 1.0 : 0.0;
+    wave_fence();
+    system[me.place] = entry;
+    wave_fence();
+    double x[kTheta];
+    if (!solve<false>(system, x)) {
+        wave_fence();                    // (reads the system again, rather than have the other keep it)
+        if (!solve<true>(system, x)) return false;
     }
+    const int lane = lane_id();
+#pragma unroll
+    for (int i = 0; i < kTheta; ++i) step = (lane >> 1) == i ? x[i] : step;
     return true;
 }
 
 constexpr int kMaxStarts = 5;
 
 // Dynamic LDS: kWaveDoubles doubles per wavefront.  HELD: no job has more than 64 records.
+// Three wavefronts a SIMD (168 registers): held to 128 it spills, 0.52 ms where it takes 0.39, 0.88 where it takes 0.76.
 template <bool HELD>
 __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_per_eu(3, 8))) fit_theta_kernel(FitArgs f)
 {
@@ -316,27 +595,27 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
     const double t_min = uniform_f64(best);
     // each lane keeps one record for the whole fit; usually there are no more
     Record mine = {1, 1, 1.0, 0.0, 0.0};
-    if (lane < n) mine = load_record(f, base + lane);
+    if (bit_reversed(lane) < n) mine = load_record(f, base + bit_reversed(lane));
     // (a job whose times are all infinite, NaN or negative has no such record: what is fitted to it is unspecified, what is read is its own)
     const double m_at = (double)f.m[base + (size_t)record_or_first(__builtin_amdgcn_readfirstlane(best_o), n)];
 
     // priors (Sec. 4.1, "Prior-driven exploration"): parameters without evidence are held at zero
     unsigned prior = 0u;
-    if (max_k <= 1) prior |= (1u << PX_ALPHA_SL) | (1u << PX_BETA_SL) | (1u << PX_ALPHA_SN) | (1u << PX_BETA_SN);
-    if (max_nodes <= 1) prior |= (1u << PX_ALPHA_SN) | (1u << PX_BETA_SN);
-    if (max_k <= 2) prior |= (1u << PX_BETA_SL) | (1u << PX_BETA_SN);
+    if (max_k <= 1) prior |= unknown(PX_ALPHA_SL) | unknown(PX_BETA_SL) | unknown(PX_ALPHA_SN) | unknown(PX_BETA_SN);
+    if (max_nodes <= 1) prior |= unknown(PX_ALPHA_SN) | unknown(PX_BETA_SN);
+    if (max_k <= 2) prior |= unknown(PX_BETA_SL) | unknown(PX_BETA_SN);
     prior = (unsigned)__builtin_amdgcn_readfirstlane((int)prior);
-    // lane i < 7: what the iteration keeps of unknown i (the lanes beyond hold nothing that is read)
-    const bool is_sync = lane >= PX_ALPHA_SL && lane <= PX_BETA_SN, is_gamma = lane == PX_GAMMA;
-    const bool my_prior = lane < kTheta && ((prior >> lane) & 1u);
+    // lanes 2 i and 2 i + 1, i < 7: what the iteration keeps of unknown i (the lanes beyond hold nothing that is read)
+    const int which = lane >> 1;
+    const bool is_sync = which >= PX_ALPHA_SL && which <= PX_BETA_SN, is_gamma = which == PX_GAMMA;
+    const bool my_prior = which < kTheta && ((prior >> lane) & 1u);
     // the default starting value of this lane's sync parameter
-    const double sync_default = (lane == PX_ALPHA_SL || lane == PX_ALPHA_SN) ? t_min / 10.0 : t_min / 100.0;
-    double start = is_gamma ? 2.0 : (is_sync ? sync_default : (lane == PX_ALPHA_G ? t_min * 0.5 : t_min / (2.0 * m_at)));
-    if (f.init && lane < kTheta) start = f.init[(size_t)lane * f.J + j];
+    const double sync_default = (which == PX_ALPHA_SL || which == PX_ALPHA_SN) ? t_min / 10.0 : t_min / 100.0;
+    double start = is_gamma ? 2.0 : (is_sync ? sync_default : (which == PX_ALPHA_G ? t_min * 0.5 : t_min / (2.0 * m_at)));
+    if (f.init && which < kTheta) start = f.init[(size_t)which * f.J + j];
     if (my_prior) start = 0.0;
     const double scale = (!is_gamma && start > 0.0) ? start : 1.0;
     const double lo = is_gamma ? 1.0 : 0.0, hi = is_gamma ? 10.0 : __builtin_inf();
-    constexpr unsigned kAll = (1u << kTheta) - 1u;
 
     // The error has several local minima (and a flat spot at T_sync = 0 when gamma > 1), so the iteration is
     // run from a few starting points, one per wavefront, and the best end point is kept (the first one on
@@ -347,7 +626,7 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
     {
         const bool two_phase = k == 1 || k == 2;
         const double sync_factor = (k == 3) ? 3.0 : (k == 4 ? 0.3 : 1.0);
-        const double gamma0 = (k == 0) ? wave_read(start, PX_GAMMA) : (k == 1 ? 2.0 : (k == 3 ? 1.2 : 5.0));
+        const double gamma0 = (k == 0) ? wave_read(start, 2 * PX_GAMMA) : (k == 1 ? 2.0 : (k == 3 ? 1.2 : 5.0));
         double z;
         {
             double v = start;
@@ -357,7 +636,17 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
             z = v < lo ? lo : (v > hi ? hi : v);
         }
 
-        double *table = fit_lds + k * kWaveDoubles, *cur = table + kSumTable, *trial = cur + kSums;
+        double *system = fit_lds + k * kWaveDoubles;
+        if (lane < kWaveDoubles) system[lane] = 0.0;           // (the entries that are always zero)
+        const SumLane me = sum_lane();
+        double scales[kTheta];
+#pragma unroll
+        for (int i = 0; i < kTheta; ++i) {
+            scales[i] = wave_read(scale, 2 * i);
+            asm volatile("" : "+v"(scales[i]));             // (the scalar registers are taken by the constants)
+        }
+        const FitMath math = make_fit_math();
+        double cur = 0.0;                    // the lane's sum at the iterate
         double cur_sse = 0.0;
         int it = 0;
         // Up to four descents, written as one loop so that the iteration is in the code once (inlined four times it was 110 KB,
@@ -372,46 +661,45 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
                 // others staying where they are, and the iteration is continued; the better end point is kept.
                 const int ia = phase == 2 ? PX_ALPHA_SL : PX_ALPHA_SN, ib = ia + 1;
                 const unsigned zero = (unsigned)__ballot(z == 0.0);
-                const bool stuck = !((prior >> ia) & 1u) && ((zero >> ia) & 1u) && (((prior | zero) >> ib) & 1u);
+                const bool stuck = !(prior & unknown(ia)) && (zero & unknown(ia)) && ((prior | zero) & unknown(ib));
                 if (!(stuck && it < f.max_iter && cur_sse > 0.0)) continue;
-                if (lane == ia) z = sync_default / scale;
+                if (which == ia) z = sync_default / scale;
             }
             // The damped Gauss-Newton iteration from z, until it converges or the budget of steps is spent; the
             // variables in `hold` stay where they are.  Leaves the end point in z and its error in cur_sse.
-            const unsigned hold = phase == 0 ? prior | (1u << PX_GAMMA) : prior;
-            double lambda = 1e-3, moved = 0.0, zn = z;
+            const unsigned hold = phase == 0 ? prior | unknown(PX_GAMMA) : prior;
+            double lambda = 1e-3, zn = z;
             bool first = true;
+            unsigned moved = 0u, moved_little = 0u;   // unknowns the last step has changed by 1e-9 of themselves or more, 1e-15 or more
             for (;;) {
-                normal_equations<HELD>(f, j, n, zn, scale, mine, table, trial);
-                const double trial_sse = uniform_f64(trial[0]);
+                const double trial = normal_equations<HELD>(f, j, n, zn, scale, scales, mine, math);
+                const double trial_sse = wave_read(trial, 2 * 7);
                 if (first || trial_sse < cur_sse) {
-                    const double gain = (cur_sse - trial_sse) / cur_sse;
+                    const double before = cur_sse;
                     z = zn;
-                    double *sums = cur;
                     cur = trial;
-                    trial = sums;
                     cur_sse = trial_sse;
                     if (!first) {
                         lambda = lambda * 0.2 > 1e-15 ? lambda * 0.2 : 1e-15;
-                        if (gain < 1e-13 && moved < 1e-9) break;
+                        if (moved == 0u && (before - trial_sse) / before < 1e-13) break;
                     }
                     first = false;
                 } else {
                     lambda *= 5.0;
-                    if (lambda > 1e15 || moved < 1e-15) break;
+                    if (lambda > 1e15 || moved_little == 0u) break;
                 }
                 // the next trial point
                 bool found = false;
                 while (!found && it < f.max_iter && cur_sse > 0.0) {
                     ++it;
-                    const double g = cur[1 + (lane < kTheta ? lane : 0)];
+                    const double g = cur;                               // (of the lane's unknown)
                     unsigned held = hold | ((unsigned)__ballot((z <= lo && g > 0.0) || (z >= hi && g < 0.0)) & kAll);
                     // a free variable that sits on a bound and would be pushed across it joins the held set
                     double step = 0.0;
                     bool solved = false;
 #pragma unroll 1
                     for (int pass = 0; pass < kTheta + 1; ++pass) {
-                        solved = damped_step(cur, lambda, held, step);
+                        solved = damped_step(system, me, cur, lambda, held, step);
                         if (!solved) break;
                         const unsigned more = (unsigned)__ballot((z <= lo && step < 0.0) || (z >= hi && step > 0.0)) & kAll & ~held;
                         if (!more) break;
@@ -424,16 +712,10 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
                     }
                     const double v = ((held >> (lane & 31)) & 1u) ? z : z + step;
                     zn = v < lo ? lo : (v > hi ? hi : v);
-                    // the largest relative change of an unknown (lanes 0 .. 7 among themselves)
-                    const double rel = lane < kTheta ? fabs(zn - z) / (fabs(z) + 1e-12) : 0.0;
-                    double most = rel > 0.0 ? rel : 0.0, other = exchange<0>(most);
-                    most = other > most ? other : most;
-                    other = exchange<1>(most);
-                    most = other > most ? other : most;
-                    other = exchange<2>(most);
-                    most = other > most ? other : most;
-                    moved = wave_read(most, 0);
-                    if (moved == 0.0) break;
+                    const double change = fabs(zn - z), size = fabs(z) + 1e-12;
+                    moved = (unsigned)__ballot(change >= 1e-9 * size) & kAll;
+                    moved_little = (unsigned)__ballot(change >= 1e-15 * size) & kAll;
+                    if (((unsigned)__ballot(change > 0.0) & kAll) == 0u) break;
                     found = true;
                 }
                 if (!found) break;
@@ -451,21 +733,26 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
             end_sse[k] = cur_sse;
             end_it[k] = it;
         }
-        if (lane < kTheta) end_z[k][lane] = z;
+        if (which < kTheta) end_z[k][which] = z;
     }
     __syncthreads();
     if (k != 0) return;
 
+    // the arguments again, rather than keep them in scalar registers through the fit
+    typedef const FitArgs __attribute__((address_space(4))) *KernelArgs;
+    KernelArgs again = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(again));
+    const FitArgs e = *(const FitArgs *)again;
     int best_k = 0, total_it = 0;
-    for (int c = 0; c < f.n_starts; ++c) {
+    for (int c = 0; c < e.n_starts; ++c) {
         total_it += end_it[c];
         if (end_sse[c] < end_sse[best_k]) best_k = c;
     }
     const double best_sse = end_sse[best_k];
-    if (lane < kTheta) f.theta[(size_t)lane * f.J + j] = end_z[best_k][lane] * scale;
+    if (which < kTheta) e.theta[(size_t)which * e.J + j] = end_z[best_k][which] * scale;
     if (lane == 0) {
-        f.rmsle[j] = sqrt(best_sse / (double)n);
-        if (f.iterations) f.iterations[j] = total_it;
+        e.rmsle[j] = sqrt(best_sse / (double)n);
+        if (e.iterations) e.iterations[j] = total_it;
     }
 }
 
@@ -479,9 +766,8 @@ int launch_fit_theta(int J, int max_obs, int max_iter, int n_starts, const int32
     f.theta = theta; f.rmsle = rmsle; f.iterations = iterations;
     const size_t lds = sizeof(double) * kWaveDoubles * (size_t)n_starts;
     const dim3 grid((unsigned)J), block(64 * (unsigned)n_starts);
-    // The instance without the loop over further records needs 128 registers, not 162, so four wavefronts fit a SIMD: 1000 jobs of
-    // up to 48 records in 48 slots 1062 us, in 65 slots 1148 with the other (1213 while that read every record in every
-    // evaluation; 1000 jobs of up to 128 records 1345).
+    // The instance without the loop over further records multiplies where the other accumulates (1000 jobs of up to 48 records in
+    // 48 slots 829 us, in 65 slots 902 with the other).
     if (max_obs <= kWave) hipLaunchKernelGGL(fit_theta_kernel<true>, grid, block, lds, stream, f);
     else hipLaunchKernelGGL(fit_theta_kernel<false>, grid, block, lds, stream, f);
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;

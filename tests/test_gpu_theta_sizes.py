@@ -72,3 +72,28 @@ def test_a_job_without_a_usable_time_does_not_touch_the_others(n_starts, slots):
     good = [j for j in range(J) if j not in bad]
     for k in want:
         assert np.array_equal(want[k][..., good], got[k][..., good]), k
+
+
+@pytest.mark.parametrize("slots", [64, 71])
+@pytest.mark.parametrize("n_starts", [1, 3, 5])
+def test_parameters_that_no_record_feels(n_starts, slots):
+    """Jobs seen on one GPU only, on two GPUs of one node only, on one node, on several nodes only: their normal equations have
+    rows and columns of zeros.  Both instances give the same bits, the oracle's error, and zero where nothing was explored."""
+    import paper_2008_12260_amd as px
+    J = 6
+    ob = W.observations(W.custom("records", P=1, J=J, N=4, cap=4, Gm=8, Gs=4, index=840), max_obs=64)
+    seen = [(1, 1), (2, 1), (4, 1), (2, 2), (8, 2), (64, 16)]              # (GPUs, nodes) of every record of the job
+    for j, (K, nodes) in enumerate(seen):
+        ob["K"][j], ob["nodes"][j] = K, nodes
+    wide = {k: (v if k == "count" else np.concatenate([v, np.ones((J, slots - 64), v.dtype)], axis=1)) for k, v in ob.items()}
+    got = px.fit_theta(wide, n_starts=n_starts)
+    want = px.fit_theta(ob, n_starts=n_starts)
+    for k in got:
+        assert np.array_equal(got[k], want[k]), k
+    theta = got["theta"]
+    assert np.all(theta[2:6, 0] == 0.0)                                    # never more than one GPU
+    assert np.all(theta[4:6, 1:3] == 0.0)                                  # never more than one node
+    for j in range(J):
+        n = int(ob["count"][j])
+        error = TH.rmsle(theta[:, j], *(ob[k][j, :n] for k in ("K", "nodes", "m", "s", "T")))
+        assert abs(got["rmsle"][j] - error) <= 1e-12 * error + 1e-13       # as above: differences of logarithms of size 1
