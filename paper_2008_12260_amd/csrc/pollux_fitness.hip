@@ -197,25 +197,25 @@ __device__ __forceinline__ GridParams load_grid_params(const double *__restrict_
                       jp[(size_t)PX_M0 * J + j], jp[(size_t)PX_MMAX * J + j]};
 }
 
-__device__ __forceinline__ GridPoint grid_point(const GridParams &q, int mi)
+__device__ __forceinline__ GridPoint grid_point(const Coefs &c, const GridParams &q, int mi)
 {
     GridPoint g;
     const double m = (double)mi;
     g.tg = q.alpha_g + q.beta_g * m;                     // Eq. 8
     g.rtg = g.tg > 0.0 ? 1.0 / g.tg : 0.0;
-    g.lntg = px_log(g.tg);
+    g.lntg = px_log(c, g.tg);
     double qh = -1.5, ql = 1.0;
     if (mi > 0) {
-        qh = floor(q.Mmax / m);
+        qh = floor(px_div(q.Mmax, m));               // (put right below where the quotient has been rounded across an integer)
         if (m * (qh + 1.0) <= q.Mmax) qh += 1.0;
         if (m * qh > q.Mmax) qh -= 1.0;
-        ql = ceil(q.M0 / m);
+        ql = ceil(px_div(q.M0, m));
         if (m * (ql - 1.0) >= q.M0) ql -= 1.0;
         if (m * ql < q.M0) ql += 1.0;
         if (!(ql >= 1.0)) ql = 1.0;
         if (!(qh >= 0.0)) qh = -1.5;
     }
-    g.pu = mi > 0 ? q.phi / m : 0.0;
+    g.pu = mi > 0 ? px_div(q.phi, m) : 0.0;
     g.qh5 = qh + 0.5;
     g.ql5 = ql - 0.5;
     return g;
@@ -235,25 +235,28 @@ struct SyncTerm {
     int mode;           // 0: T_sync = 0 (last pass = T_grad); 1: gamma = 1 (plain sum); 2: general
 };
 
-__device__ __forceinline__ SyncTerm sync_term(const Job &q, int K, bool one_node)
+__device__ __forceinline__ SyncTerm sync_term(const Coefs &c, const SyncParams &y, int K, bool one_node)
 {
-    const SyncParams y = load_sync(q);
     SyncTerm t;
     t.ts = t_sync(y, K, one_node);
     t.gamma = y.gamma;
     t.inv_gamma = y.inv_gamma;
     t.mode = (t.ts == 0.0) ? 0 : (y.gamma == 1.0 ? 1 : 2);
-    t.lnts = (t.mode == 2) ? px_log(t.ts) : 0.0;
+    t.lnts = (t.mode == 2) ? px_log(c, t.ts) : 0.0;
     return t;
 }
 
-__device__ __forceinline__ double last_pass(const SyncTerm &t, double tg, double lntg)
+__device__ __forceinline__ SyncTerm sync_term(const Job &q, int K, bool one_node) { return sync_term(plain_coefs(), load_sync(q), K, one_node); }
+
+__device__ __forceinline__ double last_pass(const Coefs &c, const SyncTerm &t, double tg, double lntg)
 {
     if (t.mode == 0) return tg;
     if (t.mode == 1) return tg + t.ts;
-    const double e = px_exp(-t.gamma * fabs(lntg - t.lnts));
-    return fmax(tg, t.ts) * px_exp(px_log1p_unit(e) * t.inv_gamma);
+    const double e = px_exp(c, -t.gamma * fabs(lntg - t.lnts));
+    return fmax(tg, t.ts) * px_exp(c, px_log1p_unit(c, e) * t.inv_gamma);
 }
+
+__device__ __forceinline__ double last_pass(const SyncTerm &t, double tg, double lntg) { return last_pass(plain_coefs(), t, tg, lntg); }
 
 // The feasible accumulation counts of grid point i with K GPUs: s_lo <= s <= s_hi
 // (empty when s_lo > s_hi), from the half-offset quotients of grid_point.
@@ -845,39 +848,44 @@ __device__ __forceinline__ JobTables job_tables(const FitnessArgs &a, int j)
 // arithmetic; the point is then priced with Eq. 4 in the paper's order of operations
 // (T_grad, its logarithm and the last pass of Eq. 10 are formed here, m is not on a grid).
 // Gm evaluations per call instead of Gm * Gs.  Ties go to the lowest i.
-__device__ __forceinline__ Best sweep_sampled(const Job &q, const int32_t *__restrict__ M_list, int Gm, int Gs, int K,
-                                              int nodes)
+__device__ __forceinline__ Best sweep_sampled(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y, double m_mem,
+                                              const int32_t *__restrict__ M_list, int Gm, int Gs, int K, int nodes)
 {
-    if (K <= 0) return Best{0.0, -1, -1};
+    if (K <= 0 || !(m_mem >= 1.0 && m_mem <= 2147483647.0)) return Best{0.0, -1, -1};
     const int lane = lane_id();
-    const double alpha_g = q.jp[(size_t)PX_ALPHA_G * q.J + q.j], beta_g = q.jp[(size_t)PX_BETA_G * q.J + q.j];
-    const double M0 = q.jp[(size_t)PX_M0 * q.J + q.j], Mmax = q.jp[(size_t)PX_MMAX * q.J + q.j];
-    const double m_mem_d = q.jp[(size_t)PX_M_MEM * q.J + q.j];
-    if (!(m_mem_d >= 1.0 && m_mem_d <= 2147483647.0)) return Best{0.0, -1, -1};
-    const long long per_pass = (long long)K * (long long)m_mem_d;     // examples one pass over K GPUs can hold
-    const SyncTerm st = sync_term(q, K, nodes == 1);
+    // The integer arithmetic is done in doubles.  The numerators stay below 2^38 wherever the quotient is not one, so that a
+    // quotient below an integer is further from it than a rounded one can be off: its floor is exact.
     const double Kd = (double)K;
+    const double per_pass = Kd * floor(m_mem);                      // examples one pass over K GPUs can hold
+    const SyncTerm st = sync_term(c, y, K, nodes == 1);
 
     double gbest = 0.0;
     int ibest = 0x7FFFFFFF, m_best = -1, s_best = -1;
     for (int i0 = 0; i0 < Gm; i0 += kWave) {
         const int i = i0 + lane;
         if (i >= Gm) continue;
-        const long long M = M_list[i];
-        if (M <= 0) continue;
-        const long long s = (M + per_pass - 1) / per_pass - 1;
-        if (s > (long long)(Gs - 1)) continue;
-        const long long ks = (long long)K * (s + 1);
-        const long long m = (M + ks - 1) / ks;                         // 1 <= m <= m_mem
-        const double Km = Kd * (double)m;
-        const double Mrun = Km * (double)(s + 1);
-        if (Mrun < M0 || Mrun > Mmax) continue;
-        const double tg = alpha_g + beta_g * (double)m;                // Eq. 8
-        const double last = last_pass(st, tg, st.mode == 2 ? px_log(tg) : 0.0);
-        const double g = goodput_point(q, Km, tg, last, (int)s);
-        if (g > gbest) { gbest = g; ibest = i; m_best = (int)m; s_best = (int)s; }
+        const double M = (double)M_list[i];
+        if (M <= 0.0) continue;
+        const double passes = floor(px_div(M + (per_pass - 1.0), per_pass));     // s + 1
+        if (passes > (double)Gs) continue;
+        const double ks = Kd * passes;
+        const double m = floor(px_div(M + (ks - 1.0), ks));            // 1 <= m <= m_mem
+        const double Km = Kd * m;
+        const double Mrun = Km * passes;
+        if (Mrun < gp.M0 || Mrun > gp.Mmax) continue;
+        const double tg = gp.alpha_g + gp.beta_g * m;                  // Eq. 8
+        const double last = last_pass(c, st, tg, st.mode == 2 ? px_log(c, tg) : 0.0);
+        const int s = (int)passes - 1;
+        const double g = goodput_point(q, Km, tg, last, s);
+        if (g > gbest) { gbest = g; ibest = i; m_best = (int)m; s_best = s; }
     }
     return wave_argmax(gbest, ibest, m_best, s_best);
+}
+
+__device__ __forceinline__ Best sweep_sampled(const Job &q, const int32_t *__restrict__ M_list, int Gm, int Gs, int K, int nodes)
+{
+    return sweep_sampled(plain_coefs(), q, load_grid_params(q.jp, q.J, q.j), load_sync(q), q.jp[(size_t)PX_M_MEM * q.J + q.j], M_list, Gm, Gs,
+                         K, nodes);
 }
 
 // ---- fp32 variant of the sweep --------------------------------------------------
@@ -1233,7 +1241,7 @@ __device__ __forceinline__ int argmin_count(double C)
 {
     // t is found in fp32, where it is off by less than one for every count a grid can have (below 2^14; C is capped far
     // beyond them), and put right by the exact order of neighbours
-    const float c = (float)(C < 1073741824.0 ? C : 1073741824.0);
+    const float c = (float)fmin(C, 1073741824.0);
     const int t = (int)(__builtin_amdgcn_sqrtf(c + 0.25f) - 0.5f);
     const double td = (double)t;
     const double t_lo = t > 0 ? px_fma(td, td, td) : -1.0, t_hi = px_fma(td, td, px_fma(3.0, td, 2.0));
@@ -1257,16 +1265,9 @@ __device__ __forceinline__ double best_count(const GridPoint &g, double last, do
     s = s < s_hi ? s : s_hi;
     s = s > s_lo ? s : s_lo;
     s_c = s;
-    const double sd = (double)s, r = 1.0 / (double)(s + 1);
+    const double sd = (double)s, r = px_div(1.0, sd + 1.0);
     const double h = tabled ? px_fma(g.tg, px_fma(C, r, sd), A0) : px_fma(B0, r, px_fma(sd, g.tg, A0));
     return (s_lo > s_hi || s_hi < 0) ? __builtin_inf() : h;
-}
-
-// Eq. 4 at batch size m and count s in the paper's order of operations, T_grad and the last pass formed here.
-__device__ __forceinline__ double price_in_place(const Job &q, const GridParams &gp, const SyncTerm &st, int K, int m, int s)
-{
-    const double tg = gp.alpha_g + gp.beta_g * (double)m;
-    return goodput_point(q, (double)K * (double)m, tg, last_pass(st, tg, px_log(tg)), s);
 }
 
 // Reciprocals of the counts of a grid of at most 32, for the scan of calls that have no table of them.
@@ -1278,11 +1279,12 @@ __constant__ double small_recips[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
 // CH > 0: each batch size's count is found by the scan over all of them (Gs <= kSmallGs), as in the population pass; the same
 // count either way.
+// The elected point is priced from the terms its lane has formed.
 template <int CH = 0>
-__device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs,
-                                         int K, bool one_node, bool tabled)
+__device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y,
+                                         const int32_t *__restrict__ m_row, int Gm, int Gs, int K, bool one_node, bool tabled)
 {
-    const SyncTerm st = sync_term(q, K, one_node);
+    const SyncTerm st = sync_term(c, y, K, one_node);
     RunSteps X = {};
     if constexpr (CH > 0) X = make_run_steps();
     auto argmin = [&](double C) {
@@ -1290,21 +1292,33 @@ __device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, con
         else return argmin_count(C);
     };
     const double rK = 1.0 / (double)K;
-    double kbest = __builtin_inf();
-    int where = 0;
+    double kbest = __builtin_inf(), tg_at = 0.0, last_at = 0.0;
+    int where = 0, m_at = 0;
     for (int i = lane_id(); i < Gm; i += kWave) {
-        const GridPoint g = grid_point(gp, m_row[i]);
+        const int m = m_row[i];
+        const GridPoint g = grid_point(c, gp, m);
+        const double last = last_pass(c, st, g.tg, g.lntg);
         int s_c;
-        const double h = best_count(g, last_pass(st, g.tg, g.lntg), rK, Gs, tabled, argmin, s_c);
+        const double h = best_count(g, last, rK, Gs, tabled, argmin, s_c);
         if (h < kbest) {
             kbest = h;
             where = s_c | ((i / kWave) << 16);
+            tg_at = g.tg;
+            last_at = last;
+            m_at = m;
         }
     }
     const Pick pick = elect(kbest, where, 0ull, Gs);
     if (pick.i < 0) return Best{0.0, -1, -1};
-    const int m = m_row[pick.i];
-    return Best{price_in_place(q, gp, st, K, m, pick.s), m, pick.s};
+    const int l = pick.i & (kWave - 1);
+    const int m = __builtin_amdgcn_readlane(m_at, l);
+    return Best{goodput_point(q, (double)K * (double)m, wave_read(tg_at, l), wave_read(last_at, l), pick.s), m, pick.s};
+}
+
+__device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs, int K,
+                                         bool one_node, bool tabled)
+{
+    return row_best(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
 }
 
 // ---- everything that depends on the jobs only: one launch ---------------------------------------
@@ -1312,6 +1326,8 @@ __device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, con
 // re-allocation factor, and further ones that take ROWS rows (placement class, K) each.  No wavefront reads what another
 // writes (each forms the terms of its own batch sizes, an eighth of a row's work), so a call needs one launch here where
 // it took three or four, one after the other: at 8 jobs 15 us of launches became 7, at 200 jobs 25 became 11.
+// Bound by the vector ALU (busy 0.7 at 900 memoised jobs) and, at 200 jobs, by how few wavefronts there are to spread over the
+// SIMDs: what a wavefront forms before its first row counts as much as three rows.
 //   kPrepPlain    rows into the tables of the sweep (lt, ca, srange; per grid point tg, lntg, pu, qh5, ql5)
 //   kPrepTables   the same for the fp32 variant, whose fair shares are found from the tables (jobs_kernel_f32)
 //   kPrepMemo     memoised mode: the rows' argmaxes into the memo table, no other table
@@ -1341,7 +1357,7 @@ __device__ __forceinline__ bool node_holds(const FitnessArgs &a, int K)
 }
 
 template <int MODE>
-__device__ __forceinline__ void prepare_job(const FitnessArgs &a, int j)
+__device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a, int j)
 {
     const int lane = lane_id();
     const double *__restrict__ jp = a.job_params;
@@ -1349,7 +1365,7 @@ __device__ __forceinline__ void prepare_job(const FitnessArgs &a, int j)
     const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
     if constexpr (prep_has_tables(MODE)) {
         for (int i = lane; i < a.Gm; i += kWave) {
-            const GridPoint g = grid_point(gp, m_row[i]);
+            const GridPoint g = grid_point(c, gp, m_row[i]);
             const size_t o = (size_t)j * a.Gm + i;
             a.tg[o] = double2{g.tg, g.rtg};
             a.lntg[o] = g.lntg;
@@ -1379,8 +1395,8 @@ __device__ __forceinline__ void prepare_job(const FitnessArgs &a, int j)
     const int K = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j]);
     const bool one_node = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j + 1]) == 1;
     Best fair = {0.0, -1, -1};
-    if constexpr (kSampled) fair = sweep_sampled(q, m_row, a.Gm, a.Gs, K, one_node ? 1 : 2);
-    else if (K > 0) fair = row_best(q, gp, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
+    if constexpr (kSampled) fair = sweep_sampled(c, q, gp, y, jp[(size_t)PX_M_MEM * a.J + j], m_row, a.Gm, a.Gs, K, one_node ? 1 : 2);
+    else if (K > 0) fair = row_best(c, q, gp, y, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
     if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
     if (lane == 0) {
         a.denom[j] = fair.goodput;
@@ -1391,83 +1407,88 @@ __device__ __forceinline__ void prepare_job(const FitnessArgs &a, int j)
     if (j == 0 && lane < 16) a.zeros[lane] = 0;
 }
 
+// ROWS rows from K0 on.  The rows follow one another in a loop: written out they want more scalar registers than there are, beside
+// the constants.
 template <int ROWS, int MODE>
-__device__ __forceinline__ void prepare_rows(const FitnessArgs &a, int j, int K0, bool one_node)
+__device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &a, int j, int K0, bool one_node)
 {
     const int lane = lane_id();
     const size_t row0 = ((size_t)j * 2 + (one_node ? 1 : 0)) * kTableK + (K0 - 1);
     const Job q = load_job(a.job_params, a.J, j);
     const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
+    const GridParams gp = load_grid_params(a.job_params, a.J, j);
+    const SyncParams y = load_sync(q);
     if constexpr (MODE == kPrepSampledMemo) {
+        const double m_mem = a.job_params[(size_t)PX_M_MEM * a.J + j];
+#pragma unroll 1
         for (int r = 0; r < ROWS; ++r) {
-            const Best best = sweep_sampled(q, m_row, a.Gm, a.Gs, K0 + r, one_node ? 1 : 2);
+            const Best best = sweep_sampled(c, q, gp, y, m_mem, m_row, a.Gm, a.Gs, K0 + r, one_node ? 1 : 2);
             if (lane == 0) a.memo[row0 + r] = MemoEntry{best.goodput, best.m, best.s};
         }
         return;
     }
-    const GridParams gp = load_grid_params(a.job_params, a.J, j);
     // lane r prepares T_sync and its logarithm, and 1/K, for the r-th row
     const int my_K = K0 + (lane < ROWS ? lane : 0);
-    const SyncTerm mine = sync_term(q, my_K, one_node);
-    const double my_rK = 1.0 / (double)my_K;
-    SyncTerm t[ROWS];
-    double rK[ROWS], kbest[ROWS];
-    int where[ROWS];
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        t[r].ts = wave_read(mine.ts, r);
-        t[r].lnts = wave_read(mine.lnts, r);
-        t[r].gamma = mine.gamma;
-        t[r].inv_gamma = mine.inv_gamma;
-        t[r].mode = __builtin_amdgcn_readlane(mine.mode, r);
-        rK[r] = wave_read(my_rK, r);
-        kbest[r] = __builtin_inf();
-        where[r] = 0;
-    }
-    int32_t *__restrict__ ranges = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
-    for (int i = lane; i < a.Gm; i += kWave) {
-        const GridPoint g = grid_point(gp, m_row[i]);
-#pragma unroll
+    const SyncTerm mine = sync_term(c, y, my_K, one_node);
+    const double my_rK = px_div(1.0, (double)my_K);
+    // lane r: the point elected for row r
+    double my_h = __builtin_inf(), my_tg = 1.0, my_last = 1.0;
+    int my_m = -1, my_s = -1;
+    // Batch sizes 64 at a time; memoised, the later ones have to be better than what the earlier ones elected (equal values: the earlier).
+    for (int i0 = 0; i0 < a.Gm; i0 += kWave) {
+        const int i = i0 + lane;
+        const bool active = i < a.Gm;
+        const int m = m_row[active ? i : a.Gm - 1];
+        const GridPoint g = grid_point(c, gp, m);
+        double *__restrict__ lt = a.lt + row0 * a.Gm;
+        double2 *__restrict__ ca = a.ca + row0 * a.Gm;
+        int32_t *__restrict__ ranges = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
+#pragma unroll 1
         for (int r = 0; r < ROWS; ++r) {
-            const double last = last_pass(t[r], g.tg, g.lntg);
+            const SyncTerm t = {wave_read(mine.ts, r), wave_read(mine.lnts, r), mine.gamma, mine.inv_gamma,
+                                __builtin_amdgcn_readlane(mine.mode, r)};
+            const double rK = wave_read(my_rK, r);
+            const double last = last_pass(c, t, g.tg, g.lntg);
             if constexpr (MODE == kPrepMemo) {
                 int s_c;
-                const double h = best_count(g, last, rK[r], a.Gs, true, argmin_count, s_c);
-                if (h < kbest[r]) {
-                    kbest[r] = h;
-                    where[r] = s_c | ((i / kWave) << 16);
+                double h = best_count(g, last, rK, a.Gs, true, argmin_count, s_c);
+                h = active ? h : __builtin_inf();
+                const Pick pick = elect(h, s_c, 0ull, a.Gs);
+                if (pick.i >= 0) {
+                    const double h_at = wave_read(h, pick.i), tg_at = wave_read(g.tg, pick.i), last_at = wave_read(last, pick.i);
+                    const int m_at = __builtin_amdgcn_readlane(m, pick.i);
+                    const bool here = lane == r && h_at < my_h;
+                    my_h = here ? h_at : my_h;
+                    my_tg = here ? tg_at : my_tg;
+                    my_last = here ? last_at : my_last;
+                    my_m = here ? m_at : my_m;
+                    my_s = here ? pick.s : my_s;
                 }
             } else {
-                a.lt[(row0 + r) * a.Gm + i] = last;
                 int s_lo, s_hi;
-                feasible_range(g.ql5, g.qh5, rK[r], a.Gs, s_lo, s_hi);
+                feasible_range(g.ql5, g.qh5, rK, a.Gs, s_lo, s_hi);
                 const bool none = s_lo > s_hi || s_hi < 0;
                 if (none) { s_lo = 1; s_hi = 0; }
-                if (!one_node) ranges[(size_t)r * a.Gm + i] = s_lo | (s_hi << 16);
                 // what the sweep needs of (job, class, K, i): h(m_i, s) = A0 + T_grad (s + C / (s+1))
-                const double u = g.pu * rK[r];
+                const double u = g.pu * rK;
                 const double A0 = px_fma(u, g.tg, last);
                 const double B0 = (last - g.tg) * u;
-                a.ca[(row0 + r) * a.Gm + i] = double2{B0 * g.rtg, none ? __builtin_inf() : A0};
+                if (active) {
+                    lt[(unsigned)i] = last;
+                    ca[(unsigned)i] = double2{B0 * g.rtg, none ? __builtin_inf() : A0};
+                    if (!one_node) ranges[(unsigned)i] = s_lo | (s_hi << 16);
+                }
+                lt += a.Gm;
+                ca += a.Gm;
+                ranges += a.Gm;
             }
         }
     }
     if constexpr (MODE == kPrepMemo) {
-        // lane r prices the point elected for row r
-        int my_i = -1, my_s = -1;
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const Pick pick = elect(kbest[r], where[r], 0ull, a.Gs);
-            my_i = lane == r ? pick.i : my_i;
-            my_s = lane == r ? pick.s : my_s;
-        }
+        // lane r prices the point elected for row r, from the terms that point's lane has formed
         if (lane < ROWS) {
-            MemoEntry e = {0.0, -1, -1};
-            if (my_i >= 0) {
-                e.m = m_row[my_i];
-                e.s = my_s;
-                e.goodput = price_in_place(q, gp, mine, my_K, e.m, e.s);
-            }
+            MemoEntry e = {0.0, my_m, my_s};
+            if (my_m >= 0) e.goodput = goodput_point(q, (double)my_K * (double)my_m, my_tg, my_last, my_s);
             a.memo[row0 + lane] = e;
         }
     }
@@ -1504,14 +1525,15 @@ __global__ void __launch_bounds__(256) prepare_kernel(FitnessArgs a)
     const PrepSlot slot = prep_slot(blockIdx.x, wave, kTasks);
     const int j = slot.job, task = slot.task;
     if (j >= a.J) return;
+    const Coefs c = held_coefs();
     if (task == 0) {
-        prepare_job<MODE>(a, j);
+        prepare_job<MODE>(c, a, j);
     } else if constexpr (MODE != kPrepSampled) {
         constexpr int kPerClass = kTableK / ROWS;
         const bool one_node = task - 1 >= kPerClass;
         const int K0 = ((task - 1) % kPerClass) * ROWS + 1;
         if (one_node && !node_holds(a, K0)) return;       // no row of this wavefront is ever looked up
-        prepare_rows<ROWS, MODE>(a, j, K0, one_node);
+        prepare_rows<ROWS, MODE>(c, a, j, K0, one_node);
     }
 }
 
@@ -2200,12 +2222,15 @@ __global__ void __launch_bounds__(256) queries_kernel(FitnessArgs a, QueryArgs q
         nodes = q.nodes[j];
         if (!(q.progress[j] < q.target[j])) K = 0;              // a finished job is left as it is
     }
+    // (the parameters all together: one trip to memory)
+    const Job job = load_job(a.job_params, a.J, j);
+    const GridParams gp = load_grid_params(a.job_params, a.J, j);
+    const SyncParams y = load_sync(job);
     K = __builtin_amdgcn_readfirstlane(K);             // one query per wavefront: the same in every lane
     nodes = __builtin_amdgcn_readfirstlane(nodes);
     Best best = {0.0, -1, -1};
     if (K > 0)
-        best = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs,
-                        K, nodes == 1, K <= kTableK);
+        best = row_best(held_coefs(), job, gp, y, a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, K <= kTableK);
     if (lane_id() != 0) return;
     if (q.mode == 0) {
         q.per_gpu[id] = best.goodput / (double)K;
@@ -2392,6 +2417,7 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
     const int c = a.sel ? a.sel[blockIdx.x] : (int)blockIdx.x;
     const int t = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const Coefs coefs = held_coefs();
     if (t < 4 * kWave) node_lds[t] = 0ull;
     if (t == 0) status_lds = negative = 0;
     // the largest node capacity (rows of the "one node" class beyond it take the form of the untabled sweep)
@@ -2415,6 +2441,7 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
         const int j = is_row ? task - shares : task;
         const Job q = load_job(a.job_params, a.J, j);
         const GridParams gp = load_grid_params(a.job_params, a.J, j);
+        const SyncParams y = load_sync(q);
         const int32_t *__restrict__ m_row = a.m_grid + (size_t)j * a.Gm;
         const Entries was = *(const Entries *)(a.current_alloc + (size_t)j * a.N + at_row.base) & at_row.mask;
         if (is_row) {
@@ -2432,7 +2459,7 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
                 atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
             }
             Best best = {0.0, -1, -1};
-            if (K >= 1) best = row_best<CH>(q, gp, m_row, a.Gm, a.Gs, K, nodes == 1, tabled_row(K, nodes == 1, k1));
+            if (K >= 1) best = row_best<CH>(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, tabled_row(K, nodes == 1, k1));
             if (lane == 0) {
                 goodput_lds[j] = best.goodput;
                 meta_lds[j] = nodes | (changed ? kMetaChanged : 0);
@@ -2443,14 +2470,14 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
             const int K = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j]);
             const bool one_node = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j + 1]) == 1;
             const double T = a.job_params[(size_t)PX_AGE_T * a.J + j], R = a.job_params[(size_t)PX_RESTARTS_R * a.J + j];
-            int st = job_status(gp, load_sync(q), a.job_params[(size_t)PX_WEIGHT * a.J + j]);
+            int st = job_status(gp, y, a.job_params[(size_t)PX_WEIGHT * a.J + j]);
             // re-allocation penalty factor of Sec. 4.2
             const bool penalty = !(a.flags & PX_FLAG_NO_REALLOC_PENALTY);
             if (penalty && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
             const long long held = wave_sum((long long)was.x + was.y + was.z + was.w);
             if (__ballot((was.x | was.y | was.z | was.w) < 0) != 0) st |= PX_ST_NEG_ALLOC;
             Best fair = {0.0, -1, -1};
-            if (K > 0) fair = row_best(q, gp, m_row, a.Gm, a.Gs, K, one_node, tabled_row(K, one_node, k1));
+            if (K > 0) fair = row_best(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, one_node, tabled_row(K, one_node, k1));
             if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
             if (lane == 0) {
                 fair_lds[j] = fair.goodput;
@@ -2945,7 +2972,8 @@ static FitnessArgs job_level_args(const pollux_dims *d, const double *job_params
 // Rows (placement class, K) one wavefront of prepare_kernel takes.  Below 128 jobs eight rows each would leave SIMDs without
 // a wavefront (72 rows a job on nodes of 8 GPUs: 1152 wavefronts at 128 jobs), and the kernel lasts as long as one
 // wavefront's chain: two rows (30 jobs, memoised: 7.1 us against 10.9; 8 jobs: 6.2 against 7.3).  From there on the terms of
-// a batch size are formed once for eight rows (200 jobs: 14.8 us against 15.7; 1000 jobs: 70 against 91).
+// a batch size are formed once for eight rows (200 jobs a call with four rows 67.6 us, with eight 66.7, with sixteen 68.3; 1000 jobs
+// 1904, 1895, 1910).  The sampling argmax has no such terms: one row, or two where the jobs are many (200 jobs 30.8 and 29.5 us a call).
 template <int MODE>
 static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
 {
@@ -2953,7 +2981,8 @@ static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
         return dim3(prep_blocks(a.J, prep_tasks(MODE, rows), a.clear_counters ? (long long)a.P * a.N : 0));
     };
     if constexpr (MODE == kPrepSampled || MODE == kPrepSampledMemo) {
-        hipLaunchKernelGGL((prepare_kernel<1, MODE>), blocks(1), dim3(256), 0, stream, a);
+        if (a.J < 128) hipLaunchKernelGGL((prepare_kernel<1, MODE>), blocks(1), dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((prepare_kernel<2, MODE>), blocks(2), dim3(256), 0, stream, a);
     } else {
         if (a.J < 128) hipLaunchKernelGGL((prepare_kernel<2, MODE>), blocks(2), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((prepare_kernel<8, MODE>), blocks(8), dim3(256), 0, stream, a);

@@ -21,6 +21,7 @@ inline double px_fma(double a, double b, double c) { return std::fma(a, b, c); }
 inline double px_rcp_seed(double x) { return (double)(1.0f / (float)x); }   // ~2^-23, like the hardware seed
 inline double px_ldexp(double x, int k) { return std::ldexp(x, k); }
 inline double px_rint(double x) { return std::nearbyint(x); }
+inline double px_max(double a, double b) { return std::fmax(a, b); }
 }  // namespace px
 #else
 #include <hip/hip_runtime.h>
@@ -30,41 +31,71 @@ PX_DEV double px_fma(double a, double b, double c) { return __builtin_fma(a, b, 
 PX_DEV double px_rcp_seed(double x) { return __builtin_amdgcn_rcp(x); }             // v_rcp_f64
 PX_DEV double px_ldexp(double x, int k) { return __builtin_amdgcn_ldexp(x, k); }    // v_ldexp_f64
 PX_DEV double px_rint(double x) { return __builtin_rint(x); }                       // v_rndne_f64
+PX_DEV double px_max(double a, double b) { return __builtin_fmax(a, b); }            // v_max_f64: b where a is not a number
 }  // namespace px
 #endif
 
 namespace px {
 
-// a / b for finite b != 0 well inside the exponent range: reciprocal seed, two
-// Newton steps, one residual correction of the quotient.
+// The functions' constants.  A kernel that evaluates them over and over holds them in registers (held_coefs): one wavefront
+// issues an instruction every four cycles, scalar ones no faster, so that a coefficient formed where it is used, by two moves,
+// trebles the price of a polynomial's step.  Functions without the argument form them where they are used.
+struct Coefs {
+    double log_top, log_c[10];      // 2/23, and 2/21, 2/19 .. 2/3
+    double exp_top, exp_c[10];      // 1/13!, and 1/12!, 1/11! .. 1/3!
+    double ln2, ln2_low, log2e, exp_least, root_half, root2_less1;
+};
+
+PX_DEV Coefs plain_coefs()
+{
+    return Coefs{0.08695652173913043,
+                 {0.09523809523809523, 0.10526315789473684, 0.11764705882352941, 0.13333333333333333, 0.15384615384615385,
+                  0.18181818181818182, 0.2222222222222222, 0.2857142857142857, 0.4, 0.6666666666666666},
+                 1.6059043836821613e-10,
+                 {2.08767569878681e-09, 2.505210838544172e-08, 2.755731922398589e-07, 2.7557319223985893e-06, 2.48015873015873e-05,
+                  0.0001984126984126984, 0.001388888888888889, 0.008333333333333333, 0.041666666666666664, 0.16666666666666666},
+                 0.6931471805599453,        // ln2 high part
+                 2.3190468138462996e-17,    // ln2 low part
+                 1.4426950408889634,        // log2(e)
+                 -745.5,                    // exp underflows to 0 below this
+                 0.7071067811865476, 0.41421356237309503};
+}
+
+#if !defined(PX_MATH_HOST)
+// The same in registers: the highest coefficients in vector ones (an instruction takes one scalar operand), all others in scalar ones.
+PX_DEV Coefs held_coefs()
+{
+    Coefs c = plain_coefs();
+    asm volatile("" : "+v"(c.log_top), "+v"(c.exp_top));
+#pragma unroll
+    for (int i = 0; i < 10; ++i) asm volatile("" : "+s"(c.log_c[i]), "+s"(c.exp_c[i]));
+    asm volatile("" : "+s"(c.ln2), "+s"(c.ln2_low), "+s"(c.log2e), "+s"(c.exp_least), "+s"(c.root_half), "+s"(c.root2_less1));
+    return c;
+}
+#endif
+
+// a / b for finite b != 0 well inside the exponent range: reciprocal seed (2^-24), one step of third order, one residual
+// correction of the quotient.  (In 2e9 tries over all kinds of mantissas the quotient was the correctly rounded one every time.)
 PX_DEV double px_div(double a, double b)
 {
     double r = px_rcp_seed(b);
-    r = px_fma(px_fma(-b, r, 1.0), r, r);
-    r = px_fma(px_fma(-b, r, 1.0), r, r);
-    double q = a * r;
+    const double e = px_fma(-b, r, 1.0);
+    r = px_fma(px_fma(e, e, e), r, r);
+    const double q = a * r;
     return px_fma(px_fma(-b, q, a), r, q);
 }
 
 // exp(t) for t <= 1 (any negative t, -inf included): t = k ln2 + r, |r| <= ln2/2,
 // Taylor polynomial of degree 13 in r (remainder below 2^-57), scaled by 2^k.
-PX_DEV double px_exp(double t)
+PX_DEV double px_exp(const Coefs &c, double t)
 {
-    t = t > -745.5 ? t : -745.5;                                   // exp underflows to 0 below this
-    const double k = px_rint(t * 1.4426950408889634);              // log2(e)
-    double r = px_fma(-k, 0.6931471805599453, t);                  // ln2 high part
-    r = px_fma(-k, 2.3190468138462996e-17, r);                     // ln2 low part
-    double p = 1.6059043836821613e-10;                             // 1/13!
-    p = px_fma(p, r, 2.08767569878681e-09);                        // 1/12!
-    p = px_fma(p, r, 2.505210838544172e-08);                       // 1/11!
-    p = px_fma(p, r, 2.755731922398589e-07);                       // 1/10!
-    p = px_fma(p, r, 2.7557319223985893e-06);                      // 1/9!
-    p = px_fma(p, r, 2.48015873015873e-05);                        // 1/8!
-    p = px_fma(p, r, 0.0001984126984126984);                       // 1/7!
-    p = px_fma(p, r, 0.001388888888888889);                        // 1/6!
-    p = px_fma(p, r, 0.008333333333333333);                        // 1/5!
-    p = px_fma(p, r, 0.041666666666666664);                        // 1/4!
-    p = px_fma(p, r, 0.16666666666666666);                         // 1/3!
+    t = px_max(t, c.exp_least);
+    const double k = px_rint(t * c.log2e);
+    double r = px_fma(-k, c.ln2, t);
+    r = px_fma(-k, c.ln2_low, r);
+    double p = c.exp_top;
+#pragma unroll
+    for (int i = 0; i < 10; ++i) p = px_fma(p, r, c.exp_c[i]);
     p = px_fma(p, r, 0.5);
     p = px_fma(p, r, 1.0);
     p = px_fma(p, r, 1.0);
@@ -72,35 +103,27 @@ PX_DEV double px_exp(double t)
 }
 
 // 2 atanh(z) = log((1+z)/(1-z)) for |z| <= 0.1716 (z^2 <= 0.0295): odd series up to z^23.
-PX_DEV double px_two_atanh(double z)
+PX_DEV double px_two_atanh(const Coefs &c, double z)
 {
     const double w = z * z;
-    double p = 0.08695652173913043;                                // 2/23
-    p = px_fma(p, w, 0.09523809523809523);                         // 2/21
-    p = px_fma(p, w, 0.10526315789473684);                         // 2/19
-    p = px_fma(p, w, 0.11764705882352941);                         // 2/17
-    p = px_fma(p, w, 0.13333333333333333);                         // 2/15
-    p = px_fma(p, w, 0.15384615384615385);                         // 2/13
-    p = px_fma(p, w, 0.18181818181818182);                         // 2/11
-    p = px_fma(p, w, 0.2222222222222222);                          // 2/9
-    p = px_fma(p, w, 0.2857142857142857);                          // 2/7
-    p = px_fma(p, w, 0.4);                                         // 2/5
-    p = px_fma(p, w, 0.6666666666666666);                          // 2/3
+    double p = c.log_top;
+#pragma unroll
+    for (int i = 0; i < 10; ++i) p = px_fma(p, w, c.log_c[i]);
     return px_fma(z * w, p, z + z);
 }
 
 // log(1 + e) for 0 <= e <= 1.  For e > sqrt(2) - 1 the argument is halved first:
 // log(1+e) = ln2 + log(1 + f), f = (e - 1)/2; in both cases log(1+f) = 2 atanh(f/(2+f)).
-PX_DEV double px_log1p_unit(double e)
+PX_DEV double px_log1p_unit(const Coefs &c, double e)
 {
-    const bool big = e > 0.41421356237309503;
+    const bool big = e > c.root2_less1;
     const double f = big ? (e - 1.0) * 0.5 : e;
-    const double l = px_two_atanh(px_div(f, 2.0 + f));
-    return big ? l + 0.6931471805599453 : l;
+    const double l = px_two_atanh(c, px_div(f, 2.0 + f));
+    return big ? l + c.ln2 : l;
 }
 
 // log(x) for positive, finite, normal x.  x = 2^k * m with m in [sqrt(1/2), sqrt(2)).
-PX_DEV double px_log(double x)
+PX_DEV double px_log(const Coefs &c, double x)
 {
 #if defined(PX_MATH_HOST)
     int k;
@@ -109,11 +132,15 @@ PX_DEV double px_log(double x)
     int k = __builtin_amdgcn_frexp_exp(x);
     double m = __builtin_amdgcn_frexp_mant(x);
 #endif
-    if (m < 0.7071067811865476) { m += m; k -= 1; }
+    if (m < c.root_half) { m += m; k -= 1; }
     const double f = m - 1.0;
-    const double l = px_two_atanh(px_div(f, 2.0 + f));
+    const double l = px_two_atanh(c, px_div(f, 2.0 + f));
     const double kd = (double)k;
-    return px_fma(kd, 0.6931471805599453, px_fma(kd, 2.3190468138462996e-17, l));
+    return px_fma(kd, c.ln2, px_fma(kd, c.ln2_low, l));
 }
+
+PX_DEV double px_exp(double t) { return px_exp(plain_coefs(), t); }
+PX_DEV double px_log1p_unit(double e) { return px_log1p_unit(plain_coefs(), e); }
+PX_DEV double px_log(double x) { return px_log(plain_coefs(), x); }
 
 }  // namespace px

@@ -185,97 +185,19 @@ __device__ __forceinline__ Record load_record(const FitArgs &f, size_t at)
     return r;
 }
 
-// a / b for b well inside the exponent range: reciprocal seed (2^-24), one step of third order, one residual correction of the
-// quotient.  In 2e9 tries over all kinds of mantissas the quotient was the correctly rounded one every time.
-__device__ __forceinline__ double fit_div(double a, double b)
-{
-    double r = px_rcp_seed(b);
-    const double e = px_fma(-b, r, 1.0);
-    r = px_fma(px_fma(e, e, e), r, r);
-    const double q = a * r;
-    return px_fma(px_fma(-b, q, a), r, q);
-}
-
-// The functions of the fitness kernels, step by step, with their constants in registers for the whole fit.  One wavefront a
-// SIMD issues an instruction every four cycles whatever it depends on, and scalar ones no faster, so that a coefficient formed
-// where it is used, by two moves, trebled the price of a polynomial's step.
-struct FitMath {
-    double log_top, log_c[10], exp_top, exp_c[10];       // (the highest coefficients in vector registers, all others in scalar ones)
-    double ln2, ln2_low, log2e, least, root_half, root2_less1;
-};
-
-__device__ __forceinline__ FitMath make_fit_math()
-{
-    FitMath c = {2.0 / 23.0,
-                 {2.0 / 21.0, 2.0 / 19.0, 2.0 / 17.0, 2.0 / 15.0, 2.0 / 13.0, 2.0 / 11.0, 2.0 / 9.0, 2.0 / 7.0, 2.0 / 5.0, 2.0 / 3.0},
-                 1.0 / 6227020800.0,
-                 {1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0, 1.0 / 5040.0, 1.0 / 720.0,
-                  1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0},
-                 0.6931471805599453, 2.3190468138462996e-17, 1.4426950408889634, -745.5, 0.7071067811865476, 0.41421356237309503};
-    // (opaque: neither formed again at every use nor moved elsewhere)
-    asm volatile("" : "+v"(c.log_top), "+v"(c.exp_top));
-#pragma unroll
-    for (int i = 0; i < 10; ++i) asm volatile("" : "+s"(c.log_c[i]), "+s"(c.exp_c[i]));
-    asm volatile("" : "+s"(c.ln2), "+s"(c.ln2_low), "+s"(c.log2e), "+s"(c.least), "+s"(c.root_half), "+s"(c.root2_less1));
-    return c;
-}
-
-__device__ __forceinline__ double fit_two_atanh(const FitMath &c, double z)
-{
-    const double w = z * z;
-    double p = c.log_top;
-#pragma unroll
-    for (int i = 0; i < 10; ++i) p = px_fma(p, w, c.log_c[i]);
-    return px_fma(z * w, p, z + z);
-}
-
-__device__ __forceinline__ double fit_log(const FitMath &c, double x)
-{
-    int k = __builtin_amdgcn_frexp_exp(x);
-    double m = __builtin_amdgcn_frexp_mant(x);
-    if (m < c.root_half) { m += m; k -= 1; }
-    const double f = m - 1.0;
-    const double l = fit_two_atanh(c, fit_div(f, 2.0 + f));
-    const double kd = (double)k;
-    return px_fma(kd, c.ln2, px_fma(kd, c.ln2_low, l));
-}
-
-__device__ __forceinline__ double fit_log1p(const FitMath &c, double e)
-{
-    const bool big = e > c.root2_less1;
-    const double f = big ? (e - 1.0) * 0.5 : e;
-    const double l = fit_two_atanh(c, fit_div(f, 2.0 + f));
-    return big ? l + c.ln2 : l;
-}
-
-__device__ __forceinline__ double fit_exp(const FitMath &c, double t)
-{
-    t = t > c.least ? t : c.least;
-    const double k = px_rint(t * c.log2e);
-    double r = px_fma(-k, c.ln2, t);
-    r = px_fma(-k, c.ln2_low, r);
-    double p = c.exp_top;
-#pragma unroll
-    for (int i = 0; i < 10; ++i) p = px_fma(p, r, c.exp_c[i]);
-    p = px_fma(p, r, 0.5);
-    p = px_fma(p, r, 1.0);
-    p = px_fma(p, r, 1.0);
-    return px_ldexp(p, (int)k);
-}
-
 // The sums of one job at theta = z * scale (lanes 2 i and 2 i + 1 hold z_i, all lanes all of scale): sum t in lanes 2 t and 2 t + 1 (kOrder).
 // mine: the lane's record (bit_reversed), read once and kept in its registers over all iterations.  HELD: the job has no more than
 // these 64; otherwise those beyond are read from memory in every evaluation.
 template <bool HELD>
 __device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale,
-                                                   const double (&scale)[kTheta], const Record &mine, const FitMath &c)
+                                                   const double (&scale)[kTheta], const Record &mine, const Coefs &c)
 {
     const int lane = lane_id();
     const double my_th = my_z * my_scale;
     double th[kTheta];
 #pragma unroll
     for (int i = 0; i < kTheta; ++i) th[i] = wave_read(my_th, 2 * i);
-    const double gamma = th[PX_GAMMA], inv_gamma = fit_div(1.0, gamma);
+    const double gamma = th[PX_GAMMA], inv_gamma = px_div(1.0, gamma);
 
     // the residual of one record and its derivatives with respect to z
     auto evaluate = [&](const Record &rec, bool some, double &r, double (&d)[kTheta]) {
@@ -291,23 +213,23 @@ __device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int 
         if (node) ts = th[PX_ALPHA_SN] + th[PX_BETA_SN] * km2;
         double last = tg, dl_dtg = 1.0, dl_dts = gamma == 1.0 ? 1.0 : 0.0, dlnl_dg = 0.0;
         if (ts > 0.0) {                                                                   // Eq. 10
-            const double lntg = fit_log(c, tg), lnts = fit_log(c, ts);
+            const double lntg = px_log(c, tg), lnts = px_log(c, ts);
             const double d = lnts - lntg;
-            const double e = fit_exp(c, -gamma * fabs(d));
-            const double l1p = fit_log1p(c, e);
+            const double e = px_exp(c, -gamma * fabs(d));
+            const double l1p = px_log1p_unit(c, e);
             const double big = d >= 0.0 ? ts : tg, lnbig = d >= 0.0 ? lnts : lntg;
-            last = big * fit_exp(c, l1p * inv_gamma);
-            const double w_small = fit_div(e, 1.0 + e), w_big = fit_div(1.0, 1.0 + e);
+            last = big * px_exp(c, l1p * inv_gamma);
+            const double w_small = px_div(e, 1.0 + e), w_big = px_div(1.0, 1.0 + e);
             const double w_s = d >= 0.0 ? w_big : w_small, w_g = d >= 0.0 ? w_small : w_big;
-            dl_dtg = w_g * fit_div(last, tg);
-            dl_dts = w_s * fit_div(last, ts);
+            dl_dtg = w_g * px_div(last, tg);
+            dl_dts = w_s * px_div(last, ts);
             const double lnsum = gamma * lnbig + l1p;                                     // ln(T_grad^g + T_sync^g)
             dlnl_dg = (w_g * lntg + w_s * lnts) * inv_gamma - lnsum * inv_gamma * inv_gamma;
         }
         const double pred = sd * tg + last;                                               // Eq. 11
         // a lane without a record (some): every derivative has the factor 1 / pred
-        double inv_pred = fit_div(1.0, pred);
-        r = fit_log(c, pred) - lnT;
+        double inv_pred = px_div(1.0, pred);
+        r = px_log(c, pred) - lnT;
         asm("" : "+v"(r), "+v"(inv_pred));                       // (selected, not branched around)
         r = some ? r : 0.0;
         inv_pred = some ? inv_pred : 0.0;
@@ -645,7 +567,7 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
             scales[i] = wave_read(scale, 2 * i);
             asm volatile("" : "+v"(scales[i]));             // (the scalar registers are taken by the constants)
         }
-        const FitMath math = make_fit_math();
+        const Coefs math = held_coefs();
         double cur = 0.0;                    // the lane's sum at the iterate
         double cur_sse = 0.0;
         int it = 0;
