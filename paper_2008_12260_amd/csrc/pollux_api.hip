@@ -226,11 +226,14 @@ int pollux_generation(const pollux_dims *dims, int32_t *population, const double
     if (rc != PX_OK) return rc;
     rc = check_device();
     if (rc != PX_OK) return rc;
+    pollux_dims kept = *dims;
+    kept.flags |= PX_FLAG_KEEP_JOB_TABLES;
+    if (px::generation_in_one(kept, *params))
+        return px::launch_generation(&kept, population, job_params, m_grid, fair_share, current_alloc, node_capacity, p, delta, params,
+                                     workspace, fitness, best_m, best_s, best_goodput, speedup, violations, (hipStream_t)hip_stream);
     rc = px::launch_ga_step(dims, population, fitness, node_capacity, params, workspace, population, inherit_rows,
                             (hipStream_t)hip_stream);
     if (rc != PX_OK) return rc;
-    pollux_dims kept = *dims;
-    kept.flags |= PX_FLAG_KEEP_JOB_TABLES;
     return px::launch_fitness(&kept, population, job_params, m_grid, fair_share, current_alloc, node_capacity, p, delta,
                               workspace, fitness, best_m, best_s, best_goodput, speedup, violations, nullptr, nullptr,
                               (int)params->elite_k, inherit_rows, (hipStream_t)hip_stream);

@@ -29,9 +29,10 @@
 //   small calls       small_kernel does everything in one launch: up to 252 candidates and 16 groups of 64 batch sizes over all
 //                     jobs (small_call)
 // For pollux_generation the population pass takes a list of candidates, the children of the search step.  With
-// PX_GA_INHERIT_ROWS an unchanged row takes over the results of the row it was copied from: in the children's instance of
-// memo_candidates_kernel where that is the pass, not at all in small_kernel (a row there costs no launch), and otherwise in
-// inherit_kernel, which also lists the rows the step has changed per job for pairs_kernel.
+// PX_GA_INHERIT_ROWS an unchanged row takes over the results of the row it was copied from: memoised, on rows of 4 to 64 nodes, in
+// child_kernel, which forms the child as well; in the children's instance of memo_candidates_kernel on longer ones; not at all in
+// small_kernel (a row there costs no launch); and otherwise in inherit_kernel, which also lists the rows the step has changed per
+// job for pairs_kernel.
 //
 // How one wavefront sweeps the grid of a (candidate, job) pair.  Lane l owns
 // the batch sizes m_i, i = l, l+64, ...; it walks s = 0..Gs-1.  Dividing Eq. 4
@@ -73,6 +74,7 @@
 #include "pollux_host.h"
 #include "pollux_launch.h"
 #include "pollux_math.h"
+#include "pollux_step.h"
 
 namespace px {
 
@@ -2287,12 +2289,13 @@ __device__ __forceinline__ T tree_sum(const T *red)
     return wave_tree_sum((red[l] + red[l + 2 * kWave]) + (red[l + kWave] + red[l + 3 * kWave]));
 }
 
+// (the powers behind everything else: their code is long, and a kernel of a few microseconds waits for every line it has to fetch)
 __device__ __forceinline__ double pmean_term(double s, double w, double p)
 {
-    if (p == 0.0) return w * log(s);      // log(0) = -inf
-    if (p == 1.0) return w * s;
-    if (p == -1.0) return w * (1.0 / s);  // 1/0 = +inf, as pow(0, -1)
-    return w * pow(s, p);                 // pow(0, p<0) = +inf
+    if (__builtin_expect(p == -1.0, 1)) return w * (1.0 / s);  // 1/0 = +inf, as pow(0, -1)
+    if (__builtin_expect(p == 1.0, 1)) return w * s;
+    if (__builtin_expect(p == 0.0, 0)) return w * log(s);      // log(0) = -inf
+    return w * pow(s, p);                                      // pow(0, p<0) = +inf
 }
 
 __device__ __forceinline__ float pmean_term(float s, float w, float p)
@@ -2303,9 +2306,9 @@ __device__ __forceinline__ float pmean_term(float s, float w, float p)
 
 __device__ __forceinline__ double pmean_finish(double mean, double p)
 {
-    if (p == 0.0) return exp(mean);
-    if (p == 1.0) return mean;
-    if (p == -1.0) return 1.0 / mean;
+    if (__builtin_expect(p == -1.0, 1)) return 1.0 / mean;
+    if (__builtin_expect(p == 1.0, 1)) return mean;
+    if (__builtin_expect(p == 0.0, 0)) return exp(mean);
     return pow(mean, 1.0 / p);
 }
 __device__ __forceinline__ float pmean_finish(float mean, float p) { return p == 0.0f ? expf(mean) : powf(mean, 1.0f / p); }
@@ -2610,7 +2613,7 @@ __global__ void __launch_bounds__(256) inherit_kernel(FitnessArgs a)
 // all.  Rows of at most 64 entries (SHORT) come four to a load, 16 lanes each.
 //   2048 candidates of 900 jobs on 250 nodes: 1169 us with a wavefront per (candidate, job) reading entry by entry, 0.34 ms so.
 // KIND: the fp64 grid, the fp32 variant, or the sampling argmax.
-// CHILD: the children of a search step that inherits rows (see inherit_kernel for the rule): a row held unchanged takes over
+// CHILD: the children of a search step that inherits rows (see inherit_kernel for the rule; rows that child_kernel does not take): a row held unchanged takes over
 // the results of the row it was copied from, only the others are read back and looked up.  One launch in place of three
 // (inherit_kernel, pairs_kernel over the listed rows, candidates_kernel: 14 us a generation at 30 jobs, 15 at 200).  A child
 // that satisfies both constraints by construction has no violations; any other is evaluated in full, counters included.
@@ -2622,6 +2625,140 @@ constexpr int kMemoChunkJobs = 4 * kCandThreads;    // jobs between two finishin
 constexpr int kMemoNodes = 4 * kWave;               // the longest row
 constexpr int kInherited = -1;                      // row_lds: the row takes over the results of candidate x
 enum MemoKind { kMemoGrid, kMemoF32, kMemoSampled };
+
+// A row's share of the constraint counters: the few lanes that hold a non-zero entry (a job sits on few nodes) add their four
+// entries, zeros included (a negative entry as it is): one branch per row instead of one per entry.
+__device__ __forceinline__ void add_to_nodes(unsigned long long *node_lds, const RowLane &at_row, const Entries &w, int nodes)
+{
+    if ((w.x | w.y | w.z | w.w) != 0) {
+        const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
+        unsigned long long *to = node_lds + at_row.base;
+        atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
+        atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
+        atomicAdd(&to[2], (unsigned long long)(long long)w.z + (w.z > 0 ? one_job : 0ull));
+        atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
+    }
+}
+
+// Four rows per load: K and nodes | changed of the row the lane's group of 16 lanes holds (live: it holds one).
+__device__ __forceinline__ int2 reduce_rows(const RowLane &at_row, const Entries &v, const Entries &was, bool live, bool count_nodes,
+                                            unsigned long long *node_lds, bool &any_neg)
+{
+    const Entries mask = live ? at_row.mask : Entries{0, 0, 0, 0};
+    const Entries w = v & mask, differs = (v ^ was) & mask;
+    const int positive = (w.x > 0 ? 1 : 0) + (w.y > 0 ? 1 : 0) + (w.z > 0 ? 1 : 0) + (w.w > 0 ? 1 : 0);
+    // one word carries two small counts: positive entries (at most 64) and lanes that differ
+    const int counts = row16_sum(positive | ((differs.x | differs.y | differs.z | differs.w) != 0 ? 1 << 12 : 0));
+    const int K = row16_sum((w.x + w.y) + (w.z + w.w));
+    any_neg |= __ballot((w.x | w.y | w.z | w.w) < 0) != 0ull;
+    if (count_nodes) add_to_nodes(node_lds, at_row, w, counts & 0xFFF);
+    return make_int2(K, (counts & 0xFFF) | ((counts >> 12) != 0 ? kMetaChanged : 0));
+}
+
+// What a thread asks for ahead of its first pair (child_kernel): the results of the row's source, and the job's figures.
+struct PairAhead {
+    int from = -1;                   // the candidate those results are of, or -1: none
+    double goodput = 0.0;
+    int meta = 0, m = 0, s = 0;
+    bool job = false;                // the job's figures are there
+    double denom = 0.0, factor = 0.0, weight = 0.0;
+};
+
+// Thread t < kCandThreads finishes the pairs of jobs jc + t, jc + t + kCandThreads, ... < jc + jobs of candidate c (rows: K and nodes |
+// changed per job, or candidate and kInherited): looks the result up, or takes it over, and adds the job's term of the mean.
+template <int KIND, bool CHILD, bool PAIRS, typename REAL>
+__device__ __forceinline__ void finish_pairs(const FitnessArgs &a, int c, int jc, int jobs, int k1, const int2 *rows, PairAhead ahead,
+                                             REAL &acc, REAL &wsum)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = lane_id();
+    const double *__restrict__ wt = a.job_params + (size_t)PX_WEIGHT * a.J;
+    const REAL p = (REAL)a.p;
+    for (int at0 = kWave * wave; wave < 4 && at0 < jobs; at0 += kCandThreads) {
+        const int at = at0 + lane;
+        const bool mine = at < jobs;
+        const int2 row = mine ? rows[at] : make_int2(0, 0);
+        Best best = {0.0, -1, -1};
+        // rows beyond the memo table: found and priced by the whole wavefront, one after the other
+        unsigned long long pending = __ballot(row.y != kInherited && !tabled_row(row.x, (row.y & ~kMetaChanged) == 1, k1));
+        while (__builtin_expect(pending != 0ull, 0)) {
+            const int l = __ffsll(pending) - 1;
+            pending &= pending - 1;
+            const int K = __builtin_amdgcn_readlane(row.x, l);
+            const int nodes = __builtin_amdgcn_readlane(row.y, l) & ~kMetaChanged;
+            const int j = jc + at0 + l;
+            Best found;
+            if constexpr (KIND == kMemoF32) found = sweep_f32(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rk, a.Gm, a.Gs, K, nodes);
+            else if constexpr (KIND == kMemoSampled) found = sweep_sampled(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
+            else found = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
+                                  a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
+            if (lane == l) best = found;
+        }
+        if (!mine) continue;
+        const int j = jc + at;
+        const size_t pair = (size_t)c * a.J + j;
+        int d_meta = row.y;
+        if (CHILD && row.y == kInherited) {
+            if (ahead.from == row.x) {
+                best.goodput = ahead.goodput;
+                d_meta = ahead.meta;
+                best.m = ahead.m;
+                best.s = ahead.s;
+            } else {
+                const size_t from = (size_t)row.x * a.J + j;
+                best.goodput = a.G[from];
+                d_meta = a.meta[from];
+                if (a.best_m) {
+                    best.m = a.best_m[from];
+                    best.s = a.best_s[from];
+                }
+            }
+        } else if (row.x >= 1 && tabled_row(row.x, (d_meta & ~kMetaChanged) == 1, k1)) {
+            const MemoEntry e = a.memo[((size_t)j * 2 + ((d_meta & ~kMetaChanged) == 1 ? 1 : 0)) * kTableK + (row.x - 1)];
+            best.goodput = e.goodput; best.m = e.m; best.s = e.s;
+        }
+        if (a.best_m) {
+            a.best_m[pair] = best.m;
+            a.best_s[pair] = best.s;
+        }
+        if (a.best_goodput) a.best_goodput[pair] = best.goodput;
+        if constexpr (PAIRS) {
+            // what a later generation that inherits rows reads of this pair
+            a.G[pair] = best.goodput;
+            a.meta[pair] = d_meta;
+        }
+        // SPEEDUP (Eq. 15) with the re-allocation penalty, and the job's term of Eq. 14
+        const REAL d = (REAL)(ahead.job ? ahead.denom : a.denom[j]);
+        REAL s_j = d > 0 ? (REAL)best.goodput / d : (REAL)0;
+        if (d_meta & kMetaChanged) s_j = s_j * (REAL)(ahead.job ? ahead.factor : a.factor[j]);
+        if (a.speedup) a.speedup[pair] = (double)s_j;
+        const REAL w = (REAL)(ahead.job ? ahead.weight : wt[j]);
+        acc += pmean_term(s_j, w, p);
+        wsum += w;
+        ahead.from = -1;             // (that was the thread's first pair)
+        ahead.job = false;
+    }
+}
+
+// Constraint check of one node: multi-node jobs beyond the first and GPUs beyond capacity.
+__device__ __forceinline__ long long node_violations(unsigned long long counter, int capacity)
+{
+    const long long x = (long long)counter;
+    const long long asked = (x << 24) >> 24;              // low 40 bits, sign-extended
+    const long long distributed = (x - asked) >> 40;
+    const long long over = asked - (long long)capacity;
+    return (distributed > 1 ? distributed - 1 : 0) + (over > 0 ? over : 0);
+}
+
+// The fitness of candidate c from the sums of its jobs' terms and its violations, by one thread.
+template <typename REAL>
+__device__ __forceinline__ void store_fitness(const FitnessArgs &a, int c, REAL total, REAL weight, long long V)
+{
+    const REAL mean = total / weight;
+    double f = (double)pmean_finish(mean, (REAL)a.p);
+    if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
+    if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
+    a.fitness[c] = f;
+}
 
 // WAVES: four wavefronts, or sixteen where the candidates are too few to fill the chip and their jobs many (see
 // launch_memo_candidates).
@@ -2643,7 +2780,6 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
     const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
-    const double *__restrict__ wt = a.job_params + (size_t)PX_WEIGHT * a.J;
     const int k1 = __builtin_amdgcn_readfirstlane(*a.k1);
     bool odd = true;                                         // CHILD: to be evaluated in full
     const int32_t *__restrict__ src = nullptr;
@@ -2660,18 +2796,6 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
     // what this lane holds of a row
     const RowLane at_row = row_lane(SHORT ? (lane & 15) : lane, a.N);
     auto load = [&](const int32_t *row) { return *(const Entries *)(row + at_row.base); };
-    // a row's share of the constraint counters: the few lanes that hold a non-zero entry (a job sits on few nodes) add
-    // their four entries, zeros included (a negative entry as it is): one branch per row instead of one per entry
-    auto add_to_nodes = [&](const Entries &w, int nodes) {
-        if (count_nodes && (w.x | w.y | w.z | w.w) != 0) {
-            const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
-            unsigned long long *to = node_lds + at_row.base;
-            atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
-            atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
-            atomicAdd(&to[2], (unsigned long long)(long long)w.z + (w.z > 0 ? one_job : 0ull));
-            atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
-        }
-    };
     bool any_neg = false;
     // One row per load: K and nodes | changed of the row the wavefront holds, the same in every lane.
     auto reduce_row = [&](const Entries &v, const Entries &was) {
@@ -2680,24 +2804,10 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
         const int nodes = __popcll(__ballot(w.x > 0)) + __popcll(__ballot(w.y > 0)) + __popcll(__ballot(w.z > 0)) + __popcll(__ballot(w.w > 0));
         const bool changed = __ballot((differs.x | differs.y | differs.z | differs.w) != 0) != 0;
         any_neg |= __ballot((w.x | w.y | w.z | w.w) < 0) != 0;
-        add_to_nodes(w, nodes);
+        if (count_nodes) add_to_nodes(node_lds, at_row, w, nodes);
         return make_int2(K, nodes | (changed ? kMetaChanged : 0));
     };
-    // Four rows per load: the same for the row the lane's group of 16 lanes holds (live: it holds one).
-    auto reduce_rows = [&](const Entries &v, const Entries &was, bool live) {
-        const Entries mask = live ? at_row.mask : Entries{0, 0, 0, 0};
-        const Entries w = v & mask, differs = (v ^ was) & mask;
-        const int positive = (w.x > 0 ? 1 : 0) + (w.y > 0 ? 1 : 0) + (w.z > 0 ? 1 : 0) + (w.w > 0 ? 1 : 0);
-        // one word carries two small counts: positive entries (at most 64) and lanes that differ
-        const int counts = row16_sum(positive | ((differs.x | differs.y | differs.z | differs.w) != 0 ? 1 << 12 : 0));
-        const int K = row16_sum((w.x + w.y) + (w.z + w.w));
-        any_neg |= __ballot((w.x | w.y | w.z | w.w) < 0) != 0;
-        add_to_nodes(w, counts & 0xFFF);
-        return make_int2(K, (counts & 0xFFF) | ((counts >> 12) != 0 ? kMetaChanged : 0));
-    };
-
     Real acc = 0, wsum = 0;
-    const Real p = (Real)a.p;
     for (int jc = 0; jc < a.J; jc += kMemoChunkJobs) {
         const int chunk_jobs = a.J - jc < kMemoChunkJobs ? a.J - jc : kMemoChunkJobs;
         const int32_t *__restrict__ pop = a.population + ((size_t)c * a.J + jc) * a.N;
@@ -2714,7 +2824,7 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
                 for (int q0 = 4 * wave; q0 < rows; q0 += 4 * WAVES) {
                     const int q = q0 + (lane >> 4);
                     const int at = list_lds[q < rows ? q : rows - 1];
-                    const int2 row = reduce_rows(load(pop + (size_t)at * a.N), load(cur + (size_t)at * a.N), q < rows);
+                    const int2 row = reduce_rows(at_row, load(pop + (size_t)at * a.N), load(cur + (size_t)at * a.N), q < rows, count_nodes, node_lds, any_neg);
                     if (q < rows && (lane & 15) == 0) row_lds[at] = row;
                 }
             } else {
@@ -2768,7 +2878,7 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
                     for (int u = 0; u < kAhead; ++u) {
                         if (q0 + 4 * u < rows) {
                             const int q = q0 + 4 * u + (lane >> 4);
-                            const int2 row = reduce_rows(v[u], was[u], q < rows);
+                            const int2 row = reduce_rows(at_row, v[u], was[u], q < rows, count_nodes, node_lds, any_neg);
                             if (q < rows && (lane & 15) == 0) row_lds[place(q)] = row;
                         }
                     }
@@ -2850,61 +2960,7 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
             }
         }
         __syncthreads();                                    // the chunk's rows are all put away
-        // thread t finishes the pairs of jobs jc + t, jc + t + 256, ...
-        for (int at0 = kWave * wave; wave < 4 && at0 < chunk_jobs; at0 += kCandThreads) {
-            const int at = at0 + lane;
-            const bool mine = at < chunk_jobs;
-            const int2 row = mine ? row_lds[at] : make_int2(0, 0);
-            Best best = {0.0, -1, -1};
-            // rows beyond the memo table: found and priced by the whole wavefront, one after the other
-            unsigned long long pending = __ballot(row.y != kInherited && !tabled_row(row.x, (row.y & ~kMetaChanged) == 1, k1));
-            while (pending) {
-                const int l = __ffsll(pending) - 1;
-                pending &= pending - 1;
-                const int K = __builtin_amdgcn_readlane(row.x, l);
-                const int nodes = __builtin_amdgcn_readlane(row.y, l) & ~kMetaChanged;
-                const int j = jc + at0 + l;
-                Best found;
-                if constexpr (KIND == kMemoF32) found = sweep_f32(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rk, a.Gm, a.Gs, K, nodes);
-                else if constexpr (KIND == kMemoSampled) found = sweep_sampled(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
-                else found = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
-                                      a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
-                if (lane == l) best = found;
-            }
-            if (!mine) continue;
-            const int j = jc + at;
-            const size_t pair = (size_t)c * a.J + j;
-            int d_meta = row.y;
-            if (CHILD && row.y == kInherited) {
-                const size_t from = (size_t)row.x * a.J + j;
-                best.goodput = a.G[from];
-                d_meta = a.meta[from];
-                if (a.best_m) {
-                    best.m = a.best_m[from];
-                    best.s = a.best_s[from];
-                }
-            } else if (row.x >= 1 && tabled_row(row.x, (d_meta & ~kMetaChanged) == 1, k1)) {
-                const MemoEntry e = a.memo[((size_t)j * 2 + ((d_meta & ~kMetaChanged) == 1 ? 1 : 0)) * kTableK + (row.x - 1)];
-                best.goodput = e.goodput; best.m = e.m; best.s = e.s;
-            }
-            if (a.best_m) {
-                a.best_m[pair] = best.m;
-                a.best_s[pair] = best.s;
-            }
-            if (a.best_goodput) a.best_goodput[pair] = best.goodput;
-            if constexpr (PAIRS) {
-                // what a later generation that inherits rows reads of this pair
-                a.G[pair] = best.goodput;
-                a.meta[pair] = d_meta;
-            }
-            // SPEEDUP (Eq. 15) with the re-allocation penalty, and the job's term of Eq. 14
-            const Real d = (Real)a.denom[j];
-            Real s_j = d > 0 ? (Real)best.goodput / d : (Real)0;
-            if (d_meta & kMetaChanged) s_j = s_j * (Real)a.factor[j];
-            if (a.speedup) a.speedup[pair] = (double)s_j;
-            acc += pmean_term(s_j, (Real)wt[j], p);
-            wsum += (Real)wt[j];
-        }
+        finish_pairs<KIND, CHILD, PAIRS>(a, c, jc, chunk_jobs, k1, row_lds, PairAhead(), acc, wsum);
         if (CHILD && t == 0) listed = 0;
         __syncthreads();                                    // before the next chunk's rows take their places
     }
@@ -2915,27 +2971,103 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
     if (__ballot(any_neg) != 0ull && lane == 0) atomicOr(a.status, PX_ST_NEG_ALLOC);
 
     // constraint check: per node, multi-node jobs beyond the first and GPUs beyond capacity
-    long long v = 0;
-    if (count_nodes && t < a.N) {
-        const long long x = (long long)node_lds[t];
-        const long long asked = (x << 24) >> 24;              // low 40 bits, sign-extended
-        const long long distributed = (x - asked) >> 40;
-        if (distributed > 1) v += distributed - 1;
-        const long long over = asked - (long long)a.node_capacity[t];
-        if (over > 0) v += over;
-    }
+    const long long v = count_nodes && t < a.N ? node_violations(node_lds[t], a.node_capacity[t]) : 0;
     if (t < kCandThreads) red_v[t] = v;
     __syncthreads();
     if (wave != 0) return;
     const Real total = tree_sum(red_acc), weight = tree_sum(red_w);
     const long long V = tree_sum(red_v);
-    if (t == 0) {
-        const Real mean = total / weight;
-        double f = (double)pmean_finish(mean, p);
-        if (a.violations) a.violations[c] = (int32_t)(V > 0x7FFFFFFF ? 0x7FFFFFFF : V);
-        if (V > 0 && !(a.flags & PX_FLAG_NO_CONSTRAINT_CHECK)) f = -(double)V;
-        a.fitness[c] = f;
+    if (t == 0) store_fitness(a, c, total, weight, V);
+}
+
+// ---- a child of a memoised search that inherits rows: formed and evaluated by one workgroup ----------------------
+// The step's workgroup has the child's rows and where each comes from at hand, so it goes on to the fitness: the rows held unchanged
+// take over their source's results (asked for when the parents are known, so that they arrive while the rows are copied), the
+// few others are read back and looked up.  The terms are summed as memo_candidates_kernel sums them.  A generation is two
+// launches (rank, this) where it was three: an interval of 20 generations of 256 x 30 x 16 takes 270 us where it took 326, of
+// 1000 x 200 x 64 522 where it took 586.  Bound, at 30 jobs, by its own chain: 17400 cycles, of which the parents (kernel
+// arguments, order, draws) take 3800, the rows' trip from memory 2900, the repairs 3600 and what follows them 4600.
+// For rows of 4 to 64 nodes without a GPU limit per job, up to kFinishJobs jobs (generation_in_one): longer rows are bound by the
+// copy, and 18 bytes of LDS a job hold a thousand jobs.
+constexpr int kFinishJobs = 1024;
+
+template <int KIND, int ROWS>
+__global__ void __launch_bounds__(kGaThreads) child_kernel(GaArgs g, FitnessArgs a)
+{
+    using Real = typename std::conditional<KIND == kMemoF32, float, double>::type;
+    extern __shared__ __align__(16) unsigned char ga_lds[];
+    __shared__ unsigned long long node_lds[kArrayNodes];     // per node: GPUs asked + multi-node jobs << 40, as colpack
+    __shared__ Real red_acc[kCandThreads], red_w[kCandThreads];
+    __shared__ int odd_lds, listed;
+    const GaShared sh = carve_shared(ga_lds, g.J, g.N, g.max_entries);
+    const int t = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c = a.sel[blockIdx.x];
+    const int k1 = __builtin_amdgcn_readfirstlane(*a.k1);
+    if (t < kArrayNodes) node_lds[t] = 0ull;
+    if (t == 0) listed = 0;
+    PairAhead ahead;
+    if (t < kCandThreads && t < a.J) {
+        ahead.job = true;
+        ahead.denom = a.denom[t];
+        ahead.factor = a.factor[t];
+        ahead.weight = a.job_params[(size_t)PX_WEIGHT * a.J + t];
     }
+    // the results of the row job t has if neither a move nor a repair touches it
+    auto early = [&](int cand_a, int cand_b) {
+        if (!ahead.job) return;
+        const int d = sh.dec[t];                             // (this thread's own entry)
+        if ((d >> 1) != 0) return;
+        ahead.from = (d & 1) ? cand_b : cand_a;
+        const size_t from = (size_t)ahead.from * a.J + t;
+        ahead.goodput = a.G[from];
+        ahead.meta = a.meta[from];
+        if (a.best_m) {
+            ahead.m = a.best_m[from];
+            ahead.s = a.best_s[from];
+        }
+    };
+    static_assert(kCandThreads <= kGaThreads, "thread t draws the decision of job t");
+    form_child<ROWS, true, true>(g, sh, &odd_lds, early);
+    __syncthreads();
+    // the rows that have no source are read back, four to a load
+    const bool odd = odd_lds != 0;
+    const bool count_nodes = a.need_constraints && odd;
+    int2 *rows_lds = (int2 *)(sh.src + ((a.J + 1) & ~1));
+    uint16_t *list_lds = (uint16_t *)(rows_lds + a.J);
+    for (int at = t; at < a.J; at += kGaThreads) {
+        const int from = odd ? -1 : sh.src[at];
+        if (from >= 0) rows_lds[at] = make_int2(from, kInherited);
+        else list_lds[atomicAdd(&listed, 1)] = (uint16_t)at;
+    }
+    __syncthreads();
+    const int rows = __builtin_amdgcn_readfirstlane(listed);
+    const RowLane at_row = row_lane(lane & 15, a.N);
+    const int32_t *__restrict__ pop = a.population + (size_t)c * a.J * a.N;
+    bool any_neg = false;
+    for (int q0 = 4 * wave; q0 < rows; q0 += 4 * (kGaThreads / kWave)) {
+        const int q = q0 + (lane >> 4);
+        const int at = list_lds[q < rows ? q : rows - 1];
+        const Entries v = *(const Entries *)(pop + (size_t)at * a.N + at_row.base);
+        const Entries was = *(const Entries *)(a.current_alloc + (size_t)at * a.N + at_row.base);
+        const int2 row = reduce_rows(at_row, v, was, q < rows, count_nodes, node_lds, any_neg);
+        if (q < rows && (lane & 15) == 0) rows_lds[at] = row;
+    }
+    if (any_neg && lane == 0) atomicOr(a.status, PX_ST_NEG_ALLOC);
+    __syncthreads();
+    Real acc = 0, wsum = 0;
+    finish_pairs<KIND, true, true>(a, c, 0, a.J, k1, rows_lds, ahead, acc, wsum);
+    if (t < kCandThreads) {
+        red_acc[t] = acc;
+        red_w[t] = wsum;
+    }
+    const long long v = count_nodes && t < a.N ? node_violations(node_lds[t], a.node_capacity[t]) : 0;
+    __syncthreads();
+    if (wave != 0) return;
+    static_assert(kArrayNodes <= kWave, "the first wavefront holds every node's violations");
+    const Real total = tree_sum(red_acc), weight = tree_sum(red_w);
+    const long long V = wave_sum(v);
+    if (t == 0) store_fitness(a, c, total, weight, V);
 }
 
 }  // namespace px
@@ -3063,11 +3195,12 @@ int launch_copy_status(const void *workspace, int32_t *status_out, hipStream_t s
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
 }
 
-int launch_fitness(const pollux_dims *d, const int32_t *population, const double *job_params, const int32_t *m_grid,
-                   const int32_t *fair_share, const int32_t *current_alloc, const int32_t *node_capacity, double p,
-                   double delta, void *workspace, double *fitness, int32_t *best_m, int32_t *best_s,
-                   double *best_goodput, double *speedup, int32_t *violations, hipEvent_t sweep_start,
-                   hipEvent_t sweep_stop, int first_rank, bool inherit_rows, hipStream_t stream)
+// The arguments of a fitness call: all candidates, or (first_rank > 0) those of rank first_rank and beyond in the order the search
+// step left in the workspace, i.e. the slots it has just rewritten; the others keep the results they have.
+static FitnessArgs call_args(const pollux_dims *d, const int32_t *population, const double *job_params, const int32_t *m_grid,
+                             const int32_t *fair_share, const int32_t *current_alloc, const int32_t *node_capacity, double p,
+                             double delta, void *workspace, double *fitness, int32_t *best_m, int32_t *best_s,
+                             double *best_goodput, double *speedup, int32_t *violations, int first_rank)
 {
     const WorkspaceLayout L = workspace_layout(*d);
     char *ws = (char *)workspace;
@@ -3085,16 +3218,69 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     a.zeros = (int32_t *)(ws + L.zeros);
     a.colpack = (unsigned long long *)(ws + L.colpack);
     a.need_constraints = (violations != nullptr || !(d->flags & PX_FLAG_NO_CONSTRAINT_CHECK)) ? 1 : 0;
-    // first_rank > 0: only the candidates of rank first_rank and beyond in the order the search step left in the
-    // workspace, i.e. the slots it has just rewritten; the others keep the results they have
-    const int P_eff = first_rank > 0 ? d->P - first_rank : d->P;
     if (first_rank > 0) {
         a.sel = (const int32_t *)(ws + L.order) + first_rank;
-        a.n_sel = P_eff;
+        a.n_sel = d->P - first_rank;
     }
-    if (P_eff <= 0) return PX_OK;
     a.fitness = fitness; a.best_goodput = best_goodput; a.speedup = speedup;
     a.best_m = best_m; a.best_s = best_s; a.violations = violations;
+    return a;
+}
+
+// The sampling argmax of a pair depends on (job, K, one node or several) only, as the grid's does, and each of its list
+// entries takes a last pass of Eq. 10 (no table holds it): from as many candidates on as a job has rows to take the argmax
+// of (64, and one per GPU of the largest node), the call takes them once per row whether PX_FLAG_MEMOISE asks for it or
+// not (200 jobs, 1000 candidates: 165 us a call with an argmax per pair, 30 so).  P is the same in all calls that
+// share a workspace, so a generation finds the rows its fitness call has left.
+static bool memoised(const pollux_dims &d)
+{
+    const bool sampled_rows = (d.flags & PX_FLAG_SAMPLE_M) != 0 && d.P >= 2 * kTableK && d.N >= 4 && d.N <= kMemoNodes;
+    return (d.flags & PX_FLAG_MEMOISE) != 0 || sampled_rows;
+}
+
+bool generation_in_one(const pollux_dims &d, const pollux_ga_params &ga)
+{
+    return (ga.flags & PX_GA_INHERIT_ROWS) && (ga.flags & PX_GA_IN_PLACE) && !ga.job_gpu_cap && (int)ga.elite_k < d.P && memoised(d) &&
+           !small_call(d) && d.N >= 4 && d.N <= kArrayNodes && d.J <= kFinishJobs;
+}
+
+int launch_generation(const pollux_dims *d, int32_t *population, const double *job_params, const int32_t *m_grid,
+                      const int32_t *fair_share, const int32_t *current_alloc, const int32_t *node_capacity, double p,
+                      double delta, const pollux_ga_params *ga, void *workspace, double *fitness, int32_t *best_m, int32_t *best_s,
+                      double *best_goodput, double *speedup, int32_t *violations, hipStream_t stream)
+{
+    const FitnessArgs a = call_args(d, population, job_params, m_grid, fair_share, current_alloc, node_capacity, p, delta, workspace,
+                                    fitness, best_m, best_s, best_goodput, speedup, violations, (int)ga->elite_k);
+    const GaArgs g = ga_args(d, population, fitness, node_capacity, ga, workspace, population);
+    launch_rank(g, stream);
+    const size_t lds = ga_shared_bytes(d->J, d->N);
+    const bool whole = (d->N & 3) == 0 && ((uintptr_t)population & 15) == 0;
+    const int kind = (d->flags & PX_FLAG_SAMPLE_M) ? kMemoSampled : (d->precision == 1 ? kMemoF32 : kMemoGrid);
+    const void *kernels[3][2] = {{(const void *)child_kernel<kMemoGrid, kRows64>, (const void *)child_kernel<kMemoGrid, kRows64Whole>},
+                                 {(const void *)child_kernel<kMemoF32, kRows64>, (const void *)child_kernel<kMemoF32, kRows64Whole>},
+                                 {(const void *)child_kernel<kMemoSampled, kRows64>, (const void *)child_kernel<kMemoSampled, kRows64Whole>}};
+    static_assert(kMemoGrid == 0 && kMemoF32 == 1 && kMemoSampled == 2, "the rows above");
+    static size_t allowed[3][2][kGaDevices];
+    const int rc = allow_dynamic_lds(kernels[kind][whole], lds, allowed[kind][whole]);
+    if (rc != PX_OK) return rc;
+    void *args[] = {(void *)&g, (void *)&a};
+    if (hipLaunchKernel(kernels[kind][whole], dim3((unsigned)(d->P - (int)ga->elite_k)), dim3(kGaThreads), args, lds, stream) != hipSuccess)
+        return PX_E_HIP;
+    return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
+}
+
+int launch_fitness(const pollux_dims *d, const int32_t *population, const double *job_params, const int32_t *m_grid,
+                   const int32_t *fair_share, const int32_t *current_alloc, const int32_t *node_capacity, double p,
+                   double delta, void *workspace, double *fitness, int32_t *best_m, int32_t *best_s,
+                   double *best_goodput, double *speedup, int32_t *violations, hipEvent_t sweep_start,
+                   hipEvent_t sweep_stop, int first_rank, bool inherit_rows, hipStream_t stream)
+{
+    const WorkspaceLayout L = workspace_layout(*d);
+    char *ws = (char *)workspace;
+    FitnessArgs a = call_args(d, population, job_params, m_grid, fair_share, current_alloc, node_capacity, p, delta, workspace, fitness,
+                              best_m, best_s, best_goodput, speedup, violations, first_rank);
+    const int P_eff = first_rank > 0 ? d->P - first_rank : d->P;
+    if (P_eff <= 0) return PX_OK;
 
     // unrolled s-chunk: the smallest of 8, 16, 24, 32 that covers Gs (32 with several chunks beyond that).  (21 counts in a chunk
     // of 24, and table rows staged in LDS on grids that are no whole groups of 64 too: 1021 candidates of 331 jobs with 50
@@ -3131,13 +3317,7 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     }
     const bool sampled = (d->flags & PX_FLAG_SAMPLE_M) != 0;       // fp64 only (checked by the caller)
-    // The sampling argmax of a pair depends on (job, K, one node or several) only, as the grid's does, and each of its list
-    // entries takes a last pass of Eq. 10 (no table holds it): from as many candidates on as a job has rows to take the argmax
-    // of (64, and one per GPU of the largest node), the call takes them once per row whether PX_FLAG_MEMOISE asks for it or
-    // not (200 jobs, 1000 candidates: 165 us a call with an argmax per pair, 30 so).  P is the same in all calls that
-    // share a workspace, so a generation finds the rows its fitness call has left.
-    const bool sampled_rows = sampled && d->P >= 2 * kTableK && d->N >= 4 && d->N <= kMemoNodes;
-    const bool memo = (d->flags & PX_FLAG_MEMOISE) != 0 || sampled_rows;
+    const bool memo = memoised(*d);
     // The per-node counters start every call at zero.  A call that uses them leaves them at zero again
     // (candidates_kernel clears what it reads), so a call that keeps the job tables, whose caller guarantees an
     // untouched workspace and unchanged dimensions, does not clear them once more.

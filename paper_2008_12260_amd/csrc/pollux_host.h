@@ -101,6 +101,14 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
 // inherit_rows (with first_rank > 0, after launch_ga_step with inherit_rows): rows a child holds unchanged take over
 // their parent's results, only the others are swept
 
+// pollux_generation of a memoised search that inherits rows, in two launches, for the calls generation_in_one says
+// (dims must carry PX_FLAG_KEEP_JOB_TABLES)
+bool generation_in_one(const pollux_dims &d, const pollux_ga_params &ga);
+int launch_generation(const pollux_dims *d, int32_t *population, const double *job_params, const int32_t *m_grid,
+                      const int32_t *fair_share, const int32_t *current_alloc, const int32_t *node_capacity, double p,
+                      double delta, const pollux_ga_params *ga, void *workspace, double *fitness, int32_t *best_m, int32_t *best_s,
+                      double *best_goodput, double *speedup, int32_t *violations, hipStream_t stream);
+
 // Copies the status word of `workspace` to *status_out (device memory) on the stream.
 int launch_copy_status(const void *workspace, int32_t *status_out, hipStream_t stream);
 
