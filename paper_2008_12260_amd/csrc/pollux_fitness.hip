@@ -20,7 +20,8 @@
 //   candidates_kernel per candidate (one workgroup): SPEEDUP, penalty, constraint
 //                     check from those counters and the generalized mean
 // Other calls (launch_fitness decides; a call that keeps the job tables leaves out what makes them):
-//   fp32              jobs_kernel_f32 finds the fair shares from prepare_kernel's tables, memoised memo_kernel_f32 the argmaxes
+//   fp32              memoised, memo_kernel_f32 finds the argmaxes from prepare_kernel's tables; grids of more than 32 counts have their
+//                     fair shares found so too (jobs_kernel_f32)
 //   PX_FLAG_MEMOISE   prepare_kernel takes the argmax once per (job, placement class, K <= 64) and the population pass looks it
 //                     up: memo_candidates_kernel for rows of 4 to 256 nodes, which takes a whole candidate per workgroup and
 //                     finishes its fitness as well (no per-pair scratch, no candidates_kernel); other rows in pairs_kernel
@@ -917,36 +918,32 @@ __device__ __forceinline__ JobF32 load_job_f32(const double *__restrict__ jp, in
     return q;
 }
 
-__device__ __forceinline__ Best sweep_f32(const JobF32 &q, const JobTables &tb, const double *__restrict__ rk, int Gm,
-                                          int Gs, int K, int nodes)
+// A row beyond the tables.  terms(i, m): the half-offset quotients of batch size m, the i-th (see GridPoint); rK: 1 / K.
+template <typename TERMS>
+__device__ __forceinline__ Best sweep_beyond_f32(const JobF32 &q, const int32_t *__restrict__ m_row, const TERMS &terms, double rK, int Gm,
+                                                 int Gs, int K, int nodes)
 {
-    Best out = {0.0, -1, -1};
-    if (K <= 0) return out;
     const int lane = lane_id();
     const float Kf = (float)K;
-    const double rK = K < kRecipTable ? rk[K] : 1.0 / (double)K;
     float ts = 0.0f;                                                          // Eq. 9
     if (K > 1) ts = (nodes == 1) ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
-    // Eq. 10 for K within the tables: the fp64 table of prepare_kernel, rounded to fp32 (two powf per batch size otherwise)
-    const bool tabled = tabled_row(K, nodes == 1, tb.k1);
-    const double *__restrict__ lrow = tb.lt + (unsigned)((nodes == 1 ? kTableK : 0) + (tabled ? K - 1 : 0)) * (unsigned)Gm;
-    const float tsg = (!tabled && ts != 0.0f && q.gamma != 1.0f) ? powf(ts, q.gamma) : 0.0f;
+    const float tsg = (ts != 0.0f && q.gamma != 1.0f) ? powf(ts, q.gamma) : 0.0f;
 
     float gbest = -1.0f;
     int flat = 0x7FFFFFFF, m_best = -1, s_best = -1;
     for (int i0 = 0; i0 < Gm; i0 += kWave) {
         const int i = i0 + lane;
         if (i >= Gm) continue;
-        const int m = tb.m[i];
+        const int m = m_row[i];
         const float mf = (float)m;
         const float tg = q.alpha_g + q.beta_g * mf;                           // Eq. 8
         float last;                                                           // Eq. 10
         if (ts == 0.0f) last = tg;
         else if (q.gamma == 1.0f) last = tg + ts;
-        else if (tabled) last = (float)lrow[i];
         else last = powf(powf(tg, q.gamma) + tsg, q.inv_gamma);
-        const int s_lo = (int)(tb.ql5[i] * rK);
-        int s_hi = (int)(tb.qh5[i] * rK) - 1;
+        const double2 quotients = terms(i, m);
+        const int s_lo = (int)(quotients.x * rK);
+        int s_hi = (int)(quotients.y * rK) - 1;
         s_hi = s_hi < Gs - 1 ? s_hi : Gs - 1;
         // the lane's best s by the same rearrangement as the fp64 sweep, in fp32: argmax GOODPUT = argmin h,
         // h = (last + u tg) + s tg + (last - tg) u / (s + 1), u = phi / (K m); ties to the smaller s
@@ -968,6 +965,13 @@ __device__ __forceinline__ Best sweep_f32(const JobF32 &q, const JobTables &tb, 
         }
     }
     return wave_argmax((double)gbest, flat, m_best, s_best);
+}
+
+__device__ __forceinline__ Best sweep_f32(const JobF32 &q, const JobTables &tb, const double *__restrict__ rk, int Gm, int Gs, int K, int nodes)
+{
+    if (K <= 0) return Best{0.0, -1, -1};
+    auto terms = [&](int i, int) { return double2{tb.ql5[i], tb.qh5[i]}; };
+    return sweep_beyond_f32(q, tb.m, terms, K < kRecipTable ? rk[K] : 1.0 / (double)K, Gm, Gs, K, nodes);
 }
 
 // ---- fp32 variant: the same scan-and-clamp sweep as the fp64 one ------------------------------
@@ -1277,6 +1281,9 @@ constexpr int kSmallGs = 32;
 #define PX_R4(n) 1.0 / (n), 1.0 / (n + 1), 1.0 / (n + 2), 1.0 / (n + 3)
 __constant__ double small_recips[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R4(13), PX_R4(17), PX_R4(21), PX_R4(25), PX_R4(29)};
 #undef PX_R4
+#define PX_R4(n) 1.0f / (n), 1.0f / (n + 1), 1.0f / (n + 2), 1.0f / (n + 3)
+__constant__ float small_recips_f32[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R4(13), PX_R4(17), PX_R4(21), PX_R4(25), PX_R4(29)};
+#undef PX_R4
 
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
 // CH > 0: each batch size's count is found by the scan over all of them (Gs <= kSmallGs), as in the population pass; the same
@@ -1323,6 +1330,56 @@ __device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, con
     return row_best(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
 }
 
+// The same in single precision, for a GPU count within the tables and grids of at most kSmallGs counts: term by term what
+// sweep_pick_f32 and price_point_f32 make of the tables, so the same point and the same bits.
+__device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, const GridParams &gp, const SyncParams &y,
+                                             const int32_t *__restrict__ m_row, int Gm, int Gs, int K, bool one_node)
+{
+    const RunStepsF32 X = make_run_steps_f32();
+    const SyncTerm st = sync_term(c, y, K, one_node);
+    const double rK = 1.0 / (double)K;
+    const float Kf = (float)K;
+    float ts = 0.0f;                                                          // Eq. 9
+    if (K > 1) ts = one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
+    float kbest = __builtin_inff(), last_at = 0.0f;
+    int where = 0, m_at = 0;
+    for (int i = lane_id(); i < Gm; i += kWave) {
+        const int m = m_row[i];
+        const GridPoint g = grid_point(c, gp, m);
+        const float mf = (float)m;
+        const float tg = q.alpha_g + q.beta_g * mf;                           // Eq. 8
+        float last = (float)last_pass(c, st, g.tg, g.lntg);                   // Eq. 10
+        last = ts == 0.0f ? tg : (q.gamma == 1.0f ? tg + ts : last);
+        const float u = q.phi * __builtin_amdgcn_rcpf(Kf * mf);
+        const float A0 = fmaf(u, tg, last);
+        const float C = (last - tg) * u * __builtin_amdgcn_rcpf(tg);
+        int s_lo, s_hi;
+        feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
+        const bool feasible = s_lo <= s_hi && s_hi >= 0;
+        int s_c = scan_argmin_f32<16>(C, X, (ScalarFloats)small_recips_f32, Gs);
+        s_c = s_c < s_hi ? s_c : s_hi;
+        s_c = s_c > s_lo ? s_c : s_lo;
+        const float key = fmaf(tg, fmaf(C, 1.0f / (float)(s_c + 1), (float)s_c), A0);
+        if (feasible && key < kbest) {
+            kbest = key;
+            where = s_c | ((i / kWave) << 16);
+            last_at = last;
+            m_at = m;
+        }
+    }
+    // (positive floats order like their values in double precision)
+    const Pick pick = elect((double)kbest, where, 0ull, Gs);
+    if (pick.i < 0) return Best{0.0, -1, -1};
+    const int l = pick.i & (kWave - 1);
+    const int m = __builtin_amdgcn_readlane(m_at, l);
+    const float last = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(last_at), l));
+    const float mf = (float)m, tg = q.alpha_g + q.beta_g * mf;
+    const float M = (float)K * mf * (float)(pick.s + 1);
+    const float t_iter = (float)pick.s * tg + last;                           // Eq. 11
+    const float g = (M / t_iter) * (q.a / (q.phi + M));                       // Eq. 7 x Eq. 6
+    return Best{(double)g, m, pick.s};
+}
+
 // ---- everything that depends on the jobs only: one launch ---------------------------------------
 // The wavefronts of a job: one that checks its parameters, finds its fair-share goodput (denominator of Eq. 15) and its
 // re-allocation factor, and further ones that take ROWS rows (placement class, K) each.  No wavefront reads what another
@@ -1331,7 +1388,9 @@ __device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, con
 // Bound by the vector ALU (busy 0.7 at 900 memoised jobs) and, at 200 jobs, by how few wavefronts there are to spread over the
 // SIMDs: what a wavefront forms before its first row counts as much as three rows.
 //   kPrepPlain    rows into the tables of the sweep (lt, ca, srange; per grid point tg, lntg, pu, qh5, ql5)
-//   kPrepTables   the same for the fp32 variant, whose fair shares are found from the tables (jobs_kernel_f32)
+//   kPrepTablesF32  the same for the fp32 variant, fair shares in single precision
+//   kPrepTables   the same for the fp32 variant on grids of more than kSmallGs counts: fair shares are found from the tables, by a
+//                 launch of its own (jobs_kernel_f32)
 //   kPrepMemo     memoised mode: the rows' argmaxes into the memo table, no other table
 //   kPrepSampled  the sampling argmax: fair shares only (no table)
 //   kPrepSampledMemo  and with its rows memoised
@@ -1342,9 +1401,9 @@ __device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, con
 // write the feasible counts of (job, K, i), which do not depend on the class: srange[j][K-1][i] = first | last << 16,
 // first > last when there is none.
 // Workgroups are dealt to the XCDs round-robin; a job's wavefronts run on XCD j % 8, as its pairs do.
-enum PrepMode { kPrepPlain, kPrepTables, kPrepMemo, kPrepSampled, kPrepSampledMemo };
+enum PrepMode { kPrepPlain, kPrepTables, kPrepTablesF32, kPrepMemo, kPrepSampled, kPrepSampledMemo };
 
-constexpr bool prep_has_tables(int mode) { return mode == kPrepPlain || mode == kPrepTables; }
+constexpr bool prep_has_tables(int mode) { return mode == kPrepPlain || mode == kPrepTables || mode == kPrepTablesF32; }
 constexpr int prep_tasks(int mode, int rows) { return 1 + (mode == kPrepSampled ? 0 : 2 * kTableK / rows); }
 
 // Whether some node holds at least K GPUs.
@@ -1389,7 +1448,8 @@ __device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a
         if (!(m_mem >= 1.0 && m_mem <= 2147483647.0)) st |= PX_ST_BAD_PARAM;
     }
     // re-allocation penalty factor of Sec. 4.2
-    const double factor = (T - R * a.delta) / (T + a.delta);
+    double factor = (T - R * a.delta) / (T + a.delta);
+    if constexpr (MODE == kPrepTablesF32) factor = (double)(((float)T - (float)R * (float)a.delta) / ((float)T + (float)a.delta));
     if (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
     const CurrentRow cur = current_row(a, j);
     if (cur.negative) st |= PX_ST_NEG_ALLOC;
@@ -1398,7 +1458,15 @@ __device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a
     const bool one_node = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j + 1]) == 1;
     Best fair = {0.0, -1, -1};
     if constexpr (kSampled) fair = sweep_sampled(c, q, gp, y, jp[(size_t)PX_M_MEM * a.J + j], m_row, a.Gm, a.Gs, K, one_node ? 1 : 2);
-    else if (K > 0) fair = row_best(c, q, gp, y, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
+    else if constexpr (MODE == kPrepTablesF32) {
+        auto terms = [&](int, int m) {
+            const GridPoint g = grid_point(c, gp, m);
+            return double2{g.ql5, g.qh5};
+        };
+        const JobF32 qf = load_job_f32(jp, a.J, j);
+        if (K > 0 && K <= kTableK && (!one_node || node_holds(a, K))) fair = row_best_f32(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
+        else if (K > 0) fair = sweep_beyond_f32(qf, m_row, terms, 1.0 / (double)K, a.Gm, a.Gs, K, one_node ? 1 : 2);
+    } else if (K > 0) fair = row_best(c, q, gp, y, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
     if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
     if (lane == 0) {
         a.denom[j] = fair.goodput;
@@ -1541,7 +1609,7 @@ __global__ void __launch_bounds__(256) prepare_kernel(FitnessArgs a)
 
 // ---- fp32 variant: fair shares and memo table, from the tables --------------------------------------
 
-template <int CH>
+// (grids of more than kSmallGs counts)
 __global__ void __launch_bounds__(256) jobs_kernel_f32(FitnessArgs a)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1557,7 +1625,7 @@ __global__ void __launch_bounds__(256) jobs_kernel_f32(FitnessArgs a)
     if (!(a.flags & PX_FLAG_NO_REALLOC_PENALTY) && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
     const CurrentRow cur = current_row(a, j);
     if (cur.negative) st |= PX_ST_NEG_ALLOC;
-    const Best fair = sweep_any_f32<CH>(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rsf, a.rk, a.Gm, a.Gs,
+    const Best fair = sweep_any_f32<16>(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rsf, a.rk, a.Gm, a.Gs,
                                         a.fair_share[2 * j], a.fair_share[2 * j + 1]);
     if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
     if (lane == 0) {
@@ -3341,13 +3409,14 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         a.or_job_status = 1;
         if (sampled && memo) launch_prepare_rows<kPrepSampledMemo>(a, stream);
         else if (sampled) launch_prepare_rows<kPrepSampled>(a, stream);
+        else if (f32 && d->Gs <= kSmallGs) launch_prepare_rows<kPrepTablesF32>(a, stream);
         else if (f32) launch_prepare_rows<kPrepTables>(a, stream);
         else if (memo) launch_prepare_rows<kPrepMemo>(a, stream);
         else launch_prepare_rows<kPrepPlain>(a, stream);
         if (f32) {
             const dim3 job_grid((unsigned)((d->J + kWavesPerBlock - 1) / kWavesPerBlock));
-            if (ch == 8) hipLaunchKernelGGL((jobs_kernel_f32<8>), job_grid, dim3(256), 0, stream, a);
-            else hipLaunchKernelGGL((jobs_kernel_f32<16>), job_grid, dim3(256), 0, stream, a);
+            // (up to kSmallGs counts found with everything else: 200 jobs a call of 74.6 us with a launch for them, 69.5 without)
+            if (d->Gs > kSmallGs) hipLaunchKernelGGL(jobs_kernel_f32, job_grid, dim3(256), 0, stream, a);
             if (memo) {
                 const dim3 memo_grid((unsigned)(((long long)d->J * 2 * kTableK + kWavesPerBlock - 1) / kWavesPerBlock));
                 if (ch == 8) hipLaunchKernelGGL((memo_kernel_f32<8>), memo_grid, dim3(256), 0, stream, a);
