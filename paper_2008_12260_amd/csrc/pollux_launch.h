@@ -37,8 +37,13 @@ inline unsigned prep_blocks(int jobs, int tasks, long long counters)
 
 constexpr int kMaxCandPerWave = 16;   // candidates one wavefront of pairs_kernel walks at most (lane r keeps what candidate r needs)
 
-// How many candidates a wavefront of pairs_kernel takes: enough wavefronts to fill the chip several times over.  And, for rows of at
-// most 64 nodes whose count tables are on chip (row4), whether one load covers the rows of four candidates, which with chunks of up
+// How many candidates a wavefront of pairs_kernel takes: enough wavefronts to fill the chip several times over.  Calls of 200 jobs, us
+// with 25000, 16600 and 12400 wavefronts:
+//   64 nodes, 64 x 16    125 candidates 45.6, 45.6, 34.1; 250 46.8, 38.7, 35.1; 500 47.6, 50.1 (six each), 44.9; 750 63.0, 61.6, 55.1;
+//                        1000 65.4, 64.3, 65.2; 1250 85.6 (ten), 79.0 (fifteen), 76.8: swept in fours, so in whole fours
+//   100 nodes, 64 x 16   125 39.3, 39.3, 33.8; 500 58.0, 54.7, 54.0; 1000 83.8, 83.1, 83.7; 1500 111.2, 109.4, 109.4
+//   100 nodes, 128 x 32  125 51.1, 51.2, 46.5; 500 87.5, 84.1, 84.9; 1000 131.3, 133.2, 136.9; 1500 178.2, 181.0, 180.6
+// And, for rows of at most 64 nodes whose count tables are on chip (row4), whether one load covers the rows of four candidates, which with chunks of up
 // to 16 counts also sweeps the four, a row of 16 lanes each.
 // A sweep of four saves three elections and lasts as long with one candidate as with four: it wants candidates in whole fours,
 // enough pairs to fill the chip with so few wavefronts, and narrow grids (chunk: batch sizes x chunks of 16 counts).
@@ -62,14 +67,19 @@ inline PairSplit split_pairs(int candidates, int jobs, int Gm, int Gs, bool f32,
 {
     const long long pairs = (long long)candidates * jobs;
     const int share = (candidates - 1) / kWavesPerBlock + 1;                    // a workgroup's wavefronts take the candidates in turn
-    int n = (int)(pairs / 25000 < kMaxCandPerWave ? pairs / 25000 : kMaxCandPerWave);
+    const int chunk = Gm * ((Gs + 15) / 16);
+    // What a wavefront does once (job terms, table in LDS, prices) is worth the sweeps of two candidates of 64 x 16: as many as 12400
+    // wavefronts leave each.  Wider grids weigh it less, and the last wavefronts last longer: up to six that way.
+    const long long by_25000 = pairs / 25000, by_12400 = pairs / 12400;
+    long long want = by_25000;
+    if (!inherit) want = chunk <= 64 ? by_12400 : (by_25000 > 6 ? by_25000 : (by_12400 < 6 ? by_12400 : 6));
+    int n = (int)(want < kMaxCandPerWave ? want : kMaxCandPerWave);
     n = n < share ? n : share;
     n = n > 1 ? n : 1;
     if (!row4) return PairSplit{n, false, false};
-    if (!f32 && (whole_rows || Gs > 16)) return PairSplit{n, true, false};
-    const int chunk = Gm * ((Gs + 15) / 16);
+    if (!f32 && (whole_rows || Gs > 16)) return PairSplit{Gs > 16 || n < 4 || inherit ? n : n & ~3, true, false};
     const bool four = inherit ? chunk <= 64 && pairs >= 80000 && !whole_rows : chunk <= 128 && pairs >= 8000 && share >= 4;
-    if (four && !inherit) n = n < 4 ? 4 : (n + 2) & ~3;
+    if (four && !inherit) n = n < 4 ? 4 : n & ~3;
     return PairSplit{n, four, !four && n < 4};
 }
 
