@@ -1501,40 +1501,77 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
     const int my_K = K0 + (lane < ROWS ? lane : 0);
     const SyncTerm mine = sync_term(c, y, my_K, one_node);
     const double my_rK = px_div(1.0, (double)my_K);
-    // lane r: the point elected for row r
-    double my_h = __builtin_inf(), my_tg = 1.0, my_last = 1.0;
-    int my_m = -1, my_s = -1;
-    // Batch sizes 64 at a time; memoised, the later ones have to be better than what the earlier ones elected (equal values: the earlier).
-    for (int i0 = 0; i0 < a.Gm; i0 += kWave) {
-        const int i = i0 + lane;
-        const bool active = i < a.Gm;
-        const int m = m_row[active ? i : a.Gm - 1];
-        const GridPoint g = grid_point(c, gp, m);
-        double *__restrict__ lt = a.lt + row0 * a.Gm;
-        double2 *__restrict__ ca = a.ca + row0 * a.Gm;
-        int32_t *__restrict__ ranges = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
+    if constexpr (MODE == kPrepMemo) {
+        // Batch sizes two groups of 64 at a time, one election for both; later ones have to be better than what earlier ones elected
+        // (equal values: the earlier).  Lane r: the point elected for row r.
+        double my_h = __builtin_inf(), my_tg = 1.0, my_last = 1.0;
+        int my_m = -1, my_s = -1;
+        auto groups = [&](int i0, auto TWO) __attribute__((always_inline)) {
+            constexpr bool two = decltype(TWO)::value;
+            const int i = i0 + lane;
+            const int m0 = m_row[i < a.Gm ? i : a.Gm - 1], m1 = two ? m_row[i + kWave < a.Gm ? i + kWave : a.Gm - 1] : 0;
+            const GridPoint g0 = grid_point(c, gp, m0);
+            GridPoint g1 = g0;
+            if constexpr (two) g1 = grid_point(c, gp, m1);
 #pragma unroll 1
-        for (int r = 0; r < ROWS; ++r) {
-            const SyncTerm t = {wave_read(mine.ts, r), wave_read(mine.lnts, r), mine.gamma, mine.inv_gamma,
-                                __builtin_amdgcn_readlane(mine.mode, r)};
-            const double rK = wave_read(my_rK, r);
-            const double last = last_pass(c, t, g.tg, g.lntg);
-            if constexpr (MODE == kPrepMemo) {
-                int s_c;
-                double h = best_count(g, last, rK, a.Gs, true, argmin_count, s_c);
-                h = active ? h : __builtin_inf();
-                const Pick pick = elect(h, s_c, 0ull, a.Gs);
+            for (int r = 0; r < ROWS; ++r) {
+                const SyncTerm t = {wave_read(mine.ts, r), wave_read(mine.lnts, r), mine.gamma, mine.inv_gamma,
+                                    __builtin_amdgcn_readlane(mine.mode, r)};
+                const double rK = wave_read(my_rK, r);
+                double last_at = last_pass(c, t, g0.tg, g0.lntg), tg_at = g0.tg;
+                int where, m_at = m0;
+                double h = best_count(g0, last_at, rK, a.Gs, true, argmin_count, where);
+                if (i >= a.Gm) h = __builtin_inf();
+                if constexpr (two) {
+                    const double last = last_pass(c, t, g1.tg, g1.lntg);
+                    int s_c;
+                    const double h1 = best_count(g1, last, rK, a.Gs, true, argmin_count, s_c);
+                    if (i + kWave < a.Gm && h1 < h) {
+                        h = h1;
+                        where = s_c | (1 << 16);
+                        last_at = last;
+                        tg_at = g1.tg;
+                        m_at = m1;
+                    }
+                }
+                const Pick pick = elect(h, where, 0ull, a.Gs);
                 if (pick.i >= 0) {
-                    const double h_at = wave_read(h, pick.i), tg_at = wave_read(g.tg, pick.i), last_at = wave_read(last, pick.i);
-                    const int m_at = __builtin_amdgcn_readlane(m, pick.i);
-                    const bool here = lane == r && h_at < my_h;
-                    my_h = here ? h_at : my_h;
-                    my_tg = here ? tg_at : my_tg;
-                    my_last = here ? last_at : my_last;
-                    my_m = here ? m_at : my_m;
+                    const int l = pick.i & (kWave - 1);
+                    const double h_l = wave_read(h, l), tg_l = wave_read(tg_at, l), last_l = wave_read(last_at, l);
+                    const int m_l = __builtin_amdgcn_readlane(m_at, l);
+                    const bool here = lane == r && h_l < my_h;
+                    my_h = here ? h_l : my_h;
+                    my_tg = here ? tg_l : my_tg;
+                    my_last = here ? last_l : my_last;
+                    my_m = here ? m_l : my_m;
                     my_s = here ? pick.s : my_s;
                 }
-            } else {
+            }
+        };
+        for (int i0 = 0; i0 < a.Gm; i0 += 2 * kWave) {
+            if (i0 + kWave < a.Gm) groups(i0, std::true_type());
+            else groups(i0, std::false_type());
+        }
+        // lane r prices the point elected for row r, from the terms that point's lane has formed
+        if (lane < ROWS) {
+            MemoEntry e = {0.0, my_m, my_s};
+            if (my_m >= 0) e.goodput = goodput_point(q, (double)my_K * (double)my_m, my_tg, my_last, my_s);
+            a.memo[row0 + lane] = e;
+        }
+    } else {
+        for (int i0 = 0; i0 < a.Gm; i0 += kWave) {
+            const int i = i0 + lane;
+            const bool active = i < a.Gm;
+            const GridPoint g = grid_point(c, gp, m_row[active ? i : a.Gm - 1]);
+            double *__restrict__ lt = a.lt + row0 * a.Gm;
+            double2 *__restrict__ ca = a.ca + row0 * a.Gm;
+            int32_t *__restrict__ ranges = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
+#pragma unroll 1
+            for (int r = 0; r < ROWS; ++r) {
+                const SyncTerm t = {wave_read(mine.ts, r), wave_read(mine.lnts, r), mine.gamma, mine.inv_gamma,
+                                    __builtin_amdgcn_readlane(mine.mode, r)};
+                const double rK = wave_read(my_rK, r);
+                const double last = last_pass(c, t, g.tg, g.lntg);
                 int s_lo, s_hi;
                 feasible_range(g.ql5, g.qh5, rK, a.Gs, s_lo, s_hi);
                 const bool none = s_lo > s_hi || s_hi < 0;
@@ -1552,14 +1589,6 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
                 ca += a.Gm;
                 ranges += a.Gm;
             }
-        }
-    }
-    if constexpr (MODE == kPrepMemo) {
-        // lane r prices the point elected for row r, from the terms that point's lane has formed
-        if (lane < ROWS) {
-            MemoEntry e = {0.0, my_m, my_s};
-            if (my_m >= 0) e.goodput = goodput_point(q, (double)my_K * (double)my_m, my_tg, my_last, my_s);
-            a.memo[row0 + lane] = e;
         }
     }
 }
@@ -3176,6 +3205,7 @@ static FitnessArgs job_level_args(const pollux_dims *d, const double *job_params
 //             with sixteen rows 200 jobs (1000 candidates) take 68.3 against 66.7
 //   memoised  whose rows end in an election: 140 jobs 16.5, 17.8, 18.7; 200 jobs 19.9, 19.9, 20.3; 300 jobs 34.5, 33.4, 33.4; 900 jobs
 //             81.5, 74.5, 74.5; with 128 batch sizes 140 jobs 22.1, 25.6, 27.9; 500 jobs 63.4, 61.2, 64.2; 900 jobs 107.7, 100.8, 103.3
+//             (an election for both groups of 64 batch sizes since: 500 jobs 57.1, 900 jobs 95.2)
 // The sampling argmax has no such terms: one row, or two where the jobs are many (200 jobs 30.8 and 29.5 us a call).
 template <int MODE>
 static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
