@@ -18,10 +18,10 @@
 // the starting point (they differ by four orders of magnitude).
 //
 // Bound by the vector ALU's issue, wavefront by wavefront: an instruction, scalar ones included, takes four cycles whether it
-// waits for the one before it or not, so what counts is how many there are.  An iteration is 700 (1200 with the sums through
+// waits for the one before it or not, so what counts is how many there are.  An iteration is 840 (1240 with the sums through
 // LDS, the library's roots and divisions and the polynomials' constants formed where they are used); 100 jobs, 200 iterations:
 // 0.70 ms then, 0.39 now.  Beyond 256 jobs SIMDs hold two chains and three, and the slowest job is the one whose neighbours
-// are slow: 1000 jobs of up to 48 records with three starts 1.07 ms then, 0.76 now.  Every result has the same bits: on the flat
+// are slow: 1000 jobs of up to 48 records with three starts 1.1 to 1.18 ms then, 0.78 to 0.84 now.  Every result has the same bits: on the flat
 // stretches of this error other roundings end at other parameters.
 //
 // Eq. 10 is evaluated with the larger term factored out, as in the fitness kernels:
@@ -471,7 +471,7 @@ __device__ __forceinline__ bool damped_step(double *system, const SumLane &me, d
 constexpr int kMaxStarts = 5;
 
 // Dynamic LDS: kWaveDoubles doubles per wavefront.  HELD: no job has more than 64 records.
-// Three wavefronts a SIMD (168 registers): held to 128 it spills, 0.52 ms where it takes 0.39, 0.88 where it takes 0.76.
+// Three wavefronts a SIMD (168 registers): held to 128 it spills, 0.52 ms where it takes 0.39, 0.88 where it takes 0.81.
 template <bool HELD>
 __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_per_eu(3, 8))) fit_theta_kernel(FitArgs f)
 {
