@@ -426,19 +426,30 @@ __device__ __forceinline__ bool solve(const double *system, double (&x)[kTheta])
 struct SumLane {
     unsigned unknowns;
     int place;                           // in the system in LDS
+    unsigned long long row;              // of a diagonal entry: the lanes of all sums its unknown belongs to
     bool gradient, diagonal;
 };
+
+constexpr unsigned long long lanes_of_unknown(int i)
+{
+    unsigned long long lanes = 3ull << (2 * i);
+    for (int t = 8; t < kSums; ++t) {
+        if (kOrder.row[t] == i || kOrder.column[t] == i) lanes |= 3ull << (2 * t);
+    }
+    return lanes;
+}
 
 __device__ __forceinline__ SumLane sum_lane()
 {
     const int t = lane_id() >> 1;
-    SumLane me = {t < kTheta ? 3u << (2 * t) : 0u, t * kRowDoubles + kTheta, t < kTheta, false};     // (SUM r^2: behind the last row)
+    SumLane me = {t < kTheta ? 3u << (2 * t) : 0u, t * kRowDoubles + kTheta, 0ull, t < kTheta, false};     // (SUM r^2: behind the last row)
 #pragma unroll
     for (int k = 8; k < kSums; ++k) {
         if (t == k) {
             me.unknowns = unknown(kOrder.row[k]) | unknown(kOrder.column[k]);
             me.place = kOrder.row[k] * kRowDoubles + kOrder.column[k];
             me.diagonal = kOrder.row[k] == kOrder.column[k];
+            if (me.diagonal) me.row = lanes_of_unknown(kOrder.row[k]);
         }
     }
     return me;
@@ -447,13 +458,16 @@ __device__ __forceinline__ SumLane sum_lane()
 // Solves (A + lambda diag(A)) x = -g on the free variables (x = 0 for those in `held`); `sum`: what normal_equations returned.
 // The lanes of unknown i return x_i.  A variable that no record feels (its row, column and gradient are zero: the sync
 // parameters of a job that has never run on several GPUs of one node, or any pair on the flat spot T_sync = 0) gets a pivot of
-// one; its x is zero whatever the pivot, and lambda 1e-300 would be out of inverse_root's range.
+// one; its x is zero whatever the pivot, and lambda 1e-300 would be out of inverse_root's range.  A zero on the diagonal alone
+// does not say so: the squares of derivatives below 1e-162 are zero and their products with the others and with r are not (a pair
+// started at 1e-18 of T_grad, gamma = 10).
 // Returns false if a pivot is not positive.
 __device__ __forceinline__ bool damped_step(double *system, const SumLane &me, double sum, double lambda, unsigned held, double &step)
 {
     const double damped = sum + lambda * (sum > 1e-300 ? sum : 1e-300);
     double entry = me.gradient ? -sum : (me.diagonal ? damped : sum);
-    if ((held & me.unknowns) != 0u || (me.diagonal && sum == 0.0)) entry = me.diagonal ? 1.0 : 0.0;
+    const unsigned long long felt = __builtin_amdgcn_ballot_w64(sum != 0.0);
+    if ((held & me.unknowns) != 0u || (me.diagonal && (felt & me.row) == 0ull)) entry = me.diagonal ? 1.0 : 0.0;
     wave_fence();
     system[me.place] = entry;
     wave_fence();

@@ -97,3 +97,67 @@ def test_parameters_that_no_record_feels(n_starts, slots):
         n = int(ob["count"][j])
         error = TH.rmsle(theta[:, j], *(ob[k][j, :n] for k in ("K", "nodes", "m", "s", "T")))
         assert abs(got["rmsle"][j] - error) <= 1e-12 * error + 1e-13       # as above: differences of logarithms of size 1
+
+
+def cholesky_solve(A, b):
+    """x with A x = b, by the textbook's factorisation: no entry is compared with the others, so that a pivot of 1e-303 is one."""
+    n, w, y = len(b), A.copy(), b.copy()
+    L, inv, x = np.zeros((n, n)), np.zeros(n), np.zeros(n)
+    for k in range(n):
+        assert w[k, k] > 0.0
+        inv[k] = 1.0 / np.sqrt(w[k, k])
+        L[:, k] = w[:, k] * inv[k]
+        y[k] *= inv[k]
+        y[k + 1:] -= L[k + 1:, k] * y[k]
+        w[:, k + 1:] -= np.outer(L[:, k], L[k + 1:, k])
+    for i in range(n - 1, -1, -1):
+        x[i] = (y[i] - L[i + 1:, i] @ x[i + 1:]) * inv[i]
+    return x
+
+
+def test_a_parameter_whose_derivative_is_tiny_is_not_one_that_no_record_feels():
+    """The local pair at 1e-18 of what it should be and gamma = 10: the squares of the pair's derivatives underflow, their products
+    with the residuals do not.  The damped step, (A + lambda diag(max(A_ii, 1e-300))) x = -g, is then some 1e100 long in the pair; where
+    it leads up, twenty trials at lambda = 1e-3, 5e-3 .. are rejected, and the fit ends where it began.  (With a pivot of one for the
+    pair a step of the others is accepted among them.)"""
+    import paper_2008_12260_amd as px
+    rng = np.random.default_rng(31)
+    base = np.array([0.1, 0.001, 0.05, 0.01, 0.2, 0.02, 2.0])
+    J, n, steps = 12, 40, 20
+    names = ("K", "nodes", "m", "s", "T")
+    ob = dict(count=np.full(J, n, np.int32), **{k: np.zeros((J, n), np.int32) for k in names[:4]}, T=np.zeros((J, n)))
+    init, stays = np.zeros((7, J)), []
+    for j in range(J):
+        truth = base * np.exp(0.4 * rng.standard_normal(7))
+        truth[TH.GAMMA] = rng.uniform(1.2, 6.0)
+        K = rng.integers(1, 17, n)
+        K[:3] = 4
+        nodes = np.where(rng.uniform(size=n) < 0.7, -(-K // 4), np.minimum(K, rng.integers(1, 5, n)))
+        nodes[:3] = 1
+        m, s = rng.choice([8, 16, 32, 64, 128, 256], n), rng.integers(0, 4, n)
+        for k, v in zip(names, (K, nodes, m, s, TH.t_iter(truth, K, nodes, m, s)[0])):
+            ob[k][j] = v
+        init[:, j] = truth
+        init[[TH.ALPHA_SL, TH.BETA_SL], j] *= 1e-18
+        init[TH.GAMMA, j] = 10.0
+        records = [ob[k][j] for k in names]
+        r, jac = TH.residuals_and_jacobian(init[:, j], *records)
+        d = jac * np.where(np.arange(7) == TH.GAMMA, 1.0, init[:, j])         # with respect to the unknowns over their start
+        g, A = d.T @ r, d.T @ d
+        assert A[TH.ALPHA_SL, TH.ALPHA_SL] == 0.0 and g[TH.ALPHA_SL] < 0.0
+        free = np.arange(7) != TH.GAMMA if g[TH.GAMMA] < 0.0 else np.full(7, True)     # gamma is at its bound
+        up = True
+        for k in range(steps):
+            damped = A + 1e-3 * 5.0 ** k * np.diag(np.maximum(np.diag(A), 1e-300))
+            x = cholesky_solve(damped[np.ix_(free, free)], -g[free])
+            up = up and min(x[TH.ALPHA_SL], x[TH.BETA_SL]) > 1e80             # a time of 1e60 s or more: no better than the start's
+        if up:
+            stays.append(j)
+    assert len(stays) >= 10
+    for slots in (n, 65):                                                      # one record a lane, and the loop over more
+        wide = {k: (v if k == "count" else np.concatenate([v, np.ones((J, slots - n), v.dtype)], axis=1)) for k, v in ob.items()}
+        got = px.fit_theta(wide, theta_init=init, max_iter=steps, n_starts=1)
+        for j in stays:
+            error = TH.rmsle(init[:, j], *(ob[k][j] for k in names))
+            assert got["iterations"][j] == steps and np.array_equal(got["theta"][:, j], init[:, j])
+            assert abs(got["rmsle"][j] - error) <= 1e-12 * error
