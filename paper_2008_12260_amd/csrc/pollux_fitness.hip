@@ -1521,7 +1521,7 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
                 double last_at = last_pass(c, t, g0.tg, g0.lntg), tg_at = g0.tg;
                 int where, m_at = m0;
                 double h = best_count(g0, last_at, rK, a.Gs, true, argmin_count, where);
-                if (i >= a.Gm) h = __builtin_inf();
+                if (!(i < a.Gm && h < __builtin_inf())) h = __builtin_inf();      // (not a number where T_grad overflows: no point either)
                 if constexpr (two) {
                     const double last = last_pass(c, t, g1.tg, g1.lntg);
                     int s_c;

@@ -27,6 +27,30 @@ def test_memoised_rows_on_any_grid(Gm, J):
         assert np.array_equal(got[0][k], got[1][k], equal_nan=True), k
 
 
+def test_a_batch_size_whose_time_overflows_hides_no_other():
+    """T_grad overflows at the first 64 batch sizes and not at the next 64, which share an election with them: both ways of taking
+    the argmax find the same finite point."""
+    import torch
+    import paper_2008_12260_amd as px
+    J, Gm, Gs = 20, 128, 9
+    wl = W.make(W.custom("overflow", P=9, J=J, N=40, cap=4, Gm=Gm, Gs=Gs, index=2050))
+    c, params, grid = wl.cfg, wl.job_params.copy(), wl.m_grid.copy()
+    params[W.PARAM_INDEX["beta_grad"]] = 1e306
+    params[W.PARAM_INDEX["phi"]] = 0.5
+    params[W.PARAM_INDEX["M0"]], params[W.PARAM_INDEX["M_max"]] = 8.0, 2.0 ** 20
+    grid[:, :64], grid[:, 64:] = np.arange(200, 264), np.arange(8, 72)
+    got = []
+    for flags in (0, px.PX_FLAG_MEMOISE):
+        call = px.FitnessCall(c.P, J, c.N, Gm, Gs, params, grid, wl.fair_share, wl.current_alloc, wl.node_capacity, p=c.p,
+                              delta=c.delta, flags=flags)
+        call.run(torch.as_tensor(wl.population).cuda())
+        got.append(call.results())
+    held = wl.population.sum(2) > 0
+    assert np.all(got[0]["best_goodput"][held] > 0.0) and np.all(got[0]["best_m"][held] < 72)
+    for k in got[0]:
+        assert np.array_equal(got[0][k], got[1][k], equal_nan=True), k
+
+
 @pytest.mark.parametrize("N", [16, 61, 130])
 @pytest.mark.parametrize("Gm,Gs", [(64, 16), (50, 12), (128, 32)])
 @pytest.mark.parametrize("P", [61, 62, 125, 190, 249, 311])                    # of 200 jobs: one to six candidates a wavefront
