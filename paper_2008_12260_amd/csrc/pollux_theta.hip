@@ -341,34 +341,31 @@ __device__ __forceinline__ void eliminate(double (&w)[kTheta], double &b, double
 #undef PX_IN
 }
 
-// x_K of the triangular system that is left, from x_{K+1} ..: the right-hand side's share less the column's entries times those.
-template <int K>
-__device__ __forceinline__ void substitute(double (&x)[kTheta], double column, double share, double inv)
+// Back substitution: x_K is the right-hand side's share less the column's entries times x_{K+1} .., by the pivot's root.
+// One block: the shares and columns it reads across lanes are written before it, by whatever instruction the compiler has put
+// last (a copy, a reload), so it begins with the two wait states such a read needs; within it only x changes.
+__device__ __forceinline__ void substitute(double (&x)[kTheta], const double (&column)[kTheta], const double (&share)[kTheta],
+                                           const double (&inv)[kTheta])
 {
-#define PX_BEGIN(N) "v_mov_b64_dpp %0, %1" PX_OF_UNKNOWN(N)
-#define PX_IN "v"(share), "v"(column)
-    double s;
-    // (between the last write of a column or a share and here lie at least the two instructions the reads across lanes need)
-    if constexpr (K == 6) asm("s_nop 1\n\t" PX_BEGIN(12) : "=v"(s) : "v"(share));
-    else if constexpr (K == 5) asm(PX_BEGIN(10) PX_LESS("%0", "%2", 12, "%3") : "=&v"(s) : PX_IN, "v"(x[6]));
-    else if constexpr (K == 4) asm(PX_BEGIN(8) PX_LESS("%0", "%2", 10, "%3") PX_LESS("%0", "%2", 12, "%4") : "=&v"(s) : PX_IN, "v"(x[5]), "v"(x[6]));
-    else if constexpr (K == 3)
-        asm(PX_BEGIN(6) PX_LESS("%0", "%2", 8, "%3") PX_LESS("%0", "%2", 10, "%4") PX_LESS("%0", "%2", 12, "%5")
-            : "=&v"(s) : PX_IN, "v"(x[4]), "v"(x[5]), "v"(x[6]));
-    else if constexpr (K == 2)
-        asm(PX_BEGIN(4) PX_LESS("%0", "%2", 6, "%3") PX_LESS("%0", "%2", 8, "%4") PX_LESS("%0", "%2", 10, "%5") PX_LESS("%0", "%2", 12, "%6")
-            : "=&v"(s) : PX_IN, "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]));
-    else if constexpr (K == 1)
-        asm(PX_BEGIN(2) PX_LESS("%0", "%2", 4, "%3") PX_LESS("%0", "%2", 6, "%4") PX_LESS("%0", "%2", 8, "%5") PX_LESS("%0", "%2", 10, "%6")
-            PX_LESS("%0", "%2", 12, "%7")
-            : "=&v"(s) : PX_IN, "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]));
-    else
-        asm(PX_BEGIN(0) PX_LESS("%0", "%2", 2, "%3") PX_LESS("%0", "%2", 4, "%4") PX_LESS("%0", "%2", 6, "%5") PX_LESS("%0", "%2", 8, "%6")
-            PX_LESS("%0", "%2", 10, "%7") PX_LESS("%0", "%2", 12, "%8")
-            : "=&v"(s) : PX_IN, "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]));
-    x[K] = s * inv;
-#undef PX_BEGIN
-#undef PX_IN
+#define PX_FIRST(K, N) "v_mov_b64_dpp %[x" #K "], %[s" #K "]" PX_OF_UNKNOWN(N)
+#define PX_TAKE(K, T, N) PX_LESS("%[x" #K "]", "%[c" #K "]", N, "%[x" #T "]")
+#define PX_LAST(K) "v_mul_f64 %[x" #K "], %[x" #K "], %[i" #K "]\n\t"
+    asm("s_nop 1\n\t"
+        PX_FIRST(6, 12) PX_LAST(6)
+        PX_FIRST(5, 10) PX_TAKE(5, 6, 12) PX_LAST(5)
+        PX_FIRST(4, 8) PX_TAKE(4, 5, 10) PX_TAKE(4, 6, 12) PX_LAST(4)
+        PX_FIRST(3, 6) PX_TAKE(3, 4, 8) PX_TAKE(3, 5, 10) PX_TAKE(3, 6, 12) PX_LAST(3)
+        PX_FIRST(2, 4) PX_TAKE(2, 3, 6) PX_TAKE(2, 4, 8) PX_TAKE(2, 5, 10) PX_TAKE(2, 6, 12) PX_LAST(2)
+        PX_FIRST(1, 2) PX_TAKE(1, 2, 4) PX_TAKE(1, 3, 6) PX_TAKE(1, 4, 8) PX_TAKE(1, 5, 10) PX_TAKE(1, 6, 12) PX_LAST(1)
+        PX_FIRST(0, 0) PX_TAKE(0, 1, 2) PX_TAKE(0, 2, 4) PX_TAKE(0, 3, 6) PX_TAKE(0, 4, 8) PX_TAKE(0, 5, 10) PX_TAKE(0, 6, 12) PX_LAST(0)
+        : [x0] "=&v"(x[0]), [x1] "=&v"(x[1]), [x2] "=&v"(x[2]), [x3] "=&v"(x[3]), [x4] "=&v"(x[4]), [x5] "=&v"(x[5]), [x6] "=&v"(x[6])
+        : [s0] "v"(share[0]), [s1] "v"(share[1]), [s2] "v"(share[2]), [s3] "v"(share[3]), [s4] "v"(share[4]), [s5] "v"(share[5]),
+          [s6] "v"(share[6]), [c0] "v"(column[0]), [c1] "v"(column[1]), [c2] "v"(column[2]), [c3] "v"(column[3]), [c4] "v"(column[4]),
+          [c5] "v"(column[5]), [i0] "v"(inv[0]), [i1] "v"(inv[1]), [i2] "v"(inv[2]), [i3] "v"(inv[3]), [i4] "v"(inv[4]),
+          [i5] "v"(inv[5]), [i6] "v"(inv[6]));
+#undef PX_FIRST
+#undef PX_TAKE
+#undef PX_LAST
 }
 
 // Solves the 7 x 7 system in LDS by Cholesky factorisation: unknown i's lanes hold row i (all four rows of 16 lanes do the
@@ -410,13 +407,7 @@ __device__ __forceinline__ bool solve(const double *system, double (&x)[kTheta])
     column_of(std::integral_constant<int, 6>());
     if (!PLAIN) good = off <= (1800u << 20);
     if (__builtin_amdgcn_readfirstlane((int)good) == 0) return false;
-    substitute<6>(x, 0.0, share[6], inv[6]);
-    substitute<5>(x, column[5], share[5], inv[5]);
-    substitute<4>(x, column[4], share[4], inv[4]);
-    substitute<3>(x, column[3], share[3], inv[3]);
-    substitute<2>(x, column[2], share[2], inv[2]);
-    substitute<1>(x, column[1], share[1], inv[1]);
-    substitute<0>(x, column[0], share[0], inv[0]);
+    substitute(x, column, share, inv);
     return true;
 }
 #undef PX_LESS
