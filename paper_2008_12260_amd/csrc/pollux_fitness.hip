@@ -851,15 +851,22 @@ __device__ __forceinline__ JobTables job_tables(const FitnessArgs &a, int j)
 // arithmetic; the point is then priced with Eq. 4 in the paper's order of operations
 // (T_grad, its logarithm and the last pass of Eq. 10 are formed here, m is not on a grid).
 // Gm evaluations per call instead of Gm * Gs.  Ties go to the lowest i.
+// LEAN: for pairs_kernel where rows are looked up, in which a row beyond the tables is the exception and spills because of it are not.
+template <bool LEAN>
 __device__ __forceinline__ Best sweep_sampled(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y, double m_mem,
                                               const int32_t *__restrict__ M_list, int Gm, int Gs, int K, int nodes)
 {
     if (K <= 0 || !(m_mem >= 1.0 && m_mem <= 2147483647.0)) return Best{0.0, -1, -1};
     const int lane = lane_id();
-    // The integer arithmetic is done in doubles.  The numerators stay below 2^38 wherever the quotient is not one, so that a
-    // quotient below an integer is further from it than a rounded one can be off: its floor is exact.
+    // The quotients are found in doubles: the numerators stay below 2^38 wherever the quotient is not one, so that a quotient below
+    // an integer is further from it than a rounded one can be off, and its floor is exact.  (200 jobs' rows 0.5 us quicker than with
+    // 64-bit integers, which hold ten registers less: LEAN.)
     const double Kd = (double)K;
     const double per_pass = Kd * floor(m_mem);                      // examples one pass over K GPUs can hold
+    auto quotient_up = [](double n, double d) {
+        if constexpr (LEAN) return (double)(((long long)n + ((long long)d - 1)) / (long long)d);
+        else return floor(px_div(n + (d - 1.0), d));
+    };
     const SyncTerm st = sync_term(c, y, K, nodes == 1);
 
     double gbest = 0.0;
@@ -869,10 +876,10 @@ __device__ __forceinline__ Best sweep_sampled(const Coefs &c, const Job &q, cons
         if (i >= Gm) continue;
         const double M = (double)M_list[i];
         if (M <= 0.0) continue;
-        const double passes = floor(px_div(M + (per_pass - 1.0), per_pass));     // s + 1
+        const double passes = quotient_up(M, per_pass);                // s + 1
         if (passes > (double)Gs) continue;
         const double ks = Kd * passes;
-        const double m = floor(px_div(M + (ks - 1.0), ks));            // 1 <= m <= m_mem
+        const double m = quotient_up(M, ks);                           // 1 <= m <= m_mem
         const double Km = Kd * m;
         const double Mrun = Km * passes;
         if (Mrun < gp.M0 || Mrun > gp.Mmax) continue;
@@ -885,10 +892,11 @@ __device__ __forceinline__ Best sweep_sampled(const Coefs &c, const Job &q, cons
     return wave_argmax(gbest, ibest, m_best, s_best);
 }
 
+template <bool LEAN>
 __device__ __forceinline__ Best sweep_sampled(const Job &q, const int32_t *__restrict__ M_list, int Gm, int Gs, int K, int nodes)
 {
-    return sweep_sampled(plain_coefs(), q, load_grid_params(q.jp, q.J, q.j), load_sync(q), q.jp[(size_t)PX_M_MEM * q.J + q.j], M_list, Gm, Gs,
-                         K, nodes);
+    return sweep_sampled<LEAN>(plain_coefs(), q, load_grid_params(q.jp, q.J, q.j), load_sync(q), q.jp[(size_t)PX_M_MEM * q.J + q.j], M_list, Gm,
+                               Gs, K, nodes);
 }
 
 // ---- fp32 variant of the sweep --------------------------------------------------
@@ -1288,8 +1296,8 @@ __constant__ float small_recips_f32[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), P
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
 // CH > 0: each batch size's count is found by the scan over all of them (Gs <= kSmallGs), as in the population pass; the same
 // count either way.
-// The elected point is priced from the terms its lane has formed.
-template <int CH = 0>
+// The elected point is priced from the terms its lane has formed; LEAN: from terms formed anew, which holds five registers less.
+template <int CH = 0, bool LEAN = false>
 __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y,
                                          const int32_t *__restrict__ m_row, int Gm, int Gs, int K, bool one_node, bool tabled)
 {
@@ -1312,22 +1320,30 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
         if (h < kbest) {
             kbest = h;
             where = s_c | ((i / kWave) << 16);
-            tg_at = g.tg;
-            last_at = last;
-            m_at = m;
+            if constexpr (!LEAN) {
+                tg_at = g.tg;
+                last_at = last;
+                m_at = m;
+            }
         }
     }
     const Pick pick = elect(kbest, where, 0ull, Gs);
     if (pick.i < 0) return Best{0.0, -1, -1};
+    if constexpr (LEAN) {
+        const int m = m_row[pick.i];
+        const double tg = gp.alpha_g + gp.beta_g * (double)m;
+        return Best{goodput_point(q, (double)K * (double)m, tg, last_pass(c, st, tg, px_log(c, tg)), pick.s), m, pick.s};
+    }
     const int l = pick.i & (kWave - 1);
     const int m = __builtin_amdgcn_readlane(m_at, l);
     return Best{goodput_point(q, (double)K * (double)m, wave_read(tg_at, l), wave_read(last_at, l), pick.s), m, pick.s};
 }
 
-__device__ __forceinline__ Best row_best(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs, int K,
-                                         bool one_node, bool tabled)
+template <bool LEAN>
+__device__ __forceinline__ Best row_best_plain(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs, int K,
+                                               bool one_node, bool tabled)
 {
-    return row_best(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
+    return row_best<0, LEAN>(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
 }
 
 // The same in single precision, for a GPU count within the tables and grids of at most kSmallGs counts: term by term what
@@ -1457,7 +1473,7 @@ __device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a
     const int K = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j]);
     const bool one_node = __builtin_amdgcn_readfirstlane(a.fair_share[2 * j + 1]) == 1;
     Best fair = {0.0, -1, -1};
-    if constexpr (kSampled) fair = sweep_sampled(c, q, gp, y, jp[(size_t)PX_M_MEM * a.J + j], m_row, a.Gm, a.Gs, K, one_node ? 1 : 2);
+    if constexpr (kSampled) fair = sweep_sampled<false>(c, q, gp, y, jp[(size_t)PX_M_MEM * a.J + j], m_row, a.Gm, a.Gs, K, one_node ? 1 : 2);
     else if constexpr (MODE == kPrepTablesF32) {
         auto terms = [&](int, int m) {
             const GridPoint g = grid_point(c, gp, m);
@@ -1492,7 +1508,7 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
         const double m_mem = a.job_params[(size_t)PX_M_MEM * a.J + j];
 #pragma unroll 1
         for (int r = 0; r < ROWS; ++r) {
-            const Best best = sweep_sampled(c, q, gp, y, m_mem, m_row, a.Gm, a.Gs, K0 + r, one_node ? 1 : 2);
+            const Best best = sweep_sampled<false>(c, q, gp, y, m_mem, m_row, a.Gm, a.Gs, K0 + r, one_node ? 1 : 2);
             if (lane == 0) a.memo[row0 + r] = MemoEntry{best.goodput, best.m, best.s};
         }
         return;
@@ -1712,10 +1728,14 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 enum { kRowAtATime, kFourRowsLoaded, kFourRowsSwept };      // ROW4
 constexpr bool rows_at_a_time(int ROW4) { return ROW4 == kFourRowsSwept; }
 
+// Wavefronts a SIMD.  The sampling argmax of a pair (CH = 0) spills 36 bytes a lane where eight leave it 64 registers: 74 candidates of
+// 433 jobs on 79 nodes 46.0 us, seven 40.3, six 40.4; 100 of 1000 on 250 nodes, where the rows' reading counts, 146, 118 and 124.
+constexpr int pair_waves(int CH, bool MEMO, int ROW4) { return rows_at_a_time(ROW4) ? 6 : (CH == 0 && !MEMO ? 7 : 8); }
+
 // SEL = 2: per job, the candidates listed in a.dirty[j, 0 .. a.dirty_count[j]) (row inheritance: the rows of job j that a
 // move or a repair of the search step has changed); workgroups beyond a job's list return at once.
 template <int CH, bool F32, bool MEMO, bool ROW1, bool WHOLE, int ROW4, bool RAG, int SEL>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(rows_at_a_time(ROW4) ? 6 : 8)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves(CH, MEMO, ROW4))))
 pairs_kernel(FitnessArgs a)
 {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -2207,7 +2227,7 @@ pairs_kernel(FitnessArgs a)
                 const MemoEntry e = a.memo[((size_t)j * 2 + (nodes == 1 ? 1 : 0)) * kTableK + (K - 1)];
                 best.goodput = e.goodput; best.m = e.m; best.s = e.s;
             } else {
-                best = sweep_sampled(q, tb.m, a.Gm, a.Gs, K, nodes);
+                best = sweep_sampled<MEMO>(q, tb.m, a.Gm, a.Gs, K, nodes);
             }
             if (lane == 0) {
                 const size_t pair = (size_t)c * a.J + j;
@@ -2246,7 +2266,7 @@ pairs_kernel(FitnessArgs a)
             if constexpr (F32) {
                 found = sweep_f32(qf, tbb, b.rk, b.Gm, b.Gs, K, nodes);
             } else if constexpr (MEMO) {
-                found = row_best(qb, load_grid_params(b.job_params, b.J, j), tbb.m, b.Gm, b.Gs, K, nodes == 1, false);
+                found = row_best_plain<true>(qb, load_grid_params(b.job_params, b.J, j), tbb.m, b.Gm, b.Gs, K, nodes == 1, false);
             } else {
                 const Pick pick = sweep_pick<CH, false>(qb, tbb, X, b.rs, b.rk, b.Gm, b.Gs, K, nodes);
                 found = price_point(qb, tbb, b.Gm, K, nodes == 1, pick.i, pick.s);
@@ -2785,8 +2805,8 @@ __device__ __forceinline__ void finish_pairs(const FitnessArgs &a, int c, int jc
             const int j = jc + at0 + l;
             Best found;
             if constexpr (KIND == kMemoF32) found = sweep_f32(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rk, a.Gm, a.Gs, K, nodes);
-            else if constexpr (KIND == kMemoSampled) found = sweep_sampled(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
-            else found = row_best(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
+            else if constexpr (KIND == kMemoSampled) found = sweep_sampled<false>(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
+            else found = row_best_plain<false>(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
                                   a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
             if (lane == l) best = found;
         }
