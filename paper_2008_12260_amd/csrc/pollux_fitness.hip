@@ -3108,8 +3108,12 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
 // copy, and 18 bytes of LDS a job hold a thousand jobs.
 constexpr int kFinishJobs = 1024;
 
+// Three workgroups a compute unit: at 89 registers, which only the sweep of rows beyond the memo table needs, there were two, and
+// 600 children took two rounds on 256 compute units (20 generations, 8 to 256 jobs: 1.06 to 1.12 times the three launches before, now
+// 0.83 to 0.91; 800 children 1.05, now 0.94 to 0.96; 500 and fewer as before).  At 64 registers and four workgroups 50 to 600 children
+// take 2 to 6 % longer, 800 and more 10 % less.
 template <int KIND, int ROWS>
-__global__ void __launch_bounds__(kGaThreads) child_kernel(GaArgs g, FitnessArgs a)
+__global__ void __launch_bounds__(kGaThreads) __attribute__((amdgpu_waves_per_eu(6))) child_kernel(GaArgs g, FitnessArgs a)
 {
     using Real = typename std::conditional<KIND == kMemoF32, float, double>::type;
     extern __shared__ __align__(16) unsigned char ga_lds[];

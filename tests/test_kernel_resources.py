@@ -49,3 +49,11 @@ def test_rows_priced_in_place_spill_little(kernels, which, instances, spilled):
     assert len(names) == instances
     for n in names:
         assert kernels[n]["private_segment_fixed_size"] <= spilled, n
+
+
+def test_a_compute_unit_holds_three_children(kernels):
+    names = [n for n in kernels if "child_kernel" in n]
+    assert len(names) == 6
+    for n in names:
+        # eight wavefronts a workgroup, two on each of four SIMDs of 512 registers, given out in eights
+        assert 512 // (-(-kernels[n]["vgpr_count"] // 8) * 8) >= 6, n
