@@ -3419,7 +3419,8 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const bool near = a.gs_pad <= kNearRecips;      // the kernels keep reciprocals and thresholds of all counts in LDS
     // four rows per load of a wavefront (cand_per_wave <= 16 holds); its sweeps pack a batch size's index into 15 bits
     const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF && near && !(d->flags & PX_FLAG_SAMPLE_M);
-    const PairSplit split = split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit);
+    const PairSplit split = split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit, row1,
+                                        (d->flags & PX_FLAG_SAMPLE_M) != 0);
     a.cand_per_wave = split.per_wave;
     a.stage_rows = d->Gm <= kStageGm && near && split.per_wave >= stage_candidates(a.sel != nullptr) ? 1 : 0;
     a.cand_groups = pair_groups(P_eff, split.per_wave);

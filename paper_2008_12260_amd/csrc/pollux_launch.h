@@ -37,49 +37,49 @@ inline unsigned prep_blocks(int jobs, int tasks, long long counters)
 
 constexpr int kMaxCandPerWave = 16;   // candidates one wavefront of pairs_kernel walks at most (lane r keeps what candidate r needs)
 
-// How many candidates a wavefront of pairs_kernel takes: enough wavefronts to fill the chip several times over.  Calls of 200 jobs, us
-// with 25000, 16600 and 12400 wavefronts:
-//   64 nodes, 64 x 16    125 candidates 45.6, 45.6, 34.1; 250 46.8, 38.7, 35.1; 500 47.6, 50.1 (six each), 44.9; 750 63.0, 61.6, 55.1;
-//                        1000 65.4, 64.3, 65.2; 1250 85.6 (ten), 79.0 (fifteen), 76.8: swept in fours, so in whole fours
-//   100 nodes, 64 x 16   125 39.3, 39.3, 33.8; 500 58.0, 54.7, 54.0; 1000 83.8, 83.1, 83.7; 1500 111.2, 109.4, 109.4
-//   100 nodes, 128 x 32  125 51.1, 51.2, 46.5; 500 87.5, 84.1, 84.9; 1000 131.3, 133.2, 136.9; 1500 178.2, 181.0, 180.6
-// And, for rows of at most 64 nodes whose count tables are on chip (row4), whether one load covers the rows of four candidates, which with chunks of up
-// to 16 counts also sweeps the four, a row of 16 lanes each.
-// A sweep of four saves three elections and lasts as long with one candidate as with four: it wants candidates in whole fours,
-// enough pairs to fill the chip with so few wavefronts, and narrow grids (chunk: batch sizes x chunks of 16 counts).
-// fp64 on whole rows and grids takes four always.  Calls that keep their tables, at 1.3 to 10 GPUs a job, us one at a time and
-// four at a time:
-//   17 nodes, 50 x 16, fp64    66 candidates of 30 jobs 9.1, 9.7; 166 of 30 11.5, 10.1; 300 of 100 30.9, 16.8
-//   16 nodes, 64 x 16, fp32    66 of 30 9.2, 10.0; 166 of 30 11.2, 10.5; 300 of 100 26.5, 16.4; 1300 of 100 48.0, 43.1
-// over the 16 to 64 nodes and 6 grids tried: 2000 pairs 1.04 to 1.19 times as long in fours, 5000 0.93 to 1.03, 10000 0.79 to 0.91,
-// from there on 0.65 to 0.98.  Grids of 300 take 1.4 times as long at 2000 pairs and 0.9 from 12000 on, but more again where most
-// rows are empty and fours cannot be filled (1000 candidates of 200 jobs on 128 GPUs, 500 x 12: 228 and 175): wide grids go one at a time.
-// With row inheritance a job's list is shorter than the candidates, of no length known here: its split is not rounded to fours (128
-// children of 1000 jobs, 64 x 8: 60.5 us, 67.3 in fours), and four at a time pay from 80000 pairs on (1000 children of 200 jobs on
-// 61 nodes, 64 x 16: 60.1 and 65.6; 100 children of 200 jobs 1.03 times as long), in fp32 on whole rows not at all (1.02 to 1.06).
-// entry_by_entry: ragged rows with fewer than four candidates a wavefront, none of them a generation's child (see launch_fitness).
+// How many candidates a wavefront of pairs_kernel takes, and how it reads and sweeps them.
 struct PairSplit {
     int per_wave;
-    bool four, entry_by_entry;
+    bool four;              // (rows of at most 64 nodes) one load covers the rows of four candidates, and with chunks of up to 16
+                            // counts one sweep does: a row of 16 lanes each
+    bool entry_by_entry;    // ragged rows, fewer than four candidates a wavefront, none of them a generation's child
 };
 
-inline PairSplit split_pairs(int candidates, int jobs, int Gm, int Gs, bool f32, bool row4, bool whole_rows, bool inherit)
+// row1: rows of 4 to 256 nodes.  row4: of at most 64, with count tables that fit on chip.  sampled: the sampling argmax.
+//
+// per_wave: 25000 wavefronts fill the chip several times over.  Fewer with more candidates each save what a wavefront does once (job
+// terms, table in LDS, prices), until the last wavefronts to end cost more: down to 12400 wavefronts with as many candidates as that
+// takes on short rows and narrow grids, up to six on others, up to four on rows of more than 256 nodes, which are read one after the
+// other.  (The sampling argmax of a pair has no such start to save: 40 candidates of 1000 jobs on 250 nodes, 128 sizes, 74 us, 83 with
+// three a wavefront.)  us with 25000 wavefronts and so:
+//   64 nodes, 64 x 16      200 jobs: 125 candidates 45.6, 34.1; 500 47.6, 44.9; 1250 85.6, 76.8
+//   64 nodes, 128 x 32     100 jobs, fp32: 250 candidates 42.9, 39.0
+//   100 nodes, 64 x 16     1000 jobs: 62 candidates, fp32, 73.2, 70.4; 200 candidates 97.7, 98.0 (sixteen each: 105.0)
+//   320 nodes, 32 x 16     fp32: 100 candidates of 331 jobs 54.7, 52.3; 150 of 1000 jobs 153.9, 153.9 (twelve each: 168.4)
+// four: a sweep of four saves three elections and lasts as long with one candidate as with four.  fp64 on whole rows and grids, and
+// with more than 16 counts (loads only), always.  Else from 8000 pairs on and on narrow grids (at 2000 pairs 1.04 to 1.19 times as
+// long in fours, at 5000 0.93 to 1.03, at 10000 0.79 to 0.91; grids of 300 batch sizes 1.4 times at 2000 and, with most rows empty,
+// still 1.3 at 200000), and in whole fours.  With row inheritance a job's list has no length known here: no rounding, and fours from
+// 80000 pairs on (1000 children of 200 jobs on 61 nodes, 64 x 16: 60.1 and 65.6 us one at a time), in fp32 on whole rows not at all.
+inline PairSplit split_pairs(int candidates, int jobs, int Gm, int Gs, bool f32, bool row4, bool whole_rows, bool inherit, bool row1 = true,
+                             bool sampled = false)
 {
     const long long pairs = (long long)candidates * jobs;
     const int share = (candidates - 1) / kWavesPerBlock + 1;                    // a workgroup's wavefronts take the candidates in turn
-    const int chunk = Gm * ((Gs + 15) / 16);
-    // What a wavefront does once (job terms, table in LDS, prices) is worth the sweeps of two candidates of 64 x 16: as many as 12400
-    // wavefronts leave each.  Wider grids weigh it less, and the last wavefronts last longer: up to six that way.
-    const long long by_25000 = pairs / 25000, by_12400 = pairs / 12400;
-    long long want = by_25000;
-    if (!inherit) want = chunk <= 64 ? by_12400 : (by_25000 > 6 ? by_25000 : (by_12400 < 6 ? by_12400 : 6));
+    const int chunk = Gm * ((Gs + 15) / 16);                                    // the grid's width: batch sizes x chunks of 16 counts
+    long long want = pairs / 25000;
+    if (!inherit && !sampled) {
+        const long long most = row4 && chunk <= 64 ? kMaxCandPerWave : (row1 ? 6 : 4), more = pairs / 12400;
+        const long long wider = more < most ? more : most;
+        want = want > wider ? want : wider;
+    }
     int n = (int)(want < kMaxCandPerWave ? want : kMaxCandPerWave);
     n = n < share ? n : share;
     n = n > 1 ? n : 1;
     if (!row4) return PairSplit{n, false, false};
     if (!f32 && (whole_rows || Gs > 16)) return PairSplit{Gs > 16 || n < 4 || inherit ? n : n & ~3, true, false};
     const bool four = inherit ? chunk <= 64 && pairs >= 80000 && !whole_rows : chunk <= 128 && pairs >= 8000 && share >= 4;
-    if (four && !inherit) n = n < 4 ? 4 : n & ~3;
+    if (four && !inherit) n = n < 4 ? 4 : (n + 2) & ~3;
     return PairSplit{n, four, !four && n < 4};
 }
 

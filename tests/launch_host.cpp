@@ -29,6 +29,12 @@ int px_host_split(int candidates, int jobs, int Gm, int Gs, int f32, int row4, i
     const px::PairSplit p = px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row4 != 0, whole_rows != 0, inherit != 0);
     return (p.per_wave - 1) | (p.four ? 16 : 0) | (p.entry_by_entry ? 32 : 0);
 }
+// The same for any row length (nodes).
+int px_host_split_nodes(int candidates, int jobs, int nodes, int Gm, int Gs, int f32)
+{
+    const bool row1 = nodes >= 4 && nodes <= 256, whole = nodes % 4 == 0 && Gm % 64 == 0;
+    return px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row1 && nodes <= 64, whole, false, row1).per_wave;
+}
 int px_host_pair_groups(int candidates, int per_wave) { return px::pair_groups(candidates, per_wave); }
 int px_host_record_or_first(int found, int records) { return px::record_or_first(found, records); }
 }

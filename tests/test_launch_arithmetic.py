@@ -56,6 +56,20 @@ def test_the_population_pass_takes_every_candidate(launch, f32, inherit):
                         assert not four and n < 4
 
 
+@pytest.mark.parametrize("candidates,jobs,nodes,Gm,Gs,per_wave", [
+    # 64 nodes, narrow: as many as 12400 wavefronts leave each, in whole fours where they are swept in fours
+    (61, 200, 64, 64, 16, 1), (124, 200, 64, 64, 16, 2), (125, 200, 64, 64, 16, 2), (249, 200, 64, 64, 16, 4), (434, 200, 64, 64, 16, 4),
+    (496, 200, 64, 64, 16, 8), (1000, 200, 64, 64, 16, 16), (2000, 200, 64, 64, 16, 16),
+    # wide: six, until 25000 wavefronts leave more
+    (372, 200, 64, 128, 32, 6), (371, 200, 64, 128, 32, 5), (874, 200, 64, 128, 32, 6), (875, 200, 64, 128, 32, 7), (1000, 200, 64, 128, 32, 8),
+    # rows of 65 to 256 nodes: the same at any width
+    (373, 200, 65, 64, 16, 6), (500, 200, 130, 64, 16, 6), (200, 1000, 256, 64, 16, 8), (150, 1000, 192, 32, 8, 6), (500, 200, 130, 128, 32, 6),
+    # longer, and below four nodes: four
+    (249, 200, 257, 64, 16, 4), (500, 200, 257, 64, 16, 4), (500, 200, 3, 64, 16, 4), (625, 200, 500, 128, 32, 5), (150, 1000, 320, 32, 16, 6)])
+def test_candidates_a_wavefront(launch, candidates, jobs, nodes, Gm, Gs, per_wave):
+    assert launch.px_host_split_nodes(candidates, jobs, nodes, Gm, Gs, 0) == per_wave
+
+
 def test_a_fit_starts_from_a_record_its_job_has(launch):
     for records in (1, 2, 64, 65, 1000):
         for found in (0, 1, records - 1, records, 1 << 20, 0x7FFFFFFF):        # the last: no record had a time below infinity
