@@ -3222,14 +3222,10 @@ static FitnessArgs job_level_args(const pollux_dims *d, const double *job_params
     return a;
 }
 
-// Rows (placement class, K) one wavefront of prepare_kernel takes.  The terms of its batch sizes are formed once for all of them
-// (as much work as three rows), but the kernel lasts as long as the SIMD with the most wavefronts on it.  Calls of 40 candidates, 64 x 16,
-// us with two, four and eight rows a wavefront:
-//   tables    20 jobs 17.4, 17.2, 17.5; 30 jobs 18.2, 17.6, 16.7 to 18; 50 jobs 19.4, 18.4, 16.5 to 18; 90 jobs 22.7, 21.3, 20.3 to 21.2;
-//             with sixteen rows 200 jobs (1000 candidates) take 68.3 against 66.7
-//   memoised  whose rows end in an election: 140 jobs 16.5, 17.8, 18.7; 200 jobs 19.9, 19.9, 20.3; 300 jobs 34.5, 33.4, 33.4; 900 jobs
-//             81.5, 74.5, 74.5; with 128 batch sizes 140 jobs 22.1, 25.6, 27.9; 500 jobs 63.4, 61.2, 64.2; 900 jobs 107.7, 100.8, 103.3
-//             (an election for both groups of 64 batch sizes since: 500 jobs 57.1, 900 jobs 95.2)
+// Rows (placement class, K) one wavefront of prepare_kernel takes: of the tables table_rows.  Memoised, whose rows end in an election,
+// two, from 256 jobs on four.  Calls of 40 candidates, 64 x 16, us with two, four and eight rows: 140 jobs 16.5, 17.8, 18.7; 200 jobs
+// 19.9, 19.9, 20.3; 300 jobs 34.5, 33.4, 33.4; 900 jobs 81.5, 74.5, 74.5; with 128 batch sizes 140 jobs 22.1, 25.6, 27.9; 500 jobs 63.4,
+// 61.2, 64.2; 900 jobs 107.7, 100.8, 103.3 (an election for both groups of 64 batch sizes since: 500 jobs 57.1, 900 jobs 95.2).
 // The sampling argmax has no such terms: one row, or two where the jobs are many (200 jobs 30.8 and 29.5 us a call).
 template <int MODE>
 static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
@@ -3241,9 +3237,10 @@ static void launch_prepare_rows(const FitnessArgs &a, hipStream_t stream)
         if (a.J < 128) hipLaunchKernelGGL((prepare_kernel<1, MODE>), blocks(1), dim3(256), 0, stream, a);
         else hipLaunchKernelGGL((prepare_kernel<2, MODE>), blocks(2), dim3(256), 0, stream, a);
     } else {
-        constexpr int kFew = MODE == kPrepMemo ? 2 : 4, kMany = MODE == kPrepMemo ? 4 : 8, kManyJobs = MODE == kPrepMemo ? 256 : 32;
-        if (a.J < kManyJobs) hipLaunchKernelGGL((prepare_kernel<kFew, MODE>), blocks(kFew), dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((prepare_kernel<kMany, MODE>), blocks(kMany), dim3(256), 0, stream, a);
+        const int rows = MODE == kPrepMemo ? (a.J < 256 ? 2 : 4) : table_rows(a.J, a.Gm);
+        if (rows == 2) hipLaunchKernelGGL((prepare_kernel<2, MODE>), blocks(2), dim3(256), 0, stream, a);
+        else if (rows == 4) hipLaunchKernelGGL((prepare_kernel<4, MODE>), blocks(4), dim3(256), 0, stream, a);
+        else if constexpr (MODE != kPrepMemo) hipLaunchKernelGGL((prepare_kernel<8, MODE>), blocks(8), dim3(256), 0, stream, a);
     }
 }
 

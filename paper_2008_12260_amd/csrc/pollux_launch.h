@@ -35,6 +35,23 @@ inline unsigned prep_blocks(int jobs, int tasks, long long counters)
     return (unsigned)(needed > clearing ? needed : clearing);
 }
 
+// Rows (placement class, K) of the sweep's tables one wavefront of prepare_kernel makes: eight from 128 jobs on, below that as many
+// as keep its chain, rows x groups of 64 batch sizes, short while SIMDs are idle: two, four, or eight where those fill whole rounds.
+// The terms of a group of batch sizes, formed once for all rows, are as much work as three.  Calls of 40 candidates, us with two, four
+// and eight rows:
+//    12 jobs   100 x 8 15.6, 15.7, 17.7; 257 x 8 20.4, 22.2, 28.8
+//    24 jobs   64 x 8 15.2, 14.8, 15.0; 128 x 8 18.2, 17.2, 19.3; 384 x 32 fp32 29.4, 28.2, 36.9
+//    48 jobs   64 x 8 16.7, 16.1, 15.4; 128 x 8 20.5, 19.6, 20.2; 448 x 8 45.0, 45.5, 48.1
+//    96 jobs   64 x 8 20.8, 19.0, 18.8; 128 x 8 27.6, 24.7, 26.1
+//   110 jobs   128 x 16 26.7, 26.3, 24.9 (two workgroups of eight rows a job and XCD, up to 120); 384 x 32 48.4, 49.8, 48.7
+//   127 jobs   64 x 32 21.3, 20.9, 21.1; 128 x 32 27.6, 27.4, 29.1; 320 x 16 fp32 42.0, 44.5, 51.0
+//   200 jobs   64 x 16 (1000 candidates) 66.7 with eight, 68.3 with sixteen; 1000 jobs, 32 x 8, 102.6, 87.6, 81.8
+inline int table_rows(int jobs, int Gm)
+{
+    if (jobs >= 128 || (Gm <= 64 && jobs > 32) || (Gm <= 256 && jobs > 96 && jobs <= 120)) return 8;
+    return jobs <= 16 || Gm > 256 ? 2 : 4;
+}
+
 constexpr int kMaxCandPerWave = 16;   // candidates one wavefront of pairs_kernel walks at most (lane r keeps what candidate r needs)
 
 // How many candidates a wavefront of pairs_kernel takes, and how it reads and sweeps them.

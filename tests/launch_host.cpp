@@ -35,6 +35,7 @@ int px_host_split_nodes(int candidates, int jobs, int nodes, int Gm, int Gs, int
     const bool row1 = nodes >= 4 && nodes <= 256, whole = nodes % 4 == 0 && Gm % 64 == 0;
     return px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row1 && nodes <= 64, whole, false, row1).per_wave;
 }
+int px_host_table_rows(int jobs, int Gm) { return px::table_rows(jobs, Gm); }
 int px_host_pair_groups(int candidates, int per_wave) { return px::pair_groups(candidates, per_wave); }
 int px_host_record_or_first(int found, int records) { return px::record_or_first(found, records); }
 }

@@ -20,8 +20,8 @@ def launch(tmp_path_factory):
     return L
 
 
-# wavefronts a job: itself alone; with 128 table rows eight, two or one at a time
-@pytest.mark.parametrize("tasks", [1, 17, 65, 129])
+# wavefronts a job: itself alone; with 128 table rows eight, four, two or one at a time
+@pytest.mark.parametrize("tasks", [1, 17, 33, 65, 129])
 def test_every_job_is_prepared(launch, tasks):
     for jobs in (1, 7, 8, 9, 64, 65, 72, 100, 127, 128, 129, 241, 400, 1000, 4001):
         for counters in (0, 1, 4096, 4096 * 1023, 4096 * 1024 + 1, 4096 * 1025, 16 * 4096, 20000 * 256, 30000 * 256, 1800 * 4096, 32000 * 256, 1 << 34):
@@ -32,6 +32,14 @@ def test_few_jobs_get_workgroups_to_clear_with(launch):
     assert launch.px_host_prep_blocks(1, 17, 1 << 34) == 1024
     assert launch.px_host_prep_blocks(1, 17, 4096 * 100) == 100
     assert launch.px_host_prep_blocks(1000, 17, 0) == launch.px_host_prep_blocks(1000, 17, 4096) == 4256
+
+
+@pytest.mark.parametrize("jobs,Gm,rows", [
+    (1, 1, 2), (16, 64, 2), (16, 65, 2), (17, 64, 4), (17, 65, 4), (17, 256, 4), (17, 257, 2), (32, 64, 4), (33, 64, 8), (33, 65, 4),
+    (96, 64, 8), (96, 65, 4), (96, 257, 2), (97, 65, 8), (97, 256, 8), (97, 257, 2), (120, 128, 8), (121, 64, 8), (121, 65, 4),
+    (127, 256, 4), (127, 257, 2), (128, 1, 8), (128, 257, 8), (1000, 500, 8)])
+def test_table_rows_a_wavefront(launch, jobs, Gm, rows):
+    assert launch.px_host_table_rows(jobs, Gm) == rows
 
 
 @pytest.mark.parametrize("f32", [0, 1])
