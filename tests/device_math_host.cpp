@@ -14,6 +14,19 @@ static double ulp_err(double got, long double want)
 }
 
 extern "C" {
+// How many of n quotients a / b are not the correctly rounded one, and how many have another floor than the integers' quotient
+// (integers: a and b hold integers below 2^53), with the reciprocal's seed off by `skew` of itself.
+void px_host_div_faults(const double *a, const double *b, long n, double skew, int integers, long *rounding, long *whole)
+{
+    px::seed_skew = skew;
+    *rounding = *whole = 0;
+    for (long i = 0; i < n; ++i) {
+        const double q = px::px_div(a[i], b[i]);
+        *rounding += q != a[i] / b[i];
+        if (integers) *whole += (long long)std::floor(q) != (long long)a[i] / (long long)b[i];
+    }
+    px::seed_skew = 0.0;
+}
 // which: 0 exp, 1 log1p on [0,1], 2 log, 3 the whole last pass of Eq. 10 (x = T_grad, y = T_sync, g = gamma)
 double px_host_eval(int which, double x, double y, double g)
 {

@@ -22,7 +22,20 @@ def host_math(tmp_path_factory):
     L.px_host_max_ulp.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_long]
     L.px_host_eval.restype = ctypes.c_double
     L.px_host_eval.argtypes = [ctypes.c_int, ctypes.c_double, ctypes.c_double, ctypes.c_double]
+    L.px_host_div_faults.restype = None
+    L.px_host_div_faults.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_long, ctypes.c_double, ctypes.c_int, ctypes.c_void_p,
+                                     ctypes.c_void_p]
     return L
+
+
+SEED_SKEWS = [0.0, 2.0 ** -24, -2.0 ** -24, 2.0 ** -26, -2.0 ** -26, 1.7e-8, -4.1e-8]
+
+
+def div_faults(L, a, b, skew, integers=False):
+    a, b = (np.ascontiguousarray(np.broadcast_to(x, np.broadcast(a, b).shape), np.float64) for x in (a, b))
+    out = [ctypes.c_long(), ctypes.c_long()]
+    L.px_host_div_faults(a.ctypes.data, b.ctypes.data, a.size, skew, int(integers), *(ctypes.addressof(x) for x in out))
+    return out[0].value, out[1].value
 
 
 def max_ulp(L, which, x, y=None, g=None):
@@ -67,3 +80,37 @@ def test_factored_overlap_term_matches_the_direct_power_form(host_math):
     # nearly equal terms with the largest exponent are the worst case
     ts2 = tg * (1 + rng.uniform(-1e-3, 1e-3, n))
     assert max_ulp(host_math, 3, tg, ts2, np.full(n, 10.0)) < 8.0
+
+
+@pytest.mark.parametrize("skew", SEED_SKEWS)
+def test_quotients_are_rounded_as_a_division_rounds_them(host_math, skew):
+    """px_div stands where the library's division stood: whatever the seed, on the reciprocals of GPU counts and accumulation
+    counts, all of them, and on quotients of all kinds of mantissas."""
+    counts = np.arange(1.0, 2.0 ** 14 + 1)
+    assert div_faults(host_math, 1.0, counts, skew) == (0, 0)
+    rng = np.random.default_rng(5)
+    a, b = (rng.uniform(1.0, 2.0, 400000) * 2.0 ** rng.integers(-40, 41, 400000) for _ in range(2))
+    assert div_faults(host_math, a, b, skew) == (0, 0)
+    # mantissas next to 1 and to 2; the one divisor that any such sequence may miss has a mantissa of ones only
+    ulps = 2.0 ** -52 * np.arange(2000)
+    for x in (1.0 + ulps, 2.0 - ulps[1:]):
+        for y in (1.0 + ulps[:300], 2.0 - ulps[2:300]):
+            assert div_faults(host_math, x[:, None], y[None, :], skew) == (0, 0)
+        assert div_faults(host_math, x, 2.0 - 2.0 ** -52, skew)[0] <= 1
+    assert div_faults(host_math, rng.uniform(1.0, 1e6, 200000), rng.uniform(1.0, 10.0, 200000), skew) == (0, 0)
+
+
+@pytest.mark.parametrize("skew", SEED_SKEWS)
+def test_integer_quotients_have_the_right_floor(host_math, skew):
+    """The sampling argmax divides integers in doubles: multiples of the divisor and their neighbours, numerators up to 2^38 where the
+    quotient is not one and beyond 2^53 where it is."""
+    rng = np.random.default_rng(6)
+    b = np.concatenate([np.arange(1, 3000), np.floor(np.exp(rng.uniform(0, np.log(2.0 ** 38), 60000)))])
+    for k in (1, 2, 3, 7, 64, 255, 16384):
+        for d in (-1, 0, 1):
+            a = k * b + d
+            ok = a < 2.0 ** 38
+            assert div_faults(host_math, a[ok], b[ok], skew, True)[1] == 0, (k, d)
+    b = np.floor(np.exp(rng.uniform(np.log(2.0 ** 31), np.log(2.0 ** 62), 100000)))
+    M = np.floor(np.exp(rng.uniform(0, np.log(2.0 ** 31), 100000)))
+    assert div_faults(host_math, M + (b - 1.0), b, skew, True)[1] == 0

@@ -53,7 +53,7 @@ def test_a_batch_size_whose_time_overflows_hides_no_other():
 
 @pytest.mark.parametrize("N", [16, 61, 130])
 @pytest.mark.parametrize("Gm,Gs", [(64, 16), (50, 12), (128, 32)])
-@pytest.mark.parametrize("P", [61, 62, 125, 190, 249, 311])                    # of 200 jobs: one to six candidates a wavefront
+@pytest.mark.parametrize("P", [61, 62, 125, 190, 249, 311, 373, 500, 1000])    # of 200 jobs: one to sixteen candidates a wavefront
 def test_every_split_of_the_pairs_elects_the_same(P, Gm, Gs, N):
     import torch
     import paper_2008_12260_amd as px
