@@ -36,12 +36,12 @@ FLOPS_PER_EVAL = 7                  # Eq. 4 at one grid point: 5 add/mul + 2 div
 #   valu_busy       fraction of the kernel's cycles in which the vector ALUs were busy
 PROFILED = {
     "large": {
-        "source_sha256": "b0878f2953a8e0538b02b79804cb41cbd19422f4365b798017529c781767637c",
-        "traffic_bytes": 2_079_740 * 1024 * 2 + 696_692 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
+        "source_sha256": "e4f39c308eeac0377e4b232b443834d3edd46eda8a8619d3239adb9a549c0e27",
+        "traffic_bytes": 2_079_730 * 1024 * 2 + 699_022 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
         "fp64_flops": 64 * (8.96000e5 + 1.76352e7 + 2 * 2.65925e8),
         "valu_insts": 9.91579e8,
         "scan_insts": 2.25 * 1.6777e10 / 64,
-        "valu_busy": 1.00971e9 * 4 / 1024 / (3.37324e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
+        "valu_busy": 1.00971e9 * 4 / 1024 / (3.39611e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
     },
 }
 GA_SEED = 0x2008_1226_5EED_0001

@@ -895,8 +895,8 @@ __device__ __forceinline__ Best sweep_sampled(const Coefs &c, const Job &q, cons
 template <bool LEAN>
 __device__ __forceinline__ Best sweep_sampled(const Job &q, const int32_t *__restrict__ M_list, int Gm, int Gs, int K, int nodes)
 {
-    return sweep_sampled<LEAN>(plain_coefs(), q, load_grid_params(q.jp, q.J, q.j), load_sync(q), q.jp[(size_t)PX_M_MEM * q.J + q.j], M_list, Gm,
-                               Gs, K, nodes);
+    return sweep_sampled<LEAN>(plain_coefs(), q, load_grid_params(q.jp, q.J, q.j), load_sync(q), q.jp[(size_t)PX_M_MEM * q.J + q.j],
+                               M_list, Gm, Gs, K, nodes);
 }
 
 // ---- fp32 variant of the sweep --------------------------------------------------
@@ -2730,10 +2730,11 @@ __global__ void __launch_bounds__(256) inherit_kernel(FitnessArgs a)
 // all.  Rows of at most 64 entries (SHORT) come four to a load, 16 lanes each.
 //   2048 candidates of 900 jobs on 250 nodes: 1169 us with a wavefront per (candidate, job) reading entry by entry, 0.34 ms so.
 // KIND: the fp64 grid, the fp32 variant, or the sampling argmax.
-// CHILD: the children of a search step that inherits rows (see inherit_kernel for the rule; rows that child_kernel does not take): a row held unchanged takes over
-// the results of the row it was copied from, only the others are read back and looked up.  One launch in place of three
-// (inherit_kernel, pairs_kernel over the listed rows, candidates_kernel: 14 us a generation at 30 jobs, 15 at 200).  A child
-// that satisfies both constraints by construction has no violations; any other is evaluated in full, counters included.
+// CHILD: the children of a search step that inherits rows (see inherit_kernel for the rule), where child_kernel does not take them:
+// a row held unchanged takes over the results of the row it was copied from, only the others are read back and looked up.  One
+// launch in place of three (inherit_kernel, pairs_kernel over the listed rows, candidates_kernel: 14 us a generation at 30 jobs, 15
+// at 200).  A child that satisfies both constraints by construction has no violations; any other is evaluated in full, counters
+// included.
 // Rows of more GPUs than the memo table covers are found in place by their wavefront when the chunk is finished.  (An instance
 // without that code, with a second launch for the candidates that need it, was no faster at any size: 4096 candidates of 1000
 // jobs on 256 nodes 957 us a call with the pair of launches, 856 with the one.)
@@ -2805,7 +2806,8 @@ __device__ __forceinline__ void finish_pairs(const FitnessArgs &a, int c, int jc
             const int j = jc + at0 + l;
             Best found;
             if constexpr (KIND == kMemoF32) found = sweep_f32(load_job_f32(a.job_params, a.J, j), job_tables(a, j), a.rk, a.Gm, a.Gs, K, nodes);
-            else if constexpr (KIND == kMemoSampled) found = sweep_sampled<false>(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes);
+            else if constexpr (KIND == kMemoSampled) found = sweep_sampled<false>(load_job(a.job_params, a.J, j), a.m_grid + (size_t)j * a.Gm,
+                                                                                  a.Gm, a.Gs, K, nodes);
             else found = row_best_plain<false>(load_job(a.job_params, a.J, j), load_grid_params(a.job_params, a.J, j),
                                   a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, K, nodes == 1, false);
             if (lane == l) best = found;
@@ -3101,8 +3103,8 @@ __global__ void __launch_bounds__(WAVES *kWave) memo_candidates_kernel(FitnessAr
 // The step's workgroup has the child's rows and where each comes from at hand, so it goes on to the fitness: the rows held unchanged
 // take over their source's results (asked for when the parents are known, so that they arrive while the rows are copied), the
 // few others are read back and looked up.  The terms are summed as memo_candidates_kernel sums them.  A generation is two
-// launches (rank, this) where it was three: an interval of 20 generations of 256 x 30 x 16 takes 270 us where it took 326, of
-// 1000 x 200 x 64 522 where it took 586.  Bound, at 30 jobs, by its own chain: 17400 cycles, of which the parents (kernel
+// launches (rank, this) where it was three: an interval of 20 generations of 256 x 30 x 16 takes 268 us where it took 327, of
+// 1000 x 200 x 64 515 where it took 581.  Bound, at 30 jobs, by its own chain: 17400 cycles, of which the parents (kernel
 // arguments, order, draws) take 3800, the rows' trip from memory 2900, the repairs 3600 and what follows them 4600.
 // For rows of 4 to 64 nodes without a GPU limit per job, up to kFinishJobs jobs (generation_in_one): longer rows are bound by the
 // copy, and 18 bytes of LDS a job hold a thousand jobs.

@@ -312,7 +312,8 @@ __device__ __forceinline__ void form_child(const GaArgs &a, const GaShared &sh, 
     // load of the wavefront, 16 lanes each.  The loop after this one then takes only the rows with a move.
     if constexpr (FOUR) {
         // kAhead loads are requested before the first is worked on: one after the other, each with its store and its
-        // bookkeeping, the seven loads of a wavefront at 200 jobs took longest in the kernel (19.0 us in all, 17.1 so; what is left of it is the copy, at 7 TB/s out of the caches).
+        // bookkeeping, the seven loads of a wavefront at 200 jobs took longest in the kernel (19.0 us in all, 17.1 so;
+        // what is left of it is the copy, at 7 TB/s out of the caches).
         const int g = lane >> 4, l16 = lane & 15;
         RowLane at_row = {4 * l16, Entries{-1, -1, -1, -1}};
         if constexpr (ROWS == kRows64) at_row = row_lane(l16, a.N);

@@ -21,8 +21,8 @@
 // waits for the one before it or not, so what counts is how many there are.  An iteration is 840 (1240 with the sums through
 // LDS, the library's roots and divisions and the polynomials' constants formed where they are used); 100 jobs, 200 iterations:
 // 0.70 ms then, 0.39 now.  Beyond 256 jobs SIMDs hold two chains and three, and the slowest job is the one whose neighbours
-// are slow: 1000 jobs of up to 48 records with three starts 1.1 to 1.18 ms then, 0.78 to 0.84 now.  Every result has the same bits: on the flat
-// stretches of this error other roundings end at other parameters.
+// are slow: 1000 jobs of up to 48 records with three starts 1.1 to 1.18 ms then, 0.78 to 0.84 now.  Every result has the same
+// bits: on the flat stretches of this error other roundings end at other parameters.
 //
 // Eq. 10 is evaluated with the larger term factored out, as in the fitness kernels:
 // with D = ln T_sync - ln T_grad and e = exp(-gamma |D|),
@@ -185,9 +185,9 @@ __device__ __forceinline__ Record load_record(const FitArgs &f, size_t at)
     return r;
 }
 
-// The sums of one job at theta = z * scale (lanes 2 i and 2 i + 1 hold z_i, all lanes all of scale): sum t in lanes 2 t and 2 t + 1 (kOrder).
-// mine: the lane's record (bit_reversed), read once and kept in its registers over all iterations.  HELD: the job has no more than
-// these 64; otherwise those beyond are read from memory in every evaluation.
+// The sums of one job at theta = z * scale (lanes 2 i and 2 i + 1 hold z_i, all lanes all of scale): sum t in lanes 2 t and 2 t + 1
+// (kOrder).  mine: the lane's record (bit_reversed), read once and kept in its registers over all iterations.  HELD: the job has no
+// more than these 64; otherwise those beyond are read from memory in every evaluation.
 template <bool HELD>
 __device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale,
                                                    const double (&scale)[kTheta], const Record &mine, const Coefs &c)
