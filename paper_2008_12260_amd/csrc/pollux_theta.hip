@@ -19,10 +19,13 @@
 //
 // Bound by the vector ALU's issue, wavefront by wavefront: an instruction, scalar ones included, takes four cycles whether it
 // waits for the one before it or not, so what counts is how many there are.  An iteration is 840 (1240 with the sums through
-// LDS, the library's roots and divisions and the polynomials' constants formed where they are used); 100 jobs, 200 iterations:
-// 0.70 ms then, 0.39 now.  Beyond 256 jobs SIMDs hold two chains and three, and the slowest job is the one whose neighbours
-// are slow: 1000 jobs of up to 48 records with three starts 1.1 to 1.18 ms then, 0.78 to 0.84 now.  Every result has the same
-// bits: on the flat stretches of this error other roundings end at other parameters.
+// LDS, the library's roots and divisions and the polynomials' constants formed where they are used), 540 where the trial point
+// is refused, as half of them are: its error is summed first, and only a point that is taken gets derivatives and the other
+// sums.  1000 jobs of up to 48 records with three starts, ms: 1.1 to 1.18 with the first of these forms, 0.77 to 0.82 with all sums
+// for every point, 0.69 to 0.71 now; 80 jobs with one start 0.39 and 0.36 (0.98 to 1.03 times where nearly every point is taken).
+// Beyond 256 jobs SIMDs hold two chains and three, and the slowest job is the one whose neighbours are slow (two chains of 200
+// iterations on one SIMD take 1.45 times as long as one alone).  Every result has the same bits: on the flat stretches of this error
+// other roundings end at other parameters.
 //
 // Eq. 10 is evaluated with the larger term factored out, as in the fitness kernels:
 // with D = ln T_sync - ln T_grad and e = exp(-gamma |D|),
@@ -158,6 +161,17 @@ __device__ __forceinline__ double sum_terms(const double (&term)[kSums])
     return sum + exchange<0>(sum);
 }
 
+// The sum of one term alone, in every lane, in the same tree: what sum_terms leaves in its lanes, bit by bit.
+__device__ __forceinline__ double sum_term(double term)
+{
+    double v = add_halves(term, term);
+    v = add_rows(v, v);
+    v += rotate16<8>(v);                     // (from here on lanes eight apart hold the same: four further on is as good as lane ^ 4)
+    v += rotate16<4>(v);
+    v += exchange<1>(v);
+    return v + exchange<0>(v);
+}
+
 // The value lane `src` holds, in every lane.
 __device__ __forceinline__ double wave_read(double v, int src)
 {
@@ -185,65 +199,96 @@ __device__ __forceinline__ Record load_record(const FitArgs &f, size_t at)
     return r;
 }
 
-// The sums of one job at theta = z * scale (lanes 2 i and 2 i + 1 hold z_i, all lanes all of scale): sum t in lanes 2 t and 2 t + 1
-// (kOrder).  mine: the lane's record (bit_reversed), read once and kept in its registers over all iterations.  HELD: the job has no
-// more than these 64; otherwise those beyond are read from memory in every evaluation.
+// What all lanes need of a trial point theta = z * scale (lanes 2 i and 2 i + 1 hold z_i).
+struct Theta {
+    double th[kTheta], inv_gamma;
+};
+
+__device__ __forceinline__ Theta make_theta(double my_z, double my_scale)
+{
+    Theta p;
+    const double my_th = my_z * my_scale;
+#pragma unroll
+    for (int i = 0; i < kTheta; ++i) p.th[i] = wave_read(my_th, 2 * i);
+    p.inv_gamma = px_div(1.0, p.th[PX_GAMMA]);
+    return p;
+}
+
+// One record at a trial point: the prediction and what its derivatives are made of (lntg .. l1p only where ts > 0).
+struct Prediction {
+    double tg, ts, lntg, lnts, d, e, l1p, last, pred;
+};
+
+__device__ __forceinline__ Prediction predict(const Theta &p, const Record &rec, const Coefs &c)
+{
+    Prediction q = {};
+    q.tg = p.th[PX_ALPHA_G] + p.th[PX_BETA_G] * rec.md;                               // Eq. 8
+    q.tg = q.tg > kTgradFloor ? q.tg : kTgradFloor;
+    const bool local = rec.K > 1 && rec.nodes == 1, node = rec.K > 1 && rec.nodes != 1;
+    const double km2 = (double)(rec.K - 2);
+    q.ts = 0.0;                                                                       // Eq. 9
+    if (local) q.ts = p.th[PX_ALPHA_SL] + p.th[PX_BETA_SL] * km2;
+    if (node) q.ts = p.th[PX_ALPHA_SN] + p.th[PX_BETA_SN] * km2;
+    q.last = q.tg;
+    if (q.ts > 0.0) {                                                                 // Eq. 10
+        q.lntg = px_log(c, q.tg);
+        q.lnts = px_log(c, q.ts);
+        q.d = q.lnts - q.lntg;
+        q.e = px_exp(c, -p.th[PX_GAMMA] * fabs(q.d));
+        q.l1p = px_log1p_unit(c, q.e);
+        q.last = (q.d >= 0.0 ? q.ts : q.tg) * px_exp(c, q.l1p * p.inv_gamma);
+    }
+    q.pred = rec.sd * q.tg + q.last;                                                  // Eq. 11
+    return q;
+}
+
+// The residual (some: the lane holds a record; selected, not branched around).
+__device__ __forceinline__ double residual(const Prediction &q, const Record &rec, bool some, const Coefs &c)
+{
+    double r = px_log(c, q.pred) - rec.lnT;
+    asm("" : "+v"(r));
+    return some ? r : 0.0;
+}
+
+// Its derivatives with respect to z.  In a lane without a record every one of them has the factor 1 / pred, which is made zero.
+__device__ __forceinline__ void derivatives(const Theta &p, const Prediction &q, const Record &rec, bool some,
+                                            const double (&scale)[kTheta], double (&d)[kTheta])
+{
+    const double gamma = p.th[PX_GAMMA], inv_gamma = p.inv_gamma;
+    const bool local = rec.K > 1 && rec.nodes == 1, node = rec.K > 1 && rec.nodes != 1;
+    const double km2 = (double)(rec.K - 2);
+    double dl_dtg = 1.0, dl_dts = gamma == 1.0 ? 1.0 : 0.0, dlnl_dg = 0.0;
+    if (q.ts > 0.0) {
+        const double w_small = px_div(q.e, 1.0 + q.e), w_big = px_div(1.0, 1.0 + q.e);
+        const double w_s = q.d >= 0.0 ? w_big : w_small, w_g = q.d >= 0.0 ? w_small : w_big;
+        dl_dtg = w_g * px_div(q.last, q.tg);
+        dl_dts = w_s * px_div(q.last, q.ts);
+        const double lnsum = gamma * (q.d >= 0.0 ? q.lnts : q.lntg) + q.l1p;          // ln(T_grad^g + T_sync^g)
+        dlnl_dg = (w_g * q.lntg + w_s * q.lnts) * inv_gamma - lnsum * inv_gamma * inv_gamma;
+    }
+    double inv_pred = px_div(1.0, q.pred);
+    asm("" : "+v"(inv_pred));
+    inv_pred = some ? inv_pred : 0.0;
+    d[PX_ALPHA_G] = (rec.sd + dl_dtg) * inv_pred;
+    d[PX_BETA_G] = d[PX_ALPHA_G] * rec.md;
+    const double dts = dl_dts * inv_pred;
+    d[PX_ALPHA_SL] = local ? dts : 0.0;
+    d[PX_BETA_SL] = local ? dts * km2 : 0.0;
+    d[PX_ALPHA_SN] = node ? dts : 0.0;
+    d[PX_BETA_SN] = node ? dts * km2 : 0.0;
+    d[PX_GAMMA] = q.last * dlnl_dg * inv_pred;
+#pragma unroll
+    for (int i = 0; i < kTheta; ++i) d[i] *= scale[i];
+}
+
+// The sums of one job at a trial point: sum t in lanes 2 t and 2 t + 1 (kOrder).  HELD: the job has no more than 64 records, each
+// lane's (bit_reversed) is in its registers with its prediction and residual; otherwise the records beyond `mine` are read from
+// memory in every evaluation.
 template <bool HELD>
-__device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int n, double my_z, double my_scale,
-                                                   const double (&scale)[kTheta], const Record &mine, const Coefs &c)
+__device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int n, const Theta &p, const double (&scale)[kTheta],
+                                                   const Record &mine, const Prediction &at, double r_at, const Coefs &c)
 {
     const int lane = lane_id();
-    const double my_th = my_z * my_scale;
-    double th[kTheta];
-#pragma unroll
-    for (int i = 0; i < kTheta; ++i) th[i] = wave_read(my_th, 2 * i);
-    const double gamma = th[PX_GAMMA], inv_gamma = px_div(1.0, gamma);
-
-    // the residual of one record and its derivatives with respect to z
-    auto evaluate = [&](const Record &rec, bool some, double &r, double (&d)[kTheta]) {
-        const int K = rec.K, nodes = rec.nodes;
-        const double md = rec.md, sd = rec.sd;
-        const double lnT = rec.lnT;
-        double tg = th[PX_ALPHA_G] + th[PX_BETA_G] * md;                                  // Eq. 8
-        tg = tg > kTgradFloor ? tg : kTgradFloor;
-        const bool local = K > 1 && nodes == 1, node = K > 1 && nodes != 1;
-        const double km2 = (double)(K - 2);
-        double ts = 0.0;                                                                  // Eq. 9
-        if (local) ts = th[PX_ALPHA_SL] + th[PX_BETA_SL] * km2;
-        if (node) ts = th[PX_ALPHA_SN] + th[PX_BETA_SN] * km2;
-        double last = tg, dl_dtg = 1.0, dl_dts = gamma == 1.0 ? 1.0 : 0.0, dlnl_dg = 0.0;
-        if (ts > 0.0) {                                                                   // Eq. 10
-            const double lntg = px_log(c, tg), lnts = px_log(c, ts);
-            const double d = lnts - lntg;
-            const double e = px_exp(c, -gamma * fabs(d));
-            const double l1p = px_log1p_unit(c, e);
-            const double big = d >= 0.0 ? ts : tg, lnbig = d >= 0.0 ? lnts : lntg;
-            last = big * px_exp(c, l1p * inv_gamma);
-            const double w_small = px_div(e, 1.0 + e), w_big = px_div(1.0, 1.0 + e);
-            const double w_s = d >= 0.0 ? w_big : w_small, w_g = d >= 0.0 ? w_small : w_big;
-            dl_dtg = w_g * px_div(last, tg);
-            dl_dts = w_s * px_div(last, ts);
-            const double lnsum = gamma * lnbig + l1p;                                     // ln(T_grad^g + T_sync^g)
-            dlnl_dg = (w_g * lntg + w_s * lnts) * inv_gamma - lnsum * inv_gamma * inv_gamma;
-        }
-        const double pred = sd * tg + last;                                               // Eq. 11
-        // a lane without a record (some): every derivative has the factor 1 / pred
-        double inv_pred = px_div(1.0, pred);
-        r = px_log(c, pred) - lnT;
-        asm("" : "+v"(r), "+v"(inv_pred));                       // (selected, not branched around)
-        r = some ? r : 0.0;
-        inv_pred = some ? inv_pred : 0.0;
-        d[PX_ALPHA_G] = (sd + dl_dtg) * inv_pred;
-        d[PX_BETA_G] = d[PX_ALPHA_G] * md;
-        const double dts = dl_dts * inv_pred;
-        d[PX_ALPHA_SL] = local ? dts : 0.0;
-        d[PX_BETA_SL] = local ? dts * km2 : 0.0;
-        d[PX_ALPHA_SN] = node ? dts : 0.0;
-        d[PX_BETA_SN] = node ? dts * km2 : 0.0;
-        d[PX_GAMMA] = last * dlnl_dg * inv_pred;
-#pragma unroll
-        for (int i = 0; i < kTheta; ++i) d[i] *= scale[i];
-    };
     double term[kSums];
     // (a job whose records are all held has one a lane: its products as they are)
     auto accumulate = [](double a, double b, double to) { return HELD ? a * b : px_fma(a, b, to); };
@@ -261,14 +306,20 @@ __device__ __forceinline__ double normal_equations(const FitArgs &f, int j, int 
     };
 #pragma unroll
     for (int t = 0; t < kSums; ++t) term[t] = 0.0;
-    const size_t base = (size_t)j * f.max_obs;
-    for (int o0 = 0; o0 < (HELD ? 1 : n); o0 += kWave) {
-        const int o = o0 + bit_reversed(lane);
-        Record rec = mine;
-        if (!HELD && o0 > 0) rec = load_record(f, base + (size_t)(o < n ? o : n - 1));
-        double r, d[kTheta];
-        evaluate(rec, o < n, r, d);
-        add(r, d);
+    double d[kTheta];
+    if constexpr (HELD) {
+        derivatives(p, at, mine, bit_reversed(lane) < n, scale, d);
+        add(r_at, d);
+    } else {
+        const size_t base = (size_t)j * f.max_obs;
+        for (int o0 = 0; o0 < n; o0 += kWave) {
+            const int o = o0 + bit_reversed(lane);
+            Record rec = mine;
+            if (o0 > 0) rec = load_record(f, base + (size_t)(o < n ? o : n - 1));
+            const Prediction q = predict(p, rec, c);
+            derivatives(p, q, rec, o < n, scale, d);
+            add(residual(q, rec, o < n, c), d);
+        }
     }
     return sum_terms(term);
 }
@@ -599,11 +650,25 @@ __global__ void __launch_bounds__(64 * kMaxStarts) __attribute__((amdgpu_waves_p
             bool first = true;
             unsigned moved = 0u, moved_little = 0u;   // unknowns the last step has changed by 1e-9 of themselves or more, 1e-15 or more
             for (;;) {
-                const double trial = normal_equations<HELD>(f, j, n, zn, scale, scales, mine, math);
-                const double trial_sse = wave_read(trial, 2 * 7);
+                // Half of the trial points are refused.  Their error alone decides that, so derivatives and the other sums wait for
+                // it; a point that is taken costs 35 instructions more for it.  (Guessing from the fate of the points before which
+                // of the two to begin with was slower: 0.76 ms where this takes 0.71.  Beyond 64 records a second pass over them
+                // would cost what it saves.)
+                const Theta point = make_theta(zn, scale);
+                Prediction at = {};
+                double r = 0.0, trial = 0.0, trial_sse;
+                if constexpr (HELD) {
+                    at = predict(point, mine, math);
+                    r = residual(at, mine, bit_reversed(lane) < n, math);
+                    trial_sse = uniform_f64(sum_term(r * r));
+                } else {
+                    trial = normal_equations<HELD>(f, j, n, point, scales, mine, at, r, math);
+                    trial_sse = wave_read(trial, 2 * 7);
+                }
                 if (first || trial_sse < cur_sse) {
                     const double before = cur_sse;
                     z = zn;
+                    if constexpr (HELD) trial = normal_equations<HELD>(f, j, n, point, scales, mine, at, r, math);
                     cur = trial;
                     cur_sse = trial_sse;
                     if (!first) {
