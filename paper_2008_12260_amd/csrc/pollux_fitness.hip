@@ -45,16 +45,11 @@
 // with every term non-negative.  The argmax of GOODPUT is the argmin of h over the
 // feasible points.  For one batch size (one lane) that is the argmin of w over its
 // feasible s, which form an interval s_lo..s_hi that depends on (job, K, m) only and is
-// tabled.  The lane scans w over ALL s, one fused multiply-add per grid point; the four values
-// of a group of four consecutive s are reduced with three v_min_f64, and the running minimum takes
-// that result after its low five mantissa bits have been replaced by the first position of the group (so
-// the minimum carries the group it came from and equal values resolve to the earlier group; the
-// perturbation is 2^-47 relative).  The s inside the winning group is found once per lane
-// afterwards by an exact comparison: w(s+1) < w(s) precisely when C > (s+1)(s+2), so the argmin is
-// a count of thresholds below C (scan_argmin; equal values: the smaller s).  w is convex in s
-// (C >= 0), so the feasible optimum sits at the scan's argmin clamped to s_lo..s_hi; h is
-// formed there once per lane and group of 64 batch sizes.  The wave then takes the
-// smallest h (equal values: lowest flat index), and the elected point is evaluated
+// tabled.  The lane takes the smallest w over ALL s, one fused multiply-add and one minimum per grid point.  w is convex
+// in s (C >= 0) and w(s+1) < w(s) precisely when C > (s+1)(s+2), so two exact comparisons say whether that minimum lies
+// within s_lo..s_hi; where it does not, the feasible optimum is w at the end towards it.  h is formed from it once per lane
+// and group of 64 batch sizes.  The wave then takes the smallest h (equal values: lowest flat index); only now the count
+// of the elected batch size is found, from its C by the same exact rule (feasible_count), and the elected point is evaluated
 // again with the formulas in the paper's own order (separate multiply and add, IEEE
 // division), so the reported goodput does not depend on the fast form.
 //
@@ -332,31 +327,28 @@ __device__ __forceinline__ double goodput_point(const Job &q, double Km, double 
 
 // ---- the sweep of one batch size per lane over CH accumulation counts ---------------
 // With C = B0 / T_grad the quantity to minimise is  h = A0 + T_grad w(s),  w(s) = s + C / (s+1),
-// for the lane's batch size.  The lane scans w over all accumulation counts, feasible or not;
+// for the lane's batch size.  The lane takes the smallest w over all accumulation counts, feasible or not;
 // C >= 0 makes w convex in s, and the feasible counts of a batch size form an interval (tabled
-// per (job, K, i) by prepare_kernel), so the smallest feasible w sits at the scan's argmin clamped
-// to that interval (sweep_pick).  Inside a chunk of CH counts starting at s0, per group of four
+// per (job, K, i) by prepare_kernel), so the smallest feasible w is that minimum, or w at the end of the
+// interval that lies towards it (Feasible below).  Inside a chunk of CH counts, per group of four
 // positions b = 4 G .. 4 G + 3 and lane:
 //   w_b  = C * r + (b mod 16)  one v_fma_f64 each (v_mul_f64 for 0): r = 1/(s0 + b + 1) from scalar
 //                              registers, the addend an inline constant (1, 2, 4) or one of
 //                              twelve register pairs that hold 3, 5, 6, .. 15 for the whole kernel
-//   g    = min of the four                                three v_min_f64
-//   lo   = (31 & 4 G) | (~31 & lo(g))                     v_bfi_b32
-//   kmin = min(kmin, key)                                 v_min_f64
-// so the key carries its group's first position 4 G in the low five mantissa bits (equal values resolve to
-// the earlier group): nine VALU instructions per four points; the reciprocals arrive through the
-// scalar cache.  Each run of sixteen positions has a minimum of its own (values relative to
-// the run's first position); the runs are merged after the chunk (merge_runs).  The position
-// inside the winning group is found afterwards, once per lane (sweep_pick).
+//   wmin = min(wmin, the four) four v_min_f64
+// eight VALU instructions per four points; the reciprocals arrive through the scalar cache.  Each run of sixteen
+// positions has a minimum of its own (values relative to the run's first position); the runs are merged after
+// the chunk.  Which count attains the minimum is not looked for here: one lane of sixty-four wins the election, and
+// its count follows from C when the elected point is priced (feasible_count).
+// (With every group of four carrying its position in its low mantissa bits, nine instructions per four points, and every lane
+// finding its count with five comparisons, a pair of 128 batch sizes x 32 counts took 248 vector instructions, 220 so: 4096 candidates
+// of 1000 jobs 1.78 ms against 1.66, 1000 of 200 on 64 nodes 52.5 us against 46; fp32, which also loses its tags, 52.0 against 44.7.)
 typedef const double __attribute__((address_space(4))) *ScalarDoubles;
 typedef const double __attribute__((address_space(3))) *LdsDoubles;
 typedef double Double2 __attribute__((ext_vector_type(2)));
 
 constexpr int kRun = 16;
 constexpr int runs_of(int CH) { return (CH + kRun - 1) / kRun; }
-// Chunks of 16 and 32 tag per group of four positions; chunks of 8 tag every position (twelve instructions per
-// four points, and less to find afterwards: quicker for very few counts per batch size).
-constexpr bool grouped_tags(int CH) { return CH >= 16; }
 
 // The addends that are not inline constants (3, 5 .. 15) in vector registers.  Made once
 // per kernel through an opaque statement, so that they stay in registers instead of being formed
@@ -389,17 +381,8 @@ __device__ __forceinline__ double point_w(double C, double r, const RunSteps &X)
     return g;
 }
 
-// v with TAG in its low five mantissa bits.
-template <int TAG>
-__device__ __forceinline__ double tagged(double v)
-{
-    int lo;
-    asm("v_bfi_b32 %0, 31, %1, %2" : "=v"(lo) : "n"(TAG), "v"(__double2loint(v)));
-    return __hiloint2double(__double2hiint(v), lo);
-}
-
 // Four points at positions 4 G .. 4 G + 3 of the chunk (G a compile-time group index): the
-// four values, their minimum, its key.  The volatile statements keep their order, so the
+// four values and their minimum.  The volatile statements keep their order, so the
 // reciprocals of a group are requested after the previous group's work and only one group's
 // operands occupy scalar registers.
 struct GroupRecips {
@@ -413,83 +396,72 @@ __device__ __forceinline__ GroupRecips load_group(ScalarDoubles &rs)
     return GroupRecips{rs[4 * G + 0], rs[4 * G + 1], rs[4 * G + 2], rs[4 * G + 3]};
 }
 
-template <int CH, int G>
-__device__ __forceinline__ void scan_group(double (&kmin)[runs_of(CH)], double C, const RunSteps &X, const GroupRecips &o)
+template <int CH, int G, int NC>
+__device__ __forceinline__ void scan_group(double (&wmin)[NC][runs_of(CH)], const double (&C)[NC], const RunSteps &X, const GroupRecips &o)
 {
-    const double w0 = point_w<4 * G + 0>(C, o.r0, X);
-    const double w1 = point_w<4 * G + 1>(C, o.r1, X);
-    const double w2 = point_w<4 * G + 2>(C, o.r2, X);
-    const double w3 = point_w<4 * G + 3>(C, o.r3, X);
-    if constexpr (grouped_tags(CH)) {
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        const double w0 = point_w<4 * G + 0>(C[n], o.r0, X);
+        const double w1 = point_w<4 * G + 1>(C[n], o.r1, X);
+        const double w2 = point_w<4 * G + 2>(C[n], o.r2, X);
+        const double w3 = point_w<4 * G + 3>(C[n], o.r3, X);
+        double &run = wmin[n][4 * G / kRun];
         double g, g2;
-        asm volatile("v_min_f64 %0, %2, %3\n\t"
-                     "v_min_f64 %1, %4, %5\n\t"
-                     "v_min_f64 %0, %0, %1"
-                     : "=&v"(g), "=&v"(g2)
-                     : "v"(w0), "v"(w1), "v"(w2), "v"(w3));
-        const double key = tagged<4 * G>(g);         // the first position of the group: what scan_argmin wants of it
-        if constexpr ((4 * G) % kRun == 0) kmin[4 * G / kRun] = key;      // the first group of a run starts its minimum
-        else asm volatile("v_min_f64 %0, %0, %1" : "+v"(kmin[4 * G / kRun]) : "v"(key));
-    } else {
-        const double k0 = tagged<4 * G + 0>(w0), k1 = tagged<4 * G + 1>(w1), k2 = tagged<4 * G + 2>(w2), k3 = tagged<4 * G + 3>(w3);
-        if constexpr ((4 * G) % kRun == 0) {
-            asm volatile("v_min_f64 %0, %1, %2\n\t"
-                         "v_min_f64 %0, %0, %3\n\t"
-                         "v_min_f64 %0, %0, %4"
-                         : "=&v"(kmin[4 * G / kRun])
-                         : "v"(k0), "v"(k1), "v"(k2), "v"(k3));
+        if constexpr ((4 * G) % kRun == 0) {          // the first group of a run starts its minimum
+            asm volatile("v_min_f64 %0, %2, %3\n\t"
+                         "v_min_f64 %1, %4, %5\n\t"
+                         "v_min_f64 %0, %0, %1"
+                         : "=&v"(run), "=&v"(g)
+                         : "v"(w0), "v"(w1), "v"(w2), "v"(w3));
         } else {
-            asm volatile("v_min_f64 %0, %0, %1\n\t"
-                         "v_min_f64 %0, %0, %2\n\t"
-                         "v_min_f64 %0, %0, %3\n\t"
-                         "v_min_f64 %0, %0, %4"
-                         : "+v"(kmin[4 * G / kRun])
-                         : "v"(k0), "v"(k1), "v"(k2), "v"(k3));
+            asm volatile("v_min_f64 %1, %3, %4\n\t"
+                         "v_min_f64 %2, %5, %6\n\t"
+                         "v_min_f64 %0, %0, %1\n\t"
+                         "v_min_f64 %0, %0, %2"
+                         : "+v"(run), "=&v"(g), "=&v"(g2)
+                         : "v"(w0), "v"(w1), "v"(w2), "v"(w3));
         }
     }
 }
 
 // The reciprocals of a group are requested one group ahead of their use.
-template <int CH, int G = 0>
-__device__ __forceinline__ void scan_groups(double (&kmin)[runs_of(CH)], double C, const RunSteps &X, ScalarDoubles &rs,
+template <int CH, int NC, int G = 0>
+__device__ __forceinline__ void scan_groups(double (&wmin)[NC][runs_of(CH)], const double (&C)[NC], const RunSteps &X, ScalarDoubles &rs,
                                             GroupRecips cur)
 {
     if constexpr (4 * G < CH) {
         asm volatile("" : "+s"(cur.r0), "+s"(cur.r1), "+s"(cur.r2), "+s"(cur.r3));
         GroupRecips next = cur;
         if constexpr (4 * (G + 1) < CH) next = load_group<G + 1>(rs);
-        scan_group<CH, G>(kmin, C, X, cur);
-        scan_groups<CH, G + 1>(kmin, C, X, rs, next);
+        scan_group<CH, G, NC>(wmin, C, X, cur);
+        scan_groups<CH, NC, G + 1>(wmin, C, X, rs, next);
     }
 }
 
-// min(lower, upper + D) for the minima of two neighbouring stretches of positions, the upper
-// one starting D positions later; D is formed from inline constants.  The sum gets
-// the group bits of `upper` back.
-template <int D>
-__device__ __forceinline__ double merge_runs(double lower, double upper)
+__device__ __forceinline__ double min_f64(double a, double b)
 {
-    static_assert(D == 16, "an offset that is a product of inline constants");
-    double moved;
-    asm("v_fma_f64 %0, 4.0, 4.0, %1" : "=v"(moved) : "v"(upper));
-    int lo;
-    asm("v_bfi_b32 %0, 31, %1, %2" : "=v"(lo) : "v"(__double2loint(upper)), "v"(__double2loint(moved)));
-    const double key = __hiloint2double(__double2hiint(moved), lo);
-    double out;
-    asm("v_min_f64 %0, %1, %2" : "=v"(out) : "v"(lower), "v"(key));
+    double out;                                        // (the bare instruction: the operands are results of arithmetic)
+    asm("v_min_f64 %0, %1, %2" : "=v"(out) : "v"(a), "v"(b));
     return out;
 }
 
-// CH points starting at accumulation count s0; rs points at s0.  Returns the smallest key of
-// w over the chunk (values relative to s0; in the low five bits the first position of the group of four, or the position).
-template <int CH>
-__device__ __forceinline__ double scan_chunk(double C, const RunSteps &X, ScalarDoubles rs)
+// CH points starting at accumulation count s0; rs points at s0.  out: the smallest w over the chunk, relative to s0.
+template <int CH, int NC>
+__device__ __forceinline__ void scan_chunk(double (&out)[NC], const double (&C)[NC], const RunSteps &X, ScalarDoubles rs)
 {
     static_assert(CH == 8 || CH == 16 || CH == 24 || CH == 32, "one or two runs");
-    double kmin[runs_of(CH)];
-    scan_groups<CH>(kmin, C, X, rs, load_group<0>(rs));
-    if constexpr (runs_of(CH) == 1) return kmin[0];
-    else return merge_runs<kRun>(kmin[0], kmin[1]);
+    double wmin[NC][runs_of(CH)];
+    scan_groups<CH, NC>(wmin, C, X, rs, load_group<0>(rs));
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        out[n] = wmin[n][0];
+        if constexpr (runs_of(CH) == 2) {
+            static_assert(kRun == 16, "the offset of the second run is a product of inline constants");
+            double moved;
+            asm("v_fma_f64 %0, 4.0, 4.0, %1" : "=v"(moved) : "v"(wmin[n][1]));
+            out[n] = min_f64(out[n], moved);
+        }
+    }
 }
 
 // The same chunk for a GPU count beyond the tables, written as a plain loop (rare, so
@@ -508,73 +480,74 @@ __device__ __forceinline__ double sweep_chunk_plain(double tg, double A0s, doubl
     return kmin;
 }
 
-// The accumulation count with the smallest w(s) = s + C / (s + 1) among s = 0, 1, ... (all counts of the grid,
-// rounded up to whole chunks: the reciprocals are padded), equal values to the lower count, for the lane's own C >= 0.
-// near: a copy of the reciprocals in LDS with the thresholds U[t] = t (t+1) behind them, when has_near.
-template <int CH>
-__device__ __forceinline__ int scan_argmin(double C, const RunSteps &X, ScalarDoubles rsc, int Gs, LdsDoubles near, bool has_near)
+// The smallest w(s) = s + C / (s + 1) over s = 0, 1, ... (all counts of the grid, rounded up to whole chunks: the reciprocals
+// are padded), for NC values C >= 0 of each lane, which share the reciprocals.
+template <int CH, int NC>
+__device__ __forceinline__ void scan_mins(double (&wmin)[NC], const double (&C)[NC], const RunSteps &X, ScalarDoubles rsc, int Gs)
 {
-    // the argmin of w over all counts (the first count of its group of four, where keys carry groups): low bits of the
-    // smallest key, chunk by chunk
-    double wmin = scan_chunk<CH>(C, X, rsc);
-    int g_star = __double2loint(wmin) & 31;
+    scan_chunk<CH, NC>(wmin, C, X, rsc);
     // (the bound goes through an opaque statement: every inlined copy of this loop then tests it with a scalar
     // comparison of its own, instead of sharing one truth value that the compiler carries around as a lane mask and
     // negates with two vector instructions)
     asm volatile("" : "+s"(Gs));
     for (int s0 = CH; s0 < Gs; s0 += CH) {
-        const double w = scan_chunk<CH>(C, X, rsc + s0);
-        const double moved = w + (double)s0;            // strictly smaller only: ties keep the smaller s
-        if (moved < wmin) {
-            wmin = moved;
-            g_star = s0 + (__double2loint(w) & 31);
-        }
+        double w[NC];
+        scan_chunk<CH, NC>(w, C, X, rsc + s0);
+#pragma unroll
+        for (int n = 0; n < NC; ++n) wmin[n] = min_f64(wmin[n], w[n] + (double)s0);
     }
-    // The keys of the scan carry index bits in their low mantissa bits, so what the scan has found is the
-    // argmin up to values that agree to 2^-47; w is convex, so only neighbouring counts can agree that
-    // closely, and the true argmin lies next to what the scan found.  The order of neighbours is known
-    // exactly: w(s+1) < w(s) precisely when C > (s+1)(s+2), both sides exact in fp64.  With
-    // U[t] = t (t+1) (U[0] = -1, so that the result never falls below 0) the argmin over all counts is the
-    // number of t >= 0 with C > U[t], less one; only the t around the scan's result need to be looked at.
-    int s_star;
-    if constexpr (grouped_tags(CH)) {
-        // the scan names a group of four counts 4 g .. 4 g + 3: the argmin is 4 g - 1 plus the number of
-        // t = 4 g .. 4 g + 4 with C > U[t]
-        const int t0 = g_star;
-        s_star = t0 - 1;
-        if (has_near) {
-            // all five requested together: three reads in a row cost three LDS round trips per batch size, and after
-            // the scan the registers its values occupied are free
-            LdsDoubles u = near + kNearU + t0;
-            const Double2 a01 = *(const Double2 __attribute__((address_space(3))) *)u;
-            const Double2 a23 = *(const Double2 __attribute__((address_space(3))) *)(u + 2);
-            const double a4 = u[4];
-            s_star += (C > a01.x ? 1 : 0) + (C > a01.y ? 1 : 0);
-            s_star += (C > a23.x ? 1 : 0) + (C > a23.y ? 1 : 0);
-            s_star += C > a4 ? 1 : 0;
-        } else {
-            const double td = (double)t0;
-            s_star += (C > (t0 > 0 ? px_fma(td, td, td) : -1.0) ? 1 : 0);
-            s_star += (C > px_fma(td, td, px_fma(3.0, td, 2.0)) ? 1 : 0);
-            s_star += (C > px_fma(td, td, px_fma(5.0, td, 6.0)) ? 1 : 0);
-            s_star += (C > px_fma(td, td, px_fma(7.0, td, 12.0)) ? 1 : 0);
-            s_star += (C > px_fma(td, td, px_fma(9.0, td, 20.0)) ? 1 : 0);
-        }
-    } else {
-        // the scan names a count: one step down or up if its neighbour is better
-        s_star = g_star;
-        double t_lo, t_hi;
-        if (has_near) {
-            t_lo = near[kNearU + s_star];
-            t_hi = near[kNearU + s_star + 1];
-        } else {
-            const double sd = (double)s_star;
-            t_lo = s_star > 0 ? px_fma(sd, sd, sd) : -1.0;
-            t_hi = px_fma(sd, sd, px_fma(3.0, sd, 2.0));
-        }
-        s_star = C <= t_lo ? s_star - 1 : (C > t_hi ? s_star + 1 : s_star);
-    }
-    return s_star;
+}
+
+template <int CH>
+__device__ __forceinline__ double scan_min(double C, const RunSteps &X, ScalarDoubles rsc, int Gs)
+{
+    const double Cs[1] = {C};
+    double wmin[1];
+    scan_mins<CH, 1>(wmin, Cs, X, rsc, Gs);
+    return wmin[0];
+}
+
+// ---- the feasible counts of a batch size --------------------------------------------
+// w(s+1) < w(s) precisely when C > (s+1)(s+2), both sides exact in fp64.  With U[t] = t (t+1) the argmin of w over all counts
+// therefore lies below the feasible ones s_lo .. s_hi precisely when C <= U[s_lo] (for s_lo = 0 that is C = 0, where w(0) is the
+// minimum anyway), and beyond them precisely when C > U[s_hi + 1]; the smallest feasible w is then w(s_lo) or w(s_hi), and the
+// minimum over all counts else.  None of this waits for the scan.
+struct Feasible {
+    int outside;        // the argmin over all counts is not feasible
+    double w;           // w at the end of the interval towards it
+};
+
+// bounds: s_lo | s_hi << 16.  near: pairs (1 / (s + 1), s) in LDS with the U[t] behind them.
+__device__ __forceinline__ Feasible feasible_end(double C, int bounds, LdsDoubles near)
+{
+    const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
+    const bool above = C > near[kNearU + 1 + s_hi];
+    const Double2 rc = *(const Double2 __attribute__((address_space(3))) *)(near + 2 * (above ? s_hi : s_lo));
+    return Feasible{(int)above | (int)(C <= near[kNearU + s_lo]), px_fma(C, rc.x, rc.y)};
+}
+
+// The same without a table of thresholds; recip(s, (double)s): 1 / (s + 1).
+template <typename RECIP>
+__device__ __forceinline__ Feasible feasible_end(double C, int s_lo, int s_hi, const RECIP &recip)
+{
+    const double lo = (double)s_lo, hi = (double)s_hi;
+    const bool above = C > px_fma(hi, hi, px_fma(3.0, hi, 2.0));
+    const int s = above ? s_hi : s_lo;
+    const double sd = above ? hi : lo;
+    return Feasible{(int)above | (int)(C <= px_fma(lo, lo, lo)), px_fma(C, recip(s, sd), sd)};
+}
+
+// The feasible count s_lo .. s_hi with the smallest w (no scan): the largest t with C > t (t + 1), clamped.
+// t is found in fp32, where sqrt(C + 1/4) - 1/2 is off by less than 0.003 for every count a grid can have (below 2^14); taken 0.01
+// lower it is t or t - 1, and the exact order of neighbours says which.  (C = 0: t = 0.  Any C beyond the grid: s_hi.)
+__device__ __forceinline__ int feasible_count(double C, int s_lo, int s_hi)
+{
+    int t = (int)(__builtin_amdgcn_sqrtf((float)C + 0.25f) - 0.51f);
+    t = t < s_hi ? t : s_hi;
+    const double td = (double)t;
+    t += C > px_fma(td, td, px_fma(3.0, td, 2.0)) ? 1 : 0;
+    t = t < s_hi ? t : s_hi;
+    return t > s_lo ? t : s_lo;
 }
 
 // The grid point a sweep elects: index into the job's batch-size grid and accumulation
@@ -618,39 +591,33 @@ __device__ __forceinline__ Pick elect(double kbest, int where, unsigned long lon
     return Pick{((wwhere >> 16) | (int)((second >> wl) & 1ull)) * kWave + wl, wwhere & 0xFFFF};
 }
 
-// All 64 lanes call this with the same (job, K >= 1, nodes).  Every lane returns the same result:
-// the feasible point with the smallest h over the whole grid (equal values resolve to the
-// lowest flat index i * Gs + s).
-// TABLED: last pass and feasible ranges come from the job's tables (K <= kTableK), else they are formed here.
+// All 64 lanes call this with the same (job, nodes, K within the tables).  Every lane returns the same result: the batch size
+// (index into the job's grid) of the feasible point with the smallest h over the whole grid, equal values to the lowest
+// index, or -1 when no point is feasible.  Its count is found where it is priced (price_tabled).
 // WHOLE: the caller has checked that Gm is a multiple of 64, so no lane runs past the grid of batch sizes.
-template <int CH, bool TABLED, bool WHOLE = false, bool STAGED = false>
-__device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, const RunSteps &X, const double *__restrict__ rs,
-                                           const double *__restrict__ rk, int Gm, int Gs, int K, int nodes,
-                                           LdsDoubles near = nullptr, bool has_near = false, int staged_row = -1)
+template <int CH, bool WHOLE = false, bool STAGED = false>
+__device__ __forceinline__ int sweep_pick(int lane, const JobTables &tb, const RunSteps &X, const double *__restrict__ rs, int Gm, int Gs, int K,
+                                          int nodes, LdsDoubles near, bool has_near, int staged_row)
 {
     // near: a copy of rs in LDS (quicker to read per lane) when has_near
-    // staged_row: where in `near` the terms of this (class, K) are staged (TABLED and STAGED; see kStageBase), or -1;
+    // staged_row: where in `near` the terms of this (class, K) are staged (STAGED; see kStageBase), or -1;
     // rows are staged only together with has_near
-    const int lane = lane_id();
     K = __builtin_amdgcn_readfirstlane(K);        // the same in every lane (see above): kept in scalar registers
     nodes = __builtin_amdgcn_readfirstlane(nodes);
-    // 1/K arrives through the scalar cache
-    const double rK = K < kRecipTable ? ((ScalarDoubles)rk)[K] : 1.0 / (double)K;
     const bool one_node = nodes == 1;
     // offsets inside one job's tables fit 32 bits (Gm <= 2^20)
-    const double2 *__restrict__ carow = tb.ca + (unsigned)((one_node ? kTableK : 0) + (TABLED ? K - 1 : 0)) * (unsigned)Gm;
-    const int32_t *__restrict__ srow = tb.srange + (unsigned)(TABLED ? K - 1 : 0) * (unsigned)Gm;
-    SyncTerm st = {0.0, 0.0, 1.0, 1.0, 0};
-    if constexpr (!TABLED) st = sync_term(q, K, one_node);
+    const double2 *__restrict__ carow = tb.ca + (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm;
+    const int32_t *__restrict__ srow = tb.srange + (unsigned)(K - 1) * (unsigned)Gm;
 
     // where this lane's terms of a staged row start in LDS (bytes from `near`): the (C, A0) pairs, the feasible ranges
     const unsigned at_ca = ((unsigned)lane << 4) + 8u * (unsigned)staged_row;
     const unsigned at_range = ((unsigned)lane << 2) + 8u * (unsigned)(staged_row + 2 * kStageGm);
 
     double kbest = __builtin_inf();   // smallest h seen by this lane
-    int where = 0;                    // its accumulation count | (index of its group of 64 batch sizes) << 16
-    unsigned long long second = 0;    // staged terms: the lanes whose `where` belongs to the second group (no index in `where`)
+    int where = 0;                    // the index of its group of 64 batch sizes << 16
+    unsigned long long second = 0;    // staged terms: the lanes whose best belongs to the second group (no index in `where`)
     const ScalarDoubles rsc = (ScalarDoubles)rs;
+    auto in_memory = [&](int s, double) { return *(const double *)((const char *)rs + 8u * (unsigned)s); };
 
     // One group of 64 batch sizes starting at i0.  G: the group's index when the terms are staged in LDS (the caller
     // stages only grids of one or two groups, so the index is a compile-time constant and the group's offset goes
@@ -662,97 +629,47 @@ __device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, co
         const int il = active ? i : Gm - 1;
         // a uniform base plus a 32-bit byte offset per lane: the address needs no 64-bit vector arithmetic;
         // the offsets of the 16-byte and the 4-byte entries are one shift-and-add each on the lane number
-        const unsigned at = (unsigned)il * 8u;
         // (the opaque statement keeps the two shifted counters on the scalar unit)
         unsigned i16 = (unsigned)i0 << 4, i4 = (unsigned)i0 << 2;
         asm("" : "+s"(i16), "+s"(i4));
         const unsigned at16 = WHOLE ? ((unsigned)lane << 4) + i16 : (unsigned)il * 16u;
         const unsigned at4 = WHOLE ? ((unsigned)lane << 2) + i4 : (unsigned)il * 4u;
-        double key = __builtin_inf();    // h of this batch size at its best feasible count s_c
-        int s_c = 0;
-        bool feasible;
-        if constexpr (TABLED) {
-            double tg, C, A0;                        // A0 = +inf when the batch size has no feasible count
-            int bounds;
-            if constexpr (g >= 0) {
-                // the row's offset is added to the lane's once per call; the group's is a constant
-                typedef const char __attribute__((address_space(3))) *LdsBytes;
-                const Double2 car = *(const Double2 __attribute__((address_space(3))) *)((LdsBytes)near + at_ca + 16 * kWave * g);
-                C = car.x;
-                A0 = car.y;
-                tg = *(LdsDoubles)((LdsBytes)near + ((unsigned)lane << 4) + (8 * kStageBase + 16 * kWave * g));
-                bounds = *(const int __attribute__((address_space(3))) *)((LdsBytes)near + at_range + 4 * kWave * g);
-            } else {
-                tg = *(const double *)((const char *)tb.tg + at16);
-                const double2 car = *(const double2 *)((const char *)carow + at16);
-                C = car.x;
-                A0 = car.y;
-                bounds = *(const int32_t *)((const char *)srow + at4);
-            }
-            const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
-            feasible = active;
-            // (rows are staged only in a workgroup that also keeps the table of reciprocals and thresholds in LDS)
-            const bool tables_near = g >= 0 ? true : has_near;
-            const int s_star = scan_argmin<CH>(C, X, rsc, Gs, near, tables_near);
-            // convex w, feasible counts s_lo .. s_hi: the constrained argmin is the clamped one
-            s_c = s_star < s_hi ? s_star : s_hi;
-            s_c = s_c > s_lo ? s_c : s_lo;
-            double r_c, sd_c;
-            if (tables_near) {
-                const Double2 rc = *(const Double2 __attribute__((address_space(3))) *)(near + 2 * s_c);
-                r_c = rc.x;
-                sd_c = rc.y;
-            } else {
-                r_c = *(const double *)((const char *)rs + 8u * (unsigned)s_c);
-                sd_c = (double)s_c;
-            }
-            const double w_c = px_fma(C, r_c, sd_c);
-            key = px_fma(tg, w_c, A0);
+        double tg, C, A0;                        // A0 = +inf when the batch size has no feasible count
+        int bounds;
+        if constexpr (g >= 0) {
+            // the row's offset is added to the lane's once per call; the group's is a constant
+            typedef const char __attribute__((address_space(3))) *LdsBytes;
+            const Double2 car = *(const Double2 __attribute__((address_space(3))) *)((LdsBytes)near + at_ca + 16 * kWave * g);
+            C = car.x;
+            A0 = car.y;
+            tg = *(LdsDoubles)((LdsBytes)near + ((unsigned)lane << 4) + (8 * kStageBase + 16 * kWave * g));
+            bounds = *(const int __attribute__((address_space(3))) *)((LdsBytes)near + at_range + 4 * kWave * g);
         } else {
-            const double2 tgr = *(const double2 *)((const char *)tb.tg + 2u * at);
-            const double tg = tgr.x;
-            const double last = last_pass(st, tg, tb.lntg[il]);
-            const double u = *(const double *)((const char *)tb.pu + at) * rK;
-            const double A0 = px_fma(u, tg, last);
-            const double B0 = (last - tg) * u;
-            int s_lo = 1, s_hi = 0;
-            feasible_range(tb.ql5[il], tb.qh5[il], rK, Gs, s_lo, s_hi);
-            if (!active) s_hi = -1;
-            for (int s0 = 0; s0 < Gs; s0 += CH) {
-                const double A0s = s0 == 0 ? A0 : px_fma((double)s0, tg, A0);
-                const double kmin = sweep_chunk_plain<CH>(tg, A0s, B0, rs + s0, s_lo - s0, s_hi - s0);
-                if (kmin < key) {
-                    key = kmin;
-                    s_c = s0 + (__double2loint(kmin) & 31);
-                }
-            }
-            feasible = key < __builtin_inf();
-            if (feasible) {
-                // the same exact order of neighbours as in the tabled path, inside the feasible counts; the key
-                // is then formed again without index bits
-                const double C = B0 * tgr.y, sd = (double)s_c;
-                const double t_lo = px_fma(sd, sd, sd), t_hi = px_fma(sd, sd, px_fma(3.0, sd, 2.0));
-                if (s_c > s_lo && C <= t_lo) s_c -= 1;
-                else if (s_c < s_hi && C > t_hi) s_c += 1;
-                key = px_fma(B0, rs[s_c], px_fma((double)s_c, tg, A0));
-            }
+            tg = *(const double *)((const char *)tb.tg + at16);
+            const double2 car = *(const double2 *)((const char *)carow + at16);
+            C = car.x;
+            A0 = car.y;
+            bounds = *(const int32_t *)((const char *)srow + at4);
         }
+        // (rows are staged only in a workgroup that also keeps the table of reciprocals and thresholds in LDS)
+        const double wmin = scan_min<CH>(C, X, rsc, Gs);
+        const Feasible f = g >= 0 || has_near ? feasible_end(C, bounds, near) : feasible_end(C, bounds & 0xFFFF, bounds >> 16, in_memory);
+        const double key = px_fma(tg, f.outside ? f.w : wmin, A0);
         if constexpr (g == 0) {
             // the first group starts the lane's minimum (a batch size without a feasible count has h = +inf)
             kbest = key;
-            where = s_c;
         } else if constexpr (g == 1) {
             // which lanes hold a batch size of the second group stays a lane mask in scalar registers
-            const bool better = key < kbest;
-            second = __builtin_amdgcn_ballot_w64(better);
-            kbest = better ? key : kbest;
-            where = better ? s_c : where;
-        } else if (feasible && key < kbest) {
+            // (the smaller of a number and a NaN, where T_grad overflows, is the number)
+            const double least = min_f64(kbest, key);
+            second = __builtin_amdgcn_ballot_w64(least != kbest);
+            kbest = least;
+        } else if (active && key < kbest) {
             kbest = key;
-            where = s_c | ((i0 / kWave) << 16);
+            where = (i0 / kWave) << 16;
         }
     };
-    if (TABLED && STAGED && staged_row >= 0) {
+    if (STAGED && staged_row >= 0) {
         group(0, std::integral_constant<int, 0>());
         if (Gm > kWave) group(kWave, std::integral_constant<int, 1>());
     } else {
@@ -762,15 +679,67 @@ __device__ __forceinline__ Pick sweep_pick(const Job &q, const JobTables &tb, co
             asm volatile("s_add_i32 %0, %0, 64" : "+s"(i0) : : "scc");
         }
     }
+    return elect(kbest, where, second, Gs).i;
+}
 
-    return elect(kbest, where, second, Gs);
+// The sweep of a row the tables do not hold, by a plain loop over the feasible counts of each batch size; it returns the
+// elected point.  rs, rk: 1 / (s + 1), 1 / K.
+template <int CH>
+__device__ __forceinline__ Pick sweep_pick_beyond(const Job &q, const JobTables &tb, const double *__restrict__ rs, const double *__restrict__ rk,
+                                                  int Gm, int Gs, int K, int nodes)
+{
+    const int lane = lane_id();
+    K = __builtin_amdgcn_readfirstlane(K);
+    nodes = __builtin_amdgcn_readfirstlane(nodes);
+    // 1/K arrives through the scalar cache
+    const double rK = K < kRecipTable ? ((ScalarDoubles)rk)[K] : 1.0 / (double)K;
+    const SyncTerm st = sync_term(q, K, nodes == 1);
+    double kbest = __builtin_inf();   // smallest h seen by this lane
+    int where = 0;                    // its accumulation count | (index of its group of 64 batch sizes) << 16
+    for (int i0 = 0; i0 < Gm; i0 += kWave) {
+        const int i = i0 + lane;
+        const bool active = i < Gm;
+        const int il = active ? i : Gm - 1;
+        const double2 tgr = tb.tg[il];
+        const double tg = tgr.x;
+        const double last = last_pass(st, tg, tb.lntg[il]);
+        const double u = tb.pu[il] * rK;
+        const double A0 = px_fma(u, tg, last);
+        const double B0 = (last - tg) * u;
+        int s_lo = 1, s_hi = 0, s_c = 0;
+        feasible_range(tb.ql5[il], tb.qh5[il], rK, Gs, s_lo, s_hi);
+        if (!active) s_hi = -1;
+        double key = __builtin_inf();    // h of this batch size at its best feasible count s_c
+        for (int s0 = 0; s0 < Gs; s0 += CH) {
+            const double A0s = s0 == 0 ? A0 : px_fma((double)s0, tg, A0);
+            const double kmin = sweep_chunk_plain<CH>(tg, A0s, B0, rs + s0, s_lo - s0, s_hi - s0);
+            if (kmin < key) {
+                key = kmin;
+                s_c = s0 + (__double2loint(kmin) & 31);
+            }
+        }
+        if (key < __builtin_inf()) {
+            // the plain loop's keys carry the count in their low bits: the exact order of neighbours inside the feasible
+            // counts, and the key again without index bits
+            const double C = B0 * tgr.y, sd = (double)s_c;
+            const double t_lo = px_fma(sd, sd, sd), t_hi = px_fma(sd, sd, px_fma(3.0, sd, 2.0));
+            if (s_c > s_lo && C <= t_lo) s_c -= 1;
+            else if (s_c < s_hi && C > t_hi) s_c += 1;
+            key = px_fma(B0, rs[s_c], px_fma((double)s_c, tg, A0));
+            if (key < kbest) {
+                kbest = key;
+                where = s_c | ((i0 / kWave) << 16);
+            }
+        }
+    }
+    return elect(kbest, where, 0ull, Gs);
 }
 
 // The same election for four (job, K, nodes) at once, one per row of 16 lanes, for small grids, where a sweep per
 // wavefront spends more on its cross-lane steps than on the grid: every row of 16 lanes calls this with its own
 // K (1 .. kTableK) and its own one_node (the same in all 16 lanes of a row; the job is the same for the whole
 // wavefront), lane l of a row takes batch sizes l, l + 16, ..., and every lane of a row returns the row's
-// result: (i << 16) | s of the feasible point with the smallest h, equal values to the lowest (i, s), or -1 when
+// result: the batch size of the feasible point with the smallest h, equal values to the lowest, or -1 when
 // the row has no feasible point.  Per (K, batch size) the arithmetic is that of sweep_pick, instruction for
 // instruction, so both elect the same point.
 template <int CH, bool WHOLE>
@@ -783,39 +752,42 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
     const unsigned ca_row = (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm * 16u;
     const unsigned s_row = (unsigned)(K - 1) * (unsigned)Gm * 4u;
     double kbest = __builtin_inf();   // smallest h seen by this lane
-    int where = 0;                    // its (i << 16) | s
+    int where = 0;                    // its batch size
     const ScalarDoubles rsc = (ScalarDoubles)rs;
-    for (int i0 = 0; i0 < Gm; i0 += 16) {
-        const int i = i0 + l16;
-        const bool feasible = WHOLE || i < Gm;       // WHOLE: Gm is a multiple of 64, so no lane runs past the grid
-        const unsigned il = (unsigned)(feasible ? i : Gm - 1);
-        const double tg = *(const double *)((const char *)tb.tg + 16u * il);
-        const double2 car = *(const double2 *)((const char *)tb.ca + (ca_row + 16u * il));
-        const double C = car.x, A0 = car.y;         // A0 = +inf when the batch size has no feasible count
-        const int bounds = *(const int32_t *)((const char *)tb.srange + (s_row + 4u * il));
-        const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
-        const int s_star = scan_argmin<CH>(C, X, rsc, Gs, near, has_near);
-        // convex w, feasible counts s_lo .. s_hi: the constrained argmin is the clamped one
-        int s_c = s_star < s_hi ? s_star : s_hi;
-        s_c = s_c > s_lo ? s_c : s_lo;
-        double r_c, sd_c;
-        if (has_near) {
-            const Double2 rc = *(const Double2 __attribute__((address_space(3))) *)(near + 2 * s_c);
-            r_c = rc.x;
-            sd_c = rc.y;
-        } else {
-            r_c = rs[s_c];
-            sd_c = (double)s_c;
+    auto in_memory = [&](int s, double) { return *(const double *)((const char *)rs + 8u * (unsigned)s); };
+    // NC sets of 16 batch sizes from i0 on: their terms are asked for together and share the reciprocals of the scan.
+    auto sets = [&](const int i0, auto COUNT) __attribute__((always_inline)) {
+        constexpr int NC = decltype(COUNT)::value;
+        double tg[NC], A0[NC], C[NC], wmin[NC];
+        int bounds[NC];
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            const int i = i0 + 16 * n + l16;
+            const unsigned il = (unsigned)(WHOLE || i < Gm ? i : Gm - 1);      // WHOLE: Gm is a multiple of 64, so no lane runs past the grid
+            bounds[n] = *(const int32_t *)((const char *)tb.srange + (s_row + 4u * il));
+            const double2 car = *(const double2 *)((const char *)tb.ca + (ca_row + 16u * il));
+            C[n] = car.x;
+            A0[n] = car.y;                          // A0 = +inf when the batch size has no feasible count
+            tg[n] = *(const double *)((const char *)tb.tg + 16u * il);
         }
-        const double w_c = px_fma(C, r_c, sd_c);
-        const double key = px_fma(tg, w_c, A0);
-        if (feasible && key < kbest) {
-            kbest = key;
-            where = (i << 16) | s_c;
+        scan_mins<CH, NC>(wmin, C, X, rsc, Gs);
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            const int i = i0 + 16 * n + l16;
+            const Feasible f = has_near ? feasible_end(C[n], bounds[n], near) : feasible_end(C[n], bounds[n] & 0xFFFF, bounds[n] >> 16, in_memory);
+            const double key = px_fma(tg[n], f.outside ? f.w : wmin[n], A0[n]);
+            if ((WHOLE || i < Gm) && key < kbest) {
+                kbest = key;
+                where = i;
+            }
         }
+    };
+    for (int i0 = 0; i0 < Gm; i0 += 32) {
+        if (WHOLE || i0 + 16 < Gm) sets(i0, std::integral_constant<int, 2>());
+        else sets(i0, std::integral_constant<int, 1>());
     }
     // Positive doubles order like their bit patterns: three unsigned minima over the row, the high words, the
-    // low words among the lanes that hold the smallest high word, and (i, s) among the lanes that hold both.
+    // low words among the lanes that hold the smallest high word, and the batch sizes among the lanes that hold both.
     const unsigned hi = (unsigned)__double2hiint(kbest), lo = (unsigned)__double2loint(kbest);
     const unsigned hmin = row16_min(hi);
     const unsigned lmin = row16_min(hi == hmin ? lo : 0xFFFFFFFFu);
@@ -823,17 +795,26 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
     return hmin >= 0x7FF00000u ? -1 : (int)first;             // every lane of the row still holds +inf: no point
 }
 
-// Eq. 4 at grid point (i, s) in the paper's order of operations.  Arguments may differ
-// from lane to lane.
-__device__ __forceinline__ Best price_point(const Job &q, const JobTables &tb, int Gm, int K, bool one_node, int i, int s)
+// Eq. 4 for batch size i of a tabled row at the count the sweep's minimum has there, in the paper's order of operations.  Arguments
+// may differ from lane to lane.
+__device__ __forceinline__ Best price_tabled(const Job &q, const JobTables &tb, int Gm, int K, bool one_node, int i)
+{
+    if (i < 0) return Best{0.0, -1, -1};
+    const unsigned row = (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm + (unsigned)i;
+    // (all five asked for before the first is waited for)
+    const double C = tb.ca[row].x, last = tb.lt[row], tg = tb.tg[i].x;
+    const int bounds = tb.srange[(unsigned)(K - 1) * (unsigned)Gm + (unsigned)i], m = tb.m[i];
+    const int s = feasible_count(C, bounds & 0xFFFF, bounds >> 16);
+    return Best{goodput_point(q, (double)K * (double)m, tg, last, s), m, s};
+}
+
+// The same at grid point (i, s) of a row beyond the tables.
+__device__ __forceinline__ Best price_beyond(const Job &q, const JobTables &tb, int K, bool one_node, int i, int s)
 {
     if (i < 0) return Best{0.0, -1, -1};
     const int m = tb.m[i];
     const double tg = tb.tg[i].x;
-    double last;
-    if (tabled_row(K, one_node, tb.k1)) last = tb.lt[(unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm + (unsigned)i];
-    else last = last_pass(sync_term(q, K, one_node), tg, tb.lntg[i]);
-    return Best{goodput_point(q, (double)K * (double)m, tg, last, s), m, s};
+    return Best{goodput_point(q, (double)K * (double)m, tg, last_pass(sync_term(q, K, one_node), tg, tb.lntg[i]), s), m, s};
 }
 
 __device__ __forceinline__ JobTables job_tables(const FitnessArgs &a, int j)
@@ -982,16 +963,15 @@ __device__ __forceinline__ Best sweep_f32(const JobF32 &q, const JobTables &tb, 
     return sweep_beyond_f32(q, tb.m, terms, K < kRecipTable ? rk[K] : 1.0 / (double)K, Gm, Gs, K, nodes);
 }
 
-// ---- fp32 variant: the same scan-and-clamp sweep as the fp64 one ------------------------------
-// For GPU counts within the tables.  Lane l owns batch sizes i = l, l + 64, ...; for each it scans
+// ---- fp32 variant: the same sweep as the fp64 one ------------------------------
+// For GPU counts within the tables.  Lane l owns batch sizes i = l, l + 64, ...; for each it takes the smallest
 // w(s) = s + C / (s + 1) over all accumulation counts in chunks of 16, one v_fma_f32 per grid point
 // (1/(s+1) from scalar registers, s from sixteen vector registers that hold 0 .. 15 for the whole
-// kernel), one v_bfi_b32 that puts the position in the chunk into the low four mantissa bits, and one
-// v_min3_f32 per two points: five instructions per two grid points.  The argmin over all counts is then
-// put right between neighbours (the same exact test as in fp64: w(s+1) < w(s) exactly when
-// C > (s+1)(s+2)), clamped to the feasible counts of (job, K, i) from the table, and h is formed there.
-// The wave takes the smallest h (equal values: lowest flat index).  The elected point is priced with
-// Eq. 4 in the plain form, in fp32 (price_point_f32).  T_grad, u and C are formed in fp32 from the
+// kernel) and one v_min3_f32 per two points: three instructions per two grid points.  Where the argmin over all counts is not
+// feasible w is taken at the end of the feasible counts towards it, by the same exact test as in fp64 (w(s+1) < w(s) exactly when
+// C > (s+1)(s+2); the products are exact for grids of up to 4094 counts).
+// The wave takes the smallest h (equal values: lowest batch size).  The elected point's count follows from its C, and the point is
+// priced with Eq. 4 in the plain form, in fp32 (price_point_f32).  T_grad, u and C are formed in fp32 from the
 // parameters rounded to fp32; the last pass of Eq. 10 is the fp64 table rounded to fp32.
 typedef const float __attribute__((address_space(4))) *ScalarFloats;
 typedef const float __attribute__((address_space(3))) *LdsFloats;
@@ -1011,184 +991,183 @@ __device__ __forceinline__ RunStepsF32 make_run_steps_f32()
 }
 
 // Two grid points at positions B, B + 1 of a chunk: their values of w relative to the chunk's first count,
-// tagged with their positions, folded into the running minimum.
+// folded into the running minimum.
 template <int B>
-__device__ __forceinline__ void scan_two_f32(float &kmin, float C, float r0, float r1, const RunStepsF32 &X)
+__device__ __forceinline__ void scan_two_f32(float &wmin, float C, float r0, float r1, const RunStepsF32 &X)
 {
     float w0, w1;
-    int k0, k1;
     asm("v_fma_f32 %0, %1, %2, %3" : "=v"(w0) : "v"(C), "s"(r0), "v"(X.x[B]));
     asm("v_fma_f32 %0, %1, %2, %3" : "=v"(w1) : "v"(C), "s"(r1), "v"(X.x[B + 1]));
-    asm("v_bfi_b32 %0, 15, %1, %2" : "=v"(k0) : "n"(B), "v"(__float_as_int(w0)));
-    asm("v_bfi_b32 %0, 15, %1, %2" : "=v"(k1) : "n"(B + 1), "v"(__float_as_int(w1)));
-    if constexpr (B == 0) asm("v_min_f32 %0, %1, %2" : "=v"(kmin) : "v"(__int_as_float(k0)), "v"(__int_as_float(k1)));
-    else asm("v_min3_f32 %0, %0, %1, %2" : "+v"(kmin) : "v"(__int_as_float(k0)), "v"(__int_as_float(k1)));
+    if constexpr (B == 0) asm("v_min_f32 %0, %1, %2" : "=v"(wmin) : "v"(w0), "v"(w1));
+    else asm("v_min3_f32 %0, %0, %1, %2" : "+v"(wmin) : "v"(w0), "v"(w1));
 }
 
 template <int CH, int B = 0>
-__device__ __forceinline__ void scan_chunk_f32(float &kmin, float C, ScalarFloats r, const RunStepsF32 &X)
+__device__ __forceinline__ void scan_chunk_f32(float &wmin, float C, ScalarFloats r, const RunStepsF32 &X)
 {
     if constexpr (B < CH) {
-        scan_two_f32<B>(kmin, C, r[B], r[B + 1], X);
-        scan_chunk_f32<CH, B + 2>(kmin, C, r, X);
+        scan_two_f32<B>(wmin, C, r[B], r[B + 1], X);
+        scan_chunk_f32<CH, B + 2>(wmin, C, r, X);
     }
 }
 
-// The accumulation count with the smallest w(s) among all counts of the grid, equal values to the lower count.
+// The smallest w(s) among all counts of the grid.
 template <int CH>
-__device__ __forceinline__ int scan_argmin_f32(float C, const RunStepsF32 &X, ScalarFloats rsc, int Gs)
+__device__ __forceinline__ float scan_min_f32(float C, const RunStepsF32 &X, ScalarFloats rsc, int Gs)
 {
-    // argmin of w over all counts: chunk by chunk, values relative to the chunk's first count
     float wmin;
     scan_chunk_f32<CH>(wmin, C, rsc, X);
-    int s_star = __float_as_int(wmin) & 15;
     for (int s0 = CH; s0 < Gs; s0 += CH) {
         float w;
-        scan_chunk_f32<CH>(w, C, rsc + s0, X);
-        const float moved = w + (float)s0;                               // strictly smaller only: ties keep the smaller s
-        if (moved < wmin) {
-            wmin = moved;
-            s_star = s0 + (__float_as_int(w) & 15);
-        }
+        scan_chunk_f32<CH>(w, C, rsc + s0, X);               // values relative to the chunk's first count
+        wmin = fminf(wmin, w + (float)s0);
     }
-    // neighbours in their exact order (the tags may have swapped two that agree to 2^-19)
-    {
-        const float sd = (float)s_star;
-        const float t_lo = s_star > 0 ? fmaf(sd, sd, sd) : -1.0f, t_hi = fmaf(sd, sd, fmaf(3.0f, sd, 2.0f));
-        s_star = C <= t_lo ? s_star - 1 : (C > t_hi ? s_star + 1 : s_star);
-    }
-    return s_star;
+    return wmin;
+}
+
+// Eq. 9 in fp32.
+__device__ __forceinline__ float t_sync_f32(const JobF32 &q, int K, bool one_node)
+{
+    if (K <= 1) return 0.0f;
+    return one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
+}
+
+// The terms of one batch size: h(s) = A0 + T_grad (s + C / (s + 1)).  tabled: the last pass of Eq. 10 as the fp64 table has it.
+struct TermsF32 {
+    float tg, last, A0, C;
+};
+
+__device__ __forceinline__ TermsF32 terms_f32(const JobF32 &q, float ts, float Kf, int m, float tabled)
+{
+    TermsF32 t;
+    const float mf = (float)m;
+    t.tg = q.alpha_g + q.beta_g * mf;                                         // Eq. 8
+    t.last = ts == 0.0f ? t.tg : (q.gamma == 1.0f ? t.tg + ts : tabled);      // Eq. 10
+    const float u = q.phi * __builtin_amdgcn_rcpf(Kf * mf);
+    t.A0 = fmaf(u, t.tg, t.last);
+    t.C = (t.last - t.tg) * u * __builtin_amdgcn_rcpf(t.tg);
+    return t;
+}
+
+// The smallest h over the feasible counts s_lo .. s_hi (see Feasible); wmin: the smallest w over all counts, recip(s): 1 / (s + 1).
+template <typename RECIP>
+__device__ __forceinline__ float feasible_h_f32(const TermsF32 &t, int s_lo, int s_hi, float wmin, const RECIP &recip)
+{
+    const float lo = (float)s_lo, hi = (float)s_hi;
+    const bool above = t.C > fmaf(hi, hi, fmaf(3.0f, hi, 2.0f)), below = t.C <= fmaf(lo, lo, lo);
+    const float w = fmaf(t.C, recip(above ? s_hi : s_lo), above ? hi : lo);
+    return fmaf(t.tg, (int)above | (int)below ? w : wmin, t.A0);
+}
+
+// The feasible count with the smallest w (feasible_count in fp32).
+__device__ __forceinline__ int feasible_count_f32(float C, int s_lo, int s_hi)
+{
+    int t = (int)(__builtin_amdgcn_sqrtf(C + 0.25f) - 0.51f);
+    t = t < s_hi ? t : s_hi;
+    const float td = (float)t;
+    t += C > fmaf(td, td, fmaf(3.0f, td, 2.0f)) ? 1 : 0;
+    t = t < s_hi ? t : s_hi;
+    return t > s_lo ? t : s_lo;
 }
 
 // All 64 lanes call this with the same (job, 1 <= K <= kTableK, nodes); every lane returns the same result.
-// rsf: 1/(s+1) in fp32, padded to a multiple of 32 counts; near: a copy of it in LDS when has_near.
+// rsf: 1/(s+1) in fp32, padded to a multiple of 32 counts; near: a copy of it in LDS when has_near.  Returns the batch size of the
+// feasible point with the smallest h, or -1.
 template <int CH, bool WHOLE>
-__device__ __forceinline__ Pick sweep_pick_f32(const JobF32 &q, const JobTables &tb, const RunStepsF32 &X,
-                                               const float *__restrict__ rsf, int Gm, int Gs, int K, int nodes,
-                                               LdsFloats near = nullptr, bool has_near = false)
+__device__ __forceinline__ int sweep_pick_f32(const JobF32 &q, const JobTables &tb, const RunStepsF32 &X,
+                                              const float *__restrict__ rsf, int Gm, int Gs, int K, int nodes,
+                                              LdsFloats near = nullptr, bool has_near = false)
 {
-    static_assert(CH == 8 || CH == 16, "positions of a chunk fit four tag bits");
+    static_assert(CH == 8 || CH == 16, "sixteen steps in registers");
     const int lane = lane_id();
     K = __builtin_amdgcn_readfirstlane(K);
     nodes = __builtin_amdgcn_readfirstlane(nodes);
     const bool one_node = nodes == 1;
-    const float Kf = (float)K;
-    float ts = 0.0f;                                                          // Eq. 9
-    if (K > 1) ts = one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
-    const int mode = ts == 0.0f ? 0 : (q.gamma == 1.0f ? 1 : 2);
+    const float Kf = (float)K, ts = t_sync_f32(q, K, one_node);
     const double *__restrict__ lrow = tb.lt + (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm;
     const int32_t *__restrict__ srow = tb.srange + (unsigned)(K - 1) * (unsigned)Gm;
     const ScalarFloats rsc = (ScalarFloats)rsf;
+    auto recip = [&](int s) { return has_near ? near[s] : rsf[s]; };
 
     float kbest = __builtin_inff();   // smallest h seen by this lane
-    int where = 0;                    // its accumulation count | (index of its group of 64 batch sizes) << 16
+    int where = 0;                    // the index of its group of 64 batch sizes
     for (int i0 = 0; i0 < Gm; i0 += kWave) {
         const int i = i0 + lane;
         const bool active = WHOLE || i < Gm;
         const int il = active ? i : Gm - 1;
-        const float mf = (float)tb.m[il];
-        const float tg = q.alpha_g + q.beta_g * mf;                           // Eq. 8
-        float last;                                                           // Eq. 10
-        if (mode == 0) last = tg;
-        else if (mode == 1) last = tg + ts;
-        else last = (float)lrow[il];
-        const float u = q.phi * __builtin_amdgcn_rcpf(Kf * mf);
-        const float A0 = fmaf(u, tg, last);
-        const float C = (last - tg) * u * __builtin_amdgcn_rcpf(tg);
+        const TermsF32 t = terms_f32(q, ts, Kf, tb.m[il], (float)lrow[il]);
         const int bounds = srow[il];
         const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
         const bool feasible = active && s_lo <= s_hi;
-        const int s_star = scan_argmin_f32<CH>(C, X, rsc, Gs);
-        int s_c = s_star < s_hi ? s_star : s_hi;
-        s_c = s_c > s_lo ? s_c : s_lo;
-        const float r_c = has_near ? near[s_c] : rsf[s_c];
-        const float key = fmaf(tg, fmaf(C, r_c, (float)s_c), A0);
+        const float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<CH>(t.C, X, rsc, Gs), recip);
         if (feasible && key < kbest) {
             kbest = key;
-            where = s_c | ((i0 / kWave) << 16);
+            where = i0 / kWave;
         }
     }
     // positive floats order like their bit patterns
     const unsigned bits = (unsigned)__float_as_int(kbest);
     const unsigned bmin = wave_min(bits);
-    if (bmin >= 0x7F800000u) return Pick{-1, -1};               // every lane still holds +inf (or a NaN)
+    if (bmin >= 0x7F800000u) return -1;                         // every lane still holds +inf (or a NaN)
     unsigned long long winners = __builtin_amdgcn_ballot_w64(bits == bmin);
     if (winners & (winners - 1)) {
-        // equal values: the lowest flat index i * Gs + s
+        // equal values: the lowest batch size
         const bool top = ((winners >> lane) & 1ull) != 0;
-        const int flat = ((where >> 16) * kWave + lane) * Gs + (where & 0xFFFF);
-        const int first = wave_min(top ? flat : 0x7FFFFFFF);
-        winners &= __builtin_amdgcn_ballot_w64(flat == first);
+        return wave_min(top ? where * kWave + lane : 0x7FFFFFFF);
     }
     const int wl = __ffsll(winners) - 1;
-    const int wwhere = __builtin_amdgcn_readlane(where, wl);
-    return Pick{(wwhere >> 16) * kWave + wl, wwhere & 0xFFFF};
+    return __builtin_amdgcn_readlane(where, wl) * kWave + wl;
 }
 
 // The same election for four (job, K, placement) at once, one per row of 16 lanes, as sweep_pick_rows does in fp64: lane l of
-// a row takes batch sizes l, l + 16, ...; every lane of a row returns (i << 16) | s of the row's point, or -1.  Per (K, batch
+// a row takes batch sizes l, l + 16, ...; every lane of a row returns the batch size of the row's point, or -1.  Per (K, batch
 // size) the arithmetic is that of sweep_pick_f32.
 template <int CH, bool WHOLE>
 __device__ __forceinline__ int sweep_pick_rows_f32(const JobF32 &q, const JobTables &tb, const RunStepsF32 &X, const float *__restrict__ rsf,
                                                    int Gm, int Gs, int K, bool one_node, LdsFloats near, bool has_near)
 {
     const int l16 = lane_id() & 15;
-    const float Kf = (float)K;
-    float ts = 0.0f;                                                          // Eq. 9
-    if (K > 1) ts = one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
+    const float Kf = (float)K, ts = t_sync_f32(q, K, one_node);
     // byte offsets inside one job's tables, 32 bits each (see sweep_pick_rows)
     const unsigned l_row = (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm * 8u;
     const unsigned s_row = (unsigned)(K - 1) * (unsigned)Gm * 4u;
     const ScalarFloats rsc = (ScalarFloats)rsf;
+    auto recip = [&](int s) { return has_near ? near[s] : rsf[s]; };
     float kbest = __builtin_inff();
     int where = 0x7FFFFFFF;
     for (int i0 = 0; i0 < Gm; i0 += 16) {
         const int i = i0 + l16;
         const bool active = WHOLE || i < Gm;
         const unsigned il = (unsigned)(active ? i : Gm - 1);
-        const float mf = (float)tb.m[il];
-        const float tg = q.alpha_g + q.beta_g * mf;                           // Eq. 8
-        float last = (float)*(const double *)((const char *)tb.lt + (l_row + 8u * il));     // Eq. 10
-        last = ts == 0.0f ? tg : (q.gamma == 1.0f ? tg + ts : last);
-        const float u = q.phi * __builtin_amdgcn_rcpf(Kf * mf);
-        const float A0 = fmaf(u, tg, last);
-        const float C = (last - tg) * u * __builtin_amdgcn_rcpf(tg);
+        const TermsF32 t = terms_f32(q, ts, Kf, tb.m[il], (float)*(const double *)((const char *)tb.lt + (l_row + 8u * il)));
         const int bounds = *(const int32_t *)((const char *)tb.srange + (s_row + 4u * il));
         const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
         const bool feasible = active && s_lo <= s_hi;
-        const int s_star = scan_argmin_f32<CH>(C, X, rsc, Gs);
-        int s_c = s_star < s_hi ? s_star : s_hi;
-        s_c = s_c > s_lo ? s_c : s_lo;
-        const float r_c = has_near ? near[s_c] : rsf[s_c];
-        const float key = fmaf(tg, fmaf(C, r_c, (float)s_c), A0);
+        const float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<CH>(t.C, X, rsc, Gs), recip);
         if (feasible && key < kbest) {
             kbest = key;
-            where = (i << 16) | s_c;
+            where = i;
         }
     }
-    // positive floats order like their bit patterns; equal values: the lowest (i, s)
+    // positive floats order like their bit patterns; equal values: the lowest batch size
     const unsigned bits = (unsigned)__float_as_int(kbest);
     const unsigned bmin = row16_min(bits);
     const unsigned first = row16_min(bits == bmin ? (unsigned)where : 0x7FFFFFFFu);
     return bmin >= 0x7F800000u ? -1 : (int)first;
 }
 
-// Eq. 4 at grid point (i, s) in the plain form, in fp32, for a GPU count within the tables.  Arguments may
+// Eq. 4 for batch size i at its best feasible count, in the plain form, in fp32, for a GPU count within the tables.  Arguments may
 // differ from lane to lane.
-__device__ __forceinline__ Best price_point_f32(const JobF32 &q, const JobTables &tb, int Gm, int K, bool one_node, int i, int s)
+__device__ __forceinline__ Best price_point_f32(const JobF32 &q, const JobTables &tb, int Gm, int K, bool one_node, int i)
 {
     if (i < 0) return Best{0.0, -1, -1};
     const int m = tb.m[i];
-    const float mf = (float)m;
-    const float tg = q.alpha_g + q.beta_g * mf;                               // Eq. 8
-    float ts = 0.0f;                                                          // Eq. 9
-    if (K > 1) ts = one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
-    float last;                                                               // Eq. 10
-    if (ts == 0.0f) last = tg;
-    else if (q.gamma == 1.0f) last = tg + ts;
-    else last = (float)tb.lt[(unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm + (unsigned)i];
-    const float M = (float)K * mf * (float)(s + 1);
-    const float t_iter = (float)s * tg + last;                                // Eq. 11
+    const TermsF32 t = terms_f32(q, t_sync_f32(q, K, one_node), (float)K, m,
+                                 (float)tb.lt[(unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm + (unsigned)i]);
+    const int bounds = tb.srange[(unsigned)(K - 1) * (unsigned)Gm + (unsigned)i];
+    const int s = feasible_count_f32(t.C, bounds & 0xFFFF, bounds >> 16);
+    const float M = (float)K * (float)m * (float)(s + 1);
+    const float t_iter = (float)s * t.tg + t.last;                            // Eq. 11
     const float g = (M / t_iter) * (q.a / (q.phi + M));                       // Eq. 7 x Eq. 6
     return Best{(double)g, m, s};
 }
@@ -1203,8 +1182,7 @@ __device__ __forceinline__ Best sweep_any_f32(const JobF32 &q, const JobTables &
     nodes = __builtin_amdgcn_readfirstlane(nodes);
     if (K <= 0) return Best{0.0, -1, -1};
     if (!tabled_row(K, nodes == 1, tb.k1)) return sweep_f32(q, tb, rk, Gm, Gs, K, nodes);
-    const Pick pick = sweep_pick_f32<CH, false>(q, tb, make_run_steps_f32(), rsf, Gm, Gs, K, nodes);
-    return price_point_f32(q, tb, Gm, K, nodes == 1, pick.i, pick.s);
+    return price_point_f32(q, tb, Gm, K, nodes == 1, sweep_pick_f32<CH, false>(q, tb, make_run_steps_f32(), rsf, Gm, Gs, K, nodes));
 }
 
 // ---- per job: what the status word says of its parameters, and its current row ------------------
@@ -1249,39 +1227,36 @@ __device__ __forceinline__ CurrentRow current_row(const FitnessArgs &a, int j)
 // ---- the argmax of one (job, K, placement) in place ------------------------------------------
 // What the calls that ask for a handful of argmaxes per job need (fair shares, memoised rows, rows beyond the memo table,
 // the queries outside the search): the same election as sweep_pick without any table.  Lane l forms the terms of its batch
-// sizes itself; the best accumulation count needs no scan, since w(s) = s + C / (s + 1) falls from t - 1 to t precisely when
-// C > t (t + 1), so its argmin over all counts is the largest t with C > t (t + 1), or 0.
-__device__ __forceinline__ int argmin_count(double C)
+// sizes itself; the best accumulation count needs no scan (feasible_count).
+
+// The terms of one batch size with 1/K = rK: h(s) = A0 + T_grad (s + C / (s + 1)), and its feasible counts.
+struct RowTerms {
+    double A0, B0, C;
+    int s_lo, s_hi;
+
+    __device__ __forceinline__ bool none() const { return s_lo > s_hi || s_hi < 0; }
+};
+
+__device__ __forceinline__ RowTerms row_terms(const GridPoint &g, double last, double rK, int Gs)
 {
-    // t is found in fp32, where it is off by less than one for every count a grid can have (below 2^14; C is capped far
-    // beyond them), and put right by the exact order of neighbours
-    const float c = (float)fmin(C, 1073741824.0);
-    const int t = (int)(__builtin_amdgcn_sqrtf(c + 0.25f) - 0.5f);
-    const double td = (double)t;
-    const double t_lo = t > 0 ? px_fma(td, td, td) : -1.0, t_hi = px_fma(td, td, px_fma(3.0, td, 2.0));
-    return C <= t_lo ? t - 1 : (C > t_hi ? t + 1 : t);
+    RowTerms t;
+    feasible_range(g.ql5, g.qh5, rK, Gs, t.s_lo, t.s_hi);
+    const double u = g.pu * rK;
+    t.A0 = px_fma(u, g.tg, last);
+    t.B0 = (last - g.tg) * u;
+    t.C = t.B0 * g.rtg;
+    return t;
 }
 
-// h of one batch size at its best feasible count s_c (+inf when no count is feasible).  argmin: the best count of all, given C.
-// tabled: h in the form the tables
+// h of one batch size at its best feasible count s_c (+inf when no count is feasible).  tabled: h in the form the tables
 // give it (C and A0), else in the form of the untabled sweep: rounding decides elections between equal points, so a row
 // keeps the form its sweep has.
-template <typename ARGMIN>
-__device__ __forceinline__ double best_count(const GridPoint &g, double last, double rK, int Gs, bool tabled, const ARGMIN &argmin, int &s_c)
+__device__ __forceinline__ double best_count(const GridPoint &g, const RowTerms &t, bool tabled, int &s_c)
 {
-    int s_lo, s_hi;
-    feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
-    const double u = g.pu * rK;
-    const double A0 = px_fma(u, g.tg, last);
-    const double B0 = (last - g.tg) * u;
-    const double C = B0 * g.rtg;
-    int s = argmin(C);
-    s = s < s_hi ? s : s_hi;
-    s = s > s_lo ? s : s_lo;
-    s_c = s;
-    const double sd = (double)s, r = px_div(1.0, sd + 1.0);
-    const double h = tabled ? px_fma(g.tg, px_fma(C, r, sd), A0) : px_fma(B0, r, px_fma(sd, g.tg, A0));
-    return (s_lo > s_hi || s_hi < 0) ? __builtin_inf() : h;
+    s_c = feasible_count(t.C, t.s_lo, t.s_hi);
+    const double sd = (double)s_c, r = px_div(1.0, sd + 1.0);
+    const double h = tabled ? px_fma(g.tg, px_fma(t.C, r, sd), t.A0) : px_fma(t.B0, r, px_fma(sd, g.tg, t.A0));
+    return t.none() ? __builtin_inf() : h;
 }
 
 // Reciprocals of the counts of a grid of at most 32, for the scan of calls that have no table of them.
@@ -1294,8 +1269,8 @@ __constant__ float small_recips_f32[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), P
 #undef PX_R4
 
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
-// CH > 0: each batch size's count is found by the scan over all of them (Gs <= kSmallGs), as in the population pass; the same
-// count either way.
+// CH > 0: a row within the tables; the smallest h of each batch size is found by the scan over all counts (Gs <= kSmallGs), as in the
+// population pass.
 // The elected point is priced from the terms its lane has formed; LEAN: from terms formed anew, which holds five registers less.
 template <int CH = 0, bool LEAN = false>
 __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y,
@@ -1304,22 +1279,33 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
     const SyncTerm st = sync_term(c, y, K, one_node);
     RunSteps X = {};
     if constexpr (CH > 0) X = make_run_steps();
-    auto argmin = [&](double C) {
-        if constexpr (CH > 0) return scan_argmin<CH>(C, X, (ScalarDoubles)small_recips, Gs, nullptr, false);
-        else return argmin_count(C);
-    };
     const double rK = 1.0 / (double)K;
     double kbest = __builtin_inf(), tg_at = 0.0, last_at = 0.0;
     int where = 0, m_at = 0;
+    double C_at = 0.0;               // CH > 0: what the count of the lane's best follows from
+    int lo_at = 0, hi_at = 0;
     for (int i = lane_id(); i < Gm; i += kWave) {
         const int m = m_row[i];
         const GridPoint g = grid_point(c, gp, m);
         const double last = last_pass(c, st, g.tg, g.lntg);
-        int s_c;
-        const double h = best_count(g, last, rK, Gs, tabled, argmin, s_c);
+        const RowTerms t = row_terms(g, last, rK, Gs);
+        int s_c = 0;
+        double h;
+        if constexpr (CH > 0) {
+            const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
+            h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, X, (ScalarDoubles)small_recips, Gs), t.A0);
+            if (t.none()) h = __builtin_inf();
+        } else {
+            h = best_count(g, t, tabled, s_c);
+        }
         if (h < kbest) {
             kbest = h;
             where = s_c | ((i / kWave) << 16);
+            if constexpr (CH > 0) {
+                C_at = t.C;
+                lo_at = t.s_lo;
+                hi_at = t.s_hi;
+            }
             if constexpr (!LEAN) {
                 tg_at = g.tg;
                 last_at = last;
@@ -1327,8 +1313,12 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
             }
         }
     }
-    const Pick pick = elect(kbest, where, 0ull, Gs);
+    Pick pick = elect(kbest, where, 0ull, Gs);
     if (pick.i < 0) return Best{0.0, -1, -1};
+    if constexpr (CH > 0) {
+        const int l = pick.i & (kWave - 1);
+        pick.s = feasible_count(wave_read(C_at, l), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
+    }
     if constexpr (LEAN) {
         const int m = m_row[pick.i];
         const double tg = gp.alpha_g + gp.beta_g * (double)m;
@@ -1354,46 +1344,39 @@ __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, co
     const RunStepsF32 X = make_run_steps_f32();
     const SyncTerm st = sync_term(c, y, K, one_node);
     const double rK = 1.0 / (double)K;
-    const float Kf = (float)K;
-    float ts = 0.0f;                                                          // Eq. 9
-    if (K > 1) ts = one_node ? q.alpha_sl + q.beta_sl * (float)(K - 2) : q.alpha_sn + q.beta_sn * (float)(K - 2);
-    float kbest = __builtin_inff(), last_at = 0.0f;
-    int where = 0, m_at = 0;
+    const float Kf = (float)K, ts = t_sync_f32(q, K, one_node);
+    float kbest = __builtin_inff();
+    TermsF32 at = {};                     // the lane's best: its terms, batch size and feasible counts
+    int where = 0, m_at = 0, lo_at = 0, hi_at = 0;
     for (int i = lane_id(); i < Gm; i += kWave) {
         const int m = m_row[i];
         const GridPoint g = grid_point(c, gp, m);
-        const float mf = (float)m;
-        const float tg = q.alpha_g + q.beta_g * mf;                           // Eq. 8
-        float last = (float)last_pass(c, st, g.tg, g.lntg);                   // Eq. 10
-        last = ts == 0.0f ? tg : (q.gamma == 1.0f ? tg + ts : last);
-        const float u = q.phi * __builtin_amdgcn_rcpf(Kf * mf);
-        const float A0 = fmaf(u, tg, last);
-        const float C = (last - tg) * u * __builtin_amdgcn_rcpf(tg);
+        const TermsF32 t = terms_f32(q, ts, Kf, m, (float)last_pass(c, st, g.tg, g.lntg));
         int s_lo, s_hi;
         feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
         const bool feasible = s_lo <= s_hi && s_hi >= 0;
-        int s_c = scan_argmin_f32<16>(C, X, (ScalarFloats)small_recips_f32, Gs);
-        s_c = s_c < s_hi ? s_c : s_hi;
-        s_c = s_c > s_lo ? s_c : s_lo;
-        const float key = fmaf(tg, fmaf(C, 1.0f / (float)(s_c + 1), (float)s_c), A0);
+        const float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<16>(t.C, X, (ScalarFloats)small_recips_f32, Gs),
+                                         [](int s) { return 1.0f / (float)(s + 1); });
         if (feasible && key < kbest) {
             kbest = key;
-            where = s_c | ((i / kWave) << 16);
-            last_at = last;
+            where = (i / kWave) << 16;
+            at = t;
             m_at = m;
+            lo_at = s_lo;
+            hi_at = s_hi;
         }
     }
     // (positive floats order like their values in double precision)
     const Pick pick = elect((double)kbest, where, 0ull, Gs);
     if (pick.i < 0) return Best{0.0, -1, -1};
     const int l = pick.i & (kWave - 1);
+    auto read = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
     const int m = __builtin_amdgcn_readlane(m_at, l);
-    const float last = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(last_at), l));
-    const float mf = (float)m, tg = q.alpha_g + q.beta_g * mf;
-    const float M = (float)K * mf * (float)(pick.s + 1);
-    const float t_iter = (float)pick.s * tg + last;                           // Eq. 11
+    const int s = feasible_count_f32(read(at.C), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
+    const float M = (float)K * (float)m * (float)(s + 1);
+    const float t_iter = (float)s * read(at.tg) + read(at.last);              // Eq. 11
     const float g = (M / t_iter) * (q.a / (q.phi + M));                       // Eq. 7 x Eq. 6
-    return Best{(double)g, m, pick.s};
+    return Best{(double)g, m, s};
 }
 
 // ---- everything that depends on the jobs only: one launch ---------------------------------------
@@ -1536,12 +1519,12 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
                 const double rK = wave_read(my_rK, r);
                 double last_at = last_pass(c, t, g0.tg, g0.lntg), tg_at = g0.tg;
                 int where, m_at = m0;
-                double h = best_count(g0, last_at, rK, a.Gs, true, argmin_count, where);
+                double h = best_count(g0, row_terms(g0, last_at, rK, a.Gs), true, where);
                 if (!(i < a.Gm && h < __builtin_inf())) h = __builtin_inf();      // (not a number where T_grad overflows: no point either)
                 if constexpr (two) {
                     const double last = last_pass(c, t, g1.tg, g1.lntg);
                     int s_c;
-                    const double h1 = best_count(g1, last, rK, a.Gs, true, argmin_count, s_c);
+                    const double h1 = best_count(g1, row_terms(g1, last, rK, a.Gs), true, s_c);
                     if (i + kWave < a.Gm && h1 < h) {
                         h = h1;
                         where = s_c | (1 << 16);
@@ -1768,7 +1751,7 @@ pairs_kernel(FitnessArgs a)
     // storing it waits for nothing that is on its way from memory
     static_assert(kNearRecips <= kWavesPerBlock * kWave, "one entry per thread");
     const bool near_fits = CH != 0 && !MEMO && a.gs_pad <= kNearRecips;
-    const double near_d = 1.0 / (double)((int)threadIdx.x + 1);
+    const double near_d = px_div(1.0, (double)((int)threadIdx.x + 1));
     const float near_f = 1.0f / (float)((int)threadIdx.x + 1);
     auto fill_near = [&]() {
         if (near_fits) {
@@ -1820,7 +1803,7 @@ pairs_kernel(FitnessArgs a)
     else if (vec4) cur0 = ((const int4 *)cur)[lane4];
     constexpr bool kDeferred = CH != 0;               // the grid sweeps of both precisions (not the sampling argmax)
     constexpr int kPriced = -3;                       // a row beyond the tables whose result lane r already holds (see below)
-    int d_K = 0, d_meta = 0, d_i = -1, d_s = -1;      // lane r: what candidate r of this wavefront needs at the end
+    int d_K = 0, d_meta = 0, d_i = -1, d_row = -1;    // lane r: what candidate r of this wavefront needs at the end
     RunSteps X = {};
     RunStepsF32 XF = {};
     bool any_neg = false;
@@ -2108,8 +2091,7 @@ pairs_kernel(FitnessArgs a)
                 // Which rows to stage: every pair of the workgroup votes for the row it will read, and every
                 // wavefront takes, from the same counts (so all four agree), the rows with two votes or more: those
                 // of the "one node" class first, fewer GPUs first, which is where allocations concentrate.  Lane r
-                // then notes, in the register where the count elected for its candidate will go, where that
-                // candidate's row is staged (-1: not staged).
+                // then notes where its candidate's row is staged (-1: not staged).
                 const int my_nodes = d_meta & ~kMetaChanged;
                 const bool votes = lane < rows && d_K >= 1 && tabled_row(d_K, my_nodes == 1, tb.k1);
                 const int my_row = (my_nodes == 1 ? kTableK : 0) + d_K - 1;
@@ -2140,7 +2122,7 @@ pairs_kernel(FitnessArgs a)
                         // threads 0 .. Gm-1 bring the (C, A0) pairs of the row, as many from whole_gm on its feasible ranges
                         if (t < a.Gm) ca_in[e] = tb.ca[(size_t)staged[e] * a.Gm + t];
                         else if (t >= whole_gm && t < whole_gm + a.Gm) range_in[e] = tb.srange[(size_t)(staged[e] & (kTableK - 1)) * a.Gm + (t - whole_gm)];
-                        if (votes && my_row == staged[e]) d_s = kStageBase + 2 * kStageGm + e * kStageRowDoubles;
+                        if (votes && my_row == staged[e]) d_row = kStageBase + 2 * kStageGm + e * kStageRowDoubles;
                     }
                 }
                 if (t < whole_gm) {
@@ -2165,6 +2147,8 @@ pairs_kernel(FitnessArgs a)
         // after the row pass, whose rows in flight use the registers these occupy
         if constexpr (F32) XF = make_run_steps_f32();
         else X = make_run_steps();
+        int sweep_lane = lane;
+        asm volatile("" : "+v"(sweep_lane));
         // Short rows come with small grids: there the sweeps go four candidates at a time, one per row of 16 lanes.
         constexpr bool kRows = rows_at_a_time(ROW4);
         if constexpr (kRows) {
@@ -2193,25 +2177,20 @@ pairs_kernel(FitnessArgs a)
                 const int taken = __builtin_amdgcn_ds_bpermute(((lane & 3) * 16) << 2, found);
                 if ((lane >> 2) == b) found_in_slot = taken;
             }
-            const int found = packed ? __builtin_amdgcn_ds_bpermute(slot << 2, found_in_slot) : found_in_slot;
-            d_i = found < 0 ? -1 : found >> 16;
-            d_s = found < 0 ? -1 : found & 0xFFFF;
+            d_i = packed ? __builtin_amdgcn_ds_bpermute(slot << 2, found_in_slot) : found_in_slot;
             if (lane < rows && d_K >= 1 && !tabled) d_i = kPending;
         }
         for (int r = 0; !kRows && r < rows; ++r) {
             const int K = __builtin_amdgcn_readlane(d_K, r);
             const int nodes = __builtin_amdgcn_readlane(d_meta, r) & ~kMetaChanged;
-            Pick pick = {-1, -1};
-            if (K >= 1 && !tabled_row(K, nodes == 1, tb.k1)) pick.i = kPending;   // rare: swept after the loop, outside the hot path
+            int pick = -1;
+            if (K >= 1 && !tabled_row(K, nodes == 1, tb.k1)) pick = kPending;   // rare: swept after the loop, outside the hot path
             else if (!MEMO && K >= 1) {
                 if constexpr (F32) pick = sweep_pick_f32<CH, WHOLE>(qf, tb, XF, a.rsf, a.Gm, a.Gs, K, nodes, (LdsFloats)(const float *)r_lds, has_near);
-                else pick = sweep_pick<CH, true, WHOLE, kStage>(q, tb, X, a.rs, a.rk, a.Gm, a.Gs, K, nodes, (LdsDoubles)r_lds, has_near,
-                                                        kStage ? __builtin_amdgcn_readlane(d_s, r) : -1);
+                else pick = sweep_pick<CH, WHOLE, kStage>(sweep_lane, tb, X, a.rs, a.Gm, a.Gs, K, nodes, (LdsDoubles)r_lds, has_near,
+                                                          kStage ? __builtin_amdgcn_readlane(d_row, r) : -1);
             }
-            if (lane == r) {
-                d_i = pick.i;
-                d_s = pick.s;
-            }
+            if (lane == r) d_i = pick;
         }
     } else {
         // the sampling argmax: one candidate after the other, priced where it is swept
@@ -2268,8 +2247,8 @@ pairs_kernel(FitnessArgs a)
             } else if constexpr (MEMO) {
                 found = row_best_plain<true>(qb, load_grid_params(b.job_params, b.J, j), tbb.m, b.Gm, b.Gs, K, nodes == 1, false);
             } else {
-                const Pick pick = sweep_pick<CH, false>(qb, tbb, X, b.rs, b.rk, b.Gm, b.Gs, K, nodes);
-                found = price_point(qb, tbb, b.Gm, K, nodes == 1, pick.i, pick.s);
+                const Pick pick = sweep_pick_beyond<CH>(qb, tbb, b.rs, b.rk, b.Gm, b.Gs, K, nodes);
+                found = price_beyond(qb, tbb, K, nodes == 1, pick.i, pick.s);
             }
             if (lane == l) {
                 beyond = found;
@@ -2290,9 +2269,9 @@ pairs_kernel(FitnessArgs a)
             } else if (d_i == kPriced) {
                 best = beyond;
             } else if constexpr (F32) {
-                best = price_point_f32(qf, tbb, b.Gm, d_K, nodes == 1, d_i, d_s);
+                best = price_point_f32(qf, tbb, b.Gm, d_K, nodes == 1, d_i);
             } else {
-                best = price_point(qb, tbb, b.Gm, d_K, nodes == 1, d_i, d_s);
+                best = price_tabled(qb, tbb, b.Gm, d_K, nodes == 1, d_i);
             }
             b.G[pair] = best.goodput;
             b.meta[pair] = d_meta;
@@ -2579,7 +2558,10 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
                 atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
             }
             Best best = {0.0, -1, -1};
-            if (K >= 1) best = row_best<CH>(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, tabled_row(K, nodes == 1, k1));
+            if (K >= 1) {
+                if (__builtin_expect(tabled_row(K, nodes == 1, k1), 1)) best = row_best<CH>(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, true);
+                else best = row_best_plain<false>(q, gp, m_row, a.Gm, a.Gs, K, nodes == 1, false);
+            }
             if (lane == 0) {
                 goodput_lds[j] = best.goodput;
                 meta_lds[j] = nodes | (changed ? kMetaChanged : 0);
