@@ -2505,13 +2505,67 @@ static bool small_call(const pollux_dims &d)
            d.J * groups <= kSmallJobs && (d.Gs <= 16 || groups <= 8);
 }
 
-// KEPT: the call keeps the job tables.
-template <int CH, bool KEPT>
+
+// Threads of a workgroup: sixteen wavefronts, one task each, fair shares before rows; or, with at most 32 batch sizes, one wavefront for
+// two tasks (small_halves), and four at least.
+constexpr int kSmallHalf = kWave / 2;
+static int small_threads(const pollux_dims &d, bool kept)
+{
+    if (d.Gm > kSmallHalf) return kSmallThreads;
+    const int waves = kept ? (d.J + 1) / 2 : d.J;
+    return kWave * (waves > 4 ? waves : 4);
+}
+
+// Smallest value among the lane's half of the wavefront, in every lane of that half.
+__device__ __forceinline__ unsigned half_min(unsigned v)
+{
+    v = row16_min(v);
+    const unsigned other = (unsigned)exchange<4>((int)v);            // the half's other row of 16
+    return v < other ? v : other;
+}
+
+// The argmax of two (job, K, placement) at once, one per half of the wavefront, for grids of at most 32 batch sizes; each lane's
+// arguments are its half's.  The lane that holds the elected point (the half's first where there is none) returns it in `best`
+// and is told so.  Term by term row_best<CH>: the same point, the same bits.
+template <int CH>
+__device__ __forceinline__ bool half_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y, int m, bool in_grid,
+                                          int Gs, int K, bool one_node, bool tabled, Best &best)
+{
+    SyncTerm st = sync_term(c, y, K, one_node);
+    const GridPoint g = grid_point(c, gp, m);
+    const double last = last_pass(c, st, g.tg, g.lntg);
+    const RowTerms t = row_terms(g, last, 1.0 / (double)K, Gs);
+    const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
+    double h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, make_run_steps(), (ScalarDoubles)small_recips, Gs), t.A0);
+    const int s = feasible_count(t.C, t.s_lo, t.s_hi);
+    if (__ballot(!tabled) != 0ull) {
+        int s_c;
+        const double beyond = best_count(g, t, false, s_c);
+        h = tabled ? h : beyond;
+    }
+    h = in_grid && !t.none() && h < __builtin_inf() ? h : __builtin_inf();
+    const unsigned hi = (unsigned)__double2hiint(h), lo = (unsigned)__double2loint(h);
+    const unsigned hmin = half_min(hi);
+    const unsigned lmin = half_min(hi == hmin ? lo : 0xFFFFFFFFu);
+    const unsigned lane = (unsigned)lane_id() & (kSmallHalf - 1);
+    const unsigned first = half_min(hi == hmin && lo == lmin ? lane : 0xFFu);      // equal values: the lowest batch size
+    best = Best{0.0, -1, -1};
+    if (hmin < 0x7FF00000u) best = Best{goodput_point(q, (double)K * (double)m, g.tg, last, s), m, s};
+    return lane == first;
+}
+
+// KEPT: the call keeps the job tables.  HALVES: at most 32 batch sizes.  A wavefront would leave half its lanes idle with one task, and
+// sixteen of them share four SIMDs whose issue bounds them (8 jobs, 32 x 8: 13000 of the workgroup's 19400 cycles), so a wavefront
+// takes a job's fair share and its row together, a half each, or two rows where the fair shares are kept.  The rows are reduced
+// first, a wavefront each.  Calls, us, with a wavefront a task and so: 16 candidates of 8 jobs, 32 x 8, 8.9 to 9.2, 7.9; 200 of 16 jobs,
+// 32 x 32, 13.6, 10.9; 16 of 16 on 200 nodes 14.1, 10.9; 250 of 3 jobs 8.2, 8.3.
+template <int CH, bool KEPT, bool HALVES>
 __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
 {
     __shared__ unsigned long long node_lds[4 * kWave];       // per node: GPUs asked + multi-node jobs << 40, as colpack
     __shared__ double fair_lds[kSmallJobs], factor_lds[kSmallJobs], goodput_lds[kSmallJobs];
     __shared__ int meta_lds[kSmallJobs], m_lds[kSmallJobs], s_lds[kSmallJobs];
+    __shared__ int K_lds[HALVES ? kSmallJobs : 1], held_lds[HALVES ? kSmallJobs : 1];
     __shared__ int status_lds, negative;
     const int c = a.sel ? a.sel[blockIdx.x] : (int)blockIdx.x;
     const int t = threadIdx.x, lane = lane_id();
@@ -2534,8 +2588,77 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
         kept_fair = a.denom[t];
         kept_factor = a.factor[t];
     }
+    if constexpr (HALVES) {
+        // this half's task, and what it needs of memory
+        const int half = lane / kSmallHalf, slot = KEPT ? 2 * wave + half : wave;
+        const bool is_row = KEPT || half == 1, valid = slot < a.J;
+        const int j = valid ? slot : a.J - 1, i = lane & (kSmallHalf - 1);
+        const Job q = load_job(a.job_params, a.J, j);
+        const GridParams gp = load_grid_params(a.job_params, a.J, j);
+        const SyncParams y = load_sync(q);
+        const bool in_grid = i < a.Gm;
+        const int m = a.m_grid[(size_t)j * a.Gm + (in_grid ? i : a.Gm - 1)];
+        int K = 0, fair_nodes = 0;
+        double T = 0.0, R = 0.0, weight = 0.0;
+        if constexpr (!KEPT) {
+            K = a.fair_share[2 * j];
+            fair_nodes = a.fair_share[2 * j + 1];
+            T = a.job_params[(size_t)PX_AGE_T * a.J + j];
+            R = a.job_params[(size_t)PX_RESTARTS_R * a.J + j];
+            weight = a.job_params[(size_t)PX_WEIGHT * a.J + j];
+        }
+        for (int r = wave; r < a.J; r += (int)(blockDim.x / kWave)) {
+            const Entries w = *(const Entries *)(a.population + ((size_t)c * a.J + r) * a.N + at_row.base) & at_row.mask;
+            const Entries was = *(const Entries *)(a.current_alloc + (size_t)r * a.N + at_row.base) & at_row.mask;
+            const int sum = wave_sum((w.x + w.y) + (w.z + w.w));
+            const int nodes = __popcll(__ballot(w.x > 0)) + __popcll(__ballot(w.y > 0)) + __popcll(__ballot(w.z > 0)) + __popcll(__ballot(w.w > 0));
+            const bool changed = __ballot(((w.x ^ was.x) | (w.y ^ was.y) | (w.z ^ was.z) | (w.w ^ was.w)) != 0) != 0;
+            if (__ballot((w.x | w.y | w.z | w.w) < 0) != 0 && lane == 0) negative = 1;
+            if ((w.x | w.y | w.z | w.w) != 0) {
+                const unsigned long long one_job = nodes >= 2 ? kPackJob : 0ull;
+                unsigned long long *to = node_lds + at_row.base;
+                atomicAdd(&to[0], (unsigned long long)(long long)w.x + (w.x > 0 ? one_job : 0ull));
+                atomicAdd(&to[1], (unsigned long long)(long long)w.y + (w.y > 0 ? one_job : 0ull));
+                atomicAdd(&to[2], (unsigned long long)(long long)w.z + (w.z > 0 ? one_job : 0ull));
+                atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
+            }
+            if constexpr (!KEPT) {
+                const bool held = wave_sum((long long)was.x + was.y + was.z + was.w) > 0;
+                const bool below = __ballot((was.x | was.y | was.z | was.w) < 0) != 0;
+                if (lane == 0) held_lds[r] = (held ? 1 : 0) | (below ? 2 : 0);
+            }
+            if (lane == 0) {
+                K_lds[r] = sum;
+                meta_lds[r] = nodes | (changed ? kMetaChanged : 0);
+            }
+        }
+        __syncthreads();
+        if (is_row) K = K_lds[j];
+        const bool one_node = (is_row ? meta_lds[j] & ~kMetaChanged : fair_nodes) == 1;
+        const bool wanted = K >= 1;
+        Best best;
+        bool mine = half_best<CH>(coefs, q, gp, y, m, in_grid, a.Gs, wanted ? K : 1, one_node, !wanted || tabled_row(K, one_node, k1), best);
+        if (!wanted) best = Best{0.0, -1, -1};
+        if (valid && mine) {
+            if (is_row) {
+                goodput_lds[j] = best.goodput;
+                m_lds[j] = best.m;
+                s_lds[j] = best.s;
+            } else {
+                // the job's fair share, its status and its re-allocation factor (Sec. 4.2)
+                const bool penalty = !(a.flags & PX_FLAG_NO_REALLOC_PENALTY);
+                int st = job_status(gp, y, weight);
+                if (penalty && !(T - R * a.delta > 0.0)) st |= PX_ST_BAD_RESTART;
+                if ((held_lds[j] & 2) != 0) st |= PX_ST_NEG_ALLOC;
+                if (!(best.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
+                fair_lds[j] = best.goodput;
+                factor_lds[j] = penalty && (held_lds[j] & 1) != 0 ? (T - R * a.delta) / (T + a.delta) : 1.0;
+                if (st) atomicOr(&status_lds, st);
+            }
+        }
+    }
     const int shares = KEPT ? 0 : a.J;                       // fair shares to find, before the rows
-    for (int task = wave; task < shares + a.J; task += kSmallThreads / kWave) {
+    for (int task = wave; !HALVES && task < shares + a.J; task += kSmallThreads / kWave) {
         const bool is_row = KEPT || task >= shares;
         const int j = is_row ? task - shares : task;
         const Job q = load_job(a.job_params, a.J, j);
@@ -3410,12 +3533,14 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const bool f32 = d->precision == 1;
     if (small_call(*d)) {
         if (sweep_start) (void)hipEventRecord(sweep_start, stream);
-        const dim3 grid((unsigned)P_eff), block(kSmallThreads);
-        const bool kept = (d->flags & PX_FLAG_KEEP_JOB_TABLES) != 0;
-#define PX_LAUNCH_SMALL(CH)                                                                    \
-    do {                                                                                       \
-        if (kept) hipLaunchKernelGGL((small_kernel<CH, true>), grid, block, 0, stream, a);     \
-        else hipLaunchKernelGGL((small_kernel<CH, false>), grid, block, 0, stream, a);         \
+        const bool kept = (d->flags & PX_FLAG_KEEP_JOB_TABLES) != 0, halves = d->Gm <= kSmallHalf;
+        const dim3 grid((unsigned)P_eff), block((unsigned)small_threads(*d, kept));
+#define PX_LAUNCH_SMALL(CH)                                                                                      \
+    do {                                                                                                         \
+        if (kept && halves) hipLaunchKernelGGL((small_kernel<CH, true, true>), grid, block, 0, stream, a);       \
+        else if (halves) hipLaunchKernelGGL((small_kernel<CH, false, true>), grid, block, 0, stream, a);         \
+        else if (kept) hipLaunchKernelGGL((small_kernel<CH, true, false>), grid, block, 0, stream, a);           \
+        else hipLaunchKernelGGL((small_kernel<CH, false, false>), grid, block, 0, stream, a);                    \
     } while (0)
         if (ch == 8) PX_LAUNCH_SMALL(8);
         else if (ch == 16) PX_LAUNCH_SMALL(16);
