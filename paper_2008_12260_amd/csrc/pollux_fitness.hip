@@ -1693,7 +1693,7 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 // keep an instance without them.  (1021 candidates of 331 jobs on 130 nodes: 207 us entry by entry, 134 so.)
 // WHOLE: the host has checked that Gm is a multiple of 64 (tabled sweeps then skip the test for the end of the grid).
 // ROW4: ROW1 and a row is at most 64 entries, so one load of the wavefront covers the rows of four candidates
-// (16 lanes each); cand_per_wave is at most 16.  kFourRowsSwept: the candidates are also swept four at a time (see split_pairs).
+// (16 lanes each); cand_per_wave is at most 16.  kFourRowsSwept: the candidates are also swept four at a time (see split_pairs, balanced_split).
 // SEL: only the candidates listed in a.sel are evaluated (the children a search step has just formed); the
 // wavefronts then walk positions of that list and look the candidate up where an address is formed.
 // Eight wavefronts per SIMD (64 registers); the instances that sweep four candidates at a time (rows_at_a_time)
@@ -3523,8 +3523,9 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
     const bool near = a.gs_pad <= kNearRecips;      // the kernels keep reciprocals and thresholds of all counts in LDS
     // four rows per load of a wavefront (cand_per_wave <= 16 holds); its sweeps pack a batch size's index into 15 bits
     const bool row4 = row1 && d->N <= kWave && d->Gm <= 0x7FFF && near && !(d->flags & PX_FLAG_SAMPLE_M);
-    const PairSplit split = split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit, row1,
-                                        (d->flags & PX_FLAG_SAMPLE_M) != 0);
+    const bool sampled = (d->flags & PX_FLAG_SAMPLE_M) != 0;       // fp64 only (checked by the caller)
+    const PairSplit split = balanced_split(split_pairs(P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, aligned && whole, inherit, row1, sampled),
+                                           P_eff, d->J, d->Gm, d->Gs, d->precision == 1, row4, inherit, row1, sampled);
     a.cand_per_wave = split.per_wave;
     a.stage_rows = d->Gm <= kStageGm && near && split.per_wave >= stage_candidates(a.sel != nullptr) ? 1 : 0;
     a.cand_groups = pair_groups(P_eff, split.per_wave);
@@ -3549,7 +3550,6 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     }
-    const bool sampled = (d->flags & PX_FLAG_SAMPLE_M) != 0;       // fp64 only (checked by the caller)
     const bool memo = memoised(*d);
     // The per-node counters start every call at zero.  A call that uses them leaves them at zero again
     // (candidates_kernel clears what it reads), so a call that keeps the job tables, whose caller guarantees an

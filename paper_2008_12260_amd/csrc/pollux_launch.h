@@ -63,6 +63,8 @@ struct PairSplit {
 };
 
 // row1: rows of 4 to 256 nodes.  row4: of at most 64, with count tables that fit on chip.  sampled: the sampling argmax.
+// (Where rows have 4 to 256 nodes and the candidates are known, balanced_split settles the count; the figures are of sweeps that took
+// longer than today's.)
 //
 // per_wave: 25000 wavefronts fill the chip several times over.  Fewer with more candidates each save what a wavefront does once (job
 // terms, table in LDS, prices), until the last wavefronts to end cost more: down to 12400 wavefronts with as many candidates as that
@@ -105,6 +107,50 @@ inline int pair_groups(int candidates, int per_wave)
 {
     const int group = per_wave * kWavesPerBlock;
     return (int)(((long long)candidates + group - 1) / group);
+}
+
+// The split of a call on rows of 4 to 256 nodes whose candidates are known: what all wavefronts do once (job terms, table in LDS, table
+// rows, prices: some 250 vector instructions each; 2 ns of the whole chip's time a workgroup, beyond three a compute unit) against what
+// each candidate adds to the last wavefront's chain (its sweeps, one after the other, by the grid's width: 0.3 us and 0.12 us per 64
+// batch sizes x 16 counts on rows of 65 nodes and more; 0.2 and 0.15 where four are swept at a time; 0.28 per 64 x 16 one at a time
+// on short rows).  The sum is least at about the root of pairs / 2000; this finds the least, the unequal shares of a job's last
+// workgroup included, in whole fours where four are swept at a time (a sweep lasts as long with one as with four).  Sweep and mean of
+// kept calls, us (candidates a wavefront), with split_pairs' count, so, and the least of 1 .. 16:
+//   80 nodes    60 candidates of 100 jobs, 64 x 16      13.4 (1)   12.1 (2)   12.1
+//   100 nodes   60 of 400, 64 x 16                      28.7 (1)   19.7 (5)   19.7;  128 x 32  32.8, 25.3, 25.3
+//   200 nodes   120 of 300, 64 x 16                     28.5 (2)   25.2 (6)   25.2
+//   90 nodes    500 of 200, 64 x 16                     43.3 (6)   43 (9)     42.5 (8)
+//   200 nodes   400 of 400, 64 x 16                     64.1 (6)   61.3 (10)  61.3;  128 x 32  89.8, 87.8, 87.8
+//   130 nodes   1021 of 331, 50 x 21                    115 (13)   110 (16)   110
+//   64 nodes    30 of 200, 64 x 16                      15.0 (1)   10.1 (4)   10.1
+//   64 nodes    60 of 400, 64 x 16                      32.4 (1)   15.4 (8)   15.4;  50 x 21  26.0, 18.0, 18.0
+// Fp32 and ragged short rows go four at a time from 4000 pairs on: one at a time and four, 60 x 60 on 33 nodes, 50 x 12, 10.3, 9.9, 100 x 12
+// 10.7, 10.8, fp32 64 x 16 11.0, 10.9; 40 x 40 on 22 nodes 9.1, 9.7; 44 x 137 on 57 nodes, 100 x 12, 12.6, 11.4.
+// Row inheritance, whose lists have no length known here, the sampling argmax and longer rows keep split_pairs' count.
+inline PairSplit balanced_split(PairSplit s, int candidates, int jobs, int Gm, int Gs, bool f32, bool row4, bool inherit, bool row1, bool sampled)
+{
+    if (inherit || sampled || !row1) return s;
+    const int share = (candidates - 1) / kWavesPerBlock + 1;
+    if (row4 && !s.four) {
+        if ((long long)Gm * ((Gs + 15) / 16) > 128 || (long long)candidates * jobs < 4000 || share < 4) return s;
+        s.four = true;
+        s.entry_by_entry = false;
+    }
+    const bool swept = row4 && (f32 || Gs <= 16);
+    const int step = swept ? 4 : 1;
+    if (share < step) return s.four ? PairSplit{share, true, false} : s;
+    const long long width = (long long)((Gm + 63) / 64) * ((Gs + 15) / 16);
+    const long long chain = !row4 ? 300 + 120 * width : (swept ? 200 + 150 * width : 280 * width);        // ns a candidate
+    long long least = -1;
+    for (int n = step; n <= kMaxCandPerWave && n < share + step; n += step) {
+        const long long crowd = (long long)jobs * pair_groups(candidates, n) - 768;                        // workgroups
+        const long long cost = 2 * (crowd > 0 ? crowd : 0) + chain * n;
+        if (least < 0 || cost < least) {
+            least = cost;
+            s.per_wave = n;
+        }
+    }
+    return s;
 }
 
 // The record a search over a job's records has found, or the first where it has found none (no time below infinity).

@@ -35,6 +35,14 @@ int px_host_split_nodes(int candidates, int jobs, int nodes, int Gm, int Gs, int
     const bool row1 = nodes >= 4 && nodes <= 256, whole = nodes % 4 == 0 && Gm % 64 == 0;
     return px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row1 && nodes <= 64, whole, false, row1).per_wave;
 }
+// The split a call takes: as px_host_split, in bits above 8 the workgroups a job's candidates are shared out among.
+int px_host_balanced(int candidates, int jobs, int nodes, int Gm, int Gs, int f32, int inherit)
+{
+    const bool row1 = nodes >= 4 && nodes <= 256, row4 = row1 && nodes <= 64, whole = nodes % 4 == 0 && Gm % 64 == 0;
+    const px::PairSplit p = px::balanced_split(px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row4, whole, inherit != 0, row1),
+                                               candidates, jobs, Gm, Gs, f32 != 0, row4, inherit != 0, row1, false);
+    return (p.per_wave - 1) | (p.four ? 16 : 0) | (p.entry_by_entry ? 32 : 0) | px::pair_groups(candidates, p.per_wave) << 8;
+}
 int px_host_table_rows(int jobs, int Gm) { return px::table_rows(jobs, Gm); }
 int px_host_pair_groups(int candidates, int per_wave) { return px::pair_groups(candidates, per_wave); }
 int px_host_record_or_first(int found, int records) { return px::record_or_first(found, records); }
