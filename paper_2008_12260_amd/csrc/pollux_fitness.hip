@@ -1476,6 +1476,69 @@ __device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a
     if (j == 0 && lane < 16) a.zeros[lane] = 0;
 }
 
+// The argmaxes of `rows` (K, placement) of one job, at most a wavefront's lanes: lane r holds the r-th's K, its synchronisation term, 1/K and
+// whether it takes the tables' form (see best_count), and returns its point.  The terms of a batch size are formed once for all rows.
+__device__ __forceinline__ Best argmax_rows(const Coefs &c, const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs,
+                                            int rows, int my_K, const SyncTerm &mine, double my_rK, bool my_tabled)
+{
+    // Batch sizes two groups of 64 at a time, one election for both; later ones have to be better than what earlier ones elected
+    // (equal values: the earlier).
+    const int lane = lane_id();
+    double my_h = __builtin_inf(), my_tg = 1.0, my_last = 1.0;
+    int my_m = -1, my_s = -1;
+    auto groups = [&](int i0, auto TWO) __attribute__((always_inline)) {
+        constexpr bool two = decltype(TWO)::value;
+        const int i = i0 + lane;
+        const int m0 = m_row[i < Gm ? i : Gm - 1], m1 = two ? m_row[i + kWave < Gm ? i + kWave : Gm - 1] : 0;
+        const GridPoint g0 = grid_point(c, gp, m0);
+        GridPoint g1 = g0;
+        if constexpr (two) g1 = grid_point(c, gp, m1);
+#pragma unroll 1
+        for (int r = 0; r < rows; ++r) {
+            const SyncTerm t = {wave_read(mine.ts, r), wave_read(mine.lnts, r), mine.gamma, mine.inv_gamma,
+                                __builtin_amdgcn_readlane(mine.mode, r)};
+            const double rK = wave_read(my_rK, r);
+            const bool tabled = __builtin_amdgcn_readlane((int)my_tabled, r) != 0;
+            double last_at = last_pass(c, t, g0.tg, g0.lntg), tg_at = g0.tg;
+            int where, m_at = m0;
+            double h = best_count(g0, row_terms(g0, last_at, rK, Gs), tabled, where);
+            if (!(i < Gm && h < __builtin_inf())) h = __builtin_inf();      // (not a number where T_grad overflows: no point either)
+            if constexpr (two) {
+                const double last = last_pass(c, t, g1.tg, g1.lntg);
+                int s_c;
+                const double h1 = best_count(g1, row_terms(g1, last, rK, Gs), tabled, s_c);
+                if (i + kWave < Gm && h1 < h) {
+                    h = h1;
+                    where = s_c | (1 << 16);
+                    last_at = last;
+                    tg_at = g1.tg;
+                    m_at = m1;
+                }
+            }
+            const Pick pick = elect(h, where, 0ull, Gs);
+            if (pick.i >= 0) {
+                const int l = pick.i & (kWave - 1);
+                const double h_l = wave_read(h, l), tg_l = wave_read(tg_at, l), last_l = wave_read(last_at, l);
+                const int m_l = __builtin_amdgcn_readlane(m_at, l);
+                const bool here = lane == r && h_l < my_h;
+                my_h = here ? h_l : my_h;
+                my_tg = here ? tg_l : my_tg;
+                my_last = here ? last_l : my_last;
+                my_m = here ? m_l : my_m;
+                my_s = here ? pick.s : my_s;
+            }
+        }
+    };
+    for (int i0 = 0; i0 < Gm; i0 += 2 * kWave) {
+        if (i0 + kWave < Gm) groups(i0, std::true_type());
+        else groups(i0, std::false_type());
+    }
+    // lane r prices the point elected for row r, from the terms that point's lane has formed
+    Best best = {0.0, my_m, my_s};
+    if (my_m >= 0) best.goodput = goodput_point(q, (double)my_K * (double)my_m, my_tg, my_last, my_s);
+    return best;
+}
+
 // ROWS rows from K0 on.  The rows follow one another in a loop: written out they want more scalar registers than there are, beside
 // the constants.
 template <int ROWS, int MODE>
@@ -1501,62 +1564,8 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
     const SyncTerm mine = sync_term(c, y, my_K, one_node);
     const double my_rK = px_div(1.0, (double)my_K);
     if constexpr (MODE == kPrepMemo) {
-        // Batch sizes two groups of 64 at a time, one election for both; later ones have to be better than what earlier ones elected
-        // (equal values: the earlier).  Lane r: the point elected for row r.
-        double my_h = __builtin_inf(), my_tg = 1.0, my_last = 1.0;
-        int my_m = -1, my_s = -1;
-        auto groups = [&](int i0, auto TWO) __attribute__((always_inline)) {
-            constexpr bool two = decltype(TWO)::value;
-            const int i = i0 + lane;
-            const int m0 = m_row[i < a.Gm ? i : a.Gm - 1], m1 = two ? m_row[i + kWave < a.Gm ? i + kWave : a.Gm - 1] : 0;
-            const GridPoint g0 = grid_point(c, gp, m0);
-            GridPoint g1 = g0;
-            if constexpr (two) g1 = grid_point(c, gp, m1);
-#pragma unroll 1
-            for (int r = 0; r < ROWS; ++r) {
-                const SyncTerm t = {wave_read(mine.ts, r), wave_read(mine.lnts, r), mine.gamma, mine.inv_gamma,
-                                    __builtin_amdgcn_readlane(mine.mode, r)};
-                const double rK = wave_read(my_rK, r);
-                double last_at = last_pass(c, t, g0.tg, g0.lntg), tg_at = g0.tg;
-                int where, m_at = m0;
-                double h = best_count(g0, row_terms(g0, last_at, rK, a.Gs), true, where);
-                if (!(i < a.Gm && h < __builtin_inf())) h = __builtin_inf();      // (not a number where T_grad overflows: no point either)
-                if constexpr (two) {
-                    const double last = last_pass(c, t, g1.tg, g1.lntg);
-                    int s_c;
-                    const double h1 = best_count(g1, row_terms(g1, last, rK, a.Gs), true, s_c);
-                    if (i + kWave < a.Gm && h1 < h) {
-                        h = h1;
-                        where = s_c | (1 << 16);
-                        last_at = last;
-                        tg_at = g1.tg;
-                        m_at = m1;
-                    }
-                }
-                const Pick pick = elect(h, where, 0ull, a.Gs);
-                if (pick.i >= 0) {
-                    const int l = pick.i & (kWave - 1);
-                    const double h_l = wave_read(h, l), tg_l = wave_read(tg_at, l), last_l = wave_read(last_at, l);
-                    const int m_l = __builtin_amdgcn_readlane(m_at, l);
-                    const bool here = lane == r && h_l < my_h;
-                    my_h = here ? h_l : my_h;
-                    my_tg = here ? tg_l : my_tg;
-                    my_last = here ? last_l : my_last;
-                    my_m = here ? m_l : my_m;
-                    my_s = here ? pick.s : my_s;
-                }
-            }
-        };
-        for (int i0 = 0; i0 < a.Gm; i0 += 2 * kWave) {
-            if (i0 + kWave < a.Gm) groups(i0, std::true_type());
-            else groups(i0, std::false_type());
-        }
-        // lane r prices the point elected for row r, from the terms that point's lane has formed
-        if (lane < ROWS) {
-            MemoEntry e = {0.0, my_m, my_s};
-            if (my_m >= 0) e.goodput = goodput_point(q, (double)my_K * (double)my_m, my_tg, my_last, my_s);
-            a.memo[row0 + lane] = e;
-        }
+        const Best best = argmax_rows(c, q, gp, m_row, a.Gm, a.Gs, ROWS, my_K, mine, my_rK, true);
+        if (lane < ROWS) a.memo[row0 + lane] = MemoEntry{best.goodput, best.m, best.s};
     } else {
         for (int i0 = 0; i0 < a.Gm; i0 += kWave) {
             const int i = i0 + lane;
@@ -2340,6 +2349,25 @@ __global__ void __launch_bounds__(256) queries_kernel(FitnessArgs a, QueryArgs q
         q.progress[j] = after;
         q.finished[j] = after >= q.target[j];
     }
+}
+
+// The same for many queries (per_gpu mode): `rows` of one job to a wavefront (query_rows), which share the terms of its batch sizes.
+__global__ void __launch_bounds__(256) queries_rows_kernel(FitnessArgs a, QueryArgs q, int rows)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = lane_id();
+    const int per_job = q.max_nodes + 1, waves = (per_job + rows - 1) / rows;
+    const long long id = (long long)blockIdx.x * kWavesPerBlock + wave;
+    if (id >= (long long)a.J * waves) return;
+    const int j = (int)(id / waves), n0 = (int)(id % waves) * rows;
+    const Job job = load_job(a.job_params, a.J, j);
+    const GridParams gp = load_grid_params(a.job_params, a.J, j);
+    const SyncParams y = load_sync(job);
+    const int mine = per_job - n0 < rows ? per_job - n0 : rows;
+    const int n = n0 + (lane < mine ? lane : 0), K = n == 0 ? 1 : n * q.gpus_per_node;
+    const Coefs c = held_coefs();
+    const Best best = argmax_rows(c, job, gp, a.m_grid + (size_t)j * a.Gm, a.Gm, a.Gs, mine, K, sync_term(c, y, K, n <= 1), 1.0 / (double)K,
+                                  K <= kTableK);
+    if (lane < mine) q.per_gpu[(size_t)j * per_job + n] = best.goodput / (double)K;
 }
 
 // Sec. 5.3.3: a job scales up when its goodput per GPU exceeds U of the ideal (one GPU, column 0), to the
@@ -3378,7 +3406,13 @@ static int launch_queries(const pollux_dims *d, const double *job_params, const 
     FitnessArgs a = {};
     a.J = d->J; a.Gm = d->Gm; a.Gs = d->Gs;
     a.m_grid = m_grid; a.job_params = job_params;
-    const long long queries = (long long)d->J * (q.mode == 0 ? q.max_nodes + 1 : 1);
+    const int per_job = q.mode == 0 ? q.max_nodes + 1 : 1, rows = query_rows(d->J, per_job);
+    if (rows > 1) {
+        const long long waves = (long long)d->J * ((per_job + rows - 1) / rows);
+        hipLaunchKernelGGL(queries_rows_kernel, dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(256), 0, stream, a, q, rows);
+        return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
+    }
+    const long long queries = (long long)d->J * per_job;
     const dim3 grid((unsigned)((queries + kWavesPerBlock - 1) / kWavesPerBlock));
     hipLaunchKernelGGL(queries_kernel, grid, dim3(256), 0, stream, a, q);
     return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;

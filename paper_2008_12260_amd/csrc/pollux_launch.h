@@ -153,6 +153,17 @@ inline PairSplit balanced_split(PairSplit s, int candidates, int jobs, int Gm, i
     return s;
 }
 
+// Queries (GPU count, placement) of one job that a wavefront takes.  Forming the terms of a job's batch sizes is as much work as three
+// argmaxes and is shared by them, but they follow one another: up to some six wavefronts a SIMD one each is as quick.  us with one,
+// with two, four and six: 3400 queries 64 x 16 6.3, 6.1, 6.1, 7.2; 7500 of 32 x 8 9.3, 8.4, 9.2, 9.1; 11000 of 128 x 32 16.6, 14.2, 12.9,
+// 11.8; 25000 of 64 x 16 23.7, 19.6, 17.0, 16.9 (twelve: 18.9).
+inline int query_rows(int jobs, int per_job)
+{
+    const long long want = (long long)jobs * per_job / 3000;
+    const int rows = (int)(want < 1 ? 1 : (want < 6 ? want : 6));
+    return rows < per_job ? rows : per_job;
+}
+
 // The record a search over a job's records has found, or the first where it has found none (no time below infinity).
 PX_HOST_DEVICE int record_or_first(int found, int records) { return found < records ? found : 0; }
 
