@@ -32,16 +32,16 @@ FLOPS_PER_EVAL = 7                  # Eq. 4 at one grid point: 5 add/mul + 2 div
 #   traffic_bytes   HBM bytes per launch: FETCH_SIZE and WRITE_SIZE, each scaled by what the same counter reads for a
 #                   device-to-device copy of known size in the same run
 #   fp64_flops      64 lanes x (ADD_F64 + MUL_F64 + 2 x FMA_F64 wave-instructions) per launch
-#   valu_insts      vector instructions per launch; scan_insts = those of the scan itself (2.25 per grid point)
+#   valu_insts      vector instructions per launch; scan_insts = those of the scan itself (2 per grid point)
 #   valu_busy       fraction of the kernel's cycles in which the vector ALUs were busy
 PROFILED = {
     "large": {
-        "source_sha256": "e4f39c308eeac0377e4b232b443834d3edd46eda8a8619d3239adb9a549c0e27",
-        "traffic_bytes": 2_079_730 * 1024 * 2 + 699_022 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
-        "fp64_flops": 64 * (8.96000e5 + 1.76352e7 + 2 * 2.65925e8),
-        "valu_insts": 9.91579e8,
-        "scan_insts": 2.25 * 1.6777e10 / 64,
-        "valu_busy": 1.00971e9 * 4 / 1024 / (3.39611e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
+        "source_sha256": "57779f36a2184c72e343e1bbffc9d2316d9981bf556bc5f19c1dedbb4dde18d5",
+        "traffic_bytes": 2_079_340 * 1024 * 2 + 700_522 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
+        "fp64_flops": 64 * (8.96000e5 + 1.75712e7 + 2 * 2.66373e8),
+        "valu_insts": 8.72223e8,
+        "scan_insts": 2.0 * 1.6777e10 / 64,
+        "valu_busy": 8.90600e8 * 4 / 1024 / (3.05642e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
     },
 }
 GA_SEED = 0x2008_1226_5EED_0001

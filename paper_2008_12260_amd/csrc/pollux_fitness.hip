@@ -122,7 +122,7 @@ struct FitnessArgs {
 constexpr unsigned long long kPackJob = 1ull << 40;   // one multi-node job in a colpack word
 constexpr int kNearRecips = 256;          // pairs kernel: reciprocals kept in LDS when Gs (rounded up to 32) is at most this
 // The fp64 table in LDS (in doubles): per count s the pair (1 / (s + 1), s), so that one read brings both operands of
-// w(s) = s + C / (s + 1) at the clamped count; behind the pairs the thresholds U[t] = t (t + 1).
+// w(s) = s + C / (s + 1) at an end of the feasible counts; behind the pairs the thresholds U[t] = t (t + 1).
 constexpr int kNearU = 2 * kNearRecips;
 // pairs kernel: the table rows (one per (placement class, K)) that most of a workgroup's pairs read are staged in LDS,
 // behind the reciprocals and thresholds: (T_grad, 1 / T_grad) per batch size as in memory, then per row the (C, A0)
@@ -1706,7 +1706,8 @@ __global__ void __launch_bounds__(256) memo_kernel_f32(FitnessArgs a)
 // SEL: only the candidates listed in a.sel are evaluated (the children a search step has just formed); the
 // wavefronts then walk positions of that list and look the candidate up where an address is formed.
 // Eight wavefronts per SIMD (64 registers); the instances that sweep four candidates at a time (rows_at_a_time)
-// take six (80 registers), which is what they need without spilling, and are no slower for it.
+// take six: two sets of 16 batch sizes that share the reciprocals want 80 registers (eight bytes of the row pass spill; 1000 x 200 on 64
+// nodes, 64 x 16, 62.3 us a call with one set at a time and seven wavefronts, 60.1 so, 61.3 with five wavefronts and no spill).
 // Order of a wavefront's work (ROW1): request its first rows; fill the workgroup's table in LDS (entries formed
 // in registers, so nothing waits for memory) and meet the other wavefronts; reduce the rows two at a time, and
 // hand the registers of each finished pair to the rows of the next stretch of eight; then the sweeps of its
@@ -1742,7 +1743,7 @@ pairs_kernel(FitnessArgs a)
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
-    // the reciprocals 1/(s+1) also in LDS when they fit: the clamped count of a lane reads its own entry
+    // the reciprocals 1/(s+1) also in LDS when they fit: a lane reads the entry of an end of its feasible counts
     // behind them U[t] = t (t+1), U[0] = -1: what decides the order of neighbouring counts (sweep_pick)
     // kStage: behind them the table rows most of the workgroup's pairs read (see kStageBase); stage_votes counts, per
     // (class, K), the pairs of the workgroup that read the row
@@ -2295,7 +2296,7 @@ pairs_kernel(FitnessArgs a)
 }
 
 // ---- the argmax alone, for the consumers outside the search ----------------------------
-// One wavefront per query (job, K, nodes), found in place (row_best): the job tables would cost a call 72 rows per job
+// One wavefront per query (job, K, nodes), found in place (row_best; many at once in queries_rows_kernel): the job tables would cost a call 72 rows per job
 // where it asks for one (or max_nodes + 1), and two launches (200 jobs, 17 queries each: 28 us with them).
 //   per_gpu mode   query (j, n), n = 0..max_nodes: column 0 is the job on one GPU, column n >= 1
 //                  the job on n full nodes of gpus_per_node GPUs; the goodput is divided by the
