@@ -394,7 +394,7 @@ def main():
         "frac": achieved_tflops / FP64_VECTOR_PEAK_TFLOPS, "traffic": prof["traffic_bytes"] if prof else None,
         "kernel": "px::pairs_kernel", "flops_per_eval": FLOPS_PER_EVAL, "avg_launch_ms": sweep_avg_ms,
         "note": "frac counts the 7 fp64 operations Eq. 4 asks for per grid point; the kernel executes one "
-                "multiply-add and 1.25 other vector instructions per point, see executed_flop_frac and valu_issue_frac",
+                "multiply-add and one minimum per point in its scan, see executed_flop_frac and valu_issue_frac",
         # from the instruction counters: fp64 operations executed, as a fraction of the peak
         "executed_flop_frac": (prof["fp64_flops"] / (sweep_avg_ms * 1e-3) / 1e12 / FP64_VECTOR_PEAK_TFLOPS) if prof else None,
         # share of the vector-ALU issue slots of the launch that the scan itself uses: (scan instructions / all vector
