@@ -36,7 +36,7 @@ FLOPS_PER_EVAL = 7                  # Eq. 4 at one grid point: 5 add/mul + 2 div
 #   valu_busy       fraction of the kernel's cycles in which the vector ALUs were busy
 PROFILED = {
     "large": {
-        "source_sha256": "57779f36a2184c72e343e1bbffc9d2316d9981bf556bc5f19c1dedbb4dde18d5",
+        "source_sha256": "44fff2506af3eef50628820c3b5f9f70114fa14a329ce90d7889188223386bc5",
         "traffic_bytes": 2_079_340 * 1024 * 2 + 700_522 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
         "fp64_flops": 64 * (8.96000e5 + 1.75712e7 + 2 * 2.66373e8),
         "valu_insts": 8.72223e8,

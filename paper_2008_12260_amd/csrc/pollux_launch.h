@@ -125,14 +125,17 @@ inline int pair_groups(int candidates, int per_wave)
 //   64 nodes    30 of 200, 64 x 16                      15.0 (1)   10.1 (4)   10.1
 //   64 nodes    60 of 400, 64 x 16                      32.4 (1)   15.4 (8)   15.4;  50 x 21  26.0, 18.0, 18.0
 // Fp32 and ragged short rows go four at a time from 4000 pairs on: one at a time and four, 60 x 60 on 33 nodes, 50 x 12, 10.3, 9.9, 100 x 12
-// 10.7, 10.8, fp32 64 x 16 11.0, 10.9; 40 x 40 on 22 nodes 9.1, 9.7; 44 x 137 on 57 nodes, 100 x 12, 12.6, 11.4.
+// 10.7, 10.8, fp32 64 x 16 11.0, 10.9; 40 x 40 on 22 nodes 9.1, 9.7; 44 x 137 on 57 nodes, 100 x 12, 12.6, 11.4.  Grids wider than
+// 64 batch sizes x 16 counts from 6000: fp32 69 x 64 on 8 nodes, 128 x 12, 11.3, 11.9, 242 x 24 on 6, 100 x 12, 14.5, 15.4; 51 x 120 on 15,
+// 100 x 8, 12.9, 12.3; 184 x 35 on 13, 128 x 12, 13.6, 12.4.
 // Row inheritance, whose lists have no length known here, the sampling argmax and longer rows keep split_pairs' count.
 inline PairSplit balanced_split(PairSplit s, int candidates, int jobs, int Gm, int Gs, bool f32, bool row4, bool inherit, bool row1, bool sampled)
 {
     if (inherit || sampled || !row1) return s;
     const int share = (candidates - 1) / kWavesPerBlock + 1;
     if (row4 && !s.four) {
-        if ((long long)Gm * ((Gs + 15) / 16) > 128 || (long long)candidates * jobs < 4000 || share < 4) return s;
+        const long long chunk = (long long)Gm * ((Gs + 15) / 16);
+        if (chunk > 128 || (long long)candidates * jobs < (chunk > 64 ? 6000 : 4000) || share < 4) return s;
         s.four = true;
         s.entry_by_entry = false;
     }

@@ -41,7 +41,8 @@ def test_every_candidate_is_taken_once(launch, nodes, f32):
     (30, 200, 100, 64, 16, 0, 2, 0), (60, 400, 100, 64, 16, 0, 5, 0), (60, 400, 100, 128, 32, 0, 5, 0), (120, 300, 200, 64, 16, 0, 6, 0),
     (1021, 331, 130, 50, 21, 0, 16, 0), (4096, 1000, 256, 128, 32, 0, 16, 0), (20, 30, 100, 64, 16, 0, 1, 0),
     (30, 200, 64, 64, 16, 0, 4, 1), (60, 400, 64, 64, 16, 0, 8, 1), (1000, 200, 64, 64, 16, 0, 16, 1), (12, 30, 64, 64, 16, 0, 3, 1),
-    (60, 66, 33, 50, 12, 0, 1, 0), (60, 67, 33, 50, 12, 0, 4, 1), (60, 67, 33, 129, 12, 0, 1, 0), (60, 66, 33, 64, 16, 1, 1, 0), (60, 67, 33, 64, 16, 1, 4, 1)])
+    (60, 66, 33, 50, 12, 0, 1, 0), (60, 67, 33, 50, 12, 0, 4, 1), (60, 67, 33, 129, 12, 0, 1, 0), (60, 66, 33, 64, 16, 1, 1, 0), (60, 67, 33, 64, 16, 1, 4, 1),
+    (60, 99, 33, 65, 12, 1, 1, 0), (60, 100, 33, 65, 12, 1, 4, 1), (60, 99, 33, 65, 12, 0, 1, 0), (60, 100, 33, 65, 12, 0, 4, 1)])
 def test_candidates_a_wavefront(launch, candidates, jobs, nodes, Gm, Gs, f32, per_wave, four):
     got = launch.px_host_balanced(candidates, jobs, nodes, Gm, Gs, f32, 0)
     assert ((got & 15) + 1, (got >> 4) & 1) == (per_wave, four)
