@@ -48,7 +48,8 @@
 // tabled.  The lane takes the smallest w over ALL s, one fused multiply-add and one minimum per grid point.  w is convex
 // in s (C >= 0) and w(s+1) < w(s) precisely when C > (s+1)(s+2), so two exact comparisons say whether that minimum lies
 // within s_lo..s_hi; where it does not, the feasible optimum is w at the end towards it.  h is formed from it once per lane
-// and group of 64 batch sizes.  The wave then takes the smallest h (equal values: lowest flat index); only now the count
+// and group of 64 batch sizes.  The wave then takes the smallest h (equal values: lowest flat index; elect_scanned says where the
+// scan's last places must not decide); only now the count
 // of the elected batch size is found, from its C by the same exact rule (feasible_count), and the elected point is evaluated
 // again with the formulas in the paper's own order (separate multiply and add, IEEE
 // division), so the reported goodput does not depend on the fast form.
@@ -138,6 +139,7 @@ constexpr int kStageRowDoubles = 2 * kStageGm + kStageGm / 2;
 constexpr int kStageBase = kNearU + kNearRecips + 8;
 constexpr int kStageDoubles = 2 * kStageGm + kStageRows * kStageRowDoubles;
 constexpr int kPending = -2;             // pairs kernel: grid index of a row whose sweep is still to be done
+constexpr int kClose = -4;               // grid index of a sweep whose scan cannot tell the best batch sizes apart (elect_scanned)
 constexpr int kMetaChanged = 1 << 30;   // meta[pair] = nodes | (row differs from current ? kMetaChanged : 0)
 
 // Parameters of one job (uniform across the wavefront).  The sweep itself needs only
@@ -591,9 +593,79 @@ __device__ __forceinline__ Pick elect(double kbest, int where, unsigned long lon
     return Pick{((wwhere >> 16) | (int)((second >> wl) & 1ull)) * kWave + wl, wwhere & 0xFFFF};
 }
 
+// ---- elections between values of the scan ----------------------------------------------
+// What elects a batch size is its h = fma(T_grad, fma(C, 1 / (s + 1), s), A0) at its best feasible count s: rounding decides between batch
+// sizes whose h agree to the last places, so every way to an argmax (sweeps, memoised rows, fair shares, queries) forms it so.  The
+// scan's minimum may differ from that w in the last places: beyond 16 counts it is rounded once more for each offset, and next to a
+// threshold it may be a neighbour's.  That is less than 2^-49 of h, so the scan's values elect where the smallest is alone within
+// one unit of its high word (2^-20 of itself); where another is as close (one election in 6000 on the timing cases' grids, nearly
+// all where alpha_grad = 0 and gamma = 1 make h a function of m (s + 1)), h itself decides (settle).  1000 candidates of 200 jobs on
+// 64 nodes, 64 x 16, us: 61.1 without this, 60.7 so; 80 where every election of every job is settled.
+__device__ __forceinline__ unsigned high_word(double h) { return (unsigned)__double2hiint(h); }
+
+// Whether the high words of a and b differ by at most one.
+__device__ __forceinline__ bool close_to(double a, double b)
+{
+    unsigned d;
+    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(high_word(a)), "v"(high_word(b)));
+    return d <= 1u;
+}
+
+// The second smallest of least <= second and next.
+__device__ __forceinline__ unsigned second_smallest(unsigned least, unsigned second, unsigned next)
+{
+    unsigned v;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(v) : "v"(least), "v"(second), "v"(next));
+    return v;
+}
+
+// The batch size with the smallest of the scan's h over the wavefront, -1 where there is none, kClose where it is not alone.  kbest: the
+// lane's smallest; its batch size is the lane's number + first(lane), again: the lanes of which another h is close to it.
+// Every lane returns the same result.
+template <typename FIRST>
+__device__ __forceinline__ int elect_scanned(double kbest, unsigned long long again, const FIRST &first)
+{
+    const unsigned hi = high_word(kbest), hmin = wave_min(hi);
+    if (hmin >= 0x7FF00000u) return -1;                        // every lane still holds +inf
+    const unsigned long long close = __builtin_amdgcn_ballot_w64(hi <= hmin + 1u);
+    if ((close & ((close - 1ull) | again)) != 0ull) return kClose;
+    const int wl = __builtin_ctzll(close);
+    return wl + first(wl);
+}
+
+// The elections of two rows of the tables by h itself, without a scan (two, as each waits for a trip to memory).  All 64 lanes call
+// this with the same arguments; picked: the batch sizes, equal values to the lowest.  near: as for sweep_pick, when has_near.
+__device__ __forceinline__ void settle(int (&picked)[2], int lane, const JobTables &tb, const double *__restrict__ rs, LdsDoubles near,
+                                       bool has_near, int Gm, int Gs, const int (&K)[2], const bool (&one_node)[2])
+{
+    double kbest[2] = {__builtin_inf(), __builtin_inf()};
+    int where[2] = {0, 0};
+    for (int i = lane; i < Gm; i += kWave) {
+        const double tg = tb.tg[i].x;
+        double2 car[2];
+        int bounds[2];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            car[n] = tb.ca[(unsigned)((one_node[n] ? kTableK : 0) + K[n] - 1) * (unsigned)Gm + (unsigned)i];
+            bounds[n] = tb.srange[(unsigned)(K[n] - 1) * (unsigned)Gm + (unsigned)i];
+        }
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const int s = feasible_count(car[n].x, bounds[n] & 0xFFFF, bounds[n] >> 16);
+            const double key = px_fma(tg, px_fma(car[n].x, has_near ? near[2 * s] : rs[s], (double)s), car[n].y);
+            if (key < kbest[n]) {
+                kbest[n] = key;
+                where[n] = (i / kWave) << 16;
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) picked[n] = elect(kbest[n], where[n], 0ull, Gs).i;
+}
+
 // All 64 lanes call this with the same (job, nodes, K within the tables).  Every lane returns the same result: the batch size
 // (index into the job's grid) of the feasible point with the smallest h over the whole grid, equal values to the lowest
-// index, or -1 when no point is feasible.  Its count is found where it is priced (price_tabled).
+// index, or -1 when no point is feasible, or kClose.  Its count is found where it is priced (price_tabled).
 // WHOLE: the caller has checked that Gm is a multiple of 64, so no lane runs past the grid of batch sizes.
 template <int CH, bool WHOLE = false, bool STAGED = false>
 __device__ __forceinline__ int sweep_pick(int lane, const JobTables &tb, const RunSteps &X, const double *__restrict__ rs, int Gm, int Gs, int K,
@@ -614,8 +686,9 @@ __device__ __forceinline__ int sweep_pick(int lane, const JobTables &tb, const R
     const unsigned at_range = ((unsigned)lane << 2) + 8u * (unsigned)(staged_row + 2 * kStageGm);
 
     double kbest = __builtin_inf();   // smallest h seen by this lane
-    int where = 0;                    // the index of its group of 64 batch sizes << 16
-    unsigned long long second = 0;    // staged terms: the lanes whose best belongs to the second group (no index in `where`)
+    int where = 0;                    // the first of its group of 64 batch sizes
+    unsigned long long again = 0;     // the lanes of which another h is close to the smallest (elect_scanned)
+    unsigned long long second = 0;    // staged terms: the lanes whose best belongs to the second group (no `where`)
     const ScalarDoubles rsc = (ScalarDoubles)rs;
     auto in_memory = [&](int s, double) { return *(const double *)((const char *)rs + 8u * (unsigned)s); };
 
@@ -663,23 +736,28 @@ __device__ __forceinline__ int sweep_pick(int lane, const JobTables &tb, const R
             // (the smaller of a number and a NaN, where T_grad overflows, is the number)
             const double least = min_f64(kbest, key);
             second = __builtin_amdgcn_ballot_w64(least != kbest);
+            again = __builtin_amdgcn_ballot_w64(close_to(kbest, key));
             kbest = least;
-        } else if (active && key < kbest) {
-            kbest = key;
-            where = (i0 / kWave) << 16;
+        } else {
+            const bool better = active && key < kbest;
+            again = (again & ~__builtin_amdgcn_ballot_w64(better)) | __builtin_amdgcn_ballot_w64(active && close_to(kbest, key));
+            if (better) {
+                kbest = key;
+                where = i0;
+            }
         }
     };
     if (STAGED && staged_row >= 0) {
         group(0, std::integral_constant<int, 0>());
         if (Gm > kWave) group(kWave, std::integral_constant<int, 1>());
-    } else {
-        // the counter of this loop is advanced on the scalar unit (it would otherwise be copied to a vector register)
-        for (int i0 = 0; i0 < Gm;) {
-            group(i0, std::integral_constant<int, -1>());
-            asm volatile("s_add_i32 %0, %0, 64" : "+s"(i0) : : "scc");
-        }
+        return elect_scanned(kbest, again, [&](int l) { return (int)((second >> l) & 1ull) * kWave; });
     }
-    return elect(kbest, where, second, Gs).i;
+    // the counter of this loop is advanced on the scalar unit (it would otherwise be copied to a vector register)
+    for (int i0 = 0; i0 < Gm;) {
+        group(i0, std::integral_constant<int, -1>());
+        asm volatile("s_add_i32 %0, %0, 64" : "+s"(i0) : : "scc");
+    }
+    return elect_scanned(kbest, again, [&](int l) { return __builtin_amdgcn_readlane(where, l); });
 }
 
 // The sweep of a row the tables do not hold, by a plain loop over the feasible counts of each batch size; it returns the
@@ -739,9 +817,8 @@ __device__ __forceinline__ Pick sweep_pick_beyond(const Job &q, const JobTables 
 // wavefront spends more on its cross-lane steps than on the grid: every row of 16 lanes calls this with its own
 // K (1 .. kTableK) and its own one_node (the same in all 16 lanes of a row; the job is the same for the whole
 // wavefront), lane l of a row takes batch sizes l, l + 16, ..., and every lane of a row returns the row's
-// result: the batch size of the feasible point with the smallest h, equal values to the lowest, or -1 when
-// the row has no feasible point.  Per (K, batch size) the arithmetic is that of sweep_pick, instruction for
-// instruction, so both elect the same point.
+// result: the batch size of the feasible point with the smallest h, -1 when the row has no feasible point, or
+// kClose (elect_scanned).
 template <int CH, bool WHOLE>
 __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSteps &X, const double *__restrict__ rs,
                                                int Gm, int Gs, int K, bool one_node, LdsDoubles near, bool has_near)
@@ -752,6 +829,7 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
     const unsigned ca_row = (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm * 16u;
     const unsigned s_row = (unsigned)(K - 1) * (unsigned)Gm * 4u;
     double kbest = __builtin_inf();   // smallest h seen by this lane
+    unsigned runner_up = ~0u;         // the high word of the second smallest
     int where = 0;                    // its batch size
     const ScalarDoubles rsc = (ScalarDoubles)rs;
     auto in_memory = [&](int s, double) { return *(const double *)((const char *)rs + 8u * (unsigned)s); };
@@ -776,7 +854,9 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
             const int i = i0 + 16 * n + l16;
             const Feasible f = has_near ? feasible_end(C[n], bounds[n], near) : feasible_end(C[n], bounds[n] & 0xFFFF, bounds[n] >> 16, in_memory);
             const double key = px_fma(tg[n], f.outside ? f.w : wmin[n], A0[n]);
-            if ((WHOLE || i < Gm) && key < kbest) {
+            const bool active = WHOLE || i < Gm;
+            runner_up = second_smallest(high_word(kbest), runner_up, active ? high_word(key) : ~0u);
+            if (active && key < kbest) {
                 kbest = key;
                 where = i;
             }
@@ -786,13 +866,17 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
         if (WHOLE || i0 + 16 < Gm) sets(i0, std::integral_constant<int, 2>());
         else sets(i0, std::integral_constant<int, 1>());
     }
-    // Positive doubles order like their bit patterns: three unsigned minima over the row, the high words, the
-    // low words among the lanes that hold the smallest high word, and the batch sizes among the lanes that hold both.
-    const unsigned hi = (unsigned)__double2hiint(kbest), lo = (unsigned)__double2loint(kbest);
-    const unsigned hmin = row16_min(hi);
-    const unsigned lmin = row16_min(hi == hmin ? lo : 0xFFFFFFFFu);
-    const unsigned first = row16_min(hi == hmin && lo == lmin ? (unsigned)where : 0x7FFFFFFFu);
-    return hmin >= 0x7FF00000u ? -1 : (int)first;             // every lane of the row still holds +inf: no point
+    // elect_scanned for each row of 16 lanes: one lane a row is close to its smallest h and no other h of that lane, or none of a row
+    // has a point
+    const unsigned hi = high_word(kbest), least = row16_min(hi) + 1u, bound = least < 0x7FEFFFFFu ? least : 0x7FEFFFFFu;
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(hi <= bound), again = __builtin_amdgcn_ballot_w64(runner_up <= bound);
+    int first = (int)row16_min(hi <= bound ? (unsigned)where : ~0u);
+    if (__builtin_expect(16 * __popcll(at) + __popcll(__builtin_amdgcn_ballot_w64(first == -1)) + __popcll(again) != kWave, 0)) {
+        int shift = lane_id() & 48;
+        asm volatile("" : "+v"(shift));               // (nothing of this is formed before the loop)
+        if (__popc((unsigned)(at >> shift) & 0xFFFFu) > 1 || ((unsigned)(again >> shift) & 0xFFFFu) != 0u) first = kClose;
+    }
+    return first;
 }
 
 // Eq. 4 for batch size i of a tabled row at the count the sweep's minimum has there, in the paper's order of operations.  Arguments
@@ -1270,7 +1354,7 @@ __constant__ float small_recips_f32[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), P
 
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
 // CH > 0: a row within the tables; the smallest h of each batch size is found by the scan over all counts (Gs <= kSmallGs), as in the
-// population pass.
+// population pass, and m = kClose says that row_best<0> has to decide (elect_scanned).
 // The elected point is priced from the terms its lane has formed; LEAN: from terms formed anew, which holds five registers less.
 template <int CH = 0, bool LEAN = false>
 __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y,
@@ -1284,6 +1368,7 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
     int where = 0, m_at = 0;
     double C_at = 0.0;               // CH > 0: what the count of the lane's best follows from
     int lo_at = 0, hi_at = 0;
+    int near_it = 0;                 // CH > 0: whether another h of the lane is close to its best (elect_scanned)
     for (int i = lane_id(); i < Gm; i += kWave) {
         const int m = m_row[i];
         const GridPoint g = grid_point(c, gp, m);
@@ -1294,7 +1379,8 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
         if constexpr (CH > 0) {
             const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
             h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, X, (ScalarDoubles)small_recips, Gs), t.A0);
-            if (t.none()) h = __builtin_inf();
+            if (t.none() || (i > 0 && m_row[i > 0 ? i - 1 : 0] == m)) h = __builtin_inf();       // (a twin: see the tables' rows below)
+            near_it = (h < kbest ? 0 : near_it) | (close_to(kbest, h) ? 1 : 0);
         } else {
             h = best_count(g, t, tabled, s_c);
         }
@@ -1313,8 +1399,10 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
             }
         }
     }
-    Pick pick = elect(kbest, where, 0ull, Gs);
-    if (pick.i < 0) return Best{0.0, -1, -1};
+    Pick pick;
+    if constexpr (CH > 0) pick = Pick{elect_scanned(kbest, __ballot(near_it != 0), [&](int l) { return (__builtin_amdgcn_readlane(where, l) >> 16) * kWave; }), -1};
+    else pick = elect(kbest, where, 0ull, Gs);
+    if (pick.i < 0) return Best{0.0, pick.i, -1};
     if constexpr (CH > 0) {
         const int l = pick.i & (kWave - 1);
         pick.s = feasible_count(wave_read(C_at, l), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
@@ -1395,10 +1483,11 @@ __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, co
 //   kPrepSampledMemo  and with its rows memoised
 // Rows of the "one node" class stop at the largest node capacity: a job on one node holds at most that node's GPUs.  A row
 // that claims more there, which no valid allocation does, is swept in place like a row beyond the tables (tabled_row).
-// Table rows: lt[row][i] the last pass, ca[row][i] = (C, A0) with A0 = +inf where no accumulation count is feasible (such a
-// batch size never wins an election), row = (j * 2 + one_node) * kTableK + K - 1; the rows of the "several nodes" class also
-// write the feasible counts of (job, K, i), which do not depend on the class: srange[j][K-1][i] = first | last << 16,
-// first > last when there is none.
+// Table rows: lt[row][i] the last pass, ca[row][i] = (C, A0) with A0 = +inf where no accumulation count is feasible, or where the
+// batch size is the one before it again: geometric grids round their small sizes to the same ones, of equal values the first is
+// elected, and without its twins that one is alone for elect_scanned.  Such a batch size never wins an election.
+// row = (j * 2 + one_node) * kTableK + K - 1; the rows of the "several nodes" class also write the feasible counts of (job, K, i),
+// which do not depend on the class: srange[j][K-1][i] = first | last << 16, first > last when there is none (or a twin).
 // Workgroups are dealt to the XCDs round-robin; a job's wavefronts run on XCD j % 8, as its pairs do.
 enum PrepMode { kPrepPlain, kPrepTables, kPrepTablesF32, kPrepMemo, kPrepSampled, kPrepSampledMemo };
 
@@ -1570,7 +1659,9 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
         for (int i0 = 0; i0 < a.Gm; i0 += kWave) {
             const int i = i0 + lane;
             const bool active = i < a.Gm;
-            const GridPoint g = grid_point(c, gp, m_row[active ? i : a.Gm - 1]);
+            const int il = active ? i : a.Gm - 1, m = m_row[il];
+            const bool twin = il > 0 && m_row[il > 0 ? il - 1 : 0] == m;
+            const GridPoint g = grid_point(c, gp, m);
             double *__restrict__ lt = a.lt + row0 * a.Gm;
             double2 *__restrict__ ca = a.ca + row0 * a.Gm;
             int32_t *__restrict__ ranges = a.srange + ((size_t)j * kTableK + (size_t)(K0 - 1)) * a.Gm;
@@ -1582,7 +1673,7 @@ __device__ __forceinline__ void prepare_rows(const Coefs &c, const FitnessArgs &
                 const double last = last_pass(c, t, g.tg, g.lntg);
                 int s_lo, s_hi;
                 feasible_range(g.ql5, g.qh5, rK, a.Gs, s_lo, s_hi);
-                const bool none = s_lo > s_hi || s_hi < 0;
+                const bool none = s_lo > s_hi || s_hi < 0 || twin;
                 if (none) { s_lo = 1; s_hi = 0; }
                 // what the sweep needs of (job, class, K, i): h(m_i, s) = A0 + T_grad (s + C / (s+1))
                 const double u = g.pu * rK;
@@ -2243,6 +2334,24 @@ pairs_kernel(FitnessArgs a)
         const Job qb = load_job(b.job_params, b.J, j);
         const JobTables tbb = job_tables(b, j);
 
+        // sweeps whose scan has left several batch sizes
+        if constexpr (!MEMO && !F32) {
+            unsigned long long close = __ballot(d_i == kClose);
+            int settle_lane = lane;
+            asm volatile("" : "+v"(settle_lane));          // (its addresses are formed here, not kept from the start on)
+            while (close) {
+                const int l0 = __ffsll(close) - 1;
+                close &= close - 1;
+                const int l1 = close != 0ull ? __ffsll(close) - 1 : l0;
+                close &= close - 1;
+                const int K[2] = {__builtin_amdgcn_readlane(d_K, l0), __builtin_amdgcn_readlane(d_K, l1)};
+                const bool one_node[2] = {(__builtin_amdgcn_readlane(d_meta, l0) & ~kMetaChanged) == 1,
+                                          (__builtin_amdgcn_readlane(d_meta, l1) & ~kMetaChanged) == 1};
+                int picked[2];
+                settle(picked, settle_lane, tbb, b.rs, (LdsDoubles)r_lds, b.gs_pad <= kNearRecips, b.Gm, b.Gs, K, one_node);
+                d_i = lane == l0 ? picked[0] : (lane == l1 ? picked[1] : d_i);
+            }
+        }
         // rows with more GPUs than the tables cover: the whole wavefront sweeps and prices them one by one
         Best beyond = {0.0, -1, -1};
         unsigned long long pending = __ballot(d_i == kPending);
@@ -2574,7 +2683,7 @@ __device__ __forceinline__ unsigned half_min(unsigned v)
 
 // The argmax of two (job, K, placement) at once, one per half of the wavefront, for grids of at most 32 batch sizes; each lane's
 // arguments are its half's.  The lane that holds the elected point (the half's first where there is none) returns it in `best`
-// and is told so.  Term by term row_best<CH>: the same point, the same bits.
+// and is told so.  The same point as row_best finds, the same bits.
 template <int CH>
 __device__ __forceinline__ bool half_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y, int m, bool in_grid,
                                           int Gs, int K, bool one_node, bool tabled, Best &best)
@@ -2586,20 +2695,24 @@ __device__ __forceinline__ bool half_best(const Coefs &c, const Job &q, const Gr
     const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
     double h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, make_run_steps(), (ScalarDoubles)small_recips, Gs), t.A0);
     const int s = feasible_count(t.C, t.s_lo, t.s_hi);
-    if (__ballot(!tabled) != 0ull) {
-        int s_c;
-        const double beyond = best_count(g, t, false, s_c);
-        h = tabled ? h : beyond;
-    }
     h = in_grid && !t.none() && h < __builtin_inf() ? h : __builtin_inf();
-    const unsigned hi = (unsigned)__double2hiint(h), lo = (unsigned)__double2loint(h);
-    const unsigned hmin = half_min(hi);
-    const unsigned lmin = half_min(hi == hmin ? lo : 0xFFFFFFFFu);
     const unsigned lane = (unsigned)lane_id() & (kSmallHalf - 1);
-    const unsigned first = half_min(hi == hmin && lo == lmin ? lane : 0xFFu);      // equal values: the lowest batch size
+    unsigned hi = high_word(h), hmin = half_min(hi);
+    const bool close = hmin < 0x7FF00000u && hi <= hmin + 1u;
+    bool mine = hmin < 0x7FF00000u ? close : lane == 0u;
+    // one lane a half, or h itself decides; rows beyond the tables have no other form
+    if (__popcll(__ballot(mine)) != 2 || __ballot(!tabled) != 0ull) {
+        int s_c;
+        h = best_count(g, t, tabled, s_c);
+        h = in_grid && h < __builtin_inf() ? h : __builtin_inf();
+        hi = high_word(h);
+        hmin = half_min(hi);
+        const unsigned lo = (unsigned)__double2loint(h), lmin = half_min(hi == hmin ? lo : 0xFFFFFFFFu);
+        mine = lane == half_min(hi == hmin && lo == lmin ? lane : 0xFFu);      // equal values: the lowest batch size
+    }
     best = Best{0.0, -1, -1};
     if (hmin < 0x7FF00000u) best = Best{goodput_point(q, (double)K * (double)m, g.tg, last, s), m, s};
-    return lane == first;
+    return mine;
 }
 
 // KEPT: the call keeps the job tables.  HALVES: at most 32 batch sizes.  A wavefront would leave half its lanes idle with one task, and
@@ -2730,8 +2843,10 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
             }
             Best best = {0.0, -1, -1};
             if (K >= 1) {
-                if (__builtin_expect(tabled_row(K, nodes == 1, k1), 1)) best = row_best<CH>(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, true);
-                else best = row_best_plain<false>(q, gp, m_row, a.Gm, a.Gs, K, nodes == 1, false);
+                const bool tabled = tabled_row(K, nodes == 1, k1);
+                best.m = kClose;
+                if (tabled) best = row_best<CH>(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, true);
+                if (__builtin_expect(best.m == kClose, 0)) best = row_best_plain<false>(q, gp, m_row, a.Gm, a.Gs, K, nodes == 1, tabled);
             }
             if (lane == 0) {
                 goodput_lds[j] = best.goodput;
