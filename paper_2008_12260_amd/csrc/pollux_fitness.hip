@@ -601,14 +601,30 @@ __device__ __forceinline__ Pick elect(double kbest, int where, unsigned long lon
 // one unit of its high word (2^-20 of itself); where another is as close (one election in 6000 on the timing cases' grids, nearly
 // all where alpha_grad = 0 and gamma = 1 make h a function of m (s + 1)), h itself decides (settle).  1000 candidates of 200 jobs on
 // 64 nodes, 64 x 16, us: 61.1 without this, 60.7 so; 80 where every election of every job is settled.
-__device__ __forceinline__ unsigned high_word(double h) { return (unsigned)__double2hiint(h); }
+// In single precision the scan's h has five roundings where h itself has four, so two of them can change places within ten units in the
+// last place; sixteen are close.  1000 candidates of 200 jobs on 64 nodes, 64 x 16, us: 62.7 without this, 64.2 so.
+// Positive values order like their bit patterns: the election sees high words of doubles, all bits of single ones.
+template <typename REAL>
+struct Closeness;
 
-// Whether the high words of a and b differ by at most one.
-__device__ __forceinline__ bool close_to(double a, double b)
+template <>
+struct Closeness<double> {
+    static constexpr unsigned kWindow = 1u, kInf = 0x7FF00000u;
+    static __device__ __forceinline__ unsigned bits(double h) { return (unsigned)__double2hiint(h); }
+};
+
+template <>
+struct Closeness<float> {
+    static constexpr unsigned kWindow = 16u, kInf = 0x7F800000u;
+    static __device__ __forceinline__ unsigned bits(float h) { return (unsigned)__float_as_int(h); }
+};
+
+template <typename REAL>
+__device__ __forceinline__ bool close_to(REAL a, REAL b)
 {
     unsigned d;
-    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(high_word(a)), "v"(high_word(b)));
-    return d <= 1u;
+    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(Closeness<REAL>::bits(a)), "v"(Closeness<REAL>::bits(b)));
+    return d <= Closeness<REAL>::kWindow;
 }
 
 // The second smallest of least <= second and next.
@@ -622,15 +638,32 @@ __device__ __forceinline__ unsigned second_smallest(unsigned least, unsigned sec
 // The batch size with the smallest of the scan's h over the wavefront, -1 where there is none, kClose where it is not alone.  kbest: the
 // lane's smallest; its batch size is the lane's number + first(lane), again: the lanes of which another h is close to it.
 // Every lane returns the same result.
-template <typename FIRST>
-__device__ __forceinline__ int elect_scanned(double kbest, unsigned long long again, const FIRST &first)
+template <typename REAL, typename FIRST>
+__device__ __forceinline__ int elect_scanned(REAL kbest, unsigned long long again, const FIRST &first)
 {
-    const unsigned hi = high_word(kbest), hmin = wave_min(hi);
-    if (hmin >= 0x7FF00000u) return -1;                        // every lane still holds +inf
-    const unsigned long long close = __builtin_amdgcn_ballot_w64(hi <= hmin + 1u);
+    const unsigned h = Closeness<REAL>::bits(kbest), least = wave_min(h);
+    if (least >= Closeness<REAL>::kInf) return -1;             // every lane still holds +inf
+    const unsigned long long close = __builtin_amdgcn_ballot_w64(h <= least + Closeness<REAL>::kWindow);
     if ((close & ((close - 1ull) | again)) != 0ull) return kClose;
     const int wl = __builtin_ctzll(close);
     return wl + first(wl);
+}
+
+// The same for each row of 16 lanes: its batch size is `where`, runner_up holds the bits of the lane's second smallest h.  One lane a row
+// is close to the row's smallest h and no other h of that lane, or no lane of the row has a point.
+template <typename REAL>
+__device__ __forceinline__ int elect_scanned_rows(REAL kbest, unsigned runner_up, int where)
+{
+    constexpr unsigned kMost = Closeness<REAL>::kInf - 1u;
+    const unsigned h = Closeness<REAL>::bits(kbest), least = row16_min(h) + Closeness<REAL>::kWindow, bound = least < kMost ? least : kMost;
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(h <= bound), again = __builtin_amdgcn_ballot_w64(runner_up <= bound);
+    int first = (int)row16_min(h <= bound ? (unsigned)where : ~0u);
+    if (__builtin_expect(16 * __popcll(at) + __popcll(__builtin_amdgcn_ballot_w64(first == -1)) + __popcll(again) != kWave, 0)) {
+        int shift = lane_id() & 48;
+        asm volatile("" : "+v"(shift));               // (nothing of this is formed before the loop)
+        if (__popc((unsigned)(at >> shift) & 0xFFFFu) > 1 || ((unsigned)(again >> shift) & 0xFFFFu) != 0u) first = kClose;
+    }
+    return first;
 }
 
 // The elections of two rows of the tables by h itself, without a scan (two, as each waits for a trip to memory).  All 64 lanes call
@@ -829,7 +862,7 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
     const unsigned ca_row = (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm * 16u;
     const unsigned s_row = (unsigned)(K - 1) * (unsigned)Gm * 4u;
     double kbest = __builtin_inf();   // smallest h seen by this lane
-    unsigned runner_up = ~0u;         // the high word of the second smallest
+    unsigned runner_up = ~0u;         // the bits of the second smallest (elect_scanned_rows)
     int where = 0;                    // its batch size
     const ScalarDoubles rsc = (ScalarDoubles)rs;
     auto in_memory = [&](int s, double) { return *(const double *)((const char *)rs + 8u * (unsigned)s); };
@@ -855,7 +888,7 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
             const Feasible f = has_near ? feasible_end(C[n], bounds[n], near) : feasible_end(C[n], bounds[n] & 0xFFFF, bounds[n] >> 16, in_memory);
             const double key = px_fma(tg[n], f.outside ? f.w : wmin[n], A0[n]);
             const bool active = WHOLE || i < Gm;
-            runner_up = second_smallest(high_word(kbest), runner_up, active ? high_word(key) : ~0u);
+            runner_up = second_smallest(Closeness<double>::bits(kbest), runner_up, active ? Closeness<double>::bits(key) : ~0u);
             if (active && key < kbest) {
                 kbest = key;
                 where = i;
@@ -866,17 +899,7 @@ __device__ __forceinline__ int sweep_pick_rows(const JobTables &tb, const RunSte
         if (WHOLE || i0 + 16 < Gm) sets(i0, std::integral_constant<int, 2>());
         else sets(i0, std::integral_constant<int, 1>());
     }
-    // elect_scanned for each row of 16 lanes: one lane a row is close to its smallest h and no other h of that lane, or none of a row
-    // has a point
-    const unsigned hi = high_word(kbest), least = row16_min(hi) + 1u, bound = least < 0x7FEFFFFFu ? least : 0x7FEFFFFFu;
-    const unsigned long long at = __builtin_amdgcn_ballot_w64(hi <= bound), again = __builtin_amdgcn_ballot_w64(runner_up <= bound);
-    int first = (int)row16_min(hi <= bound ? (unsigned)where : ~0u);
-    if (__builtin_expect(16 * __popcll(at) + __popcll(__builtin_amdgcn_ballot_w64(first == -1)) + __popcll(again) != kWave, 0)) {
-        int shift = lane_id() & 48;
-        asm volatile("" : "+v"(shift));               // (nothing of this is formed before the loop)
-        if (__popc((unsigned)(at >> shift) & 0xFFFFu) > 1 || ((unsigned)(again >> shift) & 0xFFFFu) != 0u) first = kClose;
-    }
-    return first;
+    return elect_scanned_rows(kbest, runner_up, where);
 }
 
 // Eq. 4 for batch size i of a tabled row at the count the sweep's minimum has there, in the paper's order of operations.  Arguments
@@ -1054,8 +1077,8 @@ __device__ __forceinline__ Best sweep_f32(const JobF32 &q, const JobTables &tb, 
 // kernel) and one v_min3_f32 per two points: three instructions per two grid points.  Where the argmin over all counts is not
 // feasible w is taken at the end of the feasible counts towards it, by the same exact test as in fp64 (w(s+1) < w(s) exactly when
 // C > (s+1)(s+2); the products are exact for grids of up to 4094 counts).
-// The wave takes the smallest h (equal values: lowest batch size).  The elected point's count follows from its C, and the point is
-// priced with Eq. 4 in the plain form, in fp32 (price_point_f32).  T_grad, u and C are formed in fp32 from the
+// The wave takes the smallest h (equal values: lowest batch size; elect_scanned, settle_f32).  The elected point's count follows from
+// its C, and the point is priced with Eq. 4 in the plain form, in fp32 (price_point_f32).  T_grad, u and C are formed in fp32 from the
 // parameters rounded to fp32; the last pass of Eq. 10 is the fp64 table rounded to fp32.
 typedef const float __attribute__((address_space(4))) *ScalarFloats;
 typedef const float __attribute__((address_space(3))) *LdsFloats;
@@ -1086,8 +1109,8 @@ __device__ __forceinline__ void scan_two_f32(float &wmin, float C, float r0, flo
     else asm("v_min3_f32 %0, %0, %1, %2" : "+v"(wmin) : "v"(w0), "v"(w1));
 }
 
-template <int CH, int B = 0>
-__device__ __forceinline__ void scan_chunk_f32(float &wmin, float C, ScalarFloats r, const RunStepsF32 &X)
+template <int CH, int B = 0, typename RECIPS>
+__device__ __forceinline__ void scan_chunk_f32(float &wmin, float C, const RECIPS &r, const RunStepsF32 &X)
 {
     if constexpr (B < CH) {
         scan_two_f32<B>(wmin, C, r[B], r[B + 1], X);
@@ -1095,18 +1118,24 @@ __device__ __forceinline__ void scan_chunk_f32(float &wmin, float C, ScalarFloat
     }
 }
 
-// The smallest w(s) among all counts of the grid.
-template <int CH>
-__device__ __forceinline__ float scan_min_f32(float C, const RunStepsF32 &X, ScalarFloats rsc, int Gs)
+// The smallest w(s) among all counts of the grid.  first: the reciprocals of the first CH counts.
+template <int CH, typename RECIPS>
+__device__ __forceinline__ float scan_min_f32(float C, const RunStepsF32 &X, ScalarFloats rsc, int Gs, const RECIPS &first)
 {
     float wmin;
-    scan_chunk_f32<CH>(wmin, C, rsc, X);
+    scan_chunk_f32<CH>(wmin, C, first, X);
     for (int s0 = CH; s0 < Gs; s0 += CH) {
         float w;
         scan_chunk_f32<CH>(w, C, rsc + s0, X);               // values relative to the chunk's first count
         wmin = fminf(wmin, w + (float)s0);
     }
     return wmin;
+}
+
+template <int CH>
+__device__ __forceinline__ float scan_min_f32(float C, const RunStepsF32 &X, ScalarFloats rsc, int Gs)
+{
+    return scan_min_f32<CH>(C, X, rsc, Gs, rsc);
 }
 
 // Eq. 9 in fp32.
@@ -1143,6 +1172,13 @@ __device__ __forceinline__ float feasible_h_f32(const TermsF32 &t, int s_lo, int
     return fmaf(t.tg, (int)above | (int)below ? w : wmin, t.A0);
 }
 
+// h at count s, as every election that needs no scan forms it (elect_scanned).
+template <typename RECIP>
+__device__ __forceinline__ float exact_h_f32(const TermsF32 &t, int s, const RECIP &recip)
+{
+    return fmaf(t.tg, fmaf(t.C, recip(s), (float)s), t.A0);
+}
+
 // The feasible count with the smallest w (feasible_count in fp32).
 __device__ __forceinline__ int feasible_count_f32(float C, int s_lo, int s_hi)
 {
@@ -1174,7 +1210,8 @@ __device__ __forceinline__ int sweep_pick_f32(const JobF32 &q, const JobTables &
     auto recip = [&](int s) { return has_near ? near[s] : rsf[s]; };
 
     float kbest = __builtin_inff();   // smallest h seen by this lane
-    int where = 0;                    // the index of its group of 64 batch sizes
+    int where = 0;                    // the first of its group of 64 batch sizes
+    unsigned long long again = 0;     // the lanes of which another h is close to the smallest (elect_scanned)
     for (int i0 = 0; i0 < Gm; i0 += kWave) {
         const int i = i0 + lane;
         const bool active = WHOLE || i < Gm;
@@ -1184,23 +1221,35 @@ __device__ __forceinline__ int sweep_pick_f32(const JobF32 &q, const JobTables &
         const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
         const bool feasible = active && s_lo <= s_hi;
         const float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<CH>(t.C, X, rsc, Gs), recip);
-        if (feasible && key < kbest) {
+        const bool better = feasible && key < kbest;
+        if (i0 > 0) again = (again & ~__builtin_amdgcn_ballot_w64(better)) | __builtin_amdgcn_ballot_w64(feasible && close_to(kbest, key));
+        if (better) {
             kbest = key;
-            where = i0 / kWave;
+            where = i0;
         }
     }
-    // positive floats order like their bit patterns
-    const unsigned bits = (unsigned)__float_as_int(kbest);
-    const unsigned bmin = wave_min(bits);
-    if (bmin >= 0x7F800000u) return -1;                         // every lane still holds +inf (or a NaN)
-    unsigned long long winners = __builtin_amdgcn_ballot_w64(bits == bmin);
-    if (winners & (winners - 1)) {
-        // equal values: the lowest batch size
-        const bool top = ((winners >> lane) & 1ull) != 0;
-        return wave_min(top ? where * kWave + lane : 0x7FFFFFFF);
+    return elect_scanned(kbest, again, [&](int l) { return __builtin_amdgcn_readlane(where, l); });
+}
+
+// The election of a row of the tables by h itself, as settle in fp64.  All 64 lanes call this with the same arguments.
+__device__ __forceinline__ int settle_f32(int lane, const JobF32 &q, const JobTables &tb, const float *__restrict__ rsf, int Gm, int Gs, int K,
+                                          bool one_node)
+{
+    const double *__restrict__ lrow = tb.lt + (unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm;
+    const int32_t *__restrict__ srow = tb.srange + (unsigned)(K - 1) * (unsigned)Gm;
+    const float Kf = (float)K, ts = t_sync_f32(q, K, one_node);
+    float kbest = __builtin_inff();
+    int where = 0;
+    for (int i = lane; i < Gm; i += kWave) {
+        const TermsF32 t = terms_f32(q, ts, Kf, tb.m[i], (float)lrow[i]);
+        const int s_lo = srow[i] & 0xFFFF, s_hi = srow[i] >> 16;
+        const float key = exact_h_f32(t, feasible_count_f32(t.C, s_lo, s_hi), [&](int s) { return rsf[s]; });
+        if (s_lo <= s_hi && key < kbest) {
+            kbest = key;
+            where = (i / kWave) << 16;
+        }
     }
-    const int wl = __ffsll(winners) - 1;
-    return __builtin_amdgcn_readlane(where, wl) * kWave + wl;
+    return elect((double)kbest, where, 0ull, Gs).i;        // (positive floats order like their values in double precision)
 }
 
 // The same election for four (job, K, placement) at once, one per row of 16 lanes, as sweep_pick_rows does in fp64: lane l of
@@ -1218,26 +1267,31 @@ __device__ __forceinline__ int sweep_pick_rows_f32(const JobF32 &q, const JobTab
     const ScalarFloats rsc = (ScalarFloats)rsf;
     auto recip = [&](int s) { return has_near ? near[s] : rsf[s]; };
     float kbest = __builtin_inff();
-    int where = 0x7FFFFFFF;
+    unsigned runner_up = ~0u;         // the bits of the second smallest (elect_scanned_rows)
+    int where = 0;
     for (int i0 = 0; i0 < Gm; i0 += 16) {
         const int i = i0 + l16;
         const bool active = WHOLE || i < Gm;
         const unsigned il = (unsigned)(active ? i : Gm - 1);
-        const TermsF32 t = terms_f32(q, ts, Kf, tb.m[il], (float)*(const double *)((const char *)tb.lt + (l_row + 8u * il)));
+        const int m = *(const int32_t *)((const char *)tb.m + 4u * il);
+        const double last = *(const double *)((const char *)tb.lt + (l_row + 8u * il));
         const int bounds = *(const int32_t *)((const char *)tb.srange + (s_row + 4u * il));
+        float first[CH];
+#pragma unroll
+        for (int b = 0; b < CH; ++b) first[b] = rsc[b];
+        __builtin_amdgcn_sched_barrier(0);            // (all are asked for before the first is waited for)
+        const TermsF32 t = terms_f32(q, ts, Kf, m, (float)last);
         const int s_lo = bounds & 0xFFFF, s_hi = bounds >> 16;
         const bool feasible = active && s_lo <= s_hi;
-        const float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<CH>(t.C, X, rsc, Gs), recip);
-        if (feasible && key < kbest) {
+        float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<CH>(t.C, X, rsc, Gs, first), recip);
+        key = feasible ? key : __int_as_float(-1);         // (not a number: never smaller, and the largest of bit patterns)
+        runner_up = second_smallest(Closeness<float>::bits(kbest), runner_up, Closeness<float>::bits(key));
+        if (key < kbest) {
             kbest = key;
             where = i;
         }
     }
-    // positive floats order like their bit patterns; equal values: the lowest batch size
-    const unsigned bits = (unsigned)__float_as_int(kbest);
-    const unsigned bmin = row16_min(bits);
-    const unsigned first = row16_min(bits == bmin ? (unsigned)where : 0x7FFFFFFFu);
-    return bmin >= 0x7F800000u ? -1 : (int)first;
+    return elect_scanned_rows(kbest, runner_up, where);
 }
 
 // Eq. 4 for batch size i at its best feasible count, in the plain form, in fp32, for a GPU count within the tables.  Arguments may
@@ -1266,7 +1320,9 @@ __device__ __forceinline__ Best sweep_any_f32(const JobF32 &q, const JobTables &
     nodes = __builtin_amdgcn_readfirstlane(nodes);
     if (K <= 0) return Best{0.0, -1, -1};
     if (!tabled_row(K, nodes == 1, tb.k1)) return sweep_f32(q, tb, rk, Gm, Gs, K, nodes);
-    return price_point_f32(q, tb, Gm, K, nodes == 1, sweep_pick_f32<CH, false>(q, tb, make_run_steps_f32(), rsf, Gm, Gs, K, nodes));
+    int i = sweep_pick_f32<CH, false>(q, tb, make_run_steps_f32(), rsf, Gm, Gs, K, nodes);
+    if (i == kClose) i = settle_f32(lane_id(), q, tb, rsf, Gm, Gs, K, nodes == 1);
+    return price_point_f32(q, tb, Gm, K, nodes == 1, i);
 }
 
 // ---- per job: what the status word says of its parameters, and its current row ------------------
@@ -1425,7 +1481,9 @@ __device__ __forceinline__ Best row_best_plain(const Job &q, const GridParams &g
 }
 
 // The same in single precision, for a GPU count within the tables and grids of at most kSmallGs counts: term by term what
-// sweep_pick_f32 and price_point_f32 make of the tables, so the same point and the same bits.
+// sweep_pick_f32 and price_point_f32 make of the tables, so the same point and the same bits.  SCAN: m = kClose says that the instance
+// without a scan has to decide (elect_scanned).
+template <bool SCAN>
 __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, const GridParams &gp, const SyncParams &y,
                                              const int32_t *__restrict__ m_row, int Gm, int Gs, int K, bool one_node)
 {
@@ -1435,16 +1493,20 @@ __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, co
     const float Kf = (float)K, ts = t_sync_f32(q, K, one_node);
     float kbest = __builtin_inff();
     TermsF32 at = {};                     // the lane's best: its terms, batch size and feasible counts
-    int where = 0, m_at = 0, lo_at = 0, hi_at = 0;
+    int where = 0, m_at = 0, lo_at = 0, hi_at = 0, near_it = 0;
+    auto recip = [](int s) { return 1.0f / (float)(s + 1); };
     for (int i = lane_id(); i < Gm; i += kWave) {
         const int m = m_row[i];
+        const bool twin = i > 0 && m_row[i > 0 ? i - 1 : 0] == m;         // (see prepare_rows)
         const GridPoint g = grid_point(c, gp, m);
         const TermsF32 t = terms_f32(q, ts, Kf, m, (float)last_pass(c, st, g.tg, g.lntg));
         int s_lo, s_hi;
         feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
-        const bool feasible = s_lo <= s_hi && s_hi >= 0;
-        const float key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<16>(t.C, X, (ScalarFloats)small_recips_f32, Gs),
-                                         [](int s) { return 1.0f / (float)(s + 1); });
+        const bool feasible = s_lo <= s_hi && s_hi >= 0 && !twin;
+        float key;
+        if constexpr (SCAN) key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<16>(t.C, X, (ScalarFloats)small_recips_f32, Gs), recip);
+        else key = exact_h_f32(t, feasible_count_f32(t.C, s_lo, s_hi), recip);
+        if (feasible) near_it = (key < kbest ? 0 : near_it) | (close_to(kbest, key) ? 1 : 0);
         if (feasible && key < kbest) {
             kbest = key;
             where = (i / kWave) << 16;
@@ -1454,10 +1516,11 @@ __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, co
             hi_at = s_hi;
         }
     }
-    // (positive floats order like their values in double precision)
-    const Pick pick = elect((double)kbest, where, 0ull, Gs);
-    if (pick.i < 0) return Best{0.0, -1, -1};
-    const int l = pick.i & (kWave - 1);
+    int i;
+    if constexpr (SCAN) i = elect_scanned(kbest, __ballot(near_it != 0), [&](int l) { return (__builtin_amdgcn_readlane(where, l) >> 16) * kWave; });
+    else i = elect((double)kbest, where, 0ull, Gs).i;      // (positive floats order like their values in double precision)
+    if (i < 0) return Best{0.0, i, -1};
+    const int l = i & (kWave - 1);
     auto read = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
     const int m = __builtin_amdgcn_readlane(m_at, l);
     const int s = feasible_count_f32(read(at.C), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
@@ -1552,8 +1615,10 @@ __device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a
             return double2{g.ql5, g.qh5};
         };
         const JobF32 qf = load_job_f32(jp, a.J, j);
-        if (K > 0 && K <= kTableK && (!one_node || node_holds(a, K))) fair = row_best_f32(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
-        else if (K > 0) fair = sweep_beyond_f32(qf, m_row, terms, 1.0 / (double)K, a.Gm, a.Gs, K, one_node ? 1 : 2);
+        if (K > 0 && K <= kTableK && (!one_node || node_holds(a, K))) {
+            fair = row_best_f32<true>(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
+            if (fair.m == kClose) fair = row_best_f32<false>(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
+        } else if (K > 0) fair = sweep_beyond_f32(qf, m_row, terms, 1.0 / (double)K, a.Gm, a.Gs, K, one_node ? 1 : 2);
     } else if (K > 0) fair = row_best(c, q, gp, y, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
     if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
     if (lane == 0) {
@@ -2335,13 +2400,19 @@ pairs_kernel(FitnessArgs a)
         const JobTables tbb = job_tables(b, j);
 
         // sweeps whose scan has left several batch sizes
-        if constexpr (!MEMO && !F32) {
+        if constexpr (!MEMO) {
             unsigned long long close = __ballot(d_i == kClose);
             int settle_lane = lane;
             asm volatile("" : "+v"(settle_lane));          // (its addresses are formed here, not kept from the start on)
             while (close) {
                 const int l0 = __ffsll(close) - 1;
                 close &= close - 1;
+                if constexpr (F32) {
+                    const int i = settle_f32(settle_lane, qf, tbb, b.rsf, b.Gm, b.Gs, __builtin_amdgcn_readlane(d_K, l0),
+                                             (__builtin_amdgcn_readlane(d_meta, l0) & ~kMetaChanged) == 1);
+                    if (lane == l0) d_i = i;
+                    continue;
+                }
                 const int l1 = close != 0ull ? __ffsll(close) - 1 : l0;
                 close &= close - 1;
                 const int K[2] = {__builtin_amdgcn_readlane(d_K, l0), __builtin_amdgcn_readlane(d_K, l1)};
@@ -2697,15 +2768,15 @@ __device__ __forceinline__ bool half_best(const Coefs &c, const Job &q, const Gr
     const int s = feasible_count(t.C, t.s_lo, t.s_hi);
     h = in_grid && !t.none() && h < __builtin_inf() ? h : __builtin_inf();
     const unsigned lane = (unsigned)lane_id() & (kSmallHalf - 1);
-    unsigned hi = high_word(h), hmin = half_min(hi);
-    const bool close = hmin < 0x7FF00000u && hi <= hmin + 1u;
+    unsigned hi = (unsigned)__double2hiint(h), hmin = half_min(hi);
+    const bool close = hmin < 0x7FF00000u && hi <= hmin + Closeness<double>::kWindow;
     bool mine = hmin < 0x7FF00000u ? close : lane == 0u;
     // one lane a half, or h itself decides; rows beyond the tables have no other form
     if (__popcll(__ballot(mine)) != 2 || __ballot(!tabled) != 0ull) {
         int s_c;
         h = best_count(g, t, tabled, s_c);
         h = in_grid && h < __builtin_inf() ? h : __builtin_inf();
-        hi = high_word(h);
+        hi = (unsigned)__double2hiint(h);
         hmin = half_min(hi);
         const unsigned lo = (unsigned)__double2loint(h), lmin = half_min(hi == hmin ? lo : 0xFFFFFFFFu);
         mine = lane == half_min(hi == hmin && lo == lmin ? lane : 0xFFu);      // equal values: the lowest batch size

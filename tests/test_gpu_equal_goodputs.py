@@ -1,6 +1,8 @@
 """Jobs whose batch sizes tie.  With alpha_grad = 0 and gamma = 1 (both bounds of the fit) the goodput depends on the total batch size
 alone, so batch sizes with a common multiple agree to the last places and rounding elects one of them: the sweeps (one candidate at a
 time, four, with rows copied on chip), small calls, memoised rows and fair shares have to round alike, whatever the number of counts."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -59,3 +61,74 @@ def test_every_way_elects_the_same_batch_size(P, J, N, Gm, Gs, first):
     ref = run_oracle(wl, population=some, current=pop[0])
     for k in ("best_goodput", "speedup"):
         assert np.max(np.abs(got[k][:9] - ref[k]) / np.where(ref[k] == 0, 1.0, ref[k])) <= 1e-12, k
+
+
+def single(x):
+    """A fraction rounded to single precision (values far from underflow)."""
+    if x == 0:
+        return x
+    e = x.numerator.bit_length() - x.denominator.bit_length()
+    while Fraction(2) ** e > x:
+        e -= 1
+    while Fraction(2) ** (e + 1) <= x:
+        e += 1
+    return Fraction(round(x * Fraction(2) ** (23 - e))) / Fraction(2) ** (23 - e)
+
+
+def elected(phi, ts, beta, K, sizes, M0, M_max, Gs):
+    """(m, s) of the smallest h = fma(T_grad, fma(C, 1 / (s + 1), s), A0), every operation rounded to single precision; equal values to
+    the first batch size.  K, the sizes and beta are powers of two, so the reciprocals 1 / (K m) and 1 / T_grad are exact."""
+    best = None
+    for m in sizes:
+        tg = beta * m
+        last = single(tg + ts)
+        u = single(phi / (K * m))
+        A0, C = single(u * tg + last), single(single(last - tg) * u) / tg
+        assert C == single(C)
+        s_lo, s_hi = max(0, -(-M0 // (K * m)) - 1), min(Gs - 1, M_max // (K * m) - 1)
+        if s_lo > s_hi:
+            continue
+        t = 0
+        while t < s_hi and C > (t + 1) * (t + 2):
+            t += 1
+        s = max(t, s_lo)
+        h = single(tg * single(C * single(Fraction(1, s + 1)) + s) + A0)
+        if best is None or h < best[0]:
+            best = (h, m, s)
+    return best[1:] if best else (-1, -1)
+
+
+@pytest.mark.parametrize("P,J,N,Gm,Gs,memo", [
+    (8, 120, 16, 7, 64, False), (48, 120, 16, 50, 33, False), (48, 120, 64, 64, 300, False), (8, 120, 130, 130, 32, False),
+    (48, 120, 128, 128, 64, False), (8, 120, 16, 130, 64, True), (8, 120, 3, 64, 48, False), (8, 120, 16, 64, 16, False)])
+def test_single_precision_elects_by_one_rounding_of_h(P, J, N, Gm, Gs, memo):
+    import paper_2008_12260_amd as px
+    wl = W.make(W.custom("ties", P=8, J=J, N=N, cap=16, Gm=Gm, Gs=Gs, index=2700 + N))
+    jp, row, rng = wl.job_params, W.PARAM_INDEX, np.random.default_rng(Gm + Gs)
+    jp[row["alpha_grad"]], jp[row["gamma"]], jp[row["beta_grad"]] = 0.0, 1.0, 2.0 ** -14
+    jp[row["beta_sync_local"]], jp[row["beta_sync_node"]] = 0.0, 0.0
+    for name, lo, hi in (("alpha_sync_local", 0.005, 0.05), ("alpha_sync_node", 0.02, 0.2), ("phi", 1e2, 1e5)):
+        jp[row[name]] = np.exp(rng.uniform(np.log(lo), np.log(hi), J)).astype(np.float32)
+    jp[row["M0"]], jp[row["M_max"]] = 32.0, 32.0 * rng.choice([32, 256, 2048], J)
+    sizes = [2, 4, 8, 16, 32, 64, 128]
+    at = np.sort(rng.choice(Gm, 7, replace=False))           # the others are too large for any job
+    wl.m_grid[:] = 1 << 20
+    wl.m_grid[:, at] = sizes
+    pop = np.zeros((P, J, N), np.int32)
+    for c in range(P):
+        pop[c, :, 0] = 2 ** (1 + c % 4)
+        if (c // 4) % 2:
+            pop[c, :, 0] //= 2
+            pop[c, :, 1] = pop[c, :, 0]
+    wl.fair_share[:, 0], wl.fair_share[:, 1] = pop[0].sum(1), 1
+    got = results(wl, pop, flags=px.PX_FLAG_MEMOISE if memo else 0, precision=1)
+    for c in range(min(P, 8)):
+        nodes = 1 + (c // 4) % 2
+        for j in range(J):
+            ts = jp[row["alpha_sync_local" if nodes == 1 else "alpha_sync_node"], j]
+            want = elected(Fraction(jp[row["phi"], j]), Fraction(ts), Fraction(1, 2 ** 14), 2 ** (1 + c % 4), sizes, 32,
+                           int(jp[row["M_max"], j]), Gs)
+            assert (got["best_m"][c, j], got["best_s"][c, j]) == want, (c, j)
+    for k in ("best_m", "best_s", "best_goodput"):
+        assert np.array_equal(got[k], got[k][np.arange(P) % 8]), k
+    assert np.array_equal(got["speedup"][0], np.where(got["best_goodput"][0] > 0.0, 1.0, 0.0))
