@@ -50,7 +50,7 @@
 // within s_lo..s_hi; where it does not, the feasible optimum is w at the end towards it.  h is formed from it once per lane
 // and group of 64 batch sizes.  The wave then takes the smallest h (equal values: lowest flat index; elect_scanned says where the
 // scan's last places must not decide); only now the count
-// of the elected batch size is found, from its C by the same exact rule (feasible_count), and the elected point is evaluated
+// of the elected batch size is found, from its C by the same exact rule (px_best_count), and the elected point is evaluated
 // again with the formulas in the paper's own order (separate multiply and add, IEEE
 // division), so the reported goodput does not depend on the fast form.
 //
@@ -341,7 +341,7 @@ __device__ __forceinline__ double goodput_point(const Job &q, double Km, double 
 // eight VALU instructions per four points; the reciprocals arrive through the scalar cache.  Each run of sixteen
 // positions has a minimum of its own (values relative to the run's first position); the runs are merged after
 // the chunk.  Which count attains the minimum is not looked for here: one lane of sixty-four wins the election, and
-// its count follows from C when the elected point is priced (feasible_count).
+// its count follows from C when the elected point is priced (px_best_count).
 // (With every group of four carrying its position in its low mantissa bits, nine instructions per four points, and every lane
 // finding its count with five comparisons, a pair of 128 batch sizes x 32 counts took 248 vector instructions, 220 so: 4096 candidates
 // of 1000 jobs 1.78 ms against 1.66, 1000 of 200 on 64 nodes 52.5 us against 46; fp32, which also loses its tags, 52.0 against 44.7.)
@@ -539,19 +539,6 @@ __device__ __forceinline__ Feasible feasible_end(double C, int s_lo, int s_hi, c
     return Feasible{(int)above | (int)(C <= px_fma(lo, lo, lo)), px_fma(C, recip(s, sd), sd)};
 }
 
-// The feasible count s_lo .. s_hi with the smallest w (no scan): the largest t with C > t (t + 1), clamped.
-// t is found in fp32, where sqrt(C + 1/4) - 1/2 is off by less than 0.003 for every count a grid can have (below 2^14); taken 0.01
-// lower it is t or t - 1, and the exact order of neighbours says which.  (C = 0: t = 0.  Any C beyond the grid: s_hi.)
-__device__ __forceinline__ int feasible_count(double C, int s_lo, int s_hi)
-{
-    int t = (int)(__builtin_amdgcn_sqrtf((float)C + 0.25f) - 0.51f);
-    t = t < s_hi ? t : s_hi;
-    const double td = (double)t;
-    t += C > px_fma(td, td, px_fma(3.0, td, 2.0)) ? 1 : 0;
-    t = t < s_hi ? t : s_hi;
-    return t > s_lo ? t : s_lo;
-}
-
 // The grid point a sweep elects: index into the job's batch-size grid and accumulation
 // count; i = -1 when no point is feasible.
 struct Pick {
@@ -684,7 +671,7 @@ __device__ __forceinline__ void settle(int (&picked)[2], int lane, const JobTabl
         }
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-            const int s = feasible_count(car[n].x, bounds[n] & 0xFFFF, bounds[n] >> 16);
+            const int s = px_best_count(car[n].x, bounds[n] & 0xFFFF, bounds[n] >> 16);
             const double key = px_fma(tg, px_fma(car[n].x, has_near ? near[2 * s] : rs[s], (double)s), car[n].y);
             if (key < kbest[n]) {
                 kbest[n] = key;
@@ -911,7 +898,7 @@ __device__ __forceinline__ Best price_tabled(const Job &q, const JobTables &tb, 
     // (all five asked for before the first is waited for)
     const double C = tb.ca[row].x, last = tb.lt[row], tg = tb.tg[i].x;
     const int bounds = tb.srange[(unsigned)(K - 1) * (unsigned)Gm + (unsigned)i], m = tb.m[i];
-    const int s = feasible_count(C, bounds & 0xFFFF, bounds >> 16);
+    const int s = px_best_count(C, bounds & 0xFFFF, bounds >> 16);
     return Best{goodput_point(q, (double)K * (double)m, tg, last, s), m, s};
 }
 
@@ -1179,17 +1166,6 @@ __device__ __forceinline__ float exact_h_f32(const TermsF32 &t, int s, const REC
     return fmaf(t.tg, fmaf(t.C, recip(s), (float)s), t.A0);
 }
 
-// The feasible count with the smallest w (feasible_count in fp32).
-__device__ __forceinline__ int feasible_count_f32(float C, int s_lo, int s_hi)
-{
-    int t = (int)(__builtin_amdgcn_sqrtf(C + 0.25f) - 0.51f);
-    t = t < s_hi ? t : s_hi;
-    const float td = (float)t;
-    t += C > fmaf(td, td, fmaf(3.0f, td, 2.0f)) ? 1 : 0;
-    t = t < s_hi ? t : s_hi;
-    return t > s_lo ? t : s_lo;
-}
-
 // All 64 lanes call this with the same (job, 1 <= K <= kTableK, nodes); every lane returns the same result.
 // rsf: 1/(s+1) in fp32, padded to a multiple of 32 counts; near: a copy of it in LDS when has_near.  Returns the batch size of the
 // feasible point with the smallest h, or -1.
@@ -1243,7 +1219,7 @@ __device__ __forceinline__ int settle_f32(int lane, const JobF32 &q, const JobTa
     for (int i = lane; i < Gm; i += kWave) {
         const TermsF32 t = terms_f32(q, ts, Kf, tb.m[i], (float)lrow[i]);
         const int s_lo = srow[i] & 0xFFFF, s_hi = srow[i] >> 16;
-        const float key = exact_h_f32(t, feasible_count_f32(t.C, s_lo, s_hi), [&](int s) { return rsf[s]; });
+        const float key = exact_h_f32(t, px_best_count(t.C, s_lo, s_hi), [&](int s) { return rsf[s]; });
         if (s_lo <= s_hi && key < kbest) {
             kbest = key;
             where = (i / kWave) << 16;
@@ -1303,7 +1279,7 @@ __device__ __forceinline__ Best price_point_f32(const JobF32 &q, const JobTables
     const TermsF32 t = terms_f32(q, t_sync_f32(q, K, one_node), (float)K, m,
                                  (float)tb.lt[(unsigned)((one_node ? kTableK : 0) + K - 1) * (unsigned)Gm + (unsigned)i]);
     const int bounds = tb.srange[(unsigned)(K - 1) * (unsigned)Gm + (unsigned)i];
-    const int s = feasible_count_f32(t.C, bounds & 0xFFFF, bounds >> 16);
+    const int s = px_best_count(t.C, bounds & 0xFFFF, bounds >> 16);
     const float M = (float)K * (float)m * (float)(s + 1);
     const float t_iter = (float)s * t.tg + t.last;                            // Eq. 11
     const float g = (M / t_iter) * (q.a / (q.phi + M));                       // Eq. 7 x Eq. 6
@@ -1367,7 +1343,7 @@ __device__ __forceinline__ CurrentRow current_row(const FitnessArgs &a, int j)
 // ---- the argmax of one (job, K, placement) in place ------------------------------------------
 // What the calls that ask for a handful of argmaxes per job need (fair shares, memoised rows, rows beyond the memo table,
 // the queries outside the search): the same election as sweep_pick without any table.  Lane l forms the terms of its batch
-// sizes itself; the best accumulation count needs no scan (feasible_count).
+// sizes itself; the best accumulation count needs no scan (px_best_count).
 
 // The terms of one batch size with 1/K = rK: h(s) = A0 + T_grad (s + C / (s + 1)), and its feasible counts.
 struct RowTerms {
@@ -1393,7 +1369,7 @@ __device__ __forceinline__ RowTerms row_terms(const GridPoint &g, double last, d
 // keeps the form its sweep has.
 __device__ __forceinline__ double best_count(const GridPoint &g, const RowTerms &t, bool tabled, int &s_c)
 {
-    s_c = feasible_count(t.C, t.s_lo, t.s_hi);
+    s_c = px_best_count(t.C, t.s_lo, t.s_hi);
     const double sd = (double)s_c, r = px_div(1.0, sd + 1.0);
     const double h = tabled ? px_fma(g.tg, px_fma(t.C, r, sd), t.A0) : px_fma(t.B0, r, px_fma(sd, g.tg, t.A0));
     return t.none() ? __builtin_inf() : h;
@@ -1461,7 +1437,7 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
     if (pick.i < 0) return Best{0.0, pick.i, -1};
     if constexpr (CH > 0) {
         const int l = pick.i & (kWave - 1);
-        pick.s = feasible_count(wave_read(C_at, l), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
+        pick.s = px_best_count(wave_read(C_at, l), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
     }
     if constexpr (LEAN) {
         const int m = m_row[pick.i];
@@ -1505,7 +1481,7 @@ __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, co
         const bool feasible = s_lo <= s_hi && s_hi >= 0 && !twin;
         float key;
         if constexpr (SCAN) key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<16>(t.C, X, (ScalarFloats)small_recips_f32, Gs), recip);
-        else key = exact_h_f32(t, feasible_count_f32(t.C, s_lo, s_hi), recip);
+        else key = exact_h_f32(t, px_best_count(t.C, s_lo, s_hi), recip);
         if (feasible) near_it = (key < kbest ? 0 : near_it) | (close_to(kbest, key) ? 1 : 0);
         if (feasible && key < kbest) {
             kbest = key;
@@ -1523,7 +1499,7 @@ __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, co
     const int l = i & (kWave - 1);
     auto read = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
     const int m = __builtin_amdgcn_readlane(m_at, l);
-    const int s = feasible_count_f32(read(at.C), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
+    const int s = px_best_count(read(at.C), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
     const float M = (float)K * (float)m * (float)(s + 1);
     const float t_iter = (float)s * read(at.tg) + read(at.last);              // Eq. 11
     const float g = (M / t_iter) * (q.a / (q.phi + M));                       // Eq. 7 x Eq. 6
@@ -2765,7 +2741,7 @@ __device__ __forceinline__ bool half_best(const Coefs &c, const Job &q, const Gr
     const RowTerms t = row_terms(g, last, 1.0 / (double)K, Gs);
     const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
     double h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, make_run_steps(), (ScalarDoubles)small_recips, Gs), t.A0);
-    const int s = feasible_count(t.C, t.s_lo, t.s_hi);
+    const int s = px_best_count(t.C, t.s_lo, t.s_hi);
     h = in_grid && !t.none() && h < __builtin_inf() ? h : __builtin_inf();
     const unsigned lane = (unsigned)lane_id() & (kSmallHalf - 1);
     unsigned hi = (unsigned)__double2hiint(h), hmin = half_min(hi);

@@ -23,6 +23,10 @@ inline double px_rcp_seed(double x) { return (double)(1.0f / (float)x) * (1.0 + 
 inline double px_ldexp(double x, int k) { return std::ldexp(x, k); }
 inline double px_rint(double x) { return std::nearbyint(x); }
 inline double px_max(double a, double b) { return std::fmax(a, b); }
+inline float px_fma(float a, float b, float c) { return std::fma(a, b, c); }
+inline float root_skew = 0.0f;      // set by a test: the hardware's root is off by up to one unit in the last place
+inline float px_sqrt(float x) { return std::sqrt(x) * (1.0f + root_skew); }
+inline float px_median0(float x, float y) { return x != x ? std::fmin(0.0f, y) : std::fmax(std::fmin(x, y), std::fmin(std::fmax(x, y), 0.0f)); }
 }  // namespace px
 #else
 #include <hip/hip_runtime.h>
@@ -33,6 +37,9 @@ PX_DEV double px_rcp_seed(double x) { return __builtin_amdgcn_rcp(x); }         
 PX_DEV double px_ldexp(double x, int k) { return __builtin_amdgcn_ldexp(x, k); }    // v_ldexp_f64
 PX_DEV double px_rint(double x) { return __builtin_rint(x); }                       // v_rndne_f64
 PX_DEV double px_max(double a, double b) { return __builtin_fmax(a, b); }            // v_max_f64: b where a is not a number
+PX_DEV float px_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+PX_DEV float px_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }                 // v_sqrt_f32
+PX_DEV float px_median0(float x, float y) { return __builtin_amdgcn_fmed3f(x, 0.0f, y); }   // v_med3_f32: min(0, y) where x is not a number
 }  // namespace px
 #endif
 
@@ -139,6 +146,20 @@ PX_DEV double px_log(const Coefs &c, double x)
     const double l = px_two_atanh(c, px_div(f, 2.0 + f));
     const double kd = (double)k;
     return px_fma(kd, c.ln2, px_fma(kd, c.ln2_low, l));
+}
+
+// The count s_lo <= s <= s_hi with the smallest w(s) = s + C / (s + 1): the largest t with C > t (t + 1), clamped (REAL = float: exact for
+// counts up to 4094).  t is found in fp32, where sqrt(C + 1/4) - 1/2 is off by less than 0.008 for every count a grid can have
+// (below 2^14); taken 0.01 lower it is t or t - 1, and the exact order of neighbours says which.  C = 0, a negative one and what is
+// no number: t = 0.  Any C beyond the grid, infinity too: s_hi (the root is clamped before it becomes a whole number).
+template <typename REAL>
+PX_DEV int px_best_count(REAL C, int s_lo, int s_hi)
+{
+    int t = (int)px_median0(px_sqrt((float)C + 0.25f) - 0.51f, (float)s_hi);
+    const REAL td = (REAL)t;
+    t += C > px_fma(td, td, px_fma((REAL)3, td, (REAL)2)) ? 1 : 0;
+    t = t < s_hi ? t : s_hi;
+    return t > s_lo ? t : s_lo;
 }
 
 PX_DEV double px_exp(double t) { return px_exp(plain_coefs(), t); }

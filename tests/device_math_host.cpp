@@ -14,6 +14,13 @@ static double ulp_err(double got, long double want)
 }
 
 extern "C" {
+// px_best_count for n values, with the root off by `skew` of itself.
+void px_host_best_counts(const double *C, long n, int s_lo, int s_hi, float skew, int single, int *count)
+{
+    px::root_skew = skew;
+    for (long i = 0; i < n; ++i) count[i] = single ? px::px_best_count((float)C[i], s_lo, s_hi) : px::px_best_count(C[i], s_lo, s_hi);
+    px::root_skew = 0.0f;
+}
 // How many of n quotients a / b are not the correctly rounded one, and how many have another floor than the integers' quotient
 // (integers: a and b hold integers below 2^53), with the reciprocal's seed off by `skew` of itself.
 void px_host_div_faults(const double *a, const double *b, long n, double skew, int integers, long *rounding, long *whole)

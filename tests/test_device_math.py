@@ -114,3 +114,34 @@ def test_integer_quotients_have_the_right_floor(host_math, skew):
     b = np.floor(np.exp(rng.uniform(np.log(2.0 ** 31), np.log(2.0 ** 62), 100000)))
     M = np.floor(np.exp(rng.uniform(0, np.log(2.0 ** 31), 100000)))
     assert div_faults(host_math, M + (b - 1.0), b, skew, True)[1] == 0
+
+
+@pytest.mark.parametrize("single", [0, 1])
+@pytest.mark.parametrize("skew", [0.0, 2.0 ** -23, -2.0 ** -23])
+def test_best_counts(host_math, single, skew):
+    """The count with the smallest s + C / (s + 1): at the thresholds t (t + 1), their neighbours and between them, far beyond the grid
+    (where the root fits no whole number), at infinity and for what is no number; clamped to any feasible counts."""
+    L = host_math
+    L.px_host_best_counts.restype = None
+    L.px_host_best_counts.argtypes = [ctypes.c_void_p, ctypes.c_long, ctypes.c_int, ctypes.c_int, ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
+    real = np.float32 if single else np.float64
+    largest = 4094 if single else 2 ** 14 - 1                # counts of a grid, and those whose products single precision holds
+    t = np.arange(largest + 1)
+    U = (t * (t + 1.0)).astype(real)
+    rng = np.random.default_rng(8)
+    inside = np.concatenate([U, np.nextafter(U, real(np.inf)), np.nextafter(U, real(0)), (rng.uniform(0.0, 1.0, 20000) * U[-1]).astype(real)])
+    inside = np.sort(inside.astype(np.float64))
+    want = np.searchsorted(t * (t + 1.0), inside, side="left") - 1           # the last t with C > t (t + 1)
+    want = np.maximum(want, 0)
+    beyond = np.array([1e9, 1e18, 5e18, 1e19, 1e30, 3e38, np.inf] + ([] if single else [1e39, 1e300]))
+    none = np.array([0.0, -0.1, -0.3, -1.0, -1e30, -np.inf, np.nan])
+
+    def counts(C, s_lo, s_hi):
+        C = np.ascontiguousarray(C, np.float64)
+        out = np.full(C.size, -99, np.int32)
+        L.px_host_best_counts(C.ctypes.data, C.size, s_lo, s_hi, skew, single, out.ctypes.data)
+        return out
+
+    for s_lo, s_hi in ((0, largest), (0, 0), (0, 31), (7, 12), (5, 5), (200, 300), (3, largest)):
+        assert np.array_equal(counts(inside, s_lo, s_hi), np.clip(want, s_lo, s_hi)), (s_lo, s_hi)
+        assert np.all(counts(beyond, s_lo, s_hi) == s_hi) and np.all(counts(none, s_lo, s_hi) == s_lo), (s_lo, s_hi)
