@@ -1375,55 +1375,31 @@ __device__ __forceinline__ double best_count(const GridPoint &g, const RowTerms 
     return t.none() ? __builtin_inf() : h;
 }
 
-// Reciprocals of the counts of a grid of at most 32, for the scan of calls that have no table of them.
+// Reciprocals of the counts of a grid of at most 32, for the scan of fair shares in single precision, which has no table of them.
 constexpr int kSmallGs = 32;
-#define PX_R4(n) 1.0 / (n), 1.0 / (n + 1), 1.0 / (n + 2), 1.0 / (n + 3)
-__constant__ double small_recips[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R4(13), PX_R4(17), PX_R4(21), PX_R4(25), PX_R4(29)};
-#undef PX_R4
 #define PX_R4(n) 1.0f / (n), 1.0f / (n + 1), 1.0f / (n + 2), 1.0f / (n + 3)
 __constant__ float small_recips_f32[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R4(13), PX_R4(17), PX_R4(21), PX_R4(25), PX_R4(29)};
 #undef PX_R4
 
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
-// CH > 0: a row within the tables; the smallest h of each batch size is found by the scan over all counts (Gs <= kSmallGs), as in the
-// population pass, and m = kClose says that row_best<0> has to decide (elect_scanned).
 // The elected point is priced from the terms its lane has formed; LEAN: from terms formed anew, which holds five registers less.
-template <int CH = 0, bool LEAN = false>
+template <bool LEAN = false>
 __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y,
                                          const int32_t *__restrict__ m_row, int Gm, int Gs, int K, bool one_node, bool tabled)
 {
     const SyncTerm st = sync_term(c, y, K, one_node);
-    RunSteps X = {};
-    if constexpr (CH > 0) X = make_run_steps();
     const double rK = 1.0 / (double)K;
     double kbest = __builtin_inf(), tg_at = 0.0, last_at = 0.0;
     int where = 0, m_at = 0;
-    double C_at = 0.0;               // CH > 0: what the count of the lane's best follows from
-    int lo_at = 0, hi_at = 0;
-    int near_it = 0;                 // CH > 0: whether another h of the lane is close to its best (elect_scanned)
     for (int i = lane_id(); i < Gm; i += kWave) {
         const int m = m_row[i];
         const GridPoint g = grid_point(c, gp, m);
         const double last = last_pass(c, st, g.tg, g.lntg);
-        const RowTerms t = row_terms(g, last, rK, Gs);
-        int s_c = 0;
-        double h;
-        if constexpr (CH > 0) {
-            const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
-            h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, X, (ScalarDoubles)small_recips, Gs), t.A0);
-            if (t.none() || (i > 0 && m_row[i > 0 ? i - 1 : 0] == m)) h = __builtin_inf();       // (a twin: see the tables' rows below)
-            near_it = (h < kbest ? 0 : near_it) | (close_to(kbest, h) ? 1 : 0);
-        } else {
-            h = best_count(g, t, tabled, s_c);
-        }
+        int s_c;
+        const double h = best_count(g, row_terms(g, last, rK, Gs), tabled, s_c);
         if (h < kbest) {
             kbest = h;
             where = s_c | ((i / kWave) << 16);
-            if constexpr (CH > 0) {
-                C_at = t.C;
-                lo_at = t.s_lo;
-                hi_at = t.s_hi;
-            }
             if constexpr (!LEAN) {
                 tg_at = g.tg;
                 last_at = last;
@@ -1431,14 +1407,8 @@ __device__ __forceinline__ Best row_best(const Coefs &c, const Job &q, const Gri
             }
         }
     }
-    Pick pick;
-    if constexpr (CH > 0) pick = Pick{elect_scanned(kbest, __ballot(near_it != 0), [&](int l) { return (__builtin_amdgcn_readlane(where, l) >> 16) * kWave; }), -1};
-    else pick = elect(kbest, where, 0ull, Gs);
-    if (pick.i < 0) return Best{0.0, pick.i, -1};
-    if constexpr (CH > 0) {
-        const int l = pick.i & (kWave - 1);
-        pick.s = px_best_count(wave_read(C_at, l), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
-    }
+    const Pick pick = elect(kbest, where, 0ull, Gs);
+    if (pick.i < 0) return Best{0.0, -1, -1};
     if constexpr (LEAN) {
         const int m = m_row[pick.i];
         const double tg = gp.alpha_g + gp.beta_g * (double)m;
@@ -1453,7 +1423,7 @@ template <bool LEAN>
 __device__ __forceinline__ Best row_best_plain(const Job &q, const GridParams &gp, const int32_t *__restrict__ m_row, int Gm, int Gs, int K,
                                                bool one_node, bool tabled)
 {
-    return row_best<0, LEAN>(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
+    return row_best<LEAN>(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
 }
 
 // The same in single precision, for a GPU count within the tables and grids of at most kSmallGs counts: term by term what
@@ -2682,21 +2652,21 @@ __global__ void __launch_bounds__(kCandThreads) candidates_kernel(FitnessArgs a)
 
 // ---- small calls: one launch -----------------------------------------------------------------------
 // A few hundred candidates of a dozen jobs are less work than the tables their sweeps would share (72 rows a job), and the call
-// lasts as long as its launches follow one another: three of 5 to 7 us each.  Here one workgroup of sixteen wavefronts takes
-// a candidate: each wavefront finds the fair-share goodput of some jobs and reduces, sweeps and prices some of the candidate's
-// rows, forming the terms of its batch sizes itself (row_best, with the scan over all counts for the rows); the node counters
-// are in LDS, and the first wavefront forms SPEEDUP and the mean, term by term and in the tree of candidates_kernel.  The same
-// results, bit by bit.  A call that starts anew leaves its fair shares and re-allocation factors in the workspace, beside the
-// status section; one that keeps the job tables (the children of a generation are such) takes them from there, which leaves a
-// wavefront one row to find.
-// The line (small_call) is drawn where a wavefront has two rows of 64 batch sizes to take, fair shares included, at 3 to 4 us a
-// row (a chain of dependent steps): 8 jobs 9.4 us a call against 15.9 in three launches, 12 jobs 11.5 against 17.5, 16 jobs 15.2
-// against 16.5, 24 jobs 20.7 against 19.3; 8 jobs with 128 batch sizes 12.1 against 17.6.  Calls that keep their tables are two
-// launches on the other side: 8 jobs 6.7 against 9.4, 16 jobs 8.9 against 9.6, and a generation of 16 jobs 17.4 against 18.5.
-// With more than 16 counts 16 jobs take 12.2 to 15.9 us against 18.4 to 19.4, but 9.1 against 8.2 keeping their tables.  Long grids
-// are groups of 64 one after the other: one job with 512 batch sizes takes 13.6 against 52 to 102 and, keeping its tables, 13.5 against
-// 12.2 on 4 GPUs a node and 38.9 on 8; one with 1024 and more than 16 counts 22.6 against 42 to 95 and, keeping them, 22.6 against
-// 16.4 and 69, so there the line lies at eight groups.  The status section holds a byte per candidate.
+// lasts as long as its launches follow one another: three of 5 to 7 us each.  Here one workgroup takes a candidate: it finds the
+// jobs' fair-share goodputs and reduces, elects and prices the candidate's rows, forming the terms of the batch sizes itself; the
+// best count of each follows from its C as for fair shares (px_best_count), so rows, shares and memoised rows are one arithmetic.
+// The node counters are in LDS, and the first wavefront forms SPEEDUP and the mean, term by term and in the tree of
+// candidates_kernel.  The same results, bit by bit.  Sixteen wavefronts share the tasks out (row_best); with at most 32 batch sizes
+// there are 4 to 16, which take two tasks each, a half of the lanes for one (half_best).  A call that starts anew leaves its fair
+// shares and re-allocation factors in the workspace, beside the status section; one that keeps the job tables (the children of a
+// generation are such) takes them from there.
+// (With a scan over all counts for the rows a kept call of 4 jobs, 100 x 32, took 7.1 to 7.5 us, 6.0 so; 14 jobs, 64 x 8, 7.9 to 8.3, 7.3.)
+// The line (small_call) is drawn where a wavefront has two rows of 64 batch sizes to take, fair shares included.  us a call here and
+// in three launches, 16 candidates: 8 jobs, 64 x 16, 8.5, 14.9, 12 jobs 10.0, 14.9, 16 jobs 12.4, 14.9 (200 candidates 12.4, 17.6),
+// 64 x 32 12.5, 18.2; 8 jobs, 128 x 16, 10.0, 16.9; 16 jobs, 32 x 32, 10.0, 15.3; one job, 512 x 16, 10.1, 27.  Keeping their tables,
+// two launches on the other side: 6.7, 8.8; 6.9, 8.7; 7.4, 8.7 (7.5, 11.5), 7.4, 11.9; 7.0, 9.6; 6.7, 8.9; 9.3, 14.2.  Long grids are groups
+// of 64 one after the other, so the line lies at sixteen groups over all jobs, eight with more than 16 counts.  The status section
+// holds a byte per candidate.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallJobs = 16;
 constexpr int kSmallCandidates = 4 * (kStatusWords - 1);
@@ -2709,9 +2679,8 @@ static bool small_call(const pollux_dims &d)
            d.J * groups <= kSmallJobs && (d.Gs <= 16 || groups <= 8);
 }
 
-
 // Threads of a workgroup: sixteen wavefronts, one task each, fair shares before rows; or, with at most 32 batch sizes, one wavefront for
-// two tasks (small_halves), and four at least.
+// two tasks (small_kernel's HALVES), and four at least.
 constexpr int kSmallHalf = kWave / 2;
 static int small_threads(const pollux_dims &d, bool kept)
 {
@@ -2731,43 +2700,32 @@ __device__ __forceinline__ unsigned half_min(unsigned v)
 // The argmax of two (job, K, placement) at once, one per half of the wavefront, for grids of at most 32 batch sizes; each lane's
 // arguments are its half's.  The lane that holds the elected point (the half's first where there is none) returns it in `best`
 // and is told so.  The same point as row_best finds, the same bits.
-template <int CH>
 __device__ __forceinline__ bool half_best(const Coefs &c, const Job &q, const GridParams &gp, const SyncParams &y, int m, bool in_grid,
                                           int Gs, int K, bool one_node, bool tabled, Best &best)
 {
     SyncTerm st = sync_term(c, y, K, one_node);
     const GridPoint g = grid_point(c, gp, m);
     const double last = last_pass(c, st, g.tg, g.lntg);
-    const RowTerms t = row_terms(g, last, 1.0 / (double)K, Gs);
-    const Feasible f = feasible_end(t.C, t.s_lo, t.s_hi, [](int, double sd) { return px_div(1.0, sd + 1.0); });
-    double h = px_fma(g.tg, f.outside ? f.w : scan_min<CH>(t.C, make_run_steps(), (ScalarDoubles)small_recips, Gs), t.A0);
-    const int s = px_best_count(t.C, t.s_lo, t.s_hi);
-    h = in_grid && !t.none() && h < __builtin_inf() ? h : __builtin_inf();
+    int s;
+    double h = best_count(g, row_terms(g, last, 1.0 / (double)K, Gs), tabled, s);
+    h = in_grid && h < __builtin_inf() ? h : __builtin_inf();
+    const unsigned hi = (unsigned)__double2hiint(h), lo = (unsigned)__double2loint(h);
+    const unsigned hmin = half_min(hi);
+    const unsigned lmin = half_min(hi == hmin ? lo : 0xFFFFFFFFu);
     const unsigned lane = (unsigned)lane_id() & (kSmallHalf - 1);
-    unsigned hi = (unsigned)__double2hiint(h), hmin = half_min(hi);
-    const bool close = hmin < 0x7FF00000u && hi <= hmin + Closeness<double>::kWindow;
-    bool mine = hmin < 0x7FF00000u ? close : lane == 0u;
-    // one lane a half, or h itself decides; rows beyond the tables have no other form
-    if (__popcll(__ballot(mine)) != 2 || __ballot(!tabled) != 0ull) {
-        int s_c;
-        h = best_count(g, t, tabled, s_c);
-        h = in_grid && h < __builtin_inf() ? h : __builtin_inf();
-        hi = (unsigned)__double2hiint(h);
-        hmin = half_min(hi);
-        const unsigned lo = (unsigned)__double2loint(h), lmin = half_min(hi == hmin ? lo : 0xFFFFFFFFu);
-        mine = lane == half_min(hi == hmin && lo == lmin ? lane : 0xFFu);      // equal values: the lowest batch size
-    }
+    const unsigned first = half_min(hi == hmin && lo == lmin ? lane : 0xFFu);      // equal values: the lowest batch size
     best = Best{0.0, -1, -1};
     if (hmin < 0x7FF00000u) best = Best{goodput_point(q, (double)K * (double)m, g.tg, last, s), m, s};
-    return mine;
+    return lane == first;
 }
 
 // KEPT: the call keeps the job tables.  HALVES: at most 32 batch sizes.  A wavefront would leave half its lanes idle with one task, and
-// sixteen of them share four SIMDs whose issue bounds them (8 jobs, 32 x 8: 13000 of the workgroup's 19400 cycles), so a wavefront
-// takes a job's fair share and its row together, a half each, or two rows where the fair shares are kept.  The rows are reduced
-// first, a wavefront each.  Calls, us, with a wavefront a task and so: 16 candidates of 8 jobs, 32 x 8, 8.9 to 9.2, 7.9; 200 of 16 jobs,
-// 32 x 32, 13.6, 10.9; 16 of 16 on 200 nodes 14.1, 10.9; 250 of 3 jobs 8.2, 8.3.
-template <int CH, bool KEPT, bool HALVES>
+// sixteen of them share four SIMDs whose issue bounds them (8 jobs, 32 x 8: 13000 of the workgroup's 19400 cycles, with a scan of the
+// counts in each), so a wavefront takes a job's fair share and its row together, a half each, or two rows where the fair shares are
+// kept.  The rows are reduced first, a wavefront each.  Calls, us, with a wavefront a task and so, both with that scan, and so without it:
+// 16 candidates of 8 jobs, 32 x 8, 8.7, 7.8, 7.1; 200 of 16 jobs, 32 x 32, 13.5, 10.8, 9.9; 16 of 16 on 200 nodes 14.0, 10.8, 10.3; 250 of 3
+// jobs 6.4, 6.6, 6.0.
+template <bool KEPT, bool HALVES>
 __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
 {
     __shared__ unsigned long long node_lds[4 * kWave];       // per node: GPUs asked + multi-node jobs << 40, as colpack
@@ -2845,7 +2803,7 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
         const bool one_node = (is_row ? meta_lds[j] & ~kMetaChanged : fair_nodes) == 1;
         const bool wanted = K >= 1;
         Best best;
-        bool mine = half_best<CH>(coefs, q, gp, y, m, in_grid, a.Gs, wanted ? K : 1, one_node, !wanted || tabled_row(K, one_node, k1), best);
+        const bool mine = half_best(coefs, q, gp, y, m, in_grid, a.Gs, wanted ? K : 1, one_node, !wanted || tabled_row(K, one_node, k1), best);
         if (!wanted) best = Best{0.0, -1, -1};
         if (valid && mine) {
             if (is_row) {
@@ -2889,12 +2847,7 @@ __global__ void __launch_bounds__(kSmallThreads) small_kernel(FitnessArgs a)
                 atomicAdd(&to[3], (unsigned long long)(long long)w.w + (w.w > 0 ? one_job : 0ull));
             }
             Best best = {0.0, -1, -1};
-            if (K >= 1) {
-                const bool tabled = tabled_row(K, nodes == 1, k1);
-                best.m = kClose;
-                if (tabled) best = row_best<CH>(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, true);
-                if (__builtin_expect(best.m == kClose, 0)) best = row_best_plain<false>(q, gp, m_row, a.Gm, a.Gs, K, nodes == 1, tabled);
-            }
+            if (K >= 1) best = row_best(coefs, q, gp, y, m_row, a.Gm, a.Gs, K, nodes == 1, tabled_row(K, nodes == 1, k1));
             if (lane == 0) {
                 goodput_lds[j] = best.goodput;
                 meta_lds[j] = nodes | (changed ? kMetaChanged : 0);
@@ -3752,17 +3705,10 @@ int launch_fitness(const pollux_dims *d, const int32_t *population, const double
         if (sweep_start) (void)hipEventRecord(sweep_start, stream);
         const bool kept = (d->flags & PX_FLAG_KEEP_JOB_TABLES) != 0, halves = d->Gm <= kSmallHalf;
         const dim3 grid((unsigned)P_eff), block((unsigned)small_threads(*d, kept));
-#define PX_LAUNCH_SMALL(CH)                                                                                      \
-    do {                                                                                                         \
-        if (kept && halves) hipLaunchKernelGGL((small_kernel<CH, true, true>), grid, block, 0, stream, a);       \
-        else if (halves) hipLaunchKernelGGL((small_kernel<CH, false, true>), grid, block, 0, stream, a);         \
-        else if (kept) hipLaunchKernelGGL((small_kernel<CH, true, false>), grid, block, 0, stream, a);           \
-        else hipLaunchKernelGGL((small_kernel<CH, false, false>), grid, block, 0, stream, a);                    \
-    } while (0)
-        if (ch == 8) PX_LAUNCH_SMALL(8);
-        else if (ch == 16) PX_LAUNCH_SMALL(16);
-        else PX_LAUNCH_SMALL(32);
-#undef PX_LAUNCH_SMALL
+        if (kept && halves) hipLaunchKernelGGL((small_kernel<true, true>), grid, block, 0, stream, a);
+        else if (halves) hipLaunchKernelGGL((small_kernel<false, true>), grid, block, 0, stream, a);
+        else if (kept) hipLaunchKernelGGL((small_kernel<true, false>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((small_kernel<false, false>), grid, block, 0, stream, a);
         if (sweep_stop) (void)hipEventRecord(sweep_stop, stream);
         return hipGetLastError() == hipSuccess ? PX_OK : PX_E_HIP;
     }
