@@ -35,13 +35,25 @@ int px_host_split_nodes(int candidates, int jobs, int nodes, int Gm, int Gs, int
     const bool row1 = nodes >= 4 && nodes <= 256, whole = nodes % 4 == 0 && Gm % 64 == 0;
     return px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row1 && nodes <= 64, whole, false, row1).per_wave;
 }
-// The split a call takes: as px_host_split, in bits above 8 the workgroups a job's candidates are shared out among.
-int px_host_balanced(int candidates, int jobs, int nodes, int Gm, int Gs, int f32, int inherit)
+// The split a call takes, and what split_pairs had for it: as px_host_split, in bits above 8 the workgroups a job's candidates are shared
+// out among.  (The sampling argmax does not read the rows of four candidates with one load.)
+static int packed(const px::PairSplit &p, int candidates)
 {
-    const bool row1 = nodes >= 4 && nodes <= 256, row4 = row1 && nodes <= 64, whole = nodes % 4 == 0 && Gm % 64 == 0;
-    const px::PairSplit p = px::balanced_split(px::split_pairs(candidates, jobs, Gm, Gs, f32 != 0, row4, whole, inherit != 0, row1),
-                                               candidates, jobs, Gm, Gs, f32 != 0, row4, inherit != 0, row1, false);
     return (p.per_wave - 1) | (p.four ? 16 : 0) | (p.entry_by_entry ? 32 : 0) | px::pair_groups(candidates, p.per_wave) << 8;
+}
+static px::PairSplit call_split(int candidates, int jobs, int nodes, int Gm, int Gs, bool f32, bool inherit, bool sampled, bool balanced)
+{
+    const bool row1 = nodes >= 4 && nodes <= 256, row4 = row1 && nodes <= 64 && !sampled, whole = nodes % 4 == 0 && Gm % 64 == 0;
+    const px::PairSplit p = px::split_pairs(candidates, jobs, Gm, Gs, f32, row4, whole, inherit, row1, sampled);
+    return balanced ? px::balanced_split(p, candidates, jobs, Gm, Gs, f32, row4, inherit, row1, sampled) : p;
+}
+int px_host_balanced(int candidates, int jobs, int nodes, int Gm, int Gs, int f32, int inherit, int sampled)
+{
+    return packed(call_split(candidates, jobs, nodes, Gm, Gs, f32 != 0, inherit != 0, sampled != 0, true), candidates);
+}
+int px_host_unbalanced(int candidates, int jobs, int nodes, int Gm, int Gs, int f32, int inherit, int sampled)
+{
+    return packed(call_split(candidates, jobs, nodes, Gm, Gs, f32 != 0, inherit != 0, sampled != 0, false), candidates);
 }
 int px_host_table_rows(int jobs, int Gm) { return px::table_rows(jobs, Gm); }
 int px_host_pair_groups(int candidates, int per_wave) { return px::pair_groups(candidates, per_wave); }

@@ -19,20 +19,18 @@ def launch(tmp_path_factory):
 @pytest.mark.parametrize("nodes", [3, 4, 33, 64, 65, 256, 257])
 def test_every_candidate_is_taken_once(launch, nodes, f32):
     """1 to 16 candidates a wavefront, no workgroup without one; whole fours where four are swept at a time, and never entry by entry
-    then; what has no length known here, and other rows, as split_pairs has it."""
+    then; row inheritance, the sampling argmax and rows of other lengths as split_pairs has it."""
     for candidates in (1, 3, 12, 13, 16, 17, 63, 100, 1000, 4096, 22000):
         for jobs in (1, 8, 30, 200, 1000, 90000):
             for Gm, Gs in ((1, 1), (64, 16), (65, 16), (128, 8), (129, 8), (64, 17), (128, 32), (4096, 4)):
-                for inherit in (0, 1):
-                    got = launch.px_host_balanced(candidates, jobs, nodes, Gm, Gs, f32, inherit)
+                for inherit, sampled in ((0, 0), (1, 0)) if f32 else ((0, 0), (1, 0), (0, 1)):
+                    call = candidates, jobs, nodes, Gm, Gs, f32, inherit, sampled
+                    got = launch.px_host_balanced(*call)
                     n, four, entries, groups = (got & 15) + 1, bool(got & 16), bool(got & 32), got >> 8
                     assert (groups - 1) * 4 * n < candidates <= groups * 4 * n
-                    whole = int(nodes % 4 == 0 and Gm % 64 == 0)
-                    row1 = 4 <= nodes <= 256
-                    if inherit or not row1:
-                        was = launch.px_host_split(candidates, jobs, Gm, Gs, f32, int(row1 and nodes <= 64), whole, inherit)
-                        assert row1 and nodes <= 64 or not four
-                        assert not row1 or got & 63 == was or nodes > 64
+                    if inherit or sampled or not 4 <= nodes <= 256:
+                        assert got == launch.px_host_unbalanced(*call), call
+                        assert not four or 4 <= nodes <= 64
                     elif nodes <= 64 and four and (f32 or Gs <= 16) and candidates > 12:
                         assert n % 4 == 0 and not entries
 
@@ -44,5 +42,5 @@ def test_every_candidate_is_taken_once(launch, nodes, f32):
     (60, 66, 33, 50, 12, 0, 1, 0), (60, 67, 33, 50, 12, 0, 4, 1), (60, 67, 33, 129, 12, 0, 1, 0), (60, 66, 33, 64, 16, 1, 1, 0), (60, 67, 33, 64, 16, 1, 4, 1),
     (60, 99, 33, 65, 12, 1, 1, 0), (60, 100, 33, 65, 12, 1, 4, 1), (60, 99, 33, 65, 12, 0, 1, 0), (60, 100, 33, 65, 12, 0, 4, 1)])
 def test_candidates_a_wavefront(launch, candidates, jobs, nodes, Gm, Gs, f32, per_wave, four):
-    got = launch.px_host_balanced(candidates, jobs, nodes, Gm, Gs, f32, 0)
+    got = launch.px_host_balanced(candidates, jobs, nodes, Gm, Gs, f32, 0, 0)
     assert ((got & 15) + 1, (got >> 4) & 1) == (per_wave, four)
