@@ -63,6 +63,29 @@ def test_every_way_elects_the_same_batch_size(P, J, N, Gm, Gs, first):
         assert np.max(np.abs(got[k][:9] - ref[k]) / np.where(ref[k] == 0, 1.0, ref[k])) <= 1e-12, k
 
 
+@pytest.mark.parametrize("P,J,N,Gm,Gs", [(40, 200, 16, 64, 16), (40, 200, 16, 100, 32), (17, 200, 130, 128, 32), (17, 200, 130, 130, 64)])
+def test_batch_sizes_a_millionth_apart_are_told_apart(P, J, N, Gm, Gs):
+    """Long consecutive batch sizes around a job's best one: their goodputs agree to six places and more, but do not tie."""
+    import paper_2008_12260_amd as px
+    wl, pop = workload(P, J, N, Gm, Gs, 2000)
+    jp, row, rng = wl.job_params, W.PARAM_INDEX, np.random.default_rng(7)
+    a, b, t = rng.uniform(0.01, 0.2, J), rng.uniform(1e-5, 1e-4, J), rng.uniform(0.005, 0.05, J)
+    pop[::2] = pop[0]
+    # without accumulation, T = a + b m + t and phi so that (a + t + b m) (1 + phi / (K m)) is least within the grid, for candidate 0
+    jp[row["alpha_grad"]], jp[row["beta_grad"]], jp[row["gamma"]], jp[row["M_max"]] = a, b, 1.0, 2.0 ** 40
+    for name in ("alpha_sync_local", "alpha_sync_node", "beta_sync_local", "beta_sync_node"):
+        jp[row[name]] = t if name.startswith("alpha") else 0.0
+    jp[row["phi"]] = (2000 + rng.uniform(0.1, 0.9, J) * Gm) ** 2 * pop[0].sum(1) * b / (a + t)
+    got, memo = results(wl, pop), results(wl, pop, px.PX_FLAG_MEMOISE)
+    inside = (got["best_m"] > 2000) & (got["best_m"] < 1999 + Gm)
+    assert inside.sum() > 0.4 * inside.size
+    for k in KEYS:
+        assert np.array_equal(got[k], memo[k]), (k, int(np.sum(got[k] != memo[k])))
+    wl.node_capacity[:] = 40
+    ref = run_oracle(wl, population=pop[:9], current=pop[0])
+    assert np.array_equal(got["best_m"][:9], ref["best_m"]) and np.array_equal(got["best_s"][:9], ref["best_s"])
+
+
 def single(x):
     """A fraction rounded to single precision (values far from underflow)."""
     if x == 0:
