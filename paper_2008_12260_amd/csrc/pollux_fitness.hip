@@ -1387,11 +1387,8 @@ __device__ __forceinline__ double best_count(const GridPoint &g, const RowTerms 
     return t.none() ? __builtin_inf() : h;
 }
 
-// Reciprocals of the counts of a grid of at most 32, for the scan of fair shares in single precision, which has no table of them.
+// The most counts of a call in one launch (small_call), and of one whose single-precision fair shares come with the tables' launch.
 constexpr int kSmallGs = 32;
-#define PX_R4(n) 1.0f / (n), 1.0f / (n + 1), 1.0f / (n + 2), 1.0f / (n + 3)
-__constant__ float small_recips_f32[kSmallGs] = {PX_R4(1), PX_R4(5), PX_R4(9), PX_R4(13), PX_R4(17), PX_R4(21), PX_R4(25), PX_R4(29)};
-#undef PX_R4
 
 // All 64 lanes call this with the same arguments; every lane returns the same result.  m_row: the job's batch sizes.
 // The elected point is priced from the terms its lane has formed; LEAN: from terms formed anew, which holds five registers less.
@@ -1438,50 +1435,37 @@ __device__ __forceinline__ Best row_best_plain(const Job &q, const GridParams &g
     return row_best<LEAN>(plain_coefs(), q, gp, load_sync(q), m_row, Gm, Gs, K, one_node, tabled);
 }
 
-// The same in single precision, for a GPU count within the tables and grids of at most kSmallGs counts: term by term what
-// sweep_pick_f32 and price_point_f32 make of the tables, so the same point and the same bits.  SCAN: m = kClose says that the instance
-// without a scan has to decide (elect_scanned).
-template <bool SCAN>
+// The same in single precision, for a GPU count within the tables: the same point as sweep_pick_f32 and price_point_f32 find, the same
+// bits (elect_scanned).
 __device__ __forceinline__ Best row_best_f32(const Coefs &c, const JobF32 &q, const GridParams &gp, const SyncParams &y,
                                              const int32_t *__restrict__ m_row, int Gm, int Gs, int K, bool one_node)
 {
-    const RunStepsF32 X = make_run_steps_f32();
     const SyncTerm st = sync_term(c, y, K, one_node);
     const double rK = 1.0 / (double)K;
     const float Kf = (float)K, ts = t_sync_f32(q, K, one_node);
     float kbest = __builtin_inff();
-    TermsF32 at = {};                     // the lane's best: its terms, batch size and feasible counts
-    int where = 0, m_at = 0, lo_at = 0, hi_at = 0, near_it = 0;
-    auto recip = [](int s) { return 1.0f / (float)(s + 1); };
+    TermsF32 at = {};                     // the lane's best: its terms and batch size
+    int where = 0, m_at = 0;
     for (int i = lane_id(); i < Gm; i += kWave) {
         const int m = m_row[i];
-        const bool twin = i > 0 && m_row[i > 0 ? i - 1 : 0] == m;         // (see prepare_rows)
         const GridPoint g = grid_point(c, gp, m);
         const TermsF32 t = terms_f32(q, ts, Kf, m, (float)last_pass(c, st, g.tg, g.lntg));
         int s_lo, s_hi;
         feasible_range(g.ql5, g.qh5, rK, Gs, s_lo, s_hi);
-        const bool feasible = s_lo <= s_hi && s_hi >= 0 && !twin;
-        float key;
-        if constexpr (SCAN) key = feasible_h_f32(t, s_lo, s_hi, scan_min_f32<16>(t.C, X, (ScalarFloats)small_recips_f32, Gs), recip);
-        else key = exact_h_f32(t, px_best_count(t.C, s_lo, s_hi), recip);
-        if (feasible) near_it = (key < kbest ? 0 : near_it) | (close_to(kbest, key) ? 1 : 0);
-        if (feasible && key < kbest) {
+        const int s_c = px_best_count(t.C, s_lo, s_hi);
+        const float key = exact_h_f32(t, s_c, [](int s) { return 1.0f / (float)(s + 1); });
+        if (s_lo <= s_hi && s_hi >= 0 && key < kbest) {
             kbest = key;
-            where = (i / kWave) << 16;
+            where = s_c | ((i / kWave) << 16);
             at = t;
             m_at = m;
-            lo_at = s_lo;
-            hi_at = s_hi;
         }
     }
-    int i;
-    if constexpr (SCAN) i = elect_scanned(kbest, __ballot(near_it != 0), [&](int l) { return (__builtin_amdgcn_readlane(where, l) >> 16) * kWave; });
-    else i = elect((double)kbest, where, 0ull, Gs).i;      // (positive floats order like their values in double precision)
-    if (i < 0) return Best{0.0, i, -1};
-    const int l = i & (kWave - 1);
+    const Pick pick = elect((double)kbest, where, 0ull, Gs);      // (positive floats order like their values in double precision)
+    if (pick.i < 0) return Best{0.0, -1, -1};
+    const int l = pick.i & (kWave - 1), s = pick.s;
     auto read = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
     const int m = __builtin_amdgcn_readlane(m_at, l);
-    const int s = px_best_count(read(at.C), __builtin_amdgcn_readlane(lo_at, l), __builtin_amdgcn_readlane(hi_at, l));
     const float M = (float)K * (float)m * (float)(s + 1);
     const float t_iter = (float)s * read(at.tg) + read(at.last);              // Eq. 11
     const float g = (M / t_iter) * (q.a / (q.phi + M));                       // Eq. 7 x Eq. 6
@@ -1573,10 +1557,8 @@ __device__ __forceinline__ void prepare_job(const Coefs &c, const FitnessArgs &a
             return double2{g.ql5, g.qh5};
         };
         const JobF32 qf = load_job_f32(jp, a.J, j);
-        if (K > 0 && K <= kTableK && (!one_node || node_holds(a, K))) {
-            fair = row_best_f32<true>(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
-            if (fair.m == kClose) fair = row_best_f32<false>(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
-        } else if (K > 0) fair = sweep_beyond_f32(qf, m_row, terms, 1.0 / (double)K, a.Gm, a.Gs, K, one_node ? 1 : 2);
+        if (K > 0 && K <= kTableK && (!one_node || node_holds(a, K))) fair = row_best_f32(c, qf, gp, y, m_row, a.Gm, a.Gs, K, one_node);
+        else if (K > 0) fair = sweep_beyond_f32(qf, m_row, terms, 1.0 / (double)K, a.Gm, a.Gs, K, one_node ? 1 : 2);
     } else if (K > 0) fair = row_best(c, q, gp, y, m_row, a.Gm, a.Gs, K, one_node, K <= kTableK && (!one_node || node_holds(a, K)));
     if (!(fair.goodput > 0.0)) st |= PX_ST_ZERO_FAIR;
     if (lane == 0) {
