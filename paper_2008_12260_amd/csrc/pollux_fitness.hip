@@ -343,7 +343,7 @@ __device__ __forceinline__ double goodput_point(const Job &q, double Km, double 
 // the chunk.  Which count attains the minimum is not looked for here: one lane of sixty-four wins the election, and
 // its count follows from C when the elected point is priced (px_best_count).
 // (With every group of four carrying its position in its low mantissa bits, nine instructions per four points, and every lane
-// finding its count with five comparisons, a pair of 128 batch sizes x 32 counts took 248 vector instructions, 220 so: 4096 candidates
+// finding its count with five comparisons, a pair of 128 batch sizes x 32 counts took 248 vector instructions, 213 so: 4096 candidates
 // of 1000 jobs 1.78 ms against 1.66, 1000 of 200 on 64 nodes 52.5 us against 46; fp32, which also loses its tags, 52.0 against 44.7.)
 typedef const double __attribute__((address_space(4))) *ScalarDoubles;
 typedef const double __attribute__((address_space(3))) *LdsDoubles;
@@ -589,7 +589,7 @@ __device__ __forceinline__ Pick elect(double kbest, int where, unsigned long lon
 // all where alpha_grad = 0 and gamma = 1 make h a function of m (s + 1)), h itself decides (settle).  1000 candidates of 200 jobs on
 // 64 nodes, 64 x 16, us: 61.1 without this, 60.7 so; 80 where every election of every job is settled.
 // In single precision the scan's h has five roundings where h itself has four, so two of them can change places within ten units in the
-// last place; sixteen are close.  1000 candidates of 200 jobs on 64 nodes, 64 x 16, us: 62.7 without this, 64.2 so.
+// last place; sixteen are close.  1000 candidates of 200 jobs on 64 nodes, 64 x 16, us: 62.8 without this, 63.8 so.
 // Positive values order like their bit patterns: the election sees high words of doubles, all bits of single ones.
 template <typename REAL>
 struct Closeness;
@@ -1853,8 +1853,8 @@ pairs_kernel(FitnessArgs a)
     bool has_near = false;
     // (the instances whose rows fit one 16-byte load per lane fill the table after they have requested their first rows)
     constexpr bool kRowsFirst = CH != 0 && ROW1;
-    // every thread brings one entry, formed by the same division as the entry of a.rs (prepare_kernel): no load, so
-    // storing it waits for nothing that is on its way from memory
+    // every thread brings one entry: no load, so storing it waits for nothing that is on its way from memory.  px_div rounds the
+    // reciprocals of whole numbers as the division does that fills a.rs (prepare_kernel): checked for all up to 2^14 by a host test
     static_assert(kNearRecips <= kWavesPerBlock * kWave, "one entry per thread");
     const bool near_fits = CH != 0 && !MEMO && a.gs_pad <= kNearRecips;
     const double near_d = px_div(1.0, (double)((int)threadIdx.x + 1));

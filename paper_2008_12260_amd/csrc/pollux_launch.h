@@ -63,8 +63,10 @@ struct PairSplit {
 };
 
 // row1: rows of 4 to 256 nodes.  row4: of at most 64, with count tables that fit on chip.  sampled: the sampling argmax.
-// (Where rows have 4 to 256 nodes and the candidates are known, balanced_split settles the count; the figures are of sweeps that took
-// longer than today's.)
+// balanced_split then sets the count of calls on rows of 65 to 256 nodes (shorter ones where the count tables do not fit) and, on shorter
+// ones, of those that go four at a time or are put to it there.  What is said here of the count holds for the others: short rows one at a
+// time (fp32 and ragged on few pairs or wide grids), row inheritance, the sampling argmax, longer rows.  Its figures are of sweeps that
+// took longer than today's.
 //
 // per_wave: 25000 wavefronts fill the chip several times over.  Fewer with more candidates each save what a wavefront does once (job
 // terms, table in LDS, prices), until the last wavefronts to end cost more: down to 12400 wavefronts with as many candidates as that
@@ -128,7 +130,8 @@ inline int pair_groups(int candidates, int per_wave)
 // 10.7, 10.8, fp32 64 x 16 11.0, 10.9; 40 x 40 on 22 nodes 9.1, 9.7; 44 x 137 on 57 nodes, 100 x 12, 12.6, 11.4.  Grids wider than
 // 64 batch sizes x 16 counts from 6000: fp32 69 x 64 on 8 nodes, 128 x 12, 11.3, 11.9, 242 x 24 on 6, 100 x 12, 14.5, 15.4; 51 x 120 on 15,
 // 100 x 8, 12.9, 12.3; 184 x 35 on 13, 128 x 12, 13.6, 12.4.
-// Row inheritance, whose lists have no length known here, the sampling argmax and longer rows keep split_pairs' count.
+// Row inheritance, whose lists have no length known here, the sampling argmax and longer rows keep split_pairs' count, and so do short
+// rows below those lines or on grids of more than 128 batch sizes x chunks of 16 counts, unless split_pairs has them in fours already.
 inline PairSplit balanced_split(PairSplit s, int candidates, int jobs, int Gm, int Gs, bool f32, bool row4, bool inherit, bool row1, bool sampled)
 {
     if (inherit || sampled || !row1) return s;
