@@ -36,12 +36,12 @@ FLOPS_PER_EVAL = 7                  # Eq. 4 at one grid point: 5 add/mul + 2 div
 #   valu_busy       fraction of the kernel's cycles in which the vector ALUs were busy
 PROFILED = {
     "large": {
-        "source_sha256": "44fff2506af3eef50628820c3b5f9f70114fa14a329ce90d7889188223386bc5",
-        "traffic_bytes": 2_079_340 * 1024 * 2 + 700_522 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
-        "fp64_flops": 64 * (8.96000e5 + 1.75712e7 + 2 * 2.66373e8),
-        "valu_insts": 8.72223e8,
+        "source_sha256": "4b4583641e4cb3cf7f8deeef8fca5111e0f079b1768ab8733c1be9a4256ad053",
+        "traffic_bytes": 2_078_810 * 1024 * 2 + 699_540 * 1024,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (launches that store m*, s*)
+        "fp64_flops": 64 * (8.96000e5 + 1.75630e7 + 2 * 2.66272e8),
+        "valu_insts": 8.73725e8,
         "scan_insts": 2.0 * 1.6777e10 / 64,
-        "valu_busy": 8.90600e8 * 4 / 1024 / (3.05642e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
+        "valu_busy": 8.88650e8 * 4 / 1024 / (3.05292e7 / 8),           # SQ_ACTIVE_INST_VALU x 4 cycles / SIMDs / cycles
     },
 }
 GA_SEED = 0x2008_1226_5EED_0001
