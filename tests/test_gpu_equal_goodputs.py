@@ -63,6 +63,29 @@ def test_every_way_elects_the_same_batch_size(P, J, N, Gm, Gs, first):
         assert np.max(np.abs(got[k][:9] - ref[k]) / np.where(ref[k] == 0, 1.0, ref[k])) <= 1e-12, k
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("J,N,Gm,Gs", [(60, 16, 64, 32), (60, 61, 64, 16), (60, 130, 100, 32), (200, 16, 64, 16), (15, 9, 32, 32)])
+def test_children_are_elected_alike(J, N, Gm, Gs, precision):
+    """The same search in which children are swept, in which only their changed rows are, and memoised."""
+    import torch
+    import paper_2008_12260_amd as px
+    wl, pop = workload(96, J, N, Gm, Gs, 6)
+    c, got = wl.cfg, []
+    for flags, inherit in ((0, False), (0, True), (px.PX_FLAG_MEMOISE | px.PX_FLAG_PAIR_RESULTS, False)):
+        call = px.FitnessCall(96, c.J, N, Gm, Gs, wl.job_params, wl.m_grid, wl.fair_share, pop[0], np.full(N, 40, np.int32), p=c.p,
+                              delta=c.delta, flags=flags, precision=precision)
+        matrices = torch.as_tensor(pop).cuda()
+        call.run(matrices)
+        for g in range(4):
+            call.generation(matrices, 77, g, 32, (1 << 32) // 16, inherit_rows=inherit)
+        got.append((matrices.cpu().numpy(), call.results()))
+    assert np.any(got[0][0] != pop)
+    for matrices, results_of in got[1:]:
+        assert np.array_equal(matrices, got[0][0])
+        for k in KEYS:
+            assert np.array_equal(results_of[k], got[0][1][k]), k
+
+
 @pytest.mark.parametrize("P,J,N,Gm,Gs", [(40, 200, 16, 64, 16), (40, 200, 16, 100, 32), (17, 200, 130, 128, 32), (17, 200, 130, 130, 64)])
 def test_batch_sizes_a_millionth_apart_are_told_apart(P, J, N, Gm, Gs):
     """Long consecutive batch sizes around a job's best one: their goodputs agree to six places and more, but do not tie."""
